@@ -12,13 +12,12 @@
 // long as the fourth density was formed about the same c, so a W-list
 // multipole is evaluated about its own box centre.
 //
-// Two kernels: one block per expansion builds its sets (in LDS) and writes
-// them to a device array, coefficient-major in the order the evaluation
-// walks them (order m, then degree n), with the factor 2 for m > 0 and, for
-// local expansions, 1/((n-m)!(n+m)!) folded in; then one wave per tile of
-// up to 64 beads of a leaf evaluates the leaf's sets and those of its W-list
-// multipoles, with the coefficients read through scalar loads (uniform over
-// the wave) and lane = target.
+// Two kernels: one block per expansion builds its sets and writes them to a
+// device array, coefficient-major in the order the evaluation walks them
+// (order m, then degree n), with the factor 2 for m > 0 and, for local
+// expansions, 1/((n-m)!(n+m)!) folded in; then one wave per tile of up to 64
+// beads of a leaf evaluates the leaf's sets and those of its W-list
+// multipoles, with lane = target and each coefficient broadcast to the lanes.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -56,98 +55,173 @@ __device__ inline double2 dcoef(const double2* C, int nmax, int n, int m, int ax
   return make_double2(0.5 * (a.y + b.y), -0.5 * (a.x + b.x));
 }
 
-// Builds the 12 evaluation sets of one expansion in LDS (box side h):
-//   D[3 + 3i + k] = h^-2 d_i L_k          (k, i = 0..2),
-//   D[i]          = C1 h^-1 L_i + C1 h^-2 d_i L_4 - C2 h^-3 d_i L_C,
-// with L_C = sum_k d_k L_k (degree <= nout; a multipole's sets have degree
-// nin + 2).  G4 (3 sets) and LC are scratch.
-__device__ void derived_sets(const double2* src, int nin, int nout, bool mult, double h, double C1, double C2,
-                             double2* D, double2* G4, double2* LC) {
-  const int To = ncoef(nout);
-  const double ih = 1.0 / h, ih2 = ih * ih, ih3 = ih2 * ih;
-  for (int w = threadIdx.x; w < 12 * To; w += blockDim.x) {
-    const int k = w / (3 * To), rem = w - k * 3 * To, i = rem / To, c = rem - i * To;
-    int n = 0;
-    while (tri(n + 1) <= c) ++n;
-    const int m = c - tri(n);
-    const double2 g = dcoef(src + k * ncoef(nin), nin, n, m, i, mult);
-    if (k < 3) D[(3 + 3 * i + k) * To + c] = make_double2(ih2 * g.x, ih2 * g.y);
-    else G4[i * To + c] = g;
-  }
-  __syncthreads();
-  const double h2 = h * h;
-  for (int c = threadIdx.x; c < To; c += blockDim.x) {
-    const double2 a = D[3 * To + c], b = D[7 * To + c], d = D[11 * To + c];
-    LC[c] = make_double2(h2 * (a.x + b.x + d.x), h2 * (a.y + b.y + d.y));
-  }
-  __syncthreads();
-  for (int w = threadIdx.x; w < 3 * To; w += blockDim.x) {
-    const int i = w / To, c = w - i * To;
-    int n = 0;
-    while (tri(n + 1) <= c) ++n;
-    const int m = c - tri(n);
-    const double2 l = getc(src + i * ncoef(nin), n, m, nin);
-    const double2 g4 = G4[i * To + c];
-    const double2 dc = dcoef(LC, nout, n, m, i, mult);
-    D[i * To + c] = make_double2(C1 * ih * l.x + C1 * ih2 * g4.x - C2 * ih3 * dc.x,
-                                 C1 * ih * l.y + C1 * ih2 * g4.y - C2 * ih3 * dc.y);
-  }
-  __syncthreads();
-}
-
-constexpr int SETS_T = 256;
+constexpr int SETS_T = 256;  // most threads per block
+constexpr int SETS_LD = 25;  // LDS row of one coefficient's 24 doubles, padded against bank conflicts
 
 // One block per (expansion, right-hand side): the 12 sets of box boxes[i]'s
 // expansion E (local: mult = false, degree p; multipole: degree p + 2),
-// written as out[((i * NRC + r) * To + k) * 12 + e] for the m-major index k.
+//   set i (i = 0..2)  = C1 h^-1 L_i + C1 h^-2 d_i L_4 - C2 h^-3 d_i L_C,
+//   set 3 + 3i + k    = h^-2 d_i L_k            (k = 0..2; h: box side),
+// with L_C = sum_k d_k L_k, written for groups of er right-hand sides as a
+// stream of doubles, for each m-major coefficient k and right-hand side of the
+// group the 12 negated imaginary parts, then the 12 real parts:
+// out[((i * NRC / er + r / er) * To + k) * 24 er + 24 (r % er) + {e, 12 + e}].
 // rscale[tri(n)+m] = 1/((n-m)!(n+m)!) (local sets only).
+// A thread forms the 24 numbers of its coefficient from the expansion in LDS
+// (degree and order decoded once) and the block writes them in runs of 192 B:
+// 2.1 ms per launch of 131k expansions at p = 16 (3.0 ms with a thread per
+// number and all sets staged in LDS).
 template <int NRC>
 __global__ void __launch_bounds__(SETS_T) k_eval_sets(int p, bool mult, const int* boxes, Tree t, const double2* E,
                                                       const double* __restrict__ rscale, double C1, double C2,
-                                                      double2* out) {
+                                                      int er, double* out) {
   constexpr int ND = 4 * NRC;
-  const int i = blockIdx.x, r = blockIdx.y;
+  const int i = blockIdx.x, r = blockIdx.y, nt = blockDim.x;
   const int b = boxes[i];
   const int T = ncoef(p), nout = mult ? p + 2 : p, To = ncoef(nout);
   extern __shared__ double2 sm[];
-  double2* D = sm;            // 12 * To
-  double2* G4 = D + 12 * To;  // 3 * To
-  double2* LC = G4 + 3 * To;  // To
-  double2* src = LC + To;     // 4 * T
+  double2* src = sm;         // 4 * T
+  double2* LC = src + 4 * T;  // To
+  double* O = reinterpret_cast<double*>(LC + To);  // To * SETS_LD
   const double2* in = E + ((int64_t)b * ND + 4 * r) * T;
-  for (int x = threadIdx.x; x < 4 * T; x += SETS_T) src[x] = in[x];
+  for (int x = threadIdx.x; x < 4 * T; x += nt) src[x] = in[x];
   __syncthreads();
-  derived_sets(src, p, nout, mult, t.h[b], C1, C2, D, G4, LC);
-  double2* o = out + ((int64_t)i * NRC + r) * To * 12;
-  for (int w = threadIdx.x; w < 12 * To; w += SETS_T) {
-    const int k = w / 12, e = w - 12 * k;
-    int m = 0, base = 0;
-    while (base + (nout - m + 1) <= k) {
-      base += nout - m + 1;
-      ++m;
+  const double h = t.h[b], ih = 1.0 / h, ih2 = ih * ih, ih3 = ih2 * ih, h2 = h * h;
+  for (int c = threadIdx.x; c < To; c += nt) {
+    int n = 0;
+    while (tri(n + 1) <= c) ++n;
+    const int m = c - tri(n);
+    double2 lc[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const double2 g = dcoef(src + k * T, p, n, m, k, mult);
+      lc[k] = make_double2(ih2 * g.x, ih2 * g.y);
     }
-    const int n = m + (k - base), c = tri(n) + m;
+    LC[c] = make_double2(h2 * (lc[0].x + lc[1].x + lc[2].x), h2 * (lc[0].y + lc[1].y + lc[2].y));
+  }
+  __syncthreads();
+  for (int c = threadIdx.x; c < To; c += nt) {
+    int n = 0;
+    while (tri(n + 1) <= c) ++n;
+    const int m = c - tri(n);
     double f = m ? 2.0 : 1.0;
     if (!mult) f *= rscale[c];
-    const double2 v = D[e * To + c];
-    o[w] = make_double2(f * v.x, f * v.y);
+    // m-major position: the columns of orders below m come first
+    double* o = O + (m * (nout + 1) - m * (m - 1) / 2 + n - m) * SETS_LD;
+    auto put = [&](int e, double2 v) {
+      o[e] = -f * v.y;
+      o[12 + e] = f * v.x;
+    };
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+#pragma unroll
+      for (int ax = 0; ax < 3; ++ax) {
+        const double2 g = dcoef(src + k * T, p, n, m, ax, mult);
+        put(3 + 3 * ax + k, make_double2(ih2 * g.x, ih2 * g.y));
+      }
+      const double2 l = getc(src + k * T, n, m, p), g4 = dcoef(src + 3 * T, p, n, m, k, mult),
+                    dc = dcoef(LC, nout, n, m, k, mult);
+      put(k, make_double2(C1 * ih * l.x + C1 * ih2 * g4.x - C2 * ih3 * dc.x,
+                          C1 * ih * l.y + C1 * ih2 * g4.y - C2 * ih3 * dc.y));
+    }
+  }
+  __syncthreads();
+  const int rg = r / er, q = r - rg * er;
+  double* o = out + (int64_t)(i * (NRC / er) + rg) * To * 24 * er + 24 * q;
+  for (int w = threadIdx.x; w < 24 * To; w += nt) {
+    const int k = w / 24, e = w - 24 * k;
+    o[(int64_t)k * 24 * er + e] = O[k * SETS_LD + e];
   }
 }
 
-// Adds the 12 sets of ER right-hand sides (at D + q stride, m-major, nmax)
-// evaluated at this lane's target, offset (vx, vy, vz) from the expansion
-// centre, box side h, to vel[q].  The harmonics are formed once for the ER
-// right-hand sides:
+// The set coefficients are the same for every lane of a wave.  They are read
+// with vector loads, 16 consecutive ones per load (lane l takes number l mod
+// 16), and each multiply-add broadcasts one of them over its row of 16 lanes
+// (DPP row_newbcast), so that the next coefficient's loads can be in flight
+// while this one is used: scalar loads of the same data (96 registers per
+// coefficient and two right-hand sides, with no room for a second batch) left
+// the wave waiting on the scalar cache, which the sets of a leaf (29 KB per
+// right-hand side at p = 16) do not fit: 15M beads, 20 right-hand sides at
+// p = 16 took 87 ms in k_eval_apply that way and take 52 ms now, 83 % of the
+// FP64 vector issue rate.  A block of multiply-adds starts with the two wait
+// states a DPP operand needs after a vector write.
+#define RPY_BC(acc, h, k) "v_fmac_f64_dpp %" #acc ", %[m], %[" #h "] row_newbcast:" #k " row_mask:0xf bank_mask:0xf\n\t"
+// the 12 imaginary parts and real parts 0..3 of s
+__device__ inline void bc_y12_x4(double m, double hx, double hy, double* s) {
+  asm("s_nop 1\n\t" RPY_BC(0, hy, 0) RPY_BC(1, hy, 1) RPY_BC(2, hy, 2) RPY_BC(3, hy, 3) RPY_BC(4, hy, 4)
+          RPY_BC(5, hy, 5) RPY_BC(6, hy, 6) RPY_BC(7, hy, 7) RPY_BC(8, hy, 8) RPY_BC(9, hy, 9) RPY_BC(10, hy, 10)
+              RPY_BC(11, hy, 11) RPY_BC(0, hx, 12) RPY_BC(1, hx, 13) RPY_BC(2, hx, 14) RPY_BC(3, hx, 15)
+      : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]), "+v"(s[4]), "+v"(s[5]), "+v"(s[6]), "+v"(s[7]), "+v"(s[8]),
+        "+v"(s[9]), "+v"(s[10]), "+v"(s[11])
+      : [m] "v"(m), [hx] "v"(hx), [hy] "v"(hy));
+}
+// real parts 4..11 of s
+__device__ inline void bc_x8(double m, double hx, double* s) {
+  asm("s_nop 1\n\t" RPY_BC(0, hx, 0) RPY_BC(1, hx, 1) RPY_BC(2, hx, 2) RPY_BC(3, hx, 3) RPY_BC(4, hx, 4)
+          RPY_BC(5, hx, 5) RPY_BC(6, hx, 6) RPY_BC(7, hx, 7)
+      : "+v"(s[4]), "+v"(s[5]), "+v"(s[6]), "+v"(s[7]), "+v"(s[8]), "+v"(s[9]), "+v"(s[10]), "+v"(s[11])
+      : [m] "v"(m), [hx] "v"(hx));
+}
+// real parts 4..11 of s, then imaginary parts 0..7 of the next right-hand side's z
+__device__ inline void bc_x8_y8(double m, double hx, double hy, double* s, double* z) {
+  asm("s_nop 1\n\t" RPY_BC(0, hx, 0) RPY_BC(1, hx, 1) RPY_BC(2, hx, 2) RPY_BC(3, hx, 3) RPY_BC(4, hx, 4)
+          RPY_BC(5, hx, 5) RPY_BC(6, hx, 6) RPY_BC(7, hx, 7) RPY_BC(8, hy, 8) RPY_BC(9, hy, 9) RPY_BC(10, hy, 10)
+              RPY_BC(11, hy, 11) RPY_BC(12, hy, 12) RPY_BC(13, hy, 13) RPY_BC(14, hy, 14) RPY_BC(15, hy, 15)
+      : "+v"(s[4]), "+v"(s[5]), "+v"(s[6]), "+v"(s[7]), "+v"(s[8]), "+v"(s[9]), "+v"(s[10]), "+v"(s[11]),
+        "+v"(z[0]), "+v"(z[1]), "+v"(z[2]), "+v"(z[3]), "+v"(z[4]), "+v"(z[5]), "+v"(z[6]), "+v"(z[7])
+      : [m] "v"(m), [hx] "v"(hx), [hy] "v"(hy));
+}
+// imaginary parts 8..11, then the 12 real parts of z
+__device__ inline void bc_y4_x12(double m, double hx, double hy, double* z) {
+  asm("s_nop 1\n\t" RPY_BC(8, hy, 0) RPY_BC(9, hy, 1) RPY_BC(10, hy, 2) RPY_BC(11, hy, 3) RPY_BC(0, hx, 4)
+          RPY_BC(1, hx, 5) RPY_BC(2, hx, 6) RPY_BC(3, hx, 7) RPY_BC(4, hx, 8) RPY_BC(5, hx, 9) RPY_BC(6, hx, 10)
+              RPY_BC(7, hx, 11) RPY_BC(8, hx, 12) RPY_BC(9, hx, 13) RPY_BC(10, hx, 14) RPY_BC(11, hx, 15)
+      : "+v"(z[0]), "+v"(z[1]), "+v"(z[2]), "+v"(z[3]), "+v"(z[4]), "+v"(z[5]), "+v"(z[6]), "+v"(z[7]), "+v"(z[8]),
+        "+v"(z[9]), "+v"(z[10]), "+v"(z[11])
+      : [m] "v"(m), [hx] "v"(hx), [hy] "v"(hy));
+}
+#undef RPY_BC
+
+// One coefficient of ER right-hand sides' sets, NV loads of 16 doubles.
+template <int ER>
+struct SetRegs {
+  static constexpr int NV = (24 * ER + 15) / 16;
+  double v[NV];
+  __device__ inline void load(const double* __restrict__ D) {
+#pragma unroll
+    for (int k = 0; k < NV; ++k) v[k] = D[16 * k];
+  }
+  // s[q][e] += x h.x - y h.y, imaginary part first
+  __device__ inline void add(double2 h, double (*s)[12]) const {
+    if constexpr (ER == 1) {
+      bc_y12_x4(v[0], h.x, h.y, s[0]);
+      bc_x8(v[1], h.x, s[0]);
+    } else {
+#pragma unroll
+      for (int q = 0; q < ER; q += 2) {
+        bc_y12_x4(v[3 * q / 2], h.x, h.y, s[q]);
+        bc_x8_y8(v[3 * q / 2 + 1], h.x, h.y, s[q], s[q + 1]);
+        bc_y4_x12(v[3 * q / 2 + 2], h.x, h.y, s[q + 1]);
+      }
+    }
+  }
+};
+
+// Adds the 12 sets of ER right-hand sides (stream D of k_eval_sets, degree
+// nmax) evaluated at this lane's target, offset (vx, vy, vz) from the
+// expansion centre, box side h, to vel[q].  All lanes of the wave must be
+// active.  The harmonics are formed once for the ER right-hand sides:
 // S_n^m = (n-m)!(n+m)! R_n^m (local; the factor is folded into the sets) or
 // I_n^m (multipole), both by
 //   h_m^m = -(2m-1) (x' + i y') h_{m-1}^{m-1},  h_0^0 = s',
 //   h_n   = (2n-1) z' h_{n-1} - ((n-1)^2 - m^2) r' h_{n-2},
 // (x', y', z', r', s') = (x, y, z, r^2, 1) or (x/r^2, y/r^2, z/r^2, 1/r^2, 1/r)
 // in box units.  Each right-hand side's sums run in the same order whatever
-// ER is.
+// ER is.  The loads run two coefficients ahead and read EV_PAD doubles past
+// the stream's end.
 template <bool MULT, int ER>
-__device__ inline void eval_sets(const double2* __restrict__ D, int64_t stride, int nmax, double vx, double vy,
-                                 double vz, double h, double C1, double (*vel)[3]) {
+__device__ inline void eval_sets(const double* __restrict__ D, int nmax, double vx, double vy, double vz, double h,
+                                 double C1, double (*vel)[3]) {
   const double ih = 1.0 / h, x = vx * ih, y = vy * ih, z = vz * ih;
   const double r2 = x * x + y * y + z * z;
   double zz, rr, ux, uy, sc;
@@ -169,14 +243,20 @@ __device__ inline void eval_sets(const double2* __restrict__ D, int64_t stride, 
   for (int q = 0; q < ER; ++q)
 #pragma unroll
     for (int e = 0; e < 12; ++e) s[q][e] = 0.0;
-  auto acc = [&](double2 hv, const double2* d) {
-#pragma unroll
-    for (int q = 0; q < ER; ++q)
-#pragma unroll
-      for (int e = 0; e < 12; ++e) s[q][e] = fma(d[q * stride + e].x, hv.x, fma(-d[q * stride + e].y, hv.y, s[q][e]));
-  };
+  const double* Dp = D + (threadIdx.x & 15);
+  SetRegs<ER> c0, c1;  // the next coefficient and the one after it
+  c0.load(Dp);
+  c1.load(Dp + 24 * ER);
+  Dp += 48 * ER;
   double2 dg = make_double2(sc, 0.0);
-  const double2* Dp = D;
+  // harmonic hv with the next coefficient
+  auto acc = [&](double2 hv) {
+    const SetRegs<ER> c = c0;
+    c0 = c1;
+    c1.load(Dp);
+    Dp += 24 * ER;
+    c.add(hv, s);
+  };
   for (int m = 0; m <= nmax; ++m) {
     if (m > 0) {
       const double f = -(2.0 * m - 1.0);
@@ -184,8 +264,7 @@ __device__ inline void eval_sets(const double2* __restrict__ D, int64_t stride, 
     }
     double2 h0 = make_double2(0.0, 0.0), h1 = dg;
     double ca = 2.0 * m + 1.0, cb = 0.0;
-    acc(h1, Dp);
-    Dp += 12;
+    acc(h1);
     int n = m + 1;
     // two degrees per trip, each overwriting the older of (h0, h1)
     for (; n + 1 <= nmax; n += 2) {
@@ -193,19 +272,17 @@ __device__ inline void eval_sets(const double2* __restrict__ D, int64_t stride, 
       h0 = make_double2(A * h1.x - Bc * h0.x, A * h1.y - Bc * h0.y);
       cb += ca;
       ca += 2.0;
-      acc(h0, Dp);
+      acc(h0);
       A = ca * zz;
       Bc = cb * rr;
       h1 = make_double2(A * h0.x - Bc * h1.x, A * h0.y - Bc * h1.y);
       cb += ca;
       ca += 2.0;
-      acc(h1, Dp + 12);
-      Dp += 24;
+      acc(h1);
     }
     if (n <= nmax) {
       const double A = ca * zz, Bc = cb * rr;
-      acc(make_double2(A * h1.x - Bc * h0.x, A * h1.y - Bc * h0.y), Dp);
-      Dp += 12;
+      acc(make_double2(A * h1.x - Bc * h0.x, A * h1.y - Bc * h0.y));
     }
   }
 #pragma unroll
@@ -217,17 +294,19 @@ __device__ inline void eval_sets(const double2* __restrict__ D, int64_t stride, 
 
 // One wave per tile (leaf box, first bead, count <= 64, leaf ordinal),
 // EV_WAVES consecutive tiles per block.  The evaluation shares the harmonics
-// of each expansion between EV_RHS right-hand sides (two: on cube-15M the
-// evaluation took 102 ms against 111 ms with one and 135 ms with four, where
-// the sums' registers cut the occupancy).
+// of each expansion between EV_RHS right-hand sides: two, whose 24 FP64 sums
+// and two coefficients in flight fit four waves per SIMD.
 constexpr int EV_WAVES = 4;
 constexpr int EV_RHS = 2;
+constexpr int EV_PAD = 48 * EV_RHS + 16;  // doubles eval_sets may read past a stream
+constexpr int eval_group(int nrc) { return nrc < EV_RHS ? nrc : EV_RHS; }
+static_assert(eval_group(2) * 1 == 2 && 4 % eval_group(4) == 0, "right-hand sides in whole groups");
 // Writes (assigns) the far-field velocity of every bead of the tile.
 template <int NRC>
-__global__ void __launch_bounds__(64 * EV_WAVES) k_eval_apply(int p, const int4* tiles, int ntiles, Tree t, List W,
+__global__ void __launch_bounds__(64 * EV_WAVES, 4) k_eval_apply(int p, const int4* tiles, int ntiles, Tree t, List W,
                                                              const int* widx,
                                                    const double* sx, const double* sy, const double* sz, int64_t n,
-                                                   const double2* __restrict__ DL, const double2* __restrict__ DW,
+                                                   const double* __restrict__ DL, const double* __restrict__ DW,
                                                    double C1, double* __restrict__ u) {
   // consecutive tiles (mostly of one leaf) share a block, hence a CU and its
   // scalar cache, and walk the same set coefficients at about the same time
@@ -240,28 +319,27 @@ __global__ void __launch_bounds__(64 * EV_WAVES) k_eval_apply(int p, const int4*
   const int T = ncoef(p), To = ncoef(p + 2);
   const double cx = t.cx[b], cy = t.cy[b], cz = t.cz[b], h = t.h[b];
   const int w0 = W.off[b], w1 = W.off[b + 1];
-  // all loads before the first store, so that the set arrays can be read
-  // through the scalar cache
-  double vel[NRC][3];
-  constexpr int ER = NRC < EV_RHS ? NRC : EV_RHS;
-  static_assert(NRC % ER == 0, "right-hand sides in whole groups of ER");
-  for (int r = 0; r < NRC; ++r) vel[r][0] = vel[r][1] = vel[r][2] = 0.0;
+  constexpr int ER = eval_group(NRC);
+#pragma unroll 1
   for (int r = 0; r < NRC; r += ER) {
-    eval_sets<false, ER>(DL + ((int64_t)tl.w * NRC + r) * T * 12, (int64_t)T * 12, p, px - cx, py - cy, pz - cz, h,
-                         C1, vel + r);
+    double vel[ER][3];
+#pragma unroll
+    for (int q = 0; q < ER; ++q) vel[q][0] = vel[q][1] = vel[q][2] = 0.0;
+    eval_sets<false, ER>(DL + (int64_t)(tl.w * (NRC / ER) + r / ER) * T * 24 * ER, p, px - cx, py - cy, pz - cz, h, C1,
+                         vel);
     for (int e = w0; e < w1; ++e) {
       const int C = W.ent[e];
       const int wi = widx[C];
       if (wi < 0) continue;  // few beads: summed directly with the near field
-      eval_sets<true, ER>(DW + ((int64_t)wi * NRC + r) * To * 12, (int64_t)To * 12, p + 2, px - t.cx[C],
-                          py - t.cy[C], pz - t.cz[C], t.h[C], C1, vel + r);
+      eval_sets<true, ER>(DW + (int64_t)(wi * (NRC / ER) + r / ER) * To * 24 * ER, p + 2, px - t.cx[C], py - t.cy[C],
+                          pz - t.cz[C], t.h[C], C1, vel);
     }
+    if (lane < tl.z)
+#pragma unroll
+      for (int q = 0; q < ER; ++q)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) u[((int64_t)(r + q) * 3 + k) * n + tl.y + lane] = vel[q][k];
   }
-  if (lane < tl.z)
-#pragma unroll
-    for (int r = 0; r < NRC; ++r)
-#pragma unroll
-      for (int k = 0; k < 3; ++k) u[((int64_t)r * 3 + k) * n + tl.y + lane] = vel[r][k];
 }
 
 // ------------------------------------------- second evaluation approach ---
@@ -400,7 +478,7 @@ __global__ void __launch_bounds__(64 * EV_WAVES) k_eval_poly_apply(int p, const 
                                                                    List W, const int* widx, const double* sx,
                                                                    const double* sy, const double* sz, int64_t n,
                                                                    const double* __restrict__ DP,
-                                                                   const double2* __restrict__ DW, double C1,
+                                                                   const double* __restrict__ DW, double C1,
                                                                    double* __restrict__ u) {
   const int ti = blockIdx.x * EV_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (ti >= ntiles) return;
@@ -438,8 +516,8 @@ __global__ void __launch_bounds__(64 * EV_WAVES) k_eval_poly_apply(int p, const 
       const int C = W.ent[e];
       const int wi = widx[C];
       if (wi < 0) continue;  // few beads: summed directly with the near field
-      eval_sets<true, 1>(DW + ((int64_t)wi * NRC + r) * To * 12, 0, p + 2, px - t.cx[C], py - t.cy[C],
-                         pz - t.cz[C], t.h[C], C1, vel + r);
+      eval_sets<true, 1>(DW + (int64_t)(wi * NRC + r) * To * 24, p + 2, px - t.cx[C], py - t.cy[C], pz - t.cz[C],
+                         t.h[C], C1, vel + r);
     }
   if (lane < tl.z)
 #pragma unroll
@@ -470,20 +548,24 @@ hipError_t launch_eval(const Launch& l, const EvalPlan& ep, Exp e, double* u) {
   const int p = l.p;
   const double C1 = 1.0 / (8.0 * PI * l.eta), C2 = l.a * l.a / (12.0 * PI * l.eta);
   auto ks = k_eval_sets<NRC>;
-  const size_t shm_l = sizeof(double2) * (16 * ncoef(p) + 4 * ncoef(p));
-  const size_t shm_m = sizeof(double2) * (16 * ncoef(p + 2) + 4 * ncoef(p));
+  const size_t shm_l = sizeof(double2) * (4 * ncoef(p) + ncoef(p)) + sizeof(double) * SETS_LD * ncoef(p);
+  const size_t shm_m = sizeof(double2) * (4 * ncoef(p) + ncoef(p + 2)) + sizeof(double) * SETS_LD * ncoef(p + 2);
+  const auto sets_t = [](int q) { return std::min(SETS_T, (ncoef(q) + 63) / 64 * 64); };
   hipError_t he = hipFuncSetAttribute(reinterpret_cast<const void*>(ks), hipFuncAttributeMaxDynamicSharedMemorySize,
                                       (int)shm_m);
   if (he != hipSuccess) return he;
+  double* DL = reinterpret_cast<double*>(e.DL);
+  double* DW = reinterpret_cast<double*>(e.DW);
+  const int er = ep.mode == EVAL_POLY ? 1 : eval_group(NRC);  // right-hand sides per set stream
   if (ep.nwbig > 0)
-    ks<<<dim3(ep.nwbig, NRC), SETS_T, shm_m, l.s>>>(p, true, ep.wbig, B->tree, e.M, l.tb->rscale, C1, C2, e.DW);
+    ks<<<dim3(ep.nwbig, NRC), sets_t(p + 2), shm_m, l.s>>>(p, true, ep.wbig, B->tree, e.M, l.tb->rscale, C1, C2, er, DW);
   he = hipGetLastError();
   if (he != hipSuccess) return he;
   if (ep.mode == EVAL_POLY) {
     // second approach: component polynomials per leaf (DL's buffer holds them)
     constexpr int ND = 4 * NRC;
     const int NM = mono_count(p);
-    double* DP = reinterpret_cast<double*>(e.DL);
+    double* DP = DL;
     const size_t shm_c = sizeof(double) * 2 * ncoef(p) * ND, shm_a = sizeof(double) * 4 * NM;
     auto kc = k_poly_conv<ND>;
     auto ka = k_poly_assemble<NRC>;
@@ -496,14 +578,14 @@ hipError_t launch_eval(const Launch& l, const EvalPlan& ep, Exp e, double* u) {
     ka<<<dim3(B->nleaf, NRC), POLY_T, shm_a, l.s>>>(p, B->leaf_ids, B->tree, e.PV, C1, C2, DP);
     if (ep.tiles.n > 0)
       k_eval_poly_apply<NRC><<<(ep.tiles.n + EV_WAVES - 1) / EV_WAVES, 64 * EV_WAVES, 0, l.s>>>(
-          p, ep.tiles.t, ep.tiles.n, B->tree, B->lists[LW], ep.widx, B->sx, B->sy, B->sz, B->n, DP, e.DW, C1, u);
+          p, ep.tiles.t, ep.tiles.n, B->tree, B->lists[LW], ep.widx, B->sx, B->sy, B->sz, B->n, DP, DW, C1, u);
     return hipGetLastError();
   }
-  ks<<<dim3(B->nleaf, NRC), SETS_T, shm_l, l.s>>>(p, false, B->leaf_ids, B->tree, e.L, l.tb->rscale, C1, C2, e.DL);
+  ks<<<dim3(B->nleaf, NRC), sets_t(p), shm_l, l.s>>>(p, false, B->leaf_ids, B->tree, e.L, l.tb->rscale, C1, C2, er, DL);
   if (ep.tiles.n > 0)
     k_eval_apply<NRC><<<(ep.tiles.n + EV_WAVES - 1) / EV_WAVES, 64 * EV_WAVES, 0, l.s>>>(
         p, ep.tiles.t, ep.tiles.n, B->tree, B->lists[LW], ep.widx, B->sx, B->sy, B->sz,
-                                                  B->n, e.DL, e.DW, C1, u);
+                                                  B->n, DL, DW, C1, u);
   return hipGetLastError();
 }
 
@@ -629,14 +711,15 @@ void free_eval_plan(EvalPlan* ep) {
 int64_t eval_sets_bytes(const Built* B, const EvalPlan& ep, int p, int nrc, int64_t* dw_bytes, int64_t* pv_bytes) {
   const int64_t per = (int64_t)sizeof(double2) * 12 * nrc;
   const int64_t nleaf = std::max(B->nleaf, 1);
-  *dw_bytes = per * ncoef(p + 2) * std::max(ep.nwbig, 1);
+  const int64_t pad = sizeof(double) * EV_PAD;
+  *dw_bytes = per * ncoef(p + 2) * std::max(ep.nwbig, 1) + pad;
   if (ep.mode == EVAL_POLY) {
     // component polynomials (in DL's buffer) and the density polynomials
     *pv_bytes = (int64_t)sizeof(double) * 4 * nrc * mono_count(p) * nleaf;
     return (int64_t)sizeof(double) * 3 * nrc * mono_count(p) * nleaf;
   }
   *pv_bytes = sizeof(double);
-  return per * ncoef(p) * nleaf;
+  return per * ncoef(p) * nleaf + pad;
 }
 
 hipError_t run_eval(const Launch& l, const EvalPlan& ep, int nrc, Exp e, double* u) {
