@@ -43,23 +43,29 @@ __global__ void k_tile_fill(const int* leaves, int nleaf, Tree t, int tile, cons
   for (int s = t.begin[b]; s < t.end[b]; s += tile) out[o++] = make_int4(b, s, min(tile, t.end[b] - s), i);
 }
 
-// Bounding box of each tile's beads: lo xyz, hi xyz.
-__global__ void k_tile_box(const int4* tiles, int nt, const double* sx, const double* sy, const double* sz,
-                           double* box) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nt) return;
+// Bounding box of each tile's beads: lo xyz, hi xyz.  One wave per tile (a
+// thread per tile read its 128 beads one after another: 56 us for 2,048
+// tiles).
+__global__ void __launch_bounds__(64) k_tile_box(const int4* tiles, const double* sx, const double* sy,
+                                                 const double* sz, double* box) {
+  const int i = blockIdx.x, lane = threadIdx.x;
   const int4 tl = tiles[i];
-  double lo[3] = {sx[tl.y], sy[tl.y], sz[tl.y]}, hi[3] = {lo[0], lo[1], lo[2]};
-  for (int j = tl.y + 1; j < tl.y + tl.z; ++j) {
-    const double v[3] = {sx[j], sy[j], sz[j]};
-    for (int k = 0; k < 3; ++k) {
-      lo[k] = fmin(lo[k], v[k]);
-      hi[k] = fmax(hi[k], v[k]);
-    }
-  }
+  const double* c[3] = {sx + tl.y, sy + tl.y, sz + tl.y};
   for (int k = 0; k < 3; ++k) {
-    box[6 * (int64_t)i + k] = lo[k];
-    box[6 * (int64_t)i + 3 + k] = hi[k];
+    double lo = c[k][0], hi = lo;
+    for (int j = lane; j < tl.z; j += 64) {
+      const double v = c[k][j];
+      lo = fmin(lo, v);
+      hi = fmax(hi, v);
+    }
+    for (int d = 1; d < 64; d <<= 1) {
+      lo = fmin(lo, __shfl_xor(lo, d));
+      hi = fmax(hi, __shfl_xor(hi, d));
+    }
+    if (lane == 0) {
+      box[6 * (int64_t)i + k] = lo;
+      box[6 * (int64_t)i + 3 + k] = hi;
+    }
   }
 }
 
@@ -83,7 +89,7 @@ int make_tiles(const Built* B, int tile, Tiles* out, hipStream_t s, Error* err) 
   k_tile_fill<<<nblk(B->nleaf, 256), 256, 0, s>>>(B->leaf_ids, B->nleaf, B->tree, tile, off, out->t);
   RPY_HIP(hipGetLastError());
   RPY_HIP(hipMalloc(&out->box, sizeof(double) * 6 * std::max(out->n, 1)));
-  if (out->n > 0) k_tile_box<<<nblk(out->n, 256), 256, 0, s>>>(out->t, out->n, B->sx, B->sy, B->sz, out->box);
+  if (out->n > 0) k_tile_box<<<out->n, 64, 0, s>>>(out->t, B->sx, B->sy, B->sz, out->box);
   RPY_HIP(hipGetLastError());
   RPY_HIP(hipStreamSynchronize(s));
   (void)hipFree(cnt); (void)hipFree(off); (void)hipFree(tmp);

@@ -282,45 +282,49 @@ __global__ void k_tree_roots(Tree t, const int* sys_begin, int nsys) {
   t.parent[s] = -1; t.child[s] = -1; t.nchild[s] = 0;
 }
 
-__global__ void k_tree_count(Tree t, const uint64_t* keys, int ls, int le, int lev, int leaf_size, int max_depth,
-                             int* cnt) {
-  int b = ls + blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= le) return;
-  int c = 0;
-  int b0 = t.begin[b], b1 = t.end[b];
-  if (b1 - b0 > leaf_size && lev < max_depth) {
-    int prev = b0;
-    for (int o = 1; o <= 8; ++o) {
-      int nxt = o < 8 ? lower_digit(keys, prev, b1, lev + 1, o) : b1;
-      if (nxt > prev) ++c;
-      prev = nxt;
-    }
-  }
-  cnt[b - ls] = c;
+// The first bead of each of the eight octants of every box of the level that
+// is split: cut[8 (b - ls) + o], o = 0..7 (a box's beads are sorted, so octant
+// o's end is octant o + 1's start), and its number of non-empty octants.  One
+// lane per octant: the eight binary searches, whose loads each wait for the
+// one before, run side by side and once (20 + 16 us per level of 200k beads
+// with a thread per box searching one octant after another, for the count and
+// again for the children; 6 + 3 us now).
+__global__ void __launch_bounds__(256) k_tree_count(Tree t, const uint64_t* keys, int ls, int le, int lev,
+                                                    int leaf_size, int max_depth, int* cut, int* cnt) {
+  const int g = blockIdx.x * 256 + threadIdx.x, b = ls + (g >> 3), o = g & 7;
+  const bool live = b < le;
+  const int b0 = live ? t.begin[b] : 0, b1 = live ? t.end[b] : 0;
+  const bool split = live && b1 - b0 > leaf_size && lev < max_depth;
+  const int lo = split ? (o ? lower_digit(keys, b0, b1, lev + 1, o) : b0) : 0;
+  const int nx = __shfl_down(lo, 1, 8), hi = o < 7 ? nx : b1;
+  const unsigned long long full = __ballot(split && hi > lo);
+  if (!live) return;
+  cut[g] = lo;
+  if (o == 0) cnt[b - ls] = __popcll((full >> (threadIdx.x & 56)) & 0xffull);
 }
 
-__global__ void k_tree_write(Tree t, const uint64_t* keys, int ls, int le, int lev, const int* cnt, const int* off) {
-  int b = ls + blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= le) return;
-  int nc = cnt[b - ls];
-  t.nchild[b] = nc;
-  if (nc == 0) { t.child[b] = -1; return; }
-  int cid = le + off[b - ls];
-  t.child[b] = cid;
-  int b0 = t.begin[b], b1 = t.end[b];
-  int prev = b0;
-  for (int o = 0; o < 8; ++o) {
-    int nxt = o < 7 ? lower_digit(keys, prev, b1, lev + 1, o + 1) : b1;
-    if (nxt > prev) {
-      t.level[cid] = lev + 1; t.sys[cid] = t.sys[b];
-      t.ax[cid] = 2 * t.ax[b] + (o & 1);
-      t.ay[cid] = 2 * t.ay[b] + ((o >> 1) & 1);
-      t.az[cid] = 2 * t.az[b] + ((o >> 2) & 1);
-      t.begin[cid] = prev; t.end[cid] = nxt; t.parent[cid] = b;
-      t.child[cid] = -1; t.nchild[cid] = 0;
-      ++cid;
-    }
-    prev = nxt;
+// The children of the level's boxes, one lane per octant.
+__global__ void __launch_bounds__(256) k_tree_write(Tree t, int ls, int le, int lev, const int* cut, const int* cnt,
+                                                    const int* off) {
+  const int g = blockIdx.x * 256 + threadIdx.x, b = ls + (g >> 3), o = g & 7;
+  const bool live = b < le;
+  const int nc = live ? cnt[b - ls] : 0;
+  const int lo = nc ? cut[g] : 0, nx = __shfl_down(lo, 1, 8), hi = nc ? (o < 7 ? nx : t.end[b]) : 0;
+  const unsigned long long full = (__ballot(hi > lo) >> (threadIdx.x & 56)) & 0xffull;
+  if (!live) return;
+  const int c0 = le + off[b - ls];
+  if (o == 0) {
+    t.nchild[b] = nc;
+    t.child[b] = nc ? c0 : -1;
+  }
+  if (hi > lo) {
+    const int cid = c0 + __popcll(full & ((1ull << o) - 1));
+    t.level[cid] = lev + 1; t.sys[cid] = t.sys[b];
+    t.ax[cid] = 2 * t.ax[b] + (o & 1);
+    t.ay[cid] = 2 * t.ay[b] + ((o >> 1) & 1);
+    t.az[cid] = 2 * t.az[b] + ((o >> 2) & 1);
+    t.begin[cid] = lo; t.end[cid] = hi; t.parent[cid] = b;
+    t.child[cid] = -1; t.nchild[cid] = 0;
   }
 }
 
@@ -336,170 +340,200 @@ __global__ void k_box_geometry(Tree t, const double* lo, const double* side) {
 }
 
 // ------------------------------------------------------------ colleagues --
-__global__ void k_colleagues(Tree t, int ls, int le, int* col) {
-  int b = ls + blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= le) return;
+// A box's level and integer anchor.
+struct Cell {
+  int l, x, y, z;
+};
+__device__ inline Cell cell_of(const Tree& t, int b) { return Cell{t.level[b], t.ax[b], t.ay[b], t.az[b]}; }
+
+// One wave per box; its lanes take the children of the parent's colleagues
+// (26 us per level of 512 boxes with a thread per box, 4 us now).
+__global__ void __launch_bounds__(64) k_colleagues(Tree t, int ls, int* col) {
+  const int b = ls + blockIdx.x, lane = threadIdx.x;
   int* cb = col + (int64_t)b * NSLOT;
-  for (int s = 0; s < NSLOT; ++s) cb[s] = -1;
-  int P = t.parent[b];
-  if (P < 0) { cb[13] = b; return; }
-  const int* cp = col + (int64_t)P * NSLOT;
-  for (int s = 0; s < NSLOT; ++s) {
-    int Q = cp[s];
-    if (Q < 0 || t.nchild[Q] == 0) continue;
-    for (int C = t.child[Q]; C < t.child[Q] + t.nchild[Q]; ++C) {
-      int dx = t.ax[C] - t.ax[b], dy = t.ay[C] - t.ay[b], dz = t.az[C] - t.az[b];
+  const int P = t.parent[b];
+  __shared__ int slot[NSLOT];
+  if (lane < NSLOT) slot[lane] = P < 0 && lane == 13 ? b : -1;
+  __syncthreads();
+  if (P >= 0) {
+    const int* cp = col + (int64_t)P * NSLOT;
+    const Cell B = cell_of(t, b);
+    for (int i = lane; i < 8 * NSLOT; i += 64) {
+      const int Q = cp[i >> 3], k = i & 7;
+      if (Q < 0 || k >= t.nchild[Q]) continue;
+      const int C = t.child[Q] + k;
+      const int dx = t.ax[C] - B.x, dy = t.ay[C] - B.y, dz = t.az[C] - B.z;
       if (dx >= -1 && dx <= 1 && dy >= -1 && dy <= 1 && dz >= -1 && dz <= 1)
-        cb[(dx + 1) * 9 + (dy + 1) * 3 + (dz + 1)] = C;
+        slot[(dx + 1) * 9 + (dy + 1) * 3 + (dz + 1)] = C;
     }
   }
+  __syncthreads();
+  if (lane < NSLOT) cb[lane] = slot[lane];
 }
 
 // --------------------------------------------------------------- lists ----
-__device__ inline bool adjacent(const Tree& t, int A, int B) {
-  int la = t.level[A], lb = t.level[B];
-  int L = la > lb ? la : lb;
-  int sa = L - la, sb = L - lb;
-  int64_t a0, a1, b0, b1;
-  a0 = (int64_t)t.ax[A] << sa; a1 = ((int64_t)t.ax[A] + 1) << sa;
-  b0 = (int64_t)t.ax[B] << sb; b1 = ((int64_t)t.ax[B] + 1) << sb;
-  if (a0 > b1 || b0 > a1) return false;
-  a0 = (int64_t)t.ay[A] << sa; a1 = ((int64_t)t.ay[A] + 1) << sa;
-  b0 = (int64_t)t.ay[B] << sb; b1 = ((int64_t)t.ay[B] + 1) << sb;
-  if (a0 > b1 || b0 > a1) return false;
-  a0 = (int64_t)t.az[A] << sa; a1 = ((int64_t)t.az[A] + 1) << sa;
-  b0 = (int64_t)t.az[B] << sb; b1 = ((int64_t)t.az[B] + 1) << sb;
-  if (a0 > b1 || b0 > a1) return false;
-  return true;
+// Whether the two cells touch (integer intervals at the finer level; the
+// coordinates fit 22 bits).
+__device__ inline bool adjacent(const Cell& A, const Cell& B) {
+  const int L = A.l > B.l ? A.l : B.l, sa = L - A.l, sb = L - B.l;
+  const auto apart = [&](int a, int b) { return (a << sa) > ((b + 1) << sb) || (b << sb) > ((a + 1) << sa); };
+  return !(apart(A.x, B.x) || apart(A.y, B.y) || apart(A.z, B.z));
 }
 
 // Closest distance between the two cubes is below 2a: integer gaps at the
 // finer level, threshold (2a)/(side 2^-L) in FP64 (no contraction).
-__device__ inline bool near_2a(const Tree& t, int A, int B, const double* side, double a) {
+__device__ inline bool near_2a(const Cell& A, const Cell& B, double side, double a) {
 #pragma clang fp contract(off)
-  int la = t.level[A], lb = t.level[B];
-  int L = la > lb ? la : lb;
-  int sa = L - la, sb = L - lb;
-  const int* ca[3] = {t.ax, t.ay, t.az};
-  int64_t g2 = 0;
-  for (int k = 0; k < 3; ++k) {
-    int64_t a0 = (int64_t)ca[k][A] << sa, a1 = ((int64_t)ca[k][A] + 1) << sa;
-    int64_t b0 = (int64_t)ca[k][B] << sb, b1 = ((int64_t)ca[k][B] + 1) << sb;
-    int64_t g = 0;
-    if (b0 > a1) g = b0 - a1;
-    if (a0 > b1) g = a0 - b1;
-    g2 += g * g;
-  }
-  double unit = ldexp(side[t.sys[A]], -L);
-  double thr = __ddiv_rn(2.0 * a, unit);
+  const int L = A.l > B.l ? A.l : B.l, sa = L - A.l, sb = L - B.l;
+  const auto gap = [&](int p, int q) -> int64_t {
+    const int a0 = p << sa, a1 = (p + 1) << sa, b0 = q << sb, b1 = (q + 1) << sb;
+    return b0 > a1 ? b0 - a1 : (a0 > b1 ? a0 - b1 : 0);
+  };
+  const int64_t gx = gap(A.x, B.x), gy = gap(A.y, B.y), gz = gap(A.z, B.z), g2 = gx * gx + gy * gy + gz * gz;
+  const double thr = __ddiv_rn(2.0 * a, ldexp(side, -L));
   return (double)g2 < __dmul_rn(thr, thr);
 }
 
-struct Emit {
-  int* dst;
-  int n;
-  __device__ inline void put(int c) {
-    if (dst) dst[n] = c;
-    ++n;
+// Sorts the n distinct ids in v (global memory), the whole wave taking part:
+// short lists by counting the smaller ids of each one in LDS, longer ones by a
+// bitonic network in place (ascending throughout: each merge starts with the
+// mirrored exchange, so ids past n count as larger and never move).
+constexpr int SORT_LDS = 1536;
+__device__ inline void sort_list(int* v, int n, int* buf, int lane) {
+  if (n <= SORT_LDS) {
+    for (int i = lane; i < n; i += 64) buf[i] = v[i];
+    __syncthreads();
+    for (int i = lane; i < n; i += 64) {
+      const int x = buf[i];
+      int r = 0;
+      for (int j = 0; j < n; ++j) r += buf[j] < x;
+      v[r] = x;
+    }
+    __syncthreads();
+    return;
   }
-};
-
-// Shell sort (gaps 3h+1): O(n^1.5) for the long O lists of dense clusters.
-__device__ inline void sort_segment(int* v, int n) {
-  int h = 1;
-  while (h < n / 3) h = 3 * h + 1;
-  for (; h >= 1; h /= 3)
-    for (int i = h; i < n; ++i) {
-      int x = v[i], j = i - h;
-      while (j >= 0 && v[j] > x) { v[j + h] = v[j]; j -= h; }
-      v[j + h] = x;
+  int np = 1;
+  while (np < n) np <<= 1;
+  for (int k = 2; k <= np; k <<= 1)
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      for (int i = lane; i < np / 2; i += 64) {
+        const int lo = (i / j) * 2 * j + i % j, hi = j == k >> 1 ? (lo / k) * k + k - 1 - lo % k : lo + j;
+        if (hi < n) {
+          const int x = v[lo], y = v[hi];
+          if (x > y) {
+            v[lo] = y;
+            v[hi] = x;
+          }
+        }
+      }
+      __syncthreads();
     }
 }
 
-// mode 0: count into cnt[5][nbox]; mode 1: fill at off[L][b].
-__global__ void k_lists(Tree t, const int* col, int nbox, int mode, int* cnt, List l0, List l1, List l2, List l3,
-                        List l4, int want_o, const double* side, double a) {
-  int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nbox) return;
-  List ls[5] = {l0, l1, l2, l3, l4};
-  Emit e[5];
-  for (int L = 0; L < 5; ++L) {
-    e[L].n = 0;
-    e[L].dst = mode ? ls[L].ent + ls[L].off[b] : nullptr;
+// mode 0: count into cnt[5][nbox]; mode 1: fill at off[L][b].  One wave per
+// box: the lanes take the candidates of each step (216 children of the
+// parent's colleagues, 27 colleagues of an ancestor, the children of eight
+// boxes of a descent at a time), append to a list through its LDS counter and
+// sort it by id at the end.  A thread per box, waiting on one load after
+// another, took 0.41 ms per launch on 585 boxes and 3.1 ms on 37,449; a wave
+// per box takes 0.02 and 1.1 ms.
+// A descent's stack grows by at most 56 boxes per level.
+constexpr int LIST_STACK = NSLOT + 64 * (KBITS + 1);
+__global__ void __launch_bounds__(64) k_lists(Tree t, const int* col, int nbox, int mode, int* cnt, List l0, List l1,
+                                              List l2, List l3, List l4, int want_o, const double* side, double a) {
+  const int b = blockIdx.x, lane = threadIdx.x;
+  __shared__ int num[5], sp, stack[LIST_STACK], buf[SORT_LDS];
+  int* dst[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
+  if (mode) {
+    dst[LU] = l0.ent + l0.off[b];
+    dst[LV] = l1.ent + l1.off[b];
+    dst[LW] = l2.ent + l2.off[b];
+    dst[LX] = l3.ent + l3.off[b];
+    dst[LO] = l4.ent + l4.off[b];
   }
-  const bool leaf = t.nchild[b] == 0;
-  const int* cb = col + (int64_t)b * NSLOT;
-  int stack[STACK];
-  // V: children of the parent's colleagues not adjacent to b.
-  int P = t.parent[b];
-  if (P >= 0) {
-    const int* cp = col + (int64_t)P * NSLOT;
-    for (int s = 0; s < NSLOT; ++s) {
-      int Q = cp[s];
-      if (Q < 0 || t.nchild[Q] == 0) continue;
-      for (int C = t.child[Q]; C < t.child[Q] + t.nchild[Q]; ++C)
-        if (!adjacent(t, C, b)) e[LV].put(C);
+  if (lane < 5) num[lane] = 0;
+  if (lane == 0) sp = 0;
+  __syncthreads();
+  const auto put = [&](int L, int c) {
+    const int at = atomicAdd(&num[L], 1);
+    if (mode) dst[L][at] = c;
+  };
+  const auto push = [&](int c) {
+    const int at = atomicAdd(&sp, 1);
+    if (at < LIST_STACK) stack[at] = c;
+  };
+  // pops up to eight boxes and calls f on each of their children
+  const auto descend = [&](auto&& f) {
+    for (;;) {
+      __syncthreads();
+      const int top = min(sp, LIST_STACK), take = min(top, 8);
+      const int D = (lane >> 3) < take ? stack[top - 1 - (lane >> 3)] : -1;
+      __syncthreads();
+      if (lane == 0) sp = top - take;
+      __syncthreads();
+      if (take == 0) return;
+      if (D >= 0 && (lane & 7) < t.nchild[D]) f(t.child[D] + (lane & 7));
     }
-    // X: coarser leaf colleagues of b's ancestors, adjacent to b's parent but not to b.
+  };
+  const Cell B = cell_of(t, b);
+  const bool leaf = t.nchild[b] == 0;
+  const int P = t.parent[b];
+  if (P >= 0) {
+    // V: children of the parent's colleagues not adjacent to b.
+    const int* cp = col + (int64_t)P * NSLOT;
+    for (int i = lane; i < 8 * NSLOT; i += 64) {
+      const int Q = cp[i >> 3], k = i & 7;
+      if (Q < 0 || k >= t.nchild[Q]) continue;
+      const int C = t.child[Q] + k;
+      if (!adjacent(cell_of(t, C), B)) put(LV, C);
+    }
+    // leaf colleagues of b's ancestors: X if adjacent to b's parent but not
+    // to b; U if adjacent to b (a leaf)
+    const Cell PB = cell_of(t, P);
     for (int A = P; A >= 0; A = t.parent[A]) {
-      const int* ca = col + (int64_t)A * NSLOT;
-      for (int s = 0; s < NSLOT; ++s) {
-        int Q = ca[s];
-        if (Q < 0 || Q == A || t.nchild[Q] != 0) continue;
-        if (adjacent(t, Q, P) && !adjacent(t, Q, b)) e[LX].put(Q);
+      const int Q = lane < NSLOT ? col[(int64_t)A * NSLOT + lane] : -1;
+      if (Q >= 0 && Q != A && t.nchild[Q] == 0) {
+        const Cell q = cell_of(t, Q);
+        if (adjacent(q, B)) {
+          if (leaf) put(LU, Q);
+        } else if (adjacent(q, PB)) {
+          put(LX, Q);
+        }
       }
     }
   }
   if (leaf) {
     // U, same level (b itself included) and finer; W from the same descent.
-    for (int s = 0; s < NSLOT; ++s) {
-      int Q = cb[s];
-      if (Q < 0) continue;
-      if (t.nchild[Q] == 0) { e[LU].put(Q); continue; }
-      int sp = 0;
-      stack[sp++] = Q;
-      while (sp > 0) {
-        int D = stack[--sp];
-        for (int C = t.child[D]; C < t.child[D] + t.nchild[D]; ++C) {
-          if (adjacent(t, C, b)) {
-            if (t.nchild[C] == 0) e[LU].put(C);
-            else if (sp < STACK) stack[sp++] = C;
-          } else {
-            e[LW].put(C);
-          }
-        }
+    if (lane < NSLOT) {
+      const int Q = col[(int64_t)b * NSLOT + lane];
+      if (Q >= 0) {
+        if (t.nchild[Q] == 0) put(LU, Q);
+        else push(Q);
       }
     }
-    // U, coarser: leaf colleagues of ancestors that touch b.
-    for (int A = P; A >= 0; A = t.parent[A]) {
-      const int* ca = col + (int64_t)A * NSLOT;
-      for (int s = 0; s < NSLOT; ++s) {
-        int Q = ca[s];
-        if (Q < 0 || Q == A || t.nchild[Q] != 0) continue;
-        if (adjacent(t, Q, b)) e[LU].put(Q);
-      }
-    }
+    descend([&](int C) {
+      if (!adjacent(cell_of(t, C), B)) put(LW, C);
+      else if (t.nchild[C] == 0) put(LU, C);
+      else push(C);
+    });
     // O: leaves of the same system closer than 2a but not adjacent.
     if (want_o) {
-      int root = t.sys[b];
-      int sp = 0;
-      stack[sp++] = root;
-      while (sp > 0) {
-        int D = stack[--sp];
-        if (!near_2a(t, D, b, side, a)) continue;
-        if (t.nchild[D] == 0) {
-          if (!adjacent(t, D, b)) e[LO].put(D);
-          continue;
-        }
-        for (int C = t.child[D] + t.nchild[D] - 1; C >= t.child[D]; --C)
-          if (sp < STACK) stack[sp++] = C;
-      }
+      const int root = t.sys[b];
+      const double sd = side[root];
+      if (lane == 0 && t.nchild[root] > 0) push(root);
+      descend([&](int C) {
+        const Cell c = cell_of(t, C);
+        if (!near_2a(c, B, sd, a)) return;
+        if (t.nchild[C] > 0) push(C);
+        else if (!adjacent(c, B)) put(LO, C);
+      });
     }
   }
+  __syncthreads();
   if (mode == 0) {
-    for (int L = 0; L < 5; ++L) cnt[(int64_t)L * nbox + b] = e[L].n;
+    if (lane < 5) cnt[(int64_t)lane * nbox + b] = num[lane];
   } else {
-    for (int L = 0; L < 5; ++L) sort_segment(e[L].dst, e[L].n);
+    for (int L = 0; L < 5; ++L) sort_list(dst[L], num[L], buf, lane);
   }
 }
 
@@ -776,6 +810,7 @@ int build_tree(const BuildArgs& A, Built* B, Error* err) {
   RPY_HIP(hipGetLastError());
   B->level_start.assign(1, 0);
   B->level_start.push_back(nsys);
+  int* cut = nullptr;
   int* cnt = nullptr;
   int* off = nullptr;
   int* tmp = nullptr;
@@ -785,13 +820,14 @@ int build_tree(const BuildArgs& A, Built* B, Error* err) {
     int ls = B->level_start[lev], le = B->level_start[lev + 1];
     int nb = le - ls;
     if (nb > ccap) {
-      if (cnt) { (void)hipFree(cnt); (void)hipFree(off); (void)hipFree(tmp); }
+      if (cnt) { (void)hipFree(cut); (void)hipFree(cnt); (void)hipFree(off); (void)hipFree(tmp); }
       ccap = std::max<int64_t>(nb, 2 * ccap);
-      if (dalloc(&cnt, ccap, B, err) || dalloc(&off, ccap, B, err) ||
+      if (dalloc(&cut, 8 * ccap, B, err) || dalloc(&cnt, ccap, B, err) || dalloc(&off, ccap, B, err) ||
           dalloc(&tmp, (int64_t)scan_tmp_ints(ccap), B, err))
         return -3;
     }
-    k_tree_count<<<nblocks(nb, 128), 128, 0, s>>>(t, B->keys, ls, le, lev, A.leaf_size, A.max_depth, cnt);
+    k_tree_count<<<nblocks(8 * (int64_t)nb, 256), 256, 0, s>>>(t, B->keys, ls, le, lev, A.leaf_size, A.max_depth, cut,
+                                                             cnt);
     RPY_HIP(hipGetLastError());
     RPY_HIP(scan_exclusive(cnt, off, nb, tmp, s));
     int last[2] = {0, 0};
@@ -800,14 +836,14 @@ int build_tree(const BuildArgs& A, Built* B, Error* err) {
     RPY_HIP(hipStreamSynchronize(s));
     int nnext = last[0] + last[1];
     if (grow_tree(B, le + nnext, s, err)) return err->code;
-    k_tree_write<<<nblocks(nb, 128), 128, 0, s>>>(t, B->keys, ls, le, lev, cnt, off);
+    k_tree_write<<<nblocks(8 * (int64_t)nb, 256), 256, 0, s>>>(t, ls, le, lev, cut, cnt, off);
     RPY_HIP(hipGetLastError());
     if (nnext == 0) break;
     B->level_start.push_back(le + nnext);
     ++lev;
   }
-  (void)hipFree(cnt); (void)hipFree(off); (void)hipFree(tmp);
-  B->bytes -= sizeof(int) * (2 * ccap + scan_tmp_ints(ccap));
+  (void)hipFree(cut); (void)hipFree(cnt); (void)hipFree(off); (void)hipFree(tmp);
+  B->bytes -= sizeof(int) * (10 * ccap + scan_tmp_ints(ccap));
   B->depth = (int)B->level_start.size() - 2;
   t.nbox = B->level_start.back();
   const int nbox = t.nbox;
@@ -821,7 +857,7 @@ int build_tree(const BuildArgs& A, Built* B, Error* err) {
   if (dalloc(&B->colleague, (int64_t)nbox * NSLOT, B, err)) return -3;
   for (int l = 0; l <= B->depth; ++l) {
     int ls = B->level_start[l], le = B->level_start[l + 1];
-    k_colleagues<<<nblocks(le - ls, 128), 128, 0, s>>>(t, ls, le, B->colleague);
+    k_colleagues<<<le - ls, 64, 0, s>>>(t, ls, B->colleague);
     RPY_HIP(hipGetLastError());
   }
 
@@ -854,7 +890,7 @@ int build_tree(const BuildArgs& A, Built* B, Error* err) {
   int* lt = nullptr;
   if (dalloc(&lcnt, 5 * (int64_t)nbox, B, err) || dalloc(&lt, (int64_t)scan_tmp_ints(nbox + 1), B, err)) return -3;
   List none[5] = {};
-  k_lists<<<nblocks(nbox, 64), 64, 0, s>>>(t, B->colleague, nbox, 0, lcnt, none[0], none[1], none[2], none[3],
+  k_lists<<<nbox, 64, 0, s>>>(t, B->colleague, nbox, 0, lcnt, none[0], none[1], none[2], none[3],
                                            none[4], want_o, B->d_side, A.a);
   RPY_HIP(hipGetLastError());
   // The five scans, then one read-back of their last offsets and counts.
@@ -886,7 +922,7 @@ int build_tree(const BuildArgs& A, Built* B, Error* err) {
   se = hipStreamSynchronize(s);
   RPY_HIP(le);
   RPY_HIP(se);
-  k_lists<<<nblocks(nbox, 64), 64, 0, s>>>(t, B->colleague, nbox, 1, lcnt, B->lists[0], B->lists[1], B->lists[2],
+  k_lists<<<nbox, 64, 0, s>>>(t, B->colleague, nbox, 1, lcnt, B->lists[0], B->lists[1], B->lists[2],
                                            B->lists[3], B->lists[4], want_o, B->d_side, A.a);
   RPY_HIP(hipGetLastError());
   RPY_HIP(hipStreamSynchronize(s));
