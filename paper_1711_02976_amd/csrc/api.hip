@@ -202,14 +202,19 @@ struct Work {
   double2* XP = nullptr;  // S->L partial sums of boxes split over several work items
   double* PV = nullptr;   // polynomial evaluation: the leaves' density polynomials
   float2* M32 = nullptr;  // mixed form: multipoles as the FP32 M->L reads them
+  double* NP = nullptr;   // near-field partial sums (null: whole tiles)
 };
-constexpr int WS_N = 11;  // arrays of Work, in the order above
+constexpr int WS_N = 12, WS_NP = 11;  // arrays of Work, in the order above
 
 struct rpy_plan_s {
   rpy::Built B;
   rpy::Tables tb{};
   rpy::Tiles tiles{};
   rpy::EvalPlan ep{};
+  rpy::NearPlan np{};
+  // no V or X entries and no evaluated W multipoles: every local expansion
+  // and so the far field's velocities are zero, and none of it is run
+  bool no_far = false;
   int p = 0, leaf_size = 0, max_depth = 14, precision = 0, m2l_mode = 2;
   int wd = 0;         // W-list boxes of at most wd beads are summed directly (< 0: none)
   int eval_mode = 0;  // rpy::EVAL_SETS or rpy::EVAL_POLY
@@ -270,6 +275,7 @@ static void ws_sizes(const rpy_plan_t* P, int nrc, int nrn, size_t sz[WS_N]) {
   sz[8] = sizeof(double2) * std::max<int64_t>(P->B.nxshared, 1) * 4 * nrc * T;
   sz[9] = (size_t)pvb;
   sz[10] = P->precision == RPY_PREC_MIXED ? sizeof(float2) * nbox * 4 * nrc * T : 256;
+  sz[WS_NP] = (size_t)rpy::near_part_bytes(P->np, nrn);
 }
 
 static hipEvent_t get_event(rpy_plan_t* P) {
@@ -319,7 +325,7 @@ static void fold_events(rpy_plan_t* P) {
 
 static void free_ws(rpy_plan_t* P) {
   Work& w = P->ws;
-  void* ps[] = {w.M, w.L, w.sF, w.u, w.uf, w.Q, w.DL, w.DW, w.XP, w.PV, w.M32};
+  void* ps[] = {w.M, w.L, w.sF, w.u, w.uf, w.Q, w.DL, w.DW, w.XP, w.PV, w.M32, w.NP};
   for (void* p : ps)
     if (p) (void)hipFree(p);
   w = Work{};
@@ -338,13 +344,14 @@ static int alloc_ws(rpy_plan_t* P, int nrc, int nrn) {
   Work& w = P->ws;
   void** dst[WS_N] = {(void**)&w.M, (void**)&w.L, (void**)&w.sF, (void**)&w.u, (void**)&w.uf,
                       (void**)&w.Q, (void**)&w.DL, (void**)&w.DW, (void**)&w.XP, (void**)&w.PV,
-                      (void**)&w.M32};
+                      (void**)&w.M32, (void**)&w.NP};
   int64_t tot = 0;
   // an injected allocation failure (rpy_plan_inject_error) hits half-way,
   // after some arrays are allocated, like a device that runs out of memory
   const int fail_at = P->inject == RPY_INJECT_ALLOC ? WS_N / 2 : WS_N;
   if (fail_at < WS_N) P->inject = -1;
   for (int k = 0; k < WS_N; ++k) {
+    if (sz[k] == 0) continue;
     if (k == fail_at || hipMalloc(dst[k], sz[k]) != hipSuccess) {
       (void)hipGetLastError();
       *dst[k] = nullptr;
@@ -378,7 +385,7 @@ static hipError_t matvec_group(rpy_plan_t* P, const rpy::Launch& l, const Work& 
   const bool haveO = B.lists[rpy::LO].len > 0, haveX = B.lists[rpy::LX].len > 0, haveW = B.lists[rpy::LW].len > 0;
   // timing mode 2 runs the near field on the plan stream too, so that each
   // phase's events measure that phase alone
-  const bool fork = P->near && P->timing != 2;
+  const bool fork = P->near && P->timing != 2 && !P->no_far;
   const hipStream_t s0 = P->stream, s1 = fork ? P->near : P->stream;
   rpy::Launch ln = l;
   ln.s = s1;
@@ -398,13 +405,22 @@ static hipError_t matvec_group(rpy_plan_t* P, const rpy::Launch& l, const Work& 
     if (he == hipSuccess) he = hipStreamWaitEvent(s1, P->ev_fork, 0);
   }
   if (he == hipSuccess)
-    he = step(RPY_PH_P2P, 1, s1, [&] { return rpy::run_p2p(ln, P->tiles, cn, w.sF, w.u, mixed); },
+    he = step(RPY_PH_P2P, 1, s1, [&] { return rpy::run_p2p(ln, P->tiles, P->np, cn, w.sF, w.u, w.NP, mixed); },
               cn >= rpy::NEAR_MC_RHS ? cn : 0);
   if (he == hipSuccess && haveO)
-    he = step(RPY_PH_OVERLAP, 1, s1, [&] { return rpy::run_overlap(ln, P->tiles, cn, w.sF, w.u, mixed); });
+    he = step(RPY_PH_OVERLAP, 1, s1, [&] { return rpy::run_overlap(ln, P->tiles, P->np, cn, w.sF, w.u, w.NP, mixed); });
   if (he == hipSuccess && haveW)
-    he = step(RPY_PH_OVERLAP, 1, s1, [&] { return rpy::run_wdirect(ln, P->tiles, cn, w.sF, w.u, mixed); });
+    he = step(RPY_PH_OVERLAP, 1, s1, [&] { return rpy::run_wdirect(ln, P->tiles, P->np, cn, w.sF, w.u, w.NP, mixed); });
   if (he == hipSuccess && fork) he = hipEventRecord(P->ev_join, s1);
+  if (P->no_far) {  // the phases run nothing (an injected error still reports)
+    for (int ph : {RPY_PH_P2M, RPY_PH_M2M, RPY_PH_M2L, RPY_PH_P2L, RPY_PH_L2L, RPY_PH_EVAL})
+      if (he == hipSuccess && (ph != RPY_PH_P2L || haveX)) he = step(ph, 0, s0, [] { return hipSuccess; });
+    if (he == hipSuccess)
+      he = step(RPY_PH_UNPERMUTE, 1, s0,
+                [&] { return rpy::unpermute_velocities(l, w.u, nullptr, r0, cn, velocities); });
+    if (P->timing && !untimed) P->acc.passes += 1;
+    return he;
+  }
   // far field on s0, pass by pass over slices of the group's forces
   bool joined = !fork;
   for (int q0 = 0; he == hipSuccess && q0 < cn;) {
@@ -914,7 +930,9 @@ rpy_status rpy_plan_batched(rpy_plan_t** out, int32_t nsys, const int64_t* count
   if (P->eval_mode == 0) P->eval_mode = P->p <= EVAL_POLY_AUTO_MAX ? rpy::EVAL_POLY : rpy::EVAL_SETS;
   if (rc == 0) rc = rpy::make_tables(P->p, &P->tb, P->stream, &err);
   if (rc == 0) rc = rpy::make_tiles(&P->B, 128, &P->tiles, P->stream, &err);
+  if (rc == 0) rc = rpy::make_near_plan(&P->B, P->tiles, P->a, P->wd, &P->np, P->stream, &err);
   if (rc == 0) rc = rpy::make_eval_plan(&P->B, P->p, P->wd, P->eval_mode, &P->ep, P->stream, &err);
+  P->no_far = P->B.lists[rpy::LV].len == 0 && P->B.lists[rpy::LX].len == 0 && P->ep.nwbig == 0;
   if (rc == 0) rc = rpy::make_m2l_map(&P->B, P->stream, &err);
   if (rc == 0) rc = rpy::make_p2l_work(&P->B, P->stream, &err);
   if (rc == 0) {
@@ -1009,11 +1027,18 @@ rpy_status rpy_matvec_noalloc(rpy_plan_t* P, int32_t nrhs, const double* forces,
   if (P->p > rpy::MAX_ORDER_MULTI) nrc = 1;
   int nrn = std::max(nrc, near_group_max(nrhs, P->precision == RPY_PREC_MIXED));
   size_t sz[WS_N], tot = 0;
+  bool split = true;  // near-field tiles split over several blocks, if the slots fit too
   for (;;) {
     ws_sizes(P, nrc, nrn, sz);
+    if (!split) sz[WS_NP] = 0;
     tot = 0;
     for (int k = 0; k < WS_N; ++k) tot += align256(sz[k]);
-    if (tot <= NOALLOC_SCRATCH_BYTES || nrn == 1) break;
+    if (tot <= NOALLOC_SCRATCH_BYTES) break;
+    if (split) {
+      split = false;
+      continue;
+    }
+    if (nrn == 1) break;
     if (nrn > nrc) nrn /= 2;
     else nrc = nrn = nrc / 2;
   }
@@ -1032,9 +1057,9 @@ rpy_status rpy_matvec_noalloc(rpy_plan_t* P, int32_t nrhs, const double* forces,
     unsigned char* q = static_cast<unsigned char*>(base);
     void** dst[WS_N] = {(void**)&w.M, (void**)&w.L, (void**)&w.sF, (void**)&w.u, (void**)&w.uf,
                         (void**)&w.Q, (void**)&w.DL, (void**)&w.DW, (void**)&w.XP, (void**)&w.PV,
-                        (void**)&w.M32};
+                        (void**)&w.M32, (void**)&w.NP};
     for (int k = 0; k < WS_N; ++k) {
-      *dst[k] = q;
+      *dst[k] = k == WS_NP && sz[k] == 0 ? nullptr : q;
       q += align256(sz[k]);
     }
   }
@@ -1341,6 +1366,7 @@ void rpy_plan_free(rpy_plan_t* P) {
   rpy::free_tables(&P->tb);
   if (P->tiles.t) (void)hipFree(P->tiles.t);
   if (P->tiles.box) (void)hipFree(P->tiles.box);
+  rpy::free_near_plan(&P->np);
   rpy::free_eval_plan(&P->ep);
   rpy::free_built(&P->B);
   delete P;

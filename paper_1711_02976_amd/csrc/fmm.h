@@ -90,7 +90,7 @@ struct Launch {
 
 // Forces (caller order, [nrhs][n][3]) -> sorted SoA [nrc][3][n] for rhs r0..r0+nrc-1.
 hipError_t permute_forces(const Launch& l, const double* F, int nrhs_total, int r0, int nrc, double* sF);
-// Near- plus far-field velocities (sorted SoA) -> caller order output.
+// Near- plus far-field velocities (sorted SoA; uf null: no far field) -> caller order output.
 hipError_t unpermute_velocities(const Launch& l, const double* u, const double* uf, int r0, int nrc, double* out);
 
 hipError_t run_p2m(const Launch& l, int nrc, const double* sF, Exp e);
@@ -122,8 +122,28 @@ int make_tiles(const Built* B, int tile, Tiles* out, hipStream_t s, Error* err);
 constexpr int NEAR_VEC_RHS = 8;
 constexpr int NEAR_MC_RHS = 16;
 constexpr int NEAR_MAX_RHS = NEAR_MC_RHS + NEAR_VEC_RHS;
-hipError_t run_p2p(const Launch& l, const Tiles& tiles, int nrc, const double* sF, double* u, int mixed);
-hipError_t run_overlap(const Launch& l, const Tiles& tiles, int nrc, const double* sF, double* u, int mixed);
+// Parts of the tiles' source chunks of one list (U, W or O), one per block:
+// no tables when no tile is split over several blocks.
+struct NearWork {
+  int n = 0;              // parts
+  int4* item = nullptr;   // (tile, first list entry, first chunk of it, chunks)
+  int* slot = nullptr;    // the part's partial-sum slot, -1: writes its sums itself
+  int* parts = nullptr;   // per tile: parts
+  int* slot0 = nullptr;   // per tile: first slot
+  int nslot = 0;
+  bool nothing = false;   // the kernel would sum no bead pair
+};
+struct NearPlan {
+  NearWork u, w, o;
+};
+int make_near_plan(const Built* B, const Tiles& tiles, double a, int wd, NearPlan* out, hipStream_t s, Error* err);
+void free_near_plan(NearPlan* p);
+int64_t near_part_bytes(const NearPlan& np, int nrn);
+// part: partial-sum slots (near_part_bytes), null: whole tiles
+hipError_t run_p2p(const Launch& l, const Tiles& tiles, const NearPlan& np, int nrc, const double* sF, double* u,
+                   double* part, int mixed);
+hipError_t run_overlap(const Launch& l, const Tiles& tiles, const NearPlan& np, int nrc, const double* sF, double* u,
+                       double* part, int mixed);
 // W-list boxes of at most Launch::wd beads are summed directly (far
 // formula) by run_wdirect; the target evaluation uses the multipoles of the
 // others only.  Per target and right-hand side the multipole route costs
@@ -131,7 +151,8 @@ hipError_t run_overlap(const Launch& l, const Tiles& tiles, int nrc, const doubl
 // operations per source bead, so the library's default threshold is
 // wdirect_default(p) = 2 (p+1)(p+2)/2 beads.
 __host__ __device__ constexpr int wdirect_default(int p) { return (p + 1) * (p + 2); }
-hipError_t run_wdirect(const Launch& l, const Tiles& tiles, int nrc, const double* sF, double* u, int mixed);
+hipError_t run_wdirect(const Launch& l, const Tiles& tiles, const NearPlan& np, int nrc, const double* sF, double* u,
+                       double* part, int mixed);
 // Exact FP64 RPY sums (Sec. 1) at k sampled targets tgt (tree order) over all
 // beads of each target's system: out [k][nrc][3].  The autotuner's reference.
 hipError_t run_direct_sample(const Launch& l, const int* tgt, int k, int nrc, const double* sF, double* out);

@@ -419,7 +419,10 @@ __global__ void k_unpermute(const double* u, const double* uf, const int* perm, 
   int64_t j = perm[i];
   for (int r = 0; r < nrc; ++r) {
     double* o = out + ((int64_t)(r0 + r) * n + j) * 3;
-    for (int k = 0; k < 3; ++k) o[k] = u[((int64_t)r * 3 + k) * n + i] + uf[((int64_t)r * 3 + k) * n + i];
+    for (int k = 0; k < 3; ++k) {
+      const int64_t x = ((int64_t)r * 3 + k) * n + i;
+      o[k] = uf ? u[x] + uf[x] : u[x];
+    }
   }
 }
 

@@ -5,7 +5,8 @@
 // not adjacent (the far field treated them with the r >= 2a formula).
 //
 // One block of P2P_T threads per target tile (a leaf, or a P2P_T-bead slice
-// of a large leaf); each lane owns one target and keeps 3 * nrc sums in
+// of a large leaf), or per part of a tile's source chunks (NearWork below);
+// each lane owns one target and keeps 3 * nrc sums in
 // registers; source beads of each U-list leaf are staged through LDS
 // (positions and forces, SoA) and read back as wave-wide broadcasts.  With
 // 16 right-hand sides (in the FP64 form plus up to 8 more on the vector units
@@ -96,6 +97,220 @@ int make_tiles(const Built* B, int tile, Tiles* out, hipStream_t s, Error* err) 
   return 0;
 }
 
+// ------------------------------------------------------- near-field work --
+// One block per tile leaves most of the chip idle when there are few tiles
+// (2,000 beads in one leaf are 16 tiles) and lets the longest tile set a
+// kernel's time when their source lists differ (two W-list neighbours of
+// dense leaves took 13 ms alone on 64 systems).  So a tile's source chunks
+// (P2P_T beads of one list entry each) are split over several blocks when it
+// has more than cap = max(1, total / NEAR_ITEMS) of them: the parts' FP64
+// sums go to slots of P2P_T targets each and are added in part order
+// (k_near_reduce), so results do not depend on timing.  With many even tiles
+// nothing is split and no table is kept.  NEAR_ITEMS blocks fill the chip
+// twice over in the lightest kernel (16 blocks of two waves per CU).
+constexpr int NEAR_ITEMS = 8192;
+
+// A W-list box of more than wmax beads is evaluated through its multipole.
+struct ChunkFilter {
+  int kind;  // LU, LW or LO
+  int wmax;  // LW
+  double four_a2;  // LO
+};
+
+// Whether the near field sums list entry C for a tile with bounding box tb
+// (lo xyz, hi xyz): W boxes of few beads only; O leaves whose cube comes
+// closer than 2a to the tile's beads.
+__device__ inline bool near_takes(const ChunkFilter& f, const Tree& t, int C, const double* tb) {
+  if (f.kind == LW) return t.end[C] - t.begin[C] <= f.wmax;
+  if (f.kind == LO) {
+    const double hc = 0.5 * t.h[C], cc[3] = {t.cx[C], t.cy[C], t.cz[C]};
+    double g2 = 0.0;
+    for (int q = 0; q < 3; ++q) {
+      const double g = fmax(0.0, fmax(cc[q] - hc - tb[3 + q], tb[q] - cc[q] - hc));
+      g2 += g * g;
+    }
+    return g2 < f.four_a2;
+  }
+  return true;
+}
+
+// cnt[i] = source chunks of tile i; stat[0] += their sum, stat[1] = max.
+__global__ void __launch_bounds__(256) k_near_count(const int4* tiles, const double* tbox, int nt, Tree t, List l,
+                                                    ChunkFilter f, int* cnt, unsigned long long* stat) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  int c = 0;
+  if (i < nt) {
+    const int b = tiles[i].x;
+    for (int e = l.off[b]; e < l.off[b + 1]; ++e) {
+      const int C = l.ent[e];
+      if (near_takes(f, t, C, tbox + 6 * (int64_t)i)) c += (t.end[C] - t.begin[C] + P2P_T - 1) / P2P_T;
+    }
+    cnt[i] = c;
+  }
+  unsigned long long s = c, m = c;
+  for (int d = 1; d < 64; d <<= 1) {
+    s += __shfl_xor(s, d);
+    const unsigned long long o = __shfl_xor(m, d);
+    m = o > m ? o : m;
+  }
+  if ((threadIdx.x & 63) == 0 && m > 0) {
+    atomicAdd(&stat[0], s);
+    atomicMax(&stat[1], m);
+  }
+}
+
+// parts[i] = blocks of tile i, held[i] = its slots (0 when it has one part).
+__global__ void k_near_parts(const int* cnt, int nt, int cap, int* parts, int* held) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= nt) return;
+  const int k = (cnt[i] + cap - 1) / cap;
+  parts[i] = k;
+  held[i] = k > 1 ? k : 0;
+}
+
+// The parts of tile i: (tile, first list entry, first chunk of it, chunks)
+// and the slot (-1: the tile has one part), its chunks split evenly.
+__global__ void k_near_fill(const int4* tiles, const double* tbox, int nt, Tree t, List l, ChunkFilter f,
+                            const int* cnt, const int* off, const int* parts, const int* slot0, int4* item, int* slot) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= nt || parts[i] == 0) return;
+  const int b = tiles[i].x, k = parts[i], c = cnt[i];
+  int e = l.off[b], ch = 0;  // the next chunk
+  for (int q = 0; q < k; ++q) {
+    int left = (int)((int64_t)c * (q + 1) / k - (int64_t)c * q / k);
+    bool first = true;
+    while (e < l.off[b + 1]) {
+      const int C = l.ent[e];
+      const int nc = near_takes(f, t, C, tbox + 6 * (int64_t)i) ? (t.end[C] - t.begin[C] + P2P_T - 1) / P2P_T : 0;
+      if (nc == ch) {  // a refused entry, or past its last chunk
+        ++e;
+        ch = 0;
+        continue;
+      }
+      if (first) {
+        item[off[i] + q] = make_int4(i, e, ch, left);
+        slot[off[i] + q] = k > 1 ? slot0[i] + q : -1;
+        first = false;
+      }
+      const int take = min(left, nc - ch);
+      ch += take;
+      left -= take;
+      if (left == 0) break;
+    }
+  }
+}
+
+// u (+)= the slots of every split tile, in part order; nq component rows.
+__global__ void __launch_bounds__(P2P_T) k_near_reduce(const int4* tiles, const int* parts, const int* slot0,
+                                                       const double* __restrict__ part, int nq, int64_t n, int add,
+                                                       double* u) {
+  const int i = blockIdx.x, k = parts[i];
+  if (k <= 1) return;
+  const int4 tl = tiles[i];
+  if ((int)threadIdx.x >= tl.z) return;
+  const int q = blockIdx.y;
+  const double* p = part + ((int64_t)slot0[i] * nq + q) * P2P_T + threadIdx.x;
+  double s = 0.0;
+  for (int j = 0; j < k; ++j) s += p[(int64_t)j * nq * P2P_T];
+  double* o = u + (int64_t)q * n + tl.y + threadIdx.x;
+  *o = add ? *o + s : s;
+}
+
+static int make_near_work(const Built* B, const Tiles& tiles, const ChunkFilter& f, NearWork* out, hipStream_t s,
+                          Error* err) {
+  *out = NearWork{};
+  const List& l = B->lists[f.kind];
+  const int nt = tiles.n;
+  if (nt == 0 || l.len == 0 || (f.kind == LW && f.wmax < 0)) return 0;
+  // scratch: the counts, two statistics, and the tables' scans
+  const size_t ntmp = scan_tmp_ints(nt);
+  unsigned long long* stat = nullptr;
+  RPY_HIP(hipMalloc(&stat, 2 * sizeof(unsigned long long) + sizeof(int) * (3 * (size_t)nt + ntmp)));
+  int* cnt = reinterpret_cast<int*>(stat + 2);
+  int *held = cnt + nt, *off = held + nt, *tmp = off + nt;
+  RPY_HIP(hipMemsetAsync(stat, 0, 2 * sizeof(unsigned long long), s));
+  k_near_count<<<nblk(nt, 256), 256, 0, s>>>(tiles.t, tiles.box, nt, B->tree, l, f, cnt, stat);
+  RPY_HIP(hipGetLastError());
+  unsigned long long hs[2] = {0, 0};
+  RPY_HIP(hipMemcpyAsync(hs, stat, sizeof(hs), hipMemcpyDeviceToHost, s));
+  RPY_HIP(hipStreamSynchronize(s));
+  const unsigned long long cap = std::max<unsigned long long>(1, (hs[0] + NEAR_ITEMS - 1) / NEAR_ITEMS);
+  out->nothing = hs[1] == 0;
+  if (hs[1] > cap) {
+    // at most total / cap + 1 per tile parts
+    const size_t most = (size_t)NEAR_ITEMS + nt;
+    RPY_HIP(hipMalloc(&out->item, sizeof(int4) * most + sizeof(int) * (most + 2 * (size_t)nt)));
+    out->slot = reinterpret_cast<int*>(out->item + most);
+    out->parts = out->slot + most;
+    out->slot0 = out->parts + nt;
+    k_near_parts<<<nblk(nt, 256), 256, 0, s>>>(cnt, nt, (int)std::min<unsigned long long>(cap, 0x7fffffff),
+                                               out->parts, held);
+    RPY_HIP(scan_exclusive(out->parts, off, nt, tmp, s));
+    RPY_HIP(scan_exclusive(held, out->slot0, nt, tmp, s));
+    k_near_fill<<<nblk(nt, 64), 64, 0, s>>>(tiles.t, tiles.box, nt, B->tree, l, f, cnt, off, out->parts, out->slot0,
+                                            out->item, out->slot);
+    RPY_HIP(hipGetLastError());
+    int last[4];
+    RPY_HIP(hipMemcpyAsync(&last[0], off + nt - 1, sizeof(int), hipMemcpyDeviceToHost, s));
+    RPY_HIP(hipMemcpyAsync(&last[1], out->parts + nt - 1, sizeof(int), hipMemcpyDeviceToHost, s));
+    RPY_HIP(hipMemcpyAsync(&last[2], out->slot0 + nt - 1, sizeof(int), hipMemcpyDeviceToHost, s));
+    RPY_HIP(hipMemcpyAsync(&last[3], held + nt - 1, sizeof(int), hipMemcpyDeviceToHost, s));
+    RPY_HIP(hipStreamSynchronize(s));
+    out->n = last[0] + last[1];
+    out->nslot = last[2] + last[3];
+  }
+  (void)hipFree(stat);
+  return 0;
+}
+
+int make_near_plan(const Built* B, const Tiles& tiles, double a, int wd, NearPlan* out, hipStream_t s, Error* err) {
+  const double four_a2 = 4.0 * a * a;
+  if (int rc = make_near_work(B, tiles, ChunkFilter{LU, 0, four_a2}, &out->u, s, err)) return rc;
+  if (int rc = make_near_work(B, tiles, ChunkFilter{LW, wd, four_a2}, &out->w, s, err)) return rc;
+  return make_near_work(B, tiles, ChunkFilter{LO, 0, four_a2}, &out->o, s, err);
+}
+
+void free_near_plan(NearPlan* p) {
+  for (NearWork* w : {&p->u, &p->w, &p->o}) {
+    if (w->item) (void)hipFree(w->item);  // the other tables follow it
+    *w = NearWork{};
+  }
+}
+
+// The part of a tile's source chunks that a block sums: from NearWork's
+// tables, or (no tables) all of tile blockIdx's list.
+struct Part {
+  int tile, e, c, left, slot;
+  __device__ inline Part(const int4* item, const int* slots, int i, const int4* tiles, const List& l) {
+    if (item) {
+      const int4 it = item[i];
+      tile = it.x;
+      e = __builtin_amdgcn_readfirstlane(it.y);
+      c = __builtin_amdgcn_readfirstlane(it.z);
+      left = __builtin_amdgcn_readfirstlane(it.w);
+      slot = __builtin_amdgcn_readfirstlane(slots[i]);
+    } else {
+      tile = i;
+      e = __builtin_amdgcn_readfirstlane(l.off[tiles[i].x]);
+      c = 0;
+      left = 0x7fffffff;
+      slot = -1;
+    }
+  }
+};
+
+// Where the sums of a block's targets go, row q = 3 r + c, target k of the
+// tile: its slot, or u (assigned, or added when ADD).
+struct Sums {
+  double* p;
+  int64_t ld;
+  __device__ inline Sums(const Part& w, const int4& tl, int nq, int64_t n, double* u, double* part) {
+    p = w.slot >= 0 ? part + (int64_t)w.slot * nq * P2P_T : u + tl.y;
+    ld = w.slot >= 0 ? P2P_T : n;
+  }
+  __device__ inline double* at(int q, int k) const { return p + (int64_t)q * ld + k; }
+};
+
 // ------------------------------------------------------------ pair math ---
 
 // Pair coefficients of the P2P sum with the far prefactor c1 = 1/(8 pi eta)
@@ -157,17 +372,19 @@ __device__ inline double rinv_of(double r2) {
 // matrix-core group) is held to 96 registers, five waves per SIMD instead of
 // four (two registers spill; 192 instead of 196 ms on cube-15M).
 template <int NRC, bool MIXED>
-__global__ void __launch_bounds__(P2P_T, (NRC == 4 && MIXED) ? 5 : 1) k_p2p(const int4* tiles, Tree t, List U, const double* sx,
+__global__ void __launch_bounds__(P2P_T, (NRC == 4 && MIXED) ? 5 : 1) k_p2p(const int4* tiles, const int4* item, const int* slots,
+                                               Tree t, List U, const double* sx,
                                                const double* sy, const double* sz, const double* sF, int64_t n,
                                                PairK<typename std::conditional<MIXED, float, double>::type> k,
-                                               double S, double c1, double* u) {
+                                               double S, double c1, double* u, double* part) {
   using R = typename std::conditional<MIXED, float, double>::type;
   using V4 = typename std::conditional<MIXED, float4, double4>::type;
   __shared__ alignas(32) R xs[P2P_T];
   __shared__ alignas(32) R ys[P2P_T];
   __shared__ alignas(32) R zs[P2P_T];
   __shared__ alignas(32) R fs[NRC * 3][P2P_T];
-  const int4 tl = tiles[xcd_run(blockIdx.x, gridDim.x)];
+  Part w(item, slots, xcd_run(blockIdx.x, gridDim.x), tiles, U);
+  const int4 tl = tiles[w.tile];
   const int b = tl.x;
   const bool valid = (int)threadIdx.x < tl.z;
   const bool wlive = (int)(threadIdx.x & ~63u) < tl.z;  // this wave holds a target of the tile
@@ -176,11 +393,11 @@ __global__ void __launch_bounds__(P2P_T, (NRC == 4 && MIXED) ? 5 : 1) k_p2p(cons
   const R xi = (R)((sx[i] - ox) * S), yi = (R)((sy[i] - oy) * S), zi = (R)((sz[i] - oz) * S);
   double acc[NRC][3];
   for (int r = 0; r < NRC; ++r) acc[r][0] = acc[r][1] = acc[r][2] = 0.0;
-  const int e0 = __builtin_amdgcn_readfirstlane(U.off[b]), e1 = __builtin_amdgcn_readfirstlane(U.off[b + 1]);
-  for (int e = e0; e < e1; ++e) {
-    const int C = __builtin_amdgcn_readfirstlane(U.ent[e]);
+  const int e1 = __builtin_amdgcn_readfirstlane(U.off[b + 1]);
+  for (; w.e < e1 && w.left > 0; ++w.e, w.c = 0) {
+    const int C = __builtin_amdgcn_readfirstlane(U.ent[w.e]);
     const int j1 = __builtin_amdgcn_readfirstlane(t.end[C]);
-    for (int jc = __builtin_amdgcn_readfirstlane(t.begin[C]); jc < j1; jc += P2P_T) {
+    for (int jc = __builtin_amdgcn_readfirstlane(t.begin[C]) + w.c * P2P_T; jc < j1 && w.left > 0; jc += P2P_T, --w.left) {
       const int ns = min(P2P_T, j1 - jc);
       // the tile is padded to a multiple of 4 sources with inert ones: zero
       // force at 1e30, where 1/r, A' and B' all evaluate to exactly zero
@@ -258,9 +475,10 @@ __global__ void __launch_bounds__(P2P_T, (NRC == 4 && MIXED) ? 5 : 1) k_p2p(cons
         for (int c = 0; c < 3; ++c) acc[r][c] += (double)ar[r][c];
     }
   }
+  const Sums o(w, tl, 3 * NRC, n, u, part);
   if (valid)
     for (int r = 0; r < NRC; ++r)
-      for (int c = 0; c < 3; ++c) u[((int64_t)r * 3 + c) * n + i] = c1 * acc[r][c];
+      for (int c = 0; c < 3; ++c) *o.at(3 * r + c, threadIdx.x) = c1 * acc[r][c];
 }
 
 // ------------------------------------------- P2P on the matrix cores ----
@@ -299,11 +517,12 @@ __device__ inline int mf_row(double, int l, int v) { return 4 * v + (l >> 4); }
 }  // namespace
 
 template <bool MIXED, int XR>
-__global__ void __launch_bounds__(64 * MF_W) k_p2p_mfma(const int4* tiles, Tree t, List U, const double* sx,
+__global__ void __launch_bounds__(64 * MF_W) k_p2p_mfma(const int4* tiles, const int4* item, const int* slots,
+                                                       Tree t, List U, const double* sx,
                                                        const double* sy, const double* sz, const double* sF,
                                                        int64_t n,
                                                        PairK<typename std::conditional<MIXED, float, double>::type> k,
-                                                       double S, double c1, double* u) {
+                                                       double S, double c1, double* u, double* part) {
   using R = typename std::conditional<MIXED, float, double>::type;
   using R4 = typename std::conditional<MIXED, float4, double4>::type;
   using VD = typename std::conditional<MIXED, v4f_t, v4d_t>::type;
@@ -311,7 +530,8 @@ __global__ void __launch_bounds__(64 * MF_W) k_p2p_mfma(const int4* tiles, Tree 
   __shared__ R4 ps[P2P_T];          // positions (x, y, z, -)
   __shared__ R fs[3][P2P_T][MF_R];  // [component][source][right-hand side]
   __shared__ alignas(16) R fx[3][P2P_T][XS];  // the XR vector-unit right-hand sides
-  const int4 tl = tiles[xcd_run(blockIdx.x, gridDim.x)];
+  Part w(item, slots, xcd_run(blockIdx.x, gridDim.x), tiles, U);
+  const int4 tl = tiles[w.tile];
   const int b = tl.x;
   const int tid = threadIdx.x, lane = tid & 63;
   const int t0 = 16 * __builtin_amdgcn_readfirstlane(tid >> 6);  // the wave's first target in the tile
@@ -333,11 +553,11 @@ __global__ void __launch_bounds__(64 * MF_W) k_p2p_mfma(const int4* tiles, Tree 
   double xacc[XH][3];  // FP64 sums of right-hand sides sk + 4 h for target ti
 #pragma unroll
   for (int h = 0; h < XH; ++h) xacc[h][0] = xacc[h][1] = xacc[h][2] = 0.0;
-  const int e0 = __builtin_amdgcn_readfirstlane(U.off[b]), e1 = __builtin_amdgcn_readfirstlane(U.off[b + 1]);
-  for (int e = e0; e < e1; ++e) {
-    const int C = __builtin_amdgcn_readfirstlane(U.ent[e]);
+  const int e1 = __builtin_amdgcn_readfirstlane(U.off[b + 1]);
+  for (; w.e < e1 && w.left > 0; ++w.e, w.c = 0) {
+    const int C = __builtin_amdgcn_readfirstlane(U.ent[w.e]);
     const int j1 = __builtin_amdgcn_readfirstlane(t.end[C]);
-    for (int jc = __builtin_amdgcn_readfirstlane(t.begin[C]); jc < j1; jc += P2P_T) {
+    for (int jc = __builtin_amdgcn_readfirstlane(t.begin[C]) + w.c * P2P_T; jc < j1 && w.left > 0; jc += P2P_T, --w.left) {
       const int ns = min(P2P_T, j1 - jc);
       // padded to a multiple of 4 sources with inert ones (zero force at 1e30)
       const int ns4 = (ns + 3) & ~3;
@@ -429,6 +649,7 @@ __global__ void __launch_bounds__(64 * MF_W) k_p2p_mfma(const int4* tiles, Tree 
     }
   }
   if (!wlive) return;
+  const Sums o(w, tl, 3 * (MF_R + XR), n, u, part);
 #pragma unroll
   for (int c = 0; c < 3; ++c)
 #pragma unroll
@@ -436,7 +657,7 @@ __global__ void __launch_bounds__(64 * MF_W) k_p2p_mfma(const int4* tiles, Tree 
       const int row = mf_row(R(0), lane, v);
       if (t0 + row < tl.z) {
         const double x = MIXED ? acc[c][v] : (double)D[c][v];
-        u[((int64_t)ti * 3 + c) * n + tl.y + t0 + row] = c1 * x;
+        *o.at(3 * ti + c, t0 + row) = c1 * x;
       }
     }
   if (t0 + ti < tl.z)
@@ -445,7 +666,7 @@ __global__ void __launch_bounds__(64 * MF_W) k_p2p_mfma(const int4* tiles, Tree 
       const int x = sk + 4 * h;
       if (x < XR)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) u[((int64_t)(MF_R + x) * 3 + c) * n + tl.y + t0 + ti] = c1 * xacc[h][c];
+        for (int c = 0; c < 3; ++c) *o.at(3 * (MF_R + x) + c, t0 + ti) = c1 * xacc[h][c];
     }
 }
 
@@ -456,17 +677,19 @@ __global__ void __launch_bounds__(64 * MF_W) k_p2p_mfma(const int4* tiles, Tree 
 // stands for (pairs closer than 2a are then corrected by the O list as
 // before).  Boxes with more than wmax beads keep the multipole route.
 template <int NRC, bool MIXED>
-__global__ void __launch_bounds__(P2P_T) k_wdirect(const int4* tiles, Tree t, List W, int wmax, const double* sx,
+__global__ void __launch_bounds__(P2P_T) k_wdirect(const int4* tiles, const int4* item, const int* slots,
+                                                   Tree t, List W, ChunkFilter filter, const double* sx,
                                                    const double* sy, const double* sz, const double* sF, int64_t n,
                                                    PairK<typename std::conditional<MIXED, float, double>::type> k,
-                                                   double S, double c1, double* u) {
+                                                   double S, double c1, double* u, double* part) {
   using R = typename std::conditional<MIXED, float, double>::type;
   __shared__ R xs[P2P_T], ys[P2P_T], zs[P2P_T];
   __shared__ R fs[NRC * 3][P2P_T];
-  const int4 tl = tiles[blockIdx.x];
+  Part w(item, slots, blockIdx.x, tiles, W);
+  const int4 tl = tiles[w.tile];
   const int b = tl.x;
-  const int e0 = __builtin_amdgcn_readfirstlane(W.off[b]), e1 = __builtin_amdgcn_readfirstlane(W.off[b + 1]);
-  if (e0 == e1) return;
+  const int e1 = __builtin_amdgcn_readfirstlane(W.off[b + 1]);
+  if (w.e == e1) return;
   const bool valid = (int)threadIdx.x < tl.z;
   const bool wlive = (int)(threadIdx.x & ~63u) < tl.z;  // this wave holds a target of the tile
   const int i = tl.y + (valid ? threadIdx.x : 0);
@@ -475,12 +698,12 @@ __global__ void __launch_bounds__(P2P_T) k_wdirect(const int4* tiles, Tree t, Li
   double acc[NRC][3];
   for (int r = 0; r < NRC; ++r) acc[r][0] = acc[r][1] = acc[r][2] = 0.0;
   bool any = false;
-  for (int e = e0; e < e1; ++e) {
-    const int C = __builtin_amdgcn_readfirstlane(W.ent[e]);
+  for (; w.e < e1 && w.left > 0; ++w.e, w.c = 0) {
+    const int C = __builtin_amdgcn_readfirstlane(W.ent[w.e]);
     const int j0 = __builtin_amdgcn_readfirstlane(t.begin[C]), j1 = __builtin_amdgcn_readfirstlane(t.end[C]);
-    if (j1 - j0 > wmax) continue;
+    if (!near_takes(filter, t, C, nullptr)) continue;
     any = true;
-    for (int jc = j0; jc < j1; jc += P2P_T) {
+    for (int jc = j0 + w.c * P2P_T; jc < j1 && w.left > 0; jc += P2P_T, --w.left) {
       const int ns = min(P2P_T, j1 - jc);
       const int ns4 = (ns + 3) & ~3;
       __syncthreads();
@@ -517,9 +740,13 @@ __global__ void __launch_bounds__(P2P_T) k_wdirect(const int4* tiles, Tree t, Li
         for (int c = 0; c < 3; ++c) acc[r][c] += (double)ar[r][c];
     }
   }
+  const Sums o(w, tl, 3 * NRC, n, u, part);
   if (valid && any)
     for (int r = 0; r < NRC; ++r)
-      for (int c = 0; c < 3; ++c) u[((int64_t)r * 3 + c) * n + i] += c1 * acc[r][c];
+      for (int c = 0; c < 3; ++c) {
+        double* x = o.at(3 * r + c, threadIdx.x);
+        *x = w.slot >= 0 ? c1 * acc[r][c] : *x + c1 * acc[r][c];
+      }
 }
 
 // ------------------------------------------------------- overlap (O) -----
@@ -543,20 +770,22 @@ __global__ void __launch_bounds__(P2P_T) k_wdirect(const int4* tiles, Tree t, Li
 constexpr int OV_G = 4;
 
 template <int NRC, bool MIXED>
-__global__ void __launch_bounds__(P2P_T) k_overlap(const int4* tiles, const double* tbox, Tree t, List O,
-                                                   double four_a2, const double* sx,
+__global__ void __launch_bounds__(P2P_T) k_overlap(const int4* tiles, const double* tbox, const int4* item,
+                                                   const int* slots, Tree t, List O, ChunkFilter filter,
+                                                   const double* sx,
                                                    const double* sy, const double* sz, const double* sF, int64_t n,
                                                    PairK<typename std::conditional<MIXED, float, double>::type> k,
-                                                   double S, double c1, double* u) {
+                                                   double S, double c1, double* u, double* part) {
   using R = typename std::conditional<MIXED, float, double>::type;
   constexpr int NG = P2P_T / OV_G;
   __shared__ R xs[P2P_T], ys[P2P_T], zs[P2P_T];
   __shared__ R fs[NRC * 3][P2P_T];
   __shared__ R gbox[NG][6];  // per source group: lo xyz, hi xyz
-  const int4 tl = tiles[blockIdx.x];
+  Part w(item, slots, blockIdx.x, tiles, O);
+  const int4 tl = tiles[w.tile];
   const int b = tl.x;
-  const int e0 = __builtin_amdgcn_readfirstlane(O.off[b]), e1 = __builtin_amdgcn_readfirstlane(O.off[b + 1]);
-  if (e0 == e1) return;
+  const int e1 = __builtin_amdgcn_readfirstlane(O.off[b + 1]);
+  if (w.e == e1) return;
   const bool valid = (int)threadIdx.x < tl.z;
   const bool wlive = (int)(threadIdx.x & ~63u) < tl.z;  // this wave holds a target of the tile
   const int i = tl.y + (valid ? threadIdx.x : 0);
@@ -568,25 +797,14 @@ __global__ void __launch_bounds__(P2P_T) k_overlap(const int4* tiles, const doub
   const R skip2 = k.four_a2 * (R)(1.0 + 1e-4);
   double acc[NRC][3];
   for (int r = 0; r < NRC; ++r) acc[r][0] = acc[r][1] = acc[r][2] = 0.0;
-  double blo[3], bhi[3];
-  for (int q = 0; q < 3; ++q) {
-    blo[q] = tbox[6 * (int64_t)blockIdx.x + q];
-    bhi[q] = tbox[6 * (int64_t)blockIdx.x + 3 + q];
-  }
-  for (int e = e0; e < e1; ++e) {
-    const int C = __builtin_amdgcn_readfirstlane(O.ent[e]);
+  double tb[6];  // the tile's bounding box
+  for (int q = 0; q < 6; ++q) tb[q] = tbox[6 * (int64_t)w.tile + q];
+  for (; w.e < e1 && w.left > 0; ++w.e, w.c = 0) {
+    const int C = __builtin_amdgcn_readfirstlane(O.ent[w.e]);
     // skip source leaves whose cube is 2a or more away from this tile's beads
-    {
-      const double hc = 0.5 * t.h[C], cc[3] = {t.cx[C], t.cy[C], t.cz[C]};
-      double g2 = 0.0;
-      for (int q = 0; q < 3; ++q) {
-        const double g = fmax(0.0, fmax(cc[q] - hc - bhi[q], blo[q] - cc[q] - hc));
-        g2 += g * g;
-      }
-      if (!(g2 < four_a2)) continue;
-    }
+    if (!near_takes(filter, t, C, tb)) continue;
     const int j1 = __builtin_amdgcn_readfirstlane(t.end[C]);
-    for (int jc = __builtin_amdgcn_readfirstlane(t.begin[C]); jc < j1; jc += P2P_T) {
+    for (int jc = __builtin_amdgcn_readfirstlane(t.begin[C]) + w.c * P2P_T; jc < j1 && w.left > 0; jc += P2P_T, --w.left) {
       const int ns = min(P2P_T, j1 - jc);
       const int ns4 = (ns + 3) & ~3;
       __syncthreads();
@@ -637,9 +855,9 @@ __global__ void __launch_bounds__(P2P_T) k_overlap(const int4* tiles, const doub
           R A, B;
           if constexpr (MIXED) {  // factored
             const R rho = (r2 - k.r2min) * rinv * k.i2a;
-            const R om = (R)1 - rho, op = (R)1 + rho, w = om * om * ri3;
-            A = ov ? -k.a3 * w * fma(fma((R)9, rho, (R)2), rho, (R)1) : (R)0;
-            B = ov ? k.a2 * w * (op * op) * ri2 : (R)0;
+            const R om = (R)1 - rho, op = (R)1 + rho, wt = om * om * ri3;
+            A = ov ? -k.a3 * wt * fma(fma((R)9, rho, (R)2), rho, (R)1) : (R)0;
+            B = ov ? k.a2 * wt * (op * op) * ri2 : (R)0;
           } else {  // the two branches and their difference (fewer operations)
             const R Af = fma(k.a3, ri3, rinv), Bf = ri3 * fma(-k.a2, ri2, (R)1);
             const R Ao = fma(-k.ock9, (r2 - k.r2min) * rinv, k.oc), Bo = k.ob * rinv;
@@ -660,9 +878,13 @@ __global__ void __launch_bounds__(P2P_T) k_overlap(const int4* tiles, const doub
         for (int c = 0; c < 3; ++c) acc[r][c] += (double)ar[r][c];
     }
   }
+  const Sums o(w, tl, 3 * NRC, n, u, part);
   if (valid)
     for (int r = 0; r < NRC; ++r)
-      for (int c = 0; c < 3; ++c) u[((int64_t)r * 3 + c) * n + i] += c1 * acc[r][c];
+      for (int c = 0; c < 3; ++c) {
+        double* x = o.at(3 * r + c, threadIdx.x);
+        *x = w.slot >= 0 ? c1 * acc[r][c] : *x + c1 * acc[r][c];
+      }
 }
 
 // Launch arguments shared by the pair kernels: the scale S (2aS in [1, 2)),
@@ -683,18 +905,38 @@ static PairLaunch pair_launch(double a, double eta) {
   return q;
 }
 
-hipError_t run_p2p(const Launch& l, const Tiles& tiles, int nrc, const double* sF, double* u, int mixed) {
+// A launch's blocks: the parts of NearWork's tables, or one per tile when it
+// has none or the caller has no partial-sum slots.
+struct NearGrid {
+  const int4* item;
+  const int* slots;
+  int blocks;
+  NearGrid(const Tiles& tiles, const NearWork& w, const double* part)
+      : item(part ? w.item : nullptr), slots(w.slot), blocks(item ? w.n : tiles.n) {}
+};
+
+static hipError_t near_reduce(const Launch& l, const Tiles& tiles, const NearWork& w, const NearGrid& g, int nq,
+                              const double* part, double* u, int add) {
+  hipError_t he = hipGetLastError();
+  if (he != hipSuccess || !g.item) return he;
+  k_near_reduce<<<dim3(tiles.n, nq), P2P_T, 0, l.s>>>(tiles.t, w.parts, w.slot0, part, nq, l.B->n, add, u);
+  return hipGetLastError();
+}
+
+hipError_t run_p2p(const Launch& l, const Tiles& tiles, const NearPlan& np, int nrc, const double* sF, double* u,
+                   double* part, int mixed) {
   if (tiles.n == 0) return hipSuccess;
   const Built* B = l.B;
   const PairLaunch q = pair_launch(l.a, l.eta);
+  const NearGrid g(tiles, np.u, part);
 #define P2P_CASE(NR)                                                                                               \
   case NR:                                                                                                         \
     if (mixed)                                                                                                     \
-      k_p2p<NR, true><<<tiles.n, P2P_T, 0, l.s>>>(tiles.t, B->tree, B->lists[LU], B->sx, B->sy, B->sz, sF, B->n,     \
-                                                  q.kf, q.S, q.c1S, u);                                            \
+      k_p2p<NR, true><<<g.blocks, P2P_T, 0, l.s>>>(tiles.t, g.item, g.slots, B->tree, B->lists[LU], B->sx, B->sy,    \
+                                                   B->sz, sF, B->n, q.kf, q.S, q.c1S, u, part);                    \
     else                                                                                                           \
-      k_p2p<NR, false><<<tiles.n, P2P_T, 0, l.s>>>(tiles.t, B->tree, B->lists[LU], B->sx, B->sy, B->sz, sF, B->n,    \
-                                                   q.kd, q.S, q.c1S, u);                                           \
+      k_p2p<NR, false><<<g.blocks, P2P_T, 0, l.s>>>(tiles.t, g.item, g.slots, B->tree, B->lists[LU], B->sx, B->sy,   \
+                                                    B->sz, sF, B->n, q.kd, q.S, q.c1S, u, part);                   \
     break;
   switch (nrc) {
     P2P_CASE(1)
@@ -703,18 +945,18 @@ hipError_t run_p2p(const Launch& l, const Tiles& tiles, int nrc, const double* s
     P2P_CASE(8)
     case MF_R:
       if (mixed)
-        k_p2p_mfma<true, 0><<<tiles.n, 64 * MF_W, 0, l.s>>>(tiles.t, B->tree, B->lists[LU], B->sx, B->sy, B->sz, sF,
-                                                            B->n, q.kf, q.S, q.c1S, u);
+        k_p2p_mfma<true, 0><<<g.blocks, 64 * MF_W, 0, l.s>>>(tiles.t, g.item, g.slots, B->tree, B->lists[LU], B->sx,
+                                                             B->sy, B->sz, sF, B->n, q.kf, q.S, q.c1S, u, part);
       else
-        k_p2p_mfma<false, 0><<<tiles.n, 64 * MF_W, 0, l.s>>>(tiles.t, B->tree, B->lists[LU], B->sx, B->sy, B->sz, sF,
-                                                             B->n, q.kd, q.S, q.c1S, u);
+        k_p2p_mfma<false, 0><<<g.blocks, 64 * MF_W, 0, l.s>>>(tiles.t, g.item, g.slots, B->tree, B->lists[LU], B->sx,
+                                                              B->sy, B->sz, sF, B->n, q.kd, q.S, q.c1S, u, part);
       break;
     // 16 + XR: the FP64 form only
 #define MF_CASE(XR)                                                                                                \
   case MF_R + XR:                                                                                                  \
     if (mixed) return hipErrorInvalidValue;                                                                        \
-    k_p2p_mfma<false, XR><<<tiles.n, 64 * MF_W, 0, l.s>>>(tiles.t, B->tree, B->lists[LU], B->sx, B->sy, B->sz, sF,   \
-                                                          B->n, q.kd, q.S, q.c1S, u);                              \
+    k_p2p_mfma<false, XR><<<g.blocks, 64 * MF_W, 0, l.s>>>(tiles.t, g.item, g.slots, B->tree, B->lists[LU], B->sx,   \
+                                                           B->sy, B->sz, sF, B->n, q.kd, q.S, q.c1S, u, part);     \
     break;
     MF_CASE(1)
     MF_CASE(2)
@@ -724,29 +966,31 @@ hipError_t run_p2p(const Launch& l, const Tiles& tiles, int nrc, const double* s
   }
 #undef P2P_CASE
 #undef MF_CASE
-  return hipGetLastError();
+  return near_reduce(l, tiles, np.u, g, 3 * nrc, part, u, 0);
 }
 
 // The overlap correction: FP32 pair arithmetic (the factored differences)
 // with FP64 sums per staged chunk in the mixed form, FP64 otherwise.
-hipError_t run_overlap(const Launch& l, const Tiles& tiles, int nrc, const double* sF, double* u, int mixed) {
+hipError_t run_overlap(const Launch& l, const Tiles& tiles, const NearPlan& np, int nrc, const double* sF, double* u,
+                       double* part, int mixed) {
   const Built* B = l.B;
-  if (tiles.n == 0 || B->lists[LO].len == 0) return hipSuccess;
+  if (tiles.n == 0 || B->lists[LO].len == 0 || np.o.nothing) return hipSuccess;
   if (nrc > NEAR_VEC_RHS) {  // launches of 8 right-hand sides, then the rest
-    const hipError_t he = run_overlap(l, tiles, NEAR_VEC_RHS, sF, u, mixed);
+    const hipError_t he = run_overlap(l, tiles, np, NEAR_VEC_RHS, sF, u, part, mixed);
     const int64_t off = (int64_t)NEAR_VEC_RHS * 3 * B->n;
-    return he != hipSuccess ? he : run_overlap(l, tiles, nrc - NEAR_VEC_RHS, sF + off, u + off, mixed);
+    return he != hipSuccess ? he : run_overlap(l, tiles, np, nrc - NEAR_VEC_RHS, sF + off, u + off, part, mixed);
   }
   const PairLaunch q = pair_launch(l.a, l.eta);
-  const double four_a2 = 4.0 * l.a * l.a;
+  const ChunkFilter f{LO, 0, 4.0 * l.a * l.a};
+  const NearGrid g(tiles, np.o, part);
 #define OV_CASE(NR)                                                                                                 \
   case NR:                                                                                                          \
     if (mixed)                                                                                                      \
-      k_overlap<NR, true><<<tiles.n, P2P_T, 0, l.s>>>(tiles.t, tiles.box, B->tree, B->lists[LO], four_a2, B->sx,    \
-                                                      B->sy, B->sz, sF, B->n, q.kf, q.S, q.c1S, u);                 \
+      k_overlap<NR, true><<<g.blocks, P2P_T, 0, l.s>>>(tiles.t, tiles.box, g.item, g.slots, B->tree, B->lists[LO],  \
+                                                       f, B->sx, B->sy, B->sz, sF, B->n, q.kf, q.S, q.c1S, u, part); \
     else                                                                                                            \
-      k_overlap<NR, false><<<tiles.n, P2P_T, 0, l.s>>>(tiles.t, tiles.box, B->tree, B->lists[LO], four_a2, B->sx,   \
-                                                       B->sy, B->sz, sF, B->n, q.kd, q.S, q.c1S, u);                \
+      k_overlap<NR, false><<<g.blocks, P2P_T, 0, l.s>>>(tiles.t, tiles.box, g.item, g.slots, B->tree, B->lists[LO], \
+                                                        f, B->sx, B->sy, B->sz, sF, B->n, q.kd, q.S, q.c1S, u, part); \
     break;
   switch (nrc) {
     OV_CASE(1)
@@ -756,29 +1000,31 @@ hipError_t run_overlap(const Launch& l, const Tiles& tiles, int nrc, const doubl
     default: return hipErrorInvalidValue;
   }
 #undef OV_CASE
-  return hipGetLastError();
+  return near_reduce(l, tiles, np.o, g, 3 * nrc, part, u, 1);
 }
 
 // The direct W sums are far-formula pair sums like the P2P: FP32 in the
 // mixed form.
-hipError_t run_wdirect(const Launch& l, const Tiles& tiles, int nrc, const double* sF, double* u, int mixed) {
+hipError_t run_wdirect(const Launch& l, const Tiles& tiles, const NearPlan& np, int nrc, const double* sF, double* u,
+                       double* part, int mixed) {
   const Built* B = l.B;
-  if (tiles.n == 0 || B->lists[LW].len == 0 || l.wd < 0) return hipSuccess;
+  if (tiles.n == 0 || B->lists[LW].len == 0 || l.wd < 0 || np.w.nothing) return hipSuccess;
   if (nrc > NEAR_VEC_RHS) {  // launches of 8 right-hand sides, then the rest
-    const hipError_t he = run_wdirect(l, tiles, NEAR_VEC_RHS, sF, u, mixed);
+    const hipError_t he = run_wdirect(l, tiles, np, NEAR_VEC_RHS, sF, u, part, mixed);
     const int64_t off = (int64_t)NEAR_VEC_RHS * 3 * B->n;
-    return he != hipSuccess ? he : run_wdirect(l, tiles, nrc - NEAR_VEC_RHS, sF + off, u + off, mixed);
+    return he != hipSuccess ? he : run_wdirect(l, tiles, np, nrc - NEAR_VEC_RHS, sF + off, u + off, part, mixed);
   }
   const PairLaunch q = pair_launch(l.a, l.eta);
-  const int wmax = l.wd;
+  const ChunkFilter f{LW, l.wd, 0.0};
+  const NearGrid g(tiles, np.w, part);
 #define WD_CASE(NR)                                                                                                 \
   case NR:                                                                                                          \
     if (mixed)                                                                                                      \
-      k_wdirect<NR, true><<<tiles.n, P2P_T, 0, l.s>>>(tiles.t, B->tree, B->lists[LW], wmax, B->sx, B->sy, B->sz, sF, \
-                                                      B->n, q.kf, q.S, q.c1S, u);                                   \
+      k_wdirect<NR, true><<<g.blocks, P2P_T, 0, l.s>>>(tiles.t, g.item, g.slots, B->tree, B->lists[LW], f, B->sx,   \
+                                                       B->sy, B->sz, sF, B->n, q.kf, q.S, q.c1S, u, part);          \
     else                                                                                                            \
-      k_wdirect<NR, false><<<tiles.n, P2P_T, 0, l.s>>>(tiles.t, B->tree, B->lists[LW], wmax, B->sx, B->sy, B->sz,    \
-                                                       sF, B->n, q.kd, q.S, q.c1S, u);                              \
+      k_wdirect<NR, false><<<g.blocks, P2P_T, 0, l.s>>>(tiles.t, g.item, g.slots, B->tree, B->lists[LW], f, B->sx,  \
+                                                        B->sy, B->sz, sF, B->n, q.kd, q.S, q.c1S, u, part);         \
     break;
   switch (nrc) {
     WD_CASE(1)
@@ -788,9 +1034,16 @@ hipError_t run_wdirect(const Launch& l, const Tiles& tiles, int nrc, const doubl
     default: return hipErrorInvalidValue;
   }
 #undef WD_CASE
-  return hipGetLastError();
+  return near_reduce(l, tiles, np.w, g, 3 * nrc, part, u, 1);
 }
 
+// Bytes of the partial-sum slots for near-field groups of nrn right-hand
+// sides (0: no tile is split).
+int64_t near_part_bytes(const NearPlan& np, int nrn) {
+  const int64_t vec = std::max(np.w.nslot, np.o.nslot);  // launches of at most NEAR_VEC_RHS
+  const int64_t rows = std::max((int64_t)np.u.nslot * nrn, vec * std::min(nrn, NEAR_VEC_RHS));
+  return rows * 3 * P2P_T * (int64_t)sizeof(double);
+}
 
 // ------------------------------------------------ sampled direct sums ---
 // The exact RPY matvec (Sec. 1, all three blocks) at a few targets, summed

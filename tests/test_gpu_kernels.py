@@ -27,6 +27,52 @@ def test_evaluation_streams(orc, p, nrhs):
     assert orc.rel_l2(u, ref) <= 1e-12
 
 
+# Near-field tiles split over several blocks (few tiles, or one list much
+# longer than the others): one bead, tiles of 1, 127, 128 and 129 beads, a leaf
+# of several chunks, on the vector units and the matrix cores; one leaf, so the
+# matvec is the direct sum and the far field is empty.
+@pytest.mark.parametrize("n,nrhs", [(1, 1), (127, 2), (128, 1), (129, 4), (1025, 1), (2500, 17), (2500, 8)])
+def test_split_single_leaf_is_direct(orc, n, nrhs):
+    w = W.uniform_cube(n, 1.0, 0.03, nrhs=nrhs, seed=310 + n)
+    log(f"split single leaf n={n} nrhs={nrhs}")
+    u, st = gpu_matvec(w.pos, w.forces, w.a, w.eta, 1e-6, leaf_size=10_000)
+    assert st["nleaf"] == 1
+    ref = orc.rpy_direct(w.pos, w.forces, w.a, w.eta)
+    assert orc.rel_l2(u, ref) <= 1e-12
+    um, _ = gpu_matvec(w.pos, w.forces, w.a, w.eta, 1e-6, leaf_size=10_000, precision="mixed")
+    assert orc.rel_l2(um, u) <= 5e-7
+
+
+# Split U, W and O lists together: clustered beads in leaves of up to 300, with
+# overlapping pairs outside U; the W boxes summed directly.
+@pytest.mark.parametrize("nrhs", [1, 3, 18])
+def test_split_adaptive_lists(orc, nrhs):
+    w = W.clustered(9000, 4, 12.0, 0.6, 0.3, nrhs, seed=320)
+    log(f"split adaptive lists nrhs={nrhs}")
+    u, st = gpu_matvec(w.pos, w.forces, w.a, w.eta, 1e-6, leaf_size=300, order=6, w_direct=10**6)
+    assert st["list_len"]["W"] > 0 and st["list_len"]["O"] > 0
+    ref = orc.fmm(w.pos, w.forces, w.a, w.eta, 6, 300, 10**6)
+    assert orc.rel_l2(u, ref) <= 1e-12
+
+
+# An empty far field: two leaves next to each other (no V, W or X entries),
+# and an injected error is still reported at a far-field phase.
+def test_empty_far_field(orc):
+    import paper_1711_02976_amd as R
+    from gpu_common import to_dev
+    w = W.uniform_cube(400, 1.0, 0.02, nrhs=5, seed=330)
+    log("empty far field n=400")
+    P = R.Plan(to_dev(w.pos), w.a, w.eta, 1e-6, leaf_size=100)
+    try:
+        st = P.stats()
+        assert st["nleaf"] > 1 and st["list_len"]["V"] == 0 and st["list_len"]["X"] == 0
+        u = P.matvec(to_dev(w.forces)).cpu().numpy()
+        assert orc.rel_l2(u, orc.rpy_direct(w.pos, w.forces, w.a, w.eta)) <= 1e-12
+        P.inject_error("eval")
+        with pytest.raises(R.RpyError):
+            P.matvec(to_dev(w.forces))
+    finally:
+        P.free()
 # Interaction lists built by a wave per box, bit-exact against the oracle's:
 # leaves of one bead, O lists longer than the sort's LDS buffer (dense beads in
 # tiny leaves), a depth cap, and the deepest tree (beads in pairs 2^-19 apart).
