@@ -928,7 +928,7 @@ rpy_status rpy_plan_batched(rpy_plan_t** out, int32_t nsys, const int64_t* count
   // library choice: the component polynomials at low orders (fewer
   // operations per target), the derivative sets above
   if (P->eval_mode == 0) P->eval_mode = P->p <= EVAL_POLY_AUTO_MAX ? rpy::EVAL_POLY : rpy::EVAL_SETS;
-  if (rc == 0) rc = rpy::make_tables(P->p, &P->tb, P->stream, &err);
+  if (rc == 0) rc = rpy::make_tables(P->p, P->precision == RPY_PREC_MIXED, &P->tb, P->stream, &err);
   if (rc == 0) rc = rpy::make_tiles(&P->B, 128, &P->tiles, P->stream, &err);
   if (rc == 0) rc = rpy::make_near_plan(&P->B, P->tiles, P->a, P->wd, &P->np, P->stream, &err);
   if (rc == 0) rc = rpy::make_eval_plan(&P->B, P->p, P->wd, P->eval_mode, &P->ep, P->stream, &err);

@@ -58,6 +58,12 @@ struct Tables {
   double* zt64;
   float* zt32;
   double* geo;
+  // k_m2l_rows (m2l_rot.hip), in the plan's precision: matrices by groups of
+  // rows, phases per offset; rows_nc columns per batch (0: not used)
+  void* rows_rot;
+  void* rows_zt;
+  void* rows_ph;
+  int rows_nc;
   double* sfac;    // [ncoef(p)] sqrt((n-m)!(n+m)!)
   double* rscale;  // [ncoef(p)] 1/((n-m)!(n+m)!)
   // S->M / S->L schedules (K = 8 and K = 16 steps per wave and pass) and
@@ -69,7 +75,9 @@ struct Tables {
   int64_t bytes;
 };
 
-int make_tables(int p, Tables* tb, hipStream_t s, Error* err);
+int make_tables(int p, int fp32, Tables* tb, hipStream_t s, Error* err);
+int make_m2l_tables(const std::vector<double>& rot, const std::vector<double>& zt, int fp32, Tables* tb, hipStream_t s,
+                    Error* err);  // m2l_rot.hip; called by make_tables
 int make_p2e_tables(int p, Tables* tb, Error* err);  // p2e.hip; called by make_tables
 
 // Host helpers (fmm.hip): paper-normalised Y_n^m for 0 <= m <= n <= p at

@@ -328,7 +328,7 @@ int compute_tables(int p, HostTables* h, Error* err) {
 }
 }  // namespace
 
-int make_tables(int p, Tables* tb, hipStream_t s, Error* err) {
+int make_tables(int p, int fp32, Tables* tb, hipStream_t s, Error* err) {
   tb->p = p;
   tb->bytes = 0;
   if (p < 0 || p > MAX_ORDER) {
@@ -379,12 +379,12 @@ int make_tables(int p, Tables* tb, hipStream_t s, Error* err) {
   RPY_HIP(hipMemcpy(tb->zt32, zt32.data(), sizeof(float) * zt32.size(), hipMemcpyHostToDevice));
   RPY_HIP(hipMemcpy(tb->geo, geo.data(), sizeof(double) * geo.size(), hipMemcpyHostToDevice));
   RPY_HIP(hipMemcpy(tb->sfac, sf.data(), sizeof(double) * sf.size(), hipMemcpyHostToDevice));
-  (void)s;
+  if (const int rc = make_m2l_tables(rot, zt, fp32, tb, s, err)) return rc;
   return make_p2e_tables(p, tb, err);
 }
 
 void free_tables(Tables* tb) {
-  void* ps[] = {tb->oct, tb->itab, tb->rot64, tb->rot32, tb->zt64, tb->zt32, tb->geo, tb->sfac, tb->rscale,
+  void* ps[] = {tb->oct, tb->itab, tb->rot64, tb->rot32, tb->zt64, tb->zt32, tb->geo, tb->rows_rot, tb->rows_zt, tb->rows_ph, tb->sfac, tb->rscale,
                 tb->p2e[0].desc, tb->p2e[0].slot, tb->p2e[0].scale, tb->p2e[1].desc, tb->p2e[1].slot,
                 tb->p2e[1].scale, tb->p2e_dk};
   for (void* q : ps)
@@ -392,6 +392,7 @@ void free_tables(Tables* tb) {
   tb->oct = tb->itab = nullptr;
   tb->rot64 = tb->zt64 = tb->geo = tb->sfac = tb->rscale = nullptr;
   tb->rot32 = tb->zt32 = nullptr;
+  tb->rows_rot = tb->rows_zt = tb->rows_ph = nullptr;
   for (P2ESched& s : tb->p2e) {
     s.desc = nullptr;
     s.slot = nullptr;

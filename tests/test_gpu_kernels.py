@@ -105,3 +105,20 @@ def test_lists_bit_exact(orc, case):
     for L in "UVWXO":
         assert np.array_equal(got["lists"][L][0], ref.lists[L][0]), L
         assert np.array_equal(got["lists"][L][1], ref.lists[L][1]), L
+
+
+# M->L at the edges of its kernels' order ranges in both precisions, one, two
+# and four right-hand sides per pass, V lists that fill batches of 64, 32 and
+# 16 columns unevenly; the FP64 form against the oracle FMM, the mixed form
+# against the FP64 one.
+@pytest.mark.parametrize("p,nrhs", [(10, 3), (11, 1), (16, 4), (17, 2), (21, 1), (21, 4), (22, 1), (27, 2)])
+def test_m2l_order_ranges(orc, p, nrhs):
+    for w in (W.uniform_cube(3000, 1.0, 0.005, nrhs=nrhs, seed=350), W.clustered(2500, 8, 10.0, 0.8, 0.05, nrhs, seed=351)):
+        log(f"M->L p={p} nrhs={nrhs} {w.name}")
+        kw = dict(order=p, leaf_size=40, w_direct=(p + 1) * (p + 2))
+        u, st = gpu_matvec(w.pos, w.forces, w.a, w.eta, 1e-6, **kw)
+        assert st["list_len"]["V"] > 0
+        ref = orc.fmm(w.pos, w.forces, w.a, w.eta, p, 40, (p + 1) * (p + 2))
+        assert orc.rel_l2(u, ref) <= 1e-12
+        um, _ = gpu_matvec(w.pos, w.forces, w.a, w.eta, 1e-6, precision="mixed", **kw)
+        assert orc.rel_l2(um, u) <= 5e-7
