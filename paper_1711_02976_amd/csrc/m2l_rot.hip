@@ -1074,7 +1074,7 @@ static hipError_t launch_rot(const Launch& l, int nrc, Exp e, const R* rot, cons
   //   FP32 17..21, 131 KB: one block of 16 waves (8 before: 64 systems of 16
   //     right-hand sides 35.6 -> 28.8 ms), all densities in one block where
   //     the V lists are too short to fill the batches of one right-hand side
-  //     (below 64 entries per box; dense clusters, 43: 27 against 31 ms, the
+  //     (below 54 entries per box; dense clusters, 43: 27 against 31 ms, the
   //     64 systems, 64: 32 against 29);
   //   FP64 up to 10: two blocks of 8 waves (order 7: 1.27 -> 0.74 ms);
   //   FP64 11..16, 160 KB: 12 waves (8 waves with all densities 78 ms, 12 with
@@ -1090,7 +1090,7 @@ static hipError_t launch_rot(const Launch& l, int nrc, Exp e, const R* rot, cons
   if constexpr (sizeof(R) == 4) {
     if (p <= 16) return launch_nd<R, 4, 16, 8, 4>(l, e, rot, zt, part, nrc);
     const List& V = l.B->lists[LV];
-    if (nrc > 1 && V.len < 64 * (int64_t)l.B->tree.nbox)
+    if (nrc > 1 && V.len < 54 * (int64_t)l.B->tree.nbox)
       return nrc == 2 ? launch_nd<R, 8, 21, 16, 4>(l, e, rot, zt, part, 1)
                       : launch_nd<R, 16, 21, 16, 4>(l, e, rot, zt, part, 1);
     return launch_nd<R, 4, 21, 16, 4>(l, e, rot, zt, part, nrc);

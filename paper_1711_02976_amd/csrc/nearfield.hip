@@ -208,12 +208,13 @@ __global__ void __launch_bounds__(P2P_T) k_near_reduce(const int4* tiles, const 
   if (k <= 1) return;
   const int4 tl = tiles[i];
   if ((int)threadIdx.x >= tl.z) return;
-  const int q = blockIdx.y;
-  const double* p = part + ((int64_t)slot0[i] * nq + q) * P2P_T + threadIdx.x;
-  double s = 0.0;
-  for (int j = 0; j < k; ++j) s += p[(int64_t)j * nq * P2P_T];
-  double* o = u + (int64_t)q * n + tl.y + threadIdx.x;
-  *o = add ? *o + s : s;
+  for (int q = blockIdx.y; q < nq; q += gridDim.y) {
+    const double* p = part + ((int64_t)slot0[i] * nq + q) * P2P_T + threadIdx.x;
+    double s = 0.0;
+    for (int j = 0; j < k; ++j) s += p[(int64_t)j * nq * P2P_T];
+    double* o = u + (int64_t)q * n + tl.y + threadIdx.x;
+    *o = add ? *o + s : s;
+  }
 }
 
 static int make_near_work(const Built* B, const Tiles& tiles, const ChunkFilter& f, NearWork* out, hipStream_t s,
@@ -497,7 +498,15 @@ __global__ void __launch_bounds__(P2P_T, (NRC == 4 && MIXED) ? 5 : 1) k_p2p(cons
 // In the FP64 form XR = 1, 2, 4 or 8 further right-hand sides ride in the
 // same launch on the vector units: each lane applies its pair block to them
 // (nine multiply-adds per right-hand side), so the pair geometry is formed
-// once for 16 + XR right-hand sides.  Their per-lane partial sums are added
+// once for 16 + XR right-hand sides.  FP32 and FP64 products and vector
+// instructions do not overlap on this chip (measured: their times add at one
+// to eight waves per SIMD), so the bound is their sum: per step nine products
+// of 32 (FP32) or 64 (FP64) cycles and about 27 (FP64 16 + 4: 80) vector
+// instructions.  The forces are staged row by row as they lie in memory, in
+// rows whose padding keeps both the stores and the reads free of bank
+// conflicts; that took the FP32 launch on 15M beads from 506 to 480 ms, 93 %
+// of that bound (index arithmetic per staged force and 16 lanes per bank
+// before).  Their per-lane partial sums are added
 // over the four source lanes of a target after each staged chunk, and lane
 // (t, k) keeps the FP64 sums of the right-hand sides k, k + 4.  (The mixed
 // form runs its extra right-hand sides in the vector kernel: there the
@@ -512,6 +521,11 @@ __device__ inline v4f_t mfma16(float a, float b, v4f_t c) { return __builtin_amd
 __device__ inline v4d_t mfma16(double a, double b, v4d_t c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
 // Row (target within the wave's 16) of item v of a 16x16 result in lane l;
 // the column (right-hand side) is l % 16 in both forms.
+// LDS row length of the staged forces: reads of lane (target t, source k) at
+// row 3 t + c, source s + k fall into 64 different banks (FP32: 12 t + k mod 64;
+// FP64: 30 t + k mod 32 per half wave); with 8 vector-unit right-hand sides a
+// shorter row, two lanes per bank, keeps two blocks per CU.
+constexpr int mf_ld(bool mixed, int xr) { return mixed ? 132 : (xr < 8 ? 138 : 131); }
 __device__ inline int mf_row(float, int l, int v) { return 4 * (l >> 4) + v; }
 __device__ inline int mf_row(double, int l, int v) { return 4 * v + (l >> 4); }
 }  // namespace
@@ -527,9 +541,11 @@ __global__ void __launch_bounds__(64 * MF_W) k_p2p_mfma(const int4* tiles, const
   using R4 = typename std::conditional<MIXED, float4, double4>::type;
   using VD = typename std::conditional<MIXED, v4f_t, v4d_t>::type;
   constexpr int XS = XR > 0 ? XR : 1, XH = (XR + 3) / 4 > 0 ? (XR + 3) / 4 : 1;
-  __shared__ R4 ps[P2P_T];          // positions (x, y, z, -)
-  __shared__ R fs[3][P2P_T][MF_R];  // [component][source][right-hand side]
-  __shared__ alignas(16) R fx[3][P2P_T][XS];  // the XR vector-unit right-hand sides
+  constexpr int ROWS = 3 * (MF_R + XR), LD = mf_ld(MIXED, XR);
+  __shared__ R4 ps[P2P_T];      // positions (x, y, z, -)
+  // forces along the sources: row 3 x + c of the vector-unit right-hand side x,
+  // then row 3 r + c of the others (both within reach of a load's offset)
+  __shared__ R fs[ROWS][LD];
   Part w(item, slots, xcd_run(blockIdx.x, gridDim.x), tiles, U);
   const int4 tl = tiles[w.tile];
   const int b = tl.x;
@@ -568,14 +584,18 @@ __global__ void __launch_bounds__(64 * MF_W) k_p2p_mfma(const int4* tiles, const
       } else if (tid < ns4) {
         ps[tid] = R4{(R)1e30, (R)1e30, (R)1e30, (R)0};
       }
-      // forces: sF row q = 3 r + c, read along the sources (coalesced)
-      for (int q = tid; q < 3 * (MF_R + XR) * P2P_T; q += 64 * MF_W) {
-        const int row = q / P2P_T, sj = q - row * P2P_T;
-        if (sj < ns4) {
-          const R v = sj < ns ? (R)sF[(int64_t)row * n + jc + sj] : (R)0;
-          if (row < 3 * MF_R) fs[row % 3][sj][row / 3] = v;
-          else fx[(row - 3 * MF_R) % 3][sj][(row - 3 * MF_R) / 3] = v;
-        }
+      // forces: rows of sF, read and stored along the sources; a thread keeps
+      // its source and takes every fourth row
+      {
+        const int sj = tid & (P2P_T - 1), row0 = __builtin_amdgcn_readfirstlane(tid / P2P_T);
+        const double* F = sF + (int64_t)row0 * n + jc + min(sj, ns - 1);
+        if (sj < ns4)
+#pragma unroll
+          for (int row = row0, q = 0; q < (ROWS + 3) / 4; ++q, row += 64 * MF_W / P2P_T, F += 64 * MF_W / P2P_T * n)
+            if (ROWS % 4 == 0 || row < ROWS) {
+              const R v = (R)*F;
+              fs[XR == 0 || row < 3 * MF_R ? row + 3 * XR : row - 3 * MF_R][sj] = sj < ns ? v : (R)0;
+            }
       }
       __syncthreads();
       if (wlive) {
@@ -606,9 +626,9 @@ __global__ void __launch_bounds__(64 * MF_W) k_p2p_mfma(const int4* tiles, const
             m[4] = bx * dz;
             m[5] = by * dz;
           }
-          f[0] = fs[0][j][ti];
-          f[1] = fs[1][j][ti];
-          f[2] = fs[2][j][ti];
+          f[0] = fs[3 * XR + 3 * ti][j];
+          f[1] = fs[3 * XR + 3 * ti + 1][j];
+          f[2] = fs[3 * XR + 3 * ti + 2][j];
           D[0] = mfma16(m[0], f[0], D[0]);
           D[1] = mfma16(m[3], f[0], D[1]);
           D[2] = mfma16(m[4], f[0], D[2]);
@@ -620,7 +640,7 @@ __global__ void __launch_bounds__(64 * MF_W) k_p2p_mfma(const int4* tiles, const
           D[2] = mfma16(m[2], f[2], D[2]);
 #pragma unroll
           for (int x = 0; x < XR; ++x) {
-            const R gx = fx[0][j][x], gy = fx[1][j][x], gz = fx[2][j][x];
+            const R gx = fs[3 * x][j], gy = fs[3 * x + 1][j], gz = fs[3 * x + 2][j];
             xa[x][0] = fma(m[0], gx, fma(m[3], gy, fma(m[4], gz, xa[x][0])));
             xa[x][1] = fma(m[3], gx, fma(m[1], gy, fma(m[5], gz, xa[x][1])));
             xa[x][2] = fma(m[4], gx, fma(m[5], gy, fma(m[2], gz, xa[x][2])));
@@ -919,7 +939,11 @@ static hipError_t near_reduce(const Launch& l, const Tiles& tiles, const NearWor
                               const double* part, double* u, int add) {
   hipError_t he = hipGetLastError();
   if (he != hipSuccess || !g.item) return he;
-  k_near_reduce<<<dim3(tiles.n, nq), P2P_T, 0, l.s>>>(tiles.t, w.parts, w.slot0, part, nq, l.B->n, add, u);
+  // rows side by side only while there are few tiles (each block of a tile
+  // that is not split ends at once, but still has to be started: 1 ms for 20k
+  // tiles and 48 rows)
+  const int gy = std::max(1, std::min(nq, 4096 / tiles.n));
+  k_near_reduce<<<dim3(tiles.n, gy), P2P_T, 0, l.s>>>(tiles.t, w.parts, w.slot0, part, nq, l.B->n, add, u);
   return hipGetLastError();
 }
 

@@ -122,3 +122,15 @@ def test_m2l_order_ranges(orc, p, nrhs):
         assert orc.rel_l2(u, ref) <= 1e-12
         um, _ = gpu_matvec(w.pos, w.forces, w.a, w.eta, 1e-6, precision="mixed", **kw)
         assert orc.rel_l2(um, u) <= 5e-7
+
+
+# Matrix-core P2P staging: source chunks of 1, 3, 125..129 and 256 beads and
+# every number of vector-unit right-hand sides in the same launch.
+@pytest.mark.parametrize("n,nrhs", [(17, 16), (131, 17), (253, 18), (129, 20), (257, 24), (384, 16)])
+def test_matrix_core_staging(orc, n, nrhs):
+    w = W.uniform_cube(n, 1.0, 0.05, nrhs=nrhs, seed=360 + n)
+    log(f"matrix-core staging n={n} nrhs={nrhs}")
+    u, st = gpu_matvec(w.pos, w.forces, w.a, w.eta, 1e-6, leaf_size=10_000)
+    assert orc.rel_l2(u, orc.rpy_direct(w.pos, w.forces, w.a, w.eta)) <= 1e-12
+    um, _ = gpu_matvec(w.pos, w.forces, w.a, w.eta, 1e-6, leaf_size=10_000, precision="mixed")
+    assert orc.rel_l2(um, u) <= 5e-7
