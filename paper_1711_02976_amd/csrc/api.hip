@@ -199,12 +199,14 @@ struct Work {
   double* Q = nullptr;    // per-bead charges for S->M / S->L [n + 64][4 nrc]
   double2* DL = nullptr;  // evaluation sets (local expansions of the leaves)
   double2* DW = nullptr;  // evaluation sets (evaluated W-list multipoles)
-  double2* XP = nullptr;  // S->L partial sums of boxes split over several work items
+  double2* XP = nullptr;  // S->M / S->L partial sums of boxes split over several work items
   double* PV = nullptr;   // polynomial evaluation: the leaves' density polynomials
   float2* M32 = nullptr;  // mixed form: multipoles as the FP32 M->L reads them
   double* NP = nullptr;   // near-field partial sums (null: whole tiles)
+  double* EP = nullptr;   // evaluation partial sums (null: whole tiles)
+  bool fine = true;       // finer work items (XP holds their slots)
 };
-constexpr int WS_N = 12, WS_NP = 11;  // arrays of Work, in the order above
+constexpr int WS_N = 13;  // arrays of Work, in the order above
 
 struct rpy_plan_s {
   rpy::Built B;
@@ -255,10 +257,11 @@ struct rpy_plan_s {
 };
 
 // Bytes of each Work array for nrc right-hand sides per far-field pass and
-// nrn per near-field group (sF and u hold a group).  Q carries 64 rows past
+// nrn per near-field group (sF and u hold a group); split: with the
+// partial-sum slots that finer work items need.  Q carries 64 rows past
 // the last bead that the S->M/S->L kernels may read (with zero weight); they
 // must hold finite values (zeros).
-static void ws_sizes(const rpy_plan_t* P, int nrc, int nrn, size_t sz[WS_N]) {
+static void ws_sizes(const rpy_plan_t* P, int nrc, int nrn, bool split, size_t sz[WS_N]) {
   const int64_t T = rpy::ncoef(P->p);
   const int64_t nbox = std::max(P->B.tree.nbox, 1);
   const int64_t n = std::max<int64_t>(P->B.n, 1);
@@ -272,10 +275,11 @@ static void ws_sizes(const rpy_plan_t* P, int nrc, int nrn, size_t sz[WS_N]) {
   sz[5] = sizeof(double) * 4 * nrc * (n + 64);
   sz[6] = dlb;
   sz[7] = (size_t)dwb;
-  sz[8] = sizeof(double2) * std::max<int64_t>(P->B.nxshared, 1) * 4 * nrc * T;
+  sz[8] = sizeof(double2) * std::max(rpy::p2e_slots(&P->B, split), 1) * 4 * nrc * T;
   sz[9] = (size_t)pvb;
   sz[10] = P->precision == RPY_PREC_MIXED ? sizeof(float2) * nbox * 4 * nrc * T : 256;
-  sz[WS_NP] = (size_t)rpy::near_part_bytes(P->np, nrn);
+  sz[11] = split ? (size_t)rpy::near_part_bytes(P->np, nrn) : 0;
+  sz[12] = split ? (size_t)rpy::eval_part_bytes(P->ep, nrc) : 0;
 }
 
 static hipEvent_t get_event(rpy_plan_t* P) {
@@ -325,7 +329,7 @@ static void fold_events(rpy_plan_t* P) {
 
 static void free_ws(rpy_plan_t* P) {
   Work& w = P->ws;
-  void* ps[] = {w.M, w.L, w.sF, w.u, w.uf, w.Q, w.DL, w.DW, w.XP, w.PV, w.M32, w.NP};
+  void* ps[] = {w.M, w.L, w.sF, w.u, w.uf, w.Q, w.DL, w.DW, w.XP, w.PV, w.M32, w.NP, w.EP};
   for (void* p : ps)
     if (p) (void)hipFree(p);
   w = Work{};
@@ -340,11 +344,11 @@ static int alloc_ws(rpy_plan_t* P, int nrc, int nrn) {
   nrn = std::max(nrn, P->ws_nrn);
   free_ws(P);
   size_t sz[WS_N];
-  ws_sizes(P, nrc, nrn, sz);
+  ws_sizes(P, nrc, nrn, true, sz);
   Work& w = P->ws;
   void** dst[WS_N] = {(void**)&w.M, (void**)&w.L, (void**)&w.sF, (void**)&w.u, (void**)&w.uf,
                       (void**)&w.Q, (void**)&w.DL, (void**)&w.DW, (void**)&w.XP, (void**)&w.PV,
-                      (void**)&w.M32, (void**)&w.NP};
+                      (void**)&w.M32, (void**)&w.NP, (void**)&w.EP};
   int64_t tot = 0;
   // an injected allocation failure (rpy_plan_inject_error) hits half-way,
   // after some arrays are allocated, like a device that runs out of memory
@@ -426,7 +430,7 @@ static hipError_t matvec_group(rpy_plan_t* P, const rpy::Launch& l, const Work& 
   for (int q0 = 0; he == hipSuccess && q0 < cn;) {
     const int c = cn - q0 >= nrc ? nrc : (cn - q0 >= 2 && nrc >= 2 ? 2 : 1);
     const double* sFq = w.sF + q0 * n3;
-    const rpy::Exp e{w.M, w.L, w.Q, w.DL, w.DW, w.XP, w.PV, w.M32};
+    const rpy::Exp e{w.M, w.L, w.Q, w.DL, w.DW, w.XP, w.EP, w.fine, w.PV, w.M32};
     he = step(RPY_PH_P2M, 1, s0, [&] { return rpy::run_p2m(l, c, sFq, e); });
     // the deepest level's M->L needs only S->M: on a third stream, beside
     // the upward pass (it writes L of other boxes than the second part)
@@ -439,7 +443,7 @@ static hipError_t matvec_group(rpy_plan_t* P, const rpy::Launch& l, const Work& 
       if (he == hipSuccess) he = step(RPY_PH_M2L, 1, P->far2, [&] { return rpy::run_m2l_rot(l2, c, e, mixed, 0); });
       if (he == hipSuccess) he = hipEventRecord(P->ev_m2l0, P->far2);
     }
-    if (he == hipSuccess) he = step(RPY_PH_M2M, nlev > 2 ? nlev - 2 : 0, s0, [&] { return rpy::run_m2m(l, c, e); });
+    if (he == hipSuccess) he = step(RPY_PH_M2M, nlev > 2 ? nlev - 2 : 0, s0, [&] { return rpy::run_m2m(l, c, e, P->eval_mode == rpy::EVAL_POLY); });
     if (he == hipSuccess) he = step(RPY_PH_M2L, 1, s0, [&] {
       if (P->m2l_mode == 1) return rpy::run_m2l(l, c, e);
       return rpy::run_m2l_rot(l, c, e, mixed, split ? 1 : -1);
@@ -934,7 +938,7 @@ rpy_status rpy_plan_batched(rpy_plan_t** out, int32_t nsys, const int64_t* count
   if (rc == 0) rc = rpy::make_eval_plan(&P->B, P->p, P->wd, P->eval_mode, &P->ep, P->stream, &err);
   P->no_far = P->B.lists[rpy::LV].len == 0 && P->B.lists[rpy::LX].len == 0 && P->ep.nwbig == 0;
   if (rc == 0) rc = rpy::make_m2l_map(&P->B, P->stream, &err);
-  if (rc == 0) rc = rpy::make_p2l_work(&P->B, P->stream, &err);
+  if (rc == 0) rc = rpy::make_p2e_work(&P->B, P->stream, &err);
   if (rc == 0) {
     // default priority (no priority argument); without it the near field
     // runs on the plan's stream
@@ -1027,10 +1031,9 @@ rpy_status rpy_matvec_noalloc(rpy_plan_t* P, int32_t nrhs, const double* forces,
   if (P->p > rpy::MAX_ORDER_MULTI) nrc = 1;
   int nrn = std::max(nrc, near_group_max(nrhs, P->precision == RPY_PREC_MIXED));
   size_t sz[WS_N], tot = 0;
-  bool split = true;  // near-field tiles split over several blocks, if the slots fit too
+  bool split = true;  // finer work items, if their partial sums fit too
   for (;;) {
-    ws_sizes(P, nrc, nrn, sz);
-    if (!split) sz[WS_NP] = 0;
+    ws_sizes(P, nrc, nrn, split, sz);
     tot = 0;
     for (int k = 0; k < WS_N; ++k) tot += align256(sz[k]);
     if (tot <= NOALLOC_SCRATCH_BYTES) break;
@@ -1057,9 +1060,10 @@ rpy_status rpy_matvec_noalloc(rpy_plan_t* P, int32_t nrhs, const double* forces,
     unsigned char* q = static_cast<unsigned char*>(base);
     void** dst[WS_N] = {(void**)&w.M, (void**)&w.L, (void**)&w.sF, (void**)&w.u, (void**)&w.uf,
                         (void**)&w.Q, (void**)&w.DL, (void**)&w.DW, (void**)&w.XP, (void**)&w.PV,
-                        (void**)&w.M32, (void**)&w.NP};
+                        (void**)&w.M32, (void**)&w.NP, (void**)&w.EP};
+    w.fine = split;
     for (int k = 0; k < WS_N; ++k) {
-      *dst[k] = k == WS_NP && sz[k] == 0 ? nullptr : q;
+      *dst[k] = sz[k] == 0 ? nullptr : q;
       q += align256(sz[k]);
     }
   }
@@ -1271,8 +1275,8 @@ rpy_status rpy_plan_stats(const rpy_plan_t* P, rpy_plan_stats_t* out) {
   out->eval_mode = P->eval_mode;
   out->tuned = P->tuned ? (P->tune_hit ? 2 : 1) : 0;
   out->tune_err = P->tune_err;
-  out->p2l_items = P->B.nxwork;
-  out->p2l_split_boxes = P->B.nxred;
+  out->p2l_items = P->B.xw[1].n;
+  out->p2l_split_boxes = P->B.xw[1].nred;
   out->bead_pass_ms = P->bead_pass_ms;
   out->sort_passes = P->sort_passes;
   return RPY_OK;

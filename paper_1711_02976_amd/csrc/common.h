@@ -103,6 +103,19 @@ struct BuildArgs {
   Spare* spare = nullptr;                   // with presorted: bead arrays to reuse, if any
 };
 
+// Work items of a particle-to-expansion launch (p2e.hip): (box, first X entry,
+// end X entry, 1 + partial-sum slot or 0) and the range of 64-bead chunks taken
+// from each entry; a box split over several items has one reduction entry
+// (box, first slot, slot count) in red.
+struct P2EWork {
+  int4* work = nullptr;  // owns the others
+  int2* chunks = nullptr;
+  int4* red = nullptr;
+  int n = 0;
+  int nslot = 0;  // partial-sum slots (items whose box is split)
+  int nred = 0;   // boxes split over several items
+};
+
 // Everything rpy_plan builds on the device.  Owned buffers are released by
 // free_built().
 struct Built {
@@ -134,16 +147,10 @@ struct Built {
   // sources need only S->M, blocks [m2l_part[1], m2l_part[2]) the others
   int* m2l_map = nullptr;
   int m2l_part[3] = {0, 0, 0};
-  // S->L work items (make_p2l_work): (box, first X entry, end X entry,
-  // 1 + partial-sum slot or 0) and the range of 64-bead chunks taken from
-  // each entry; a box split over several items has one reduction entry
-  // (box, first slot, slot count) in xred
-  int4* xwork = nullptr;
-  int2* xchunks = nullptr;
-  int4* xred = nullptr;
-  int nxwork = 0;
-  int nxshared = 0;   // partial-sum slots (items whose box is split)
-  int nxred = 0;      // boxes split over several items
+  // S->L work items, coarse and fine (the fine ones are the coarse ones where
+  // xfine says so), and S->M work items (n = 0: one block per leaf)
+  P2EWork xw[2], mw;
+  bool xfine = false;
   // bead passes of the build (bounding cubes, keys, sort, gather): GPU time
   // and radix-sort passes; 0 for a tree that copied them from another
   double bead_pass_ms = 0.0;

@@ -301,9 +301,14 @@ constexpr int EV_RHS = 2;
 constexpr int EV_PAD = 48 * EV_RHS + 16;  // doubles eval_sets may read past a stream
 constexpr int eval_group(int nrc) { return nrc < EV_RHS ? nrc : EV_RHS; }
 static_assert(eval_group(2) * 1 == 2 && 4 % eval_group(4) == 0, "right-hand sides in whole groups");
-// Writes (assigns) the far-field velocity of every bead of the tile.
+// Writes (assigns) the far-field velocity of every bead of the tile.  With a
+// part table a wave takes one expansion of a tile (the local one or a W box's)
+// and a tile with several writes its sums to slots of 64 targets, added by
+// k_eval_reduce: plans of few tiles are bound by the longest one (20k clustered
+// beads, 313 tiles: 0.43 ms for two right-hand sides, 0.08 split).
 template <int NRC>
-__global__ void __launch_bounds__(64 * EV_WAVES, 4) k_eval_apply(int p, const int4* tiles, int ntiles, Tree t, List W,
+__global__ void __launch_bounds__(64 * EV_WAVES, 4) k_eval_apply(int p, const int4* tiles, int ntiles,
+                                                             const int4* item, int nitem, double* part, Tree t, List W,
                                                              const int* widx,
                                                    const double* sx, const double* sy, const double* sz, int64_t n,
                                                    const double* __restrict__ DL, const double* __restrict__ DW,
@@ -311,22 +316,26 @@ __global__ void __launch_bounds__(64 * EV_WAVES, 4) k_eval_apply(int p, const in
   // consecutive tiles (mostly of one leaf) share a block, hence a CU and its
   // scalar cache, and walk the same set coefficients at about the same time
   const int ti = blockIdx.x * EV_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (ti >= ntiles) return;
-  const int4 tl = tiles[ti];
+  if (ti >= (item ? nitem : ntiles)) return;
+  const int4 it = item ? item[ti] : make_int4(ti, -1, -1, 0);
+  const int4 tl = tiles[it.x];
   const int b = tl.x, lane = threadIdx.x & 63;
   const int j = tl.y + min(lane, tl.z - 1);
   const double px = sx[j], py = sy[j], pz = sz[j];
   const int T = ncoef(p), To = ncoef(p + 2);
   const double cx = t.cx[b], cy = t.cy[b], cz = t.cz[b], h = t.h[b];
-  const int w0 = W.off[b], w1 = W.off[b + 1];
+  // W entries: all of the leaf's, or the part's one
+  const bool local = it.y < 0;
+  const int w0 = item ? max(it.y, 0) : W.off[b], w1 = item ? (local ? w0 : w0 + 1) : W.off[b + 1];
   constexpr int ER = eval_group(NRC);
 #pragma unroll 1
   for (int r = 0; r < NRC; r += ER) {
     double vel[ER][3];
 #pragma unroll
     for (int q = 0; q < ER; ++q) vel[q][0] = vel[q][1] = vel[q][2] = 0.0;
-    eval_sets<false, ER>(DL + (int64_t)(tl.w * (NRC / ER) + r / ER) * T * 24 * ER, p, px - cx, py - cy, pz - cz, h, C1,
-                         vel);
+    if (local)
+      eval_sets<false, ER>(DL + (int64_t)(tl.w * (NRC / ER) + r / ER) * T * 24 * ER, p, px - cx, py - cy, pz - cz, h, C1,
+                           vel);
     for (int e = w0; e < w1; ++e) {
       const int C = W.ent[e];
       const int wi = widx[C];
@@ -334,12 +343,54 @@ __global__ void __launch_bounds__(64 * EV_WAVES, 4) k_eval_apply(int p, const in
       eval_sets<true, ER>(DW + (int64_t)(wi * (NRC / ER) + r / ER) * To * 24 * ER, p + 2, px - t.cx[C], py - t.cy[C],
                           pz - t.cz[C], t.h[C], C1, vel);
     }
-    if (lane < tl.z)
+    if (lane < tl.z) {
+      double* out = it.z >= 0 ? part + (int64_t)it.z * 3 * NRC * 64 : u + tl.y;
+      const int64_t ld = it.z >= 0 ? 64 : n;
 #pragma unroll
       for (int q = 0; q < ER; ++q)
 #pragma unroll
-        for (int k = 0; k < 3; ++k) u[((int64_t)(r + q) * 3 + k) * n + tl.y + lane] = vel[q][k];
+        for (int k = 0; k < 3; ++k) out[((r + q) * 3 + k) * ld + lane] = vel[q][k];
+    }
   }
+}
+
+// The parts of every tile: cnt[i] = 1 + its leaf's evaluated W entries.
+__global__ void k_eval_count(const int4* tiles, int nt, List W, const int* widx, int* cnt) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= nt) return;
+  const int b = tiles[i].x;
+  int c = 1;
+  for (int e = W.off[b]; e < W.off[b + 1]; ++e) c += widx[W.ent[e]] >= 0;
+  cnt[i] = c;
+}
+
+// (tile, W entry or -1, slot or -1) of every part.
+__global__ void k_eval_fill(const int4* tiles, int nt, List W, const int* widx, const int* cnt, const int* off,
+                            int4* item) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= nt) return;
+  const int b = tiles[i].x, o = off[i];
+  const bool split = cnt[i] > 1;
+  item[o] = make_int4(i, -1, split ? o : -1, 0);
+  int k = o + 1;
+  for (int e = W.off[b]; e < W.off[b + 1]; ++e)
+    if (widx[W.ent[e]] >= 0) {
+      item[k] = make_int4(i, e, k, 0);
+      ++k;
+    }
+}
+
+// u = the sum of a split tile's parts, in list order; nq component rows.
+__global__ void __launch_bounds__(64) k_eval_reduce(const int4* tiles, const int* cnt, const int* off,
+                                                    const double* __restrict__ part, int nq, int64_t n, double* u) {
+  const int i = blockIdx.x, k = cnt[i], q = blockIdx.y;
+  const int4 tl = tiles[i];
+  if (k <= 1 || (int)threadIdx.x >= tl.z) return;
+  const double* p = part + ((int64_t)off[i] * nq + q) * 64 + threadIdx.x;
+  double s = 0.0;
+#pragma unroll 8
+  for (int j = 0; j < k; ++j) s += p[(int64_t)j * nq * 64];
+  u[(int64_t)q * n + tl.y + threadIdx.x] = s;
 }
 
 // ------------------------------------------- second evaluation approach ---
@@ -582,10 +633,17 @@ hipError_t launch_eval(const Launch& l, const EvalPlan& ep, Exp e, double* u) {
     return hipGetLastError();
   }
   ks<<<dim3(B->nleaf, NRC), sets_t(p), shm_l, l.s>>>(p, false, B->leaf_ids, B->tree, e.L, l.tb->rscale, C1, C2, er, DL);
-  if (ep.tiles.n > 0)
-    k_eval_apply<NRC><<<(ep.tiles.n + EV_WAVES - 1) / EV_WAVES, 64 * EV_WAVES, 0, l.s>>>(
-        p, ep.tiles.t, ep.tiles.n, B->tree, B->lists[LW], ep.widx, B->sx, B->sy, B->sz,
-                                                  B->n, DL, DW, C1, u);
+  if (ep.tiles.n > 0) {
+    const bool split = ep.item && e.EP;
+    const int waves = split ? ep.nitem : ep.tiles.n;
+    k_eval_apply<NRC><<<(waves + EV_WAVES - 1) / EV_WAVES, 64 * EV_WAVES, 0, l.s>>>(
+        p, ep.tiles.t, ep.tiles.n, split ? ep.item : nullptr, ep.nitem, e.EP, B->tree, B->lists[LW], ep.widx, B->sx,
+        B->sy, B->sz, B->n, DL, DW, C1, u);
+    he = hipGetLastError();
+    if (he == hipSuccess && split)
+      k_eval_reduce<<<dim3(ep.tiles.n, 3 * NRC), 64, 0, l.s>>>(ep.tiles.t, ep.parts, ep.slot0, e.EP, 3 * NRC, B->n, u);
+    if (he != hipSuccess) return he;
+  }
   return hipGetLastError();
 }
 
@@ -689,6 +747,28 @@ int make_eval_plan(const Built* B, int p, int wd, int mode, EvalPlan* out, hipSt
   RPY_HIP(hipMalloc(&out->wbig, sizeof(int) * std::max(out->nwbig, 1)));
   k_wbig_index<<<(nbox + 255) / 256, 256, 0, s>>>(flag, off, nbox, out->widx, out->wbig);
   RPY_HIP(hipGetLastError());
+  // one part per expansion while all of them are few enough to run at once
+  constexpr int EV_FEW = 8192;
+  const int nt = out->tiles.n;
+  if (mode == EVAL_SETS && out->nwbig > 0 && nt <= EV_FEW) {
+    int *cnt = nullptr, *po = nullptr, *pt = nullptr;
+    RPY_HIP(hipMalloc(&out->parts, sizeof(int) * (2 * (size_t)nt + scan_tmp_ints(nt))));
+    cnt = out->parts;
+    po = out->slot0 = cnt + nt;
+    pt = po + nt;
+    k_eval_count<<<(nt + 255) / 256, 256, 0, s>>>(out->tiles.t, nt, W, out->widx, cnt);
+    RPY_HIP(scan_exclusive(cnt, po, nt, pt, s));
+    RPY_HIP(hipMemcpyAsync(&last[0], po + nt - 1, sizeof(int), hipMemcpyDeviceToHost, s));
+    RPY_HIP(hipMemcpyAsync(&last[1], cnt + nt - 1, sizeof(int), hipMemcpyDeviceToHost, s));
+    RPY_HIP(hipStreamSynchronize(s));
+    const int total = last[0] + last[1];
+    if (total <= EV_FEW) {
+      RPY_HIP(hipMalloc(&out->item, sizeof(int4) * total));
+      k_eval_fill<<<(nt + 255) / 256, 256, 0, s>>>(out->tiles.t, nt, W, out->widx, cnt, po, out->item);
+      RPY_HIP(hipGetLastError());
+      out->nitem = total;
+    }
+  }
   RPY_HIP(hipStreamSynchronize(s));
   (void)hipFree(flag);
   (void)hipFree(off);
@@ -702,6 +782,11 @@ void free_eval_plan(EvalPlan* ep) {
   if (ep->widx) (void)hipFree(ep->widx);
   if (ep->wbig) (void)hipFree(ep->wbig);
   if (ep->kct) (void)hipFree(ep->kct);
+  if (ep->item) (void)hipFree(ep->item);
+  if (ep->parts) (void)hipFree(ep->parts);
+  ep->item = nullptr;
+  ep->parts = ep->slot0 = nullptr;
+  ep->nitem = 0;
   ep->tiles = Tiles{};
   ep->widx = ep->wbig = nullptr;
   ep->kct = nullptr;
@@ -720,6 +805,10 @@ int64_t eval_sets_bytes(const Built* B, const EvalPlan& ep, int p, int nrc, int6
   }
   *pv_bytes = sizeof(double);
   return per * ncoef(p) * nleaf + pad;
+}
+
+int64_t eval_part_bytes(const EvalPlan& ep, int nrc) {
+  return (int64_t)sizeof(double) * 3 * nrc * 64 * ep.nitem;
 }
 
 hipError_t run_eval(const Launch& l, const EvalPlan& ep, int nrc, Exp e, double* u) {

@@ -20,7 +20,9 @@ struct Exp {
   double* Q;  // per-bead charges [n][4 nrc] for S->M and S->L (written by run_p2m)
   double2* DL;  // evaluation sets of the leaves' local expansions (eval.hip)
   double2* DW;  // evaluation sets of the W-list multipoles that are evaluated
-  double2* XP;  // S->L partial sums of split boxes [Built::nxshared][4 nrc][T]
+  double2* XP;  // S->M / S->L partial sums of split boxes [slots][4 nrc][T]
+  double* EP;   // evaluation: partial sums of split tiles (null: whole tiles)
+  bool fine;    // finer work items for plans with few boxes (XP holds their slots)
   double* PV;   // EVAL_POLY: monomial coefficients of the leaves' local expansions
   float2* M32;  // FP32 M->L: multipoles in the paper's normalisation, [nbox][4 nrc][T]
 };
@@ -102,15 +104,17 @@ hipError_t permute_forces(const Launch& l, const double* F, int nrhs_total, int 
 hipError_t unpermute_velocities(const Launch& l, const double* u, const double* uf, int r0, int nrc, double* out);
 
 hipError_t run_p2m(const Launch& l, int nrc, const double* sF, Exp e);
-hipError_t run_m2m(const Launch& l, int nrc, Exp e);
+hipError_t run_m2m(const Launch& l, int nrc, Exp e, bool poly);  // poly: EVAL_POLY plan
 hipError_t run_m2l(const Launch& l, int nrc, Exp e);       // dense O(p^4)
 // rotation, O(p^3); part 0: target boxes of the deepest level, 1: the
 // others, -1: all
 hipError_t run_m2l_rot(const Launch& l, int nrc, Exp e, int fp32, int part = -1);
 // Fills B->m2l_map / m2l_part, which run_m2l_rot needs (m2l_rot.hip).
 int make_m2l_map(Built* B, hipStream_t s, Error* err);
-// Fills B->xwork / xchunks / nxwork, which run_p2l needs (p2e.hip).
-int make_p2l_work(Built* B, hipStream_t s, Error* err);
+// Fills B->xw and B->mw, which run_p2l and run_p2m need (p2e.hip); slots of
+// partial sums they take with fine or coarse items.
+int make_p2e_work(Built* B, hipStream_t s, Error* err);
+int p2e_slots(const Built* B, bool fine);
 hipError_t run_p2l(const Launch& l, int nrc, const double* sF, Exp e);
 hipError_t run_l2l(const Launch& l, int nrc, Exp e);
 
@@ -138,7 +142,8 @@ struct NearWork {
   int* slot = nullptr;    // the part's partial-sum slot, -1: writes its sums itself
   int* parts = nullptr;   // per tile: parts
   int* slot0 = nullptr;   // per tile: first slot
-  int nslot = 0;
+  int* red = nullptr;     // the tiles with several parts
+  int nslot = 0, nred = 0;
   bool nothing = false;   // the kernel would sum no bead pair
 };
 struct NearPlan {
@@ -183,7 +188,15 @@ struct EvalPlan {
   int nwbig = 0;
   int mode = EVAL_SETS;
   double* kct = nullptr;  // EVAL_POLY: monomial table of the regular harmonics
+  // EVAL_SETS, plans of few tiles: one part per wave and expansion of a tile,
+  // (tile, W entry or -1: the local expansion, slot or -1: writes its sums
+  // itself); per tile its parts and first slot
+  int4* item = nullptr;
+  int* parts = nullptr;  // owns slot0
+  int* slot0 = nullptr;
+  int nitem = 0;
 };
+int64_t eval_part_bytes(const EvalPlan& ep, int nrc);
 int make_eval_plan(const Built* B, int p, int wd, int mode, EvalPlan* out, hipStream_t s, Error* err);
 void free_eval_plan(EvalPlan* ep);
 // Bytes of the evaluation-set arrays for nrc right-hand sides: returns the

@@ -446,56 +446,73 @@ hipError_t unpermute_velocities(const Launch& l, const double* u, const double* 
 // One block per parent box of one level; thread t = output coefficient (n,m):
 // M_n^m(P) = sum_{k<=n,l} 2^-k M_k^l(C) conj(R_{n-k}^{m-l}(d/h_P)).
 constexpr int TR_T = 256;
+// Levels with fewer blocks than this (boxes times right-hand sides) are split
+// further: the chip holds about 512 of the unsplit ones at p = 16.
+constexpr int TR_FEW = 512;
 
-// One block per (parent box, right-hand side): thread t = output (n,m) of
-// the four densities of that right-hand side, summing the children's
-// translated multipoles in turn (Rt and the child's four densities staged in
-// LDS, the fourth re-centred on the child first); each Rt entry read serves
-// the four densities.
-template <int ND>
-__global__ void __launch_bounds__(TR_T) k_m2m(int p, int ls, Tree t, const double2* oct, double2* M) {
-  const int b = ls + blockIdx.x, d0 = 4 * blockIdx.y;
-  const int nc = t.nchild[b];
+// Coefficient (k, l) of densities d .. d + GD - 1 of one right-hand side's four
+// (src), the fourth re-centred by w: f(g, value).
+template <int GD, class F>
+__device__ inline void recentred(const double2* src, int d, int T, int k, int l, int p, const double* w, F&& f) {
+  double2 v[GD];
+#pragma unroll
+  for (int g = 0; g < GD; ++g) v[g] = getc(src + (d + g) * T, k, l, p);
+  if (GD == 4 || d == 3)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const double2 u = GD == 4 ? v[c % GD] : getc(src + c * T, k, l, p);
+      v[GD - 1].x += w[c] * u.x;
+      v[GD - 1].y += w[c] * u.y;
+    }
+#pragma unroll
+  for (int g = 0; g < GD; ++g) f(g, v[g]);
+}
+
+// One block per (parent box, GD densities): thread t = output (n,m), summing
+// the children's translated multipoles in turn (Rt and the child's densities
+// staged in LDS, the fourth re-centred on the child first).  GD = 4, the
+// densities of one right-hand side, lets each Rt entry read serve four.  A level
+// with few parents leaves the chip idle that way (64 parents at p = 16: 147 us,
+// set by one block's 8 children): there a block takes one density of one child
+// (ONE) and k_m2m_sum adds the children's shares.
+template <int ND, int GD, bool ONE>
+__global__ void __launch_bounds__(TR_T) k_m2m(int p, int ls, Tree t, const double2* oct, double2* M, double2* part) {
+  const int C0 = ONE ? ls + blockIdx.x : 0;  // the level's boxes, or (ONE) their children's
+  const int b = ONE ? t.parent[C0] : ls + blockIdx.x, d0 = GD * blockIdx.y;
+  const int nc = ONE ? 1 : t.nchild[b];
   if (nc == 0) return;
   const int T = ncoef(p), F1 = (p + 1) * (p + 1);
   extern __shared__ double2 sm[];
   double2* Rt = sm;       // F1
-  double2* Mc = sm + F1;  // [4][F1]
+  double2* Mc = sm + F1;  // [GD][F1]
   // outputs threadIdx.x and threadIdx.x + TR_T (T exceeds TR_T above order 21)
-  double2 acc[2][4];
+  double2 acc[2][GD];
   int nq[2] = {0, 0}, mq[2] = {0, 0};
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
 #pragma unroll
-    for (int g = 0; g < 4; ++g) acc[q][g] = make_double2(0, 0);
+    for (int g = 0; g < GD; ++g) acc[q][g] = make_double2(0, 0);
     const int c = threadIdx.x + q * TR_T;
     if (c < T) {
       while (tri(nq[q] + 1) <= c) ++nq[q];
       mq[q] = c - tri(nq[q]);
     }
   }
-  for (int C = t.child[b]; C < t.child[b] + nc; ++C) {
+  for (int C = ONE ? C0 : t.child[b], C1 = C + nc; C < C1; ++C) {
     const int o = (t.ax[C] & 1) | ((t.ay[C] & 1) << 1) | ((t.az[C] & 1) << 2);
     const double w[3] = {t.cx[C] - t.cx[b], t.cy[C] - t.cy[b], t.cz[C] - t.cz[b]};
     __syncthreads();
     for (int i = threadIdx.x; i < F1; i += TR_T) Rt[i] = oct[(int64_t)o * F1 + i];
-    const double2* src = M + ((int64_t)C * ND + d0) * T;
+    const double2* src = M + ((int64_t)C * ND + (d0 & ~3)) * T;
     for (int f = threadIdx.x; f < F1; f += TR_T) {
       int k = (int)sqrt((double)f);
       while (k * k > f) --k;
       while ((k + 1) * (k + 1) <= f) ++k;
       const int l = f - k * k - k;
       const double sc = ldexp(1.0, -k);
-      double2 v[4];
-#pragma unroll
-      for (int g = 0; g < 4; ++g) v[g] = getc(src + g * T, k, l, p);
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        v[3].x += w[c] * v[c].x;
-        v[3].y += w[c] * v[c].y;
-      }
-#pragma unroll
-      for (int g = 0; g < 4; ++g) Mc[g * F1 + f] = make_double2(v[g].x * sc, v[g].y * sc);
+      recentred<GD>(src, d0 & 3, T, k, l, p, w, [&](int g, double2 v) {
+        Mc[g * F1 + f] = make_double2(v.x * sc, v.y * sc);
+      });
     }
     __syncthreads();
     for (int q = 0; q < 2; ++q) {
@@ -508,51 +525,61 @@ __global__ void __launch_bounds__(TR_T) k_m2m(int p, int ls, Tree t, const doubl
         for (int l = lmin; l <= lmax; ++l) {
           const double2 r = Rt[rj - l];
 #pragma unroll
-          for (int g = 0; g < 4; ++g) cfmac(acc[q][g], Mc[g * F1 + mk + l], r);
+          for (int g = 0; g < GD; ++g) cfmac(acc[q][g], Mc[g * F1 + mk + l], r);
         }
       }
     }
   }
+  double2* out = ONE ? part + ((int64_t)blockIdx.x * ND + d0) * T : M + ((int64_t)b * ND + d0) * T;
 #pragma unroll
   for (int q = 0; q < 2; ++q)
     if (threadIdx.x + q * TR_T < T)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) M[((int64_t)b * ND + d0 + g) * T + threadIdx.x + q * TR_T] = acc[q][g];
+      for (int g = 0; g < GD; ++g) out[(int64_t)g * T + threadIdx.x + q * TR_T] = acc[q][g];
+}
+
+// The multipole of every parent of a level as the sum of its children's shares
+// (part[child - cs][nd][T]), child by child.
+__global__ void __launch_bounds__(TR_T) k_m2m_sum(int T, int nd, int ls, int cs, Tree t, const double2* part, double2* M) {
+  const int b = ls + blockIdx.x, nc = t.nchild[b];
+  if (nc == 0) return;
+  const double2* src = part + (int64_t)(t.child[b] - cs) * nd * T;
+  for (int i = blockIdx.y * TR_T + threadIdx.x; i < nd * T; i += gridDim.y * TR_T) {
+    double2 v = make_double2(0.0, 0.0);
+    for (int k = 0; k < nc; ++k) {
+      const double2 w = src[(int64_t)k * nd * T + i];
+      v.x += w.x;
+      v.y += w.y;
+    }
+    M[(int64_t)b * nd * T + i] = v;
+  }
 }
 
 // ------------------------------------------------------------------ L->L --
-// One block per (child box of one level, right-hand side); thread t =
-// output (k,l) of the four densities:
+// One block per (child box of one level, GD densities); thread t = output
+// (k,l) of the densities:
 // L_k^l(C) += 2^-(k+1) sum_{n>=k,m} L_n^m(P) R_{n-k}^{m-l}(d/h_P),
-// each Rt entry read serving the four densities.
-template <int ND>
+// each Rt entry read serving the GD densities: four, one right-hand side's, or
+// one where the level has few boxes (as in k_m2m).
+template <int ND, int GD>
 __global__ void __launch_bounds__(TR_T) k_l2l(int p, int ls, Tree t, const double2* oct, double2* L) {
-  const int b = ls + blockIdx.x, d0 = 4 * blockIdx.y;
+  const int b = ls + blockIdx.x, d0 = GD * blockIdx.y;
   const int P = t.parent[b];
   if (P < 0) return;
   const int T = ncoef(p), F1 = (p + 1) * (p + 1);
   extern __shared__ double2 sm[];
   double2* Rt = sm;       // F1
-  double2* Lp = sm + F1;  // [4][F1]
+  double2* Lp = sm + F1;  // [GD][F1]
   const int o = (t.ax[b] & 1) | ((t.ay[b] & 1) << 1) | ((t.az[b] & 1) << 2);
   const double w[3] = {t.cx[P] - t.cx[b], t.cy[P] - t.cy[b], t.cz[P] - t.cz[b]};
   for (int i = threadIdx.x; i < F1; i += TR_T) Rt[i] = oct[(int64_t)o * F1 + i];
-  const double2* src = L + ((int64_t)P * ND + d0) * T;
+  const double2* src = L + ((int64_t)P * ND + (d0 & ~3)) * T;
   for (int f = threadIdx.x; f < F1; f += TR_T) {
     int k = (int)sqrt((double)f);
     while (k * k > f) --k;
     while ((k + 1) * (k + 1) <= f) ++k;
     const int l = f - k * k - k;
-    double2 v[4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) v[g] = getc(src + g * T, k, l, p);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      v[3].x += w[c] * v[c].x;
-      v[3].y += w[c] * v[c].y;
-    }
-#pragma unroll
-    for (int g = 0; g < 4; ++g) Lp[g * F1 + f] = v[g];
+    recentred<GD>(src, d0 & 3, T, k, l, p, w, [&](int g, double2 v) { Lp[g * F1 + f] = v; });
   }
   __syncthreads();
   // outputs threadIdx.x and threadIdx.x + TR_T (T exceeds TR_T above order 21)
@@ -560,9 +587,9 @@ __global__ void __launch_bounds__(TR_T) k_l2l(int p, int ls, Tree t, const doubl
     int k = 0;
     while (tri(k + 1) <= c) ++k;
     const int l = c - tri(k);
-    double2 acc[4];
+    double2 acc[GD];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) acc[g] = make_double2(0, 0);
+    for (int g = 0; g < GD; ++g) acc[g] = make_double2(0, 0);
     for (int n = k; n <= p; ++n) {
       const int j = n - k;
       const int mmin = max(-n, l - j), mmax = min(n, l + j);
@@ -570,12 +597,12 @@ __global__ void __launch_bounds__(TR_T) k_l2l(int p, int ls, Tree t, const doubl
       for (int m = mmin; m <= mmax; ++m) {
         const double2 r = Rt[rj + m];
 #pragma unroll
-        for (int g = 0; g < 4; ++g) cfma(acc[g], Lp[g * F1 + ln + m], r);
+        for (int g = 0; g < GD; ++g) cfma(acc[g], Lp[g * F1 + ln + m], r);
       }
     }
     const double sc = ldexp(1.0, -(k + 1));
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
+    for (int g = 0; g < GD; ++g) {
       double2* out = L + ((int64_t)b * ND + d0 + g) * T + c;
       const double2 v = *out;
       *out = make_double2(v.x + sc * acc[g].x, v.y + sc * acc[g].y);
@@ -659,7 +686,7 @@ __global__ void __launch_bounds__(M2L_T) k_m2l_dense(int p, int c0, Tree t, List
     default: return hipErrorInvalidValue;                  \
   }
 
-hipError_t run_m2m(const Launch& l, int nrc, Exp e) {
+hipError_t run_m2m(const Launch& l, int nrc, Exp e, bool poly) {
   const Built* B = l.B;
   const size_t shm = sizeof(double2) * 5 * (l.p + 1) * (l.p + 1);
   // parents down to level 2 only: multipoles at levels 0 and 1 are never
@@ -667,7 +694,21 @@ hipError_t run_m2m(const Launch& l, int nrc, Exp e) {
   // leaf's colleagues, so they sit at level 2 or deeper)
   for (int lev = B->depth - 1; lev >= 2; --lev) {
     const int ls = B->level_start[lev], le = B->level_start[lev + 1];
-    DISPATCH_ND(nrc, (k_m2m<ND><<<dim3(le - ls, ND / 4), TR_T, shm, l.s>>>(l.p, ls, B->tree, l.tb->oct, e.M)));
+    // few parents: a density of a child per block, into the evaluation sets'
+    // buffer, which is free until the evaluation and holds 12 sets per leaf (a
+    // level has no more boxes than there are leaves); the polynomial form's is
+    // large enough from order 5
+    if ((le - ls) * nrc < TR_FEW && !(poly && l.p < 5)) {
+      const int ce = B->level_start[lev + 2];
+      DISPATCH_ND(nrc, (k_m2m<ND, 1, true><<<dim3(ce - le, ND), TR_T, sizeof(double2) * 2 * (l.p + 1) * (l.p + 1), l.s>>>(
+                           l.p, le, B->tree, l.tb->oct, e.M, e.DL)));
+      hipError_t err = hipGetLastError();
+      if (err != hipSuccess) return err;
+      k_m2m_sum<<<dim3(le - ls, 2 * nrc), TR_T, 0, l.s>>>(ncoef(l.p), 4 * nrc, ls, le, B->tree, e.DL, e.M);
+    } else {
+      DISPATCH_ND(nrc, (k_m2m<ND, 4, false><<<dim3(le - ls, ND / 4), TR_T, shm, l.s>>>(l.p, ls, B->tree, l.tb->oct, e.M,
+                                                                                      nullptr)));
+    }
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
   }
@@ -702,7 +743,12 @@ hipError_t run_l2l(const Launch& l, int nrc, Exp e) {
   // V or X entries there), so level 2 keeps what M->L and S->L wrote
   for (int lev = 3; lev <= B->depth; ++lev) {
     const int ls = B->level_start[lev], le = B->level_start[lev + 1];
-    DISPATCH_ND(nrc, (k_l2l<ND><<<dim3(le - ls, ND / 4), TR_T, shm, l.s>>>(l.p, ls, B->tree, l.tb->oct, e.L)));
+    if ((le - ls) * nrc < TR_FEW) {
+      DISPATCH_ND(nrc, (k_l2l<ND, 1><<<dim3(le - ls, ND), TR_T, sizeof(double2) * 2 * (l.p + 1) * (l.p + 1), l.s>>>(
+                           l.p, ls, B->tree, l.tb->oct, e.L)));
+    } else {
+      DISPATCH_ND(nrc, (k_l2l<ND, 4><<<dim3(le - ls, ND / 4), TR_T, shm, l.s>>>(l.p, ls, B->tree, l.tb->oct, e.L)));
+    }
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
   }

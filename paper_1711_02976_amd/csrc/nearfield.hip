@@ -159,22 +159,26 @@ __global__ void __launch_bounds__(256) k_near_count(const int4* tiles, const dou
   }
 }
 
-// parts[i] = blocks of tile i, held[i] = its slots (0 when it has one part).
-__global__ void k_near_parts(const int* cnt, int nt, int cap, int* parts, int* held) {
+// parts[i] = blocks of tile i, held[i] = its slots (0 when it has one part),
+// flag[i] = 1 if it has several.
+__global__ void k_near_parts(const int* cnt, int nt, int cap, int* parts, int* held, int* flag) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= nt) return;
   const int k = (cnt[i] + cap - 1) / cap;
   parts[i] = k;
   held[i] = k > 1 ? k : 0;
+  flag[i] = k > 1;
 }
 
 // The parts of tile i: (tile, first list entry, first chunk of it, chunks)
 // and the slot (-1: the tile has one part), its chunks split evenly.
 __global__ void k_near_fill(const int4* tiles, const double* tbox, int nt, Tree t, List l, ChunkFilter f,
-                            const int* cnt, const int* off, const int* parts, const int* slot0, int4* item, int* slot) {
+                            const int* cnt, const int* off, const int* parts, const int* slot0,
+                            const int* order, int4* item, int* slot, int* red) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= nt || parts[i] == 0) return;
   const int b = tiles[i].x, k = parts[i], c = cnt[i];
+  if (k > 1) red[order[i]] = i;
   int e = l.off[b], ch = 0;  // the next chunk
   for (int q = 0; q < k; ++q) {
     int left = (int)((int64_t)c * (q + 1) / k - (int64_t)c * q / k);
@@ -200,21 +204,20 @@ __global__ void k_near_fill(const int4* tiles, const double* tbox, int nt, Tree 
   }
 }
 
-// u (+)= the slots of every split tile, in part order; nq component rows.
-__global__ void __launch_bounds__(P2P_T) k_near_reduce(const int4* tiles, const int* parts, const int* slot0,
-                                                       const double* __restrict__ part, int nq, int64_t n, int add,
-                                                       double* u) {
-  const int i = blockIdx.x, k = parts[i];
-  if (k <= 1) return;
+// u (+)= the slots of a split tile (red[blockIdx.x]), in part order; one block
+// per component row.
+__global__ void __launch_bounds__(P2P_T) k_near_reduce(const int4* tiles, const int* red, const int* parts,
+                                                       const int* slot0, const double* __restrict__ part, int nq,
+                                                       int64_t n, int add, double* u) {
+  const int i = red[blockIdx.x], k = parts[i], q = blockIdx.y;
   const int4 tl = tiles[i];
   if ((int)threadIdx.x >= tl.z) return;
-  for (int q = blockIdx.y; q < nq; q += gridDim.y) {
-    const double* p = part + ((int64_t)slot0[i] * nq + q) * P2P_T + threadIdx.x;
-    double s = 0.0;
-    for (int j = 0; j < k; ++j) s += p[(int64_t)j * nq * P2P_T];
-    double* o = u + (int64_t)q * n + tl.y + threadIdx.x;
-    *o = add ? *o + s : s;
-  }
+  const double* p = part + ((int64_t)slot0[i] * nq + q) * P2P_T + threadIdx.x;
+  double s = 0.0;
+#pragma unroll 8
+  for (int j = 0; j < k; ++j) s += p[(int64_t)j * nq * P2P_T];
+  double* o = u + (int64_t)q * n + tl.y + threadIdx.x;
+  *o = add ? *o + s : s;
 }
 
 static int make_near_work(const Built* B, const Tiles& tiles, const ChunkFilter& f, NearWork* out, hipStream_t s,
@@ -226,9 +229,9 @@ static int make_near_work(const Built* B, const Tiles& tiles, const ChunkFilter&
   // scratch: the counts, two statistics, and the tables' scans
   const size_t ntmp = scan_tmp_ints(nt);
   unsigned long long* stat = nullptr;
-  RPY_HIP(hipMalloc(&stat, 2 * sizeof(unsigned long long) + sizeof(int) * (3 * (size_t)nt + ntmp)));
+  RPY_HIP(hipMalloc(&stat, 2 * sizeof(unsigned long long) + sizeof(int) * (5 * (size_t)nt + ntmp)));
   int* cnt = reinterpret_cast<int*>(stat + 2);
-  int *held = cnt + nt, *off = held + nt, *tmp = off + nt;
+  int *held = cnt + nt, *off = held + nt, *flag = off + nt, *order = flag + nt, *tmp = order + nt;
   RPY_HIP(hipMemsetAsync(stat, 0, 2 * sizeof(unsigned long long), s));
   k_near_count<<<nblk(nt, 256), 256, 0, s>>>(tiles.t, tiles.box, nt, B->tree, l, f, cnt, stat);
   RPY_HIP(hipGetLastError());
@@ -240,25 +243,30 @@ static int make_near_work(const Built* B, const Tiles& tiles, const ChunkFilter&
   if (hs[1] > cap) {
     // at most total / cap + 1 per tile parts
     const size_t most = (size_t)NEAR_ITEMS + nt;
-    RPY_HIP(hipMalloc(&out->item, sizeof(int4) * most + sizeof(int) * (most + 2 * (size_t)nt)));
+    RPY_HIP(hipMalloc(&out->item, sizeof(int4) * most + sizeof(int) * (most + 3 * (size_t)nt)));
     out->slot = reinterpret_cast<int*>(out->item + most);
     out->parts = out->slot + most;
     out->slot0 = out->parts + nt;
+    out->red = out->slot0 + nt;
     k_near_parts<<<nblk(nt, 256), 256, 0, s>>>(cnt, nt, (int)std::min<unsigned long long>(cap, 0x7fffffff),
-                                               out->parts, held);
+                                               out->parts, held, flag);
     RPY_HIP(scan_exclusive(out->parts, off, nt, tmp, s));
     RPY_HIP(scan_exclusive(held, out->slot0, nt, tmp, s));
+    RPY_HIP(scan_exclusive(flag, order, nt, tmp, s));
     k_near_fill<<<nblk(nt, 64), 64, 0, s>>>(tiles.t, tiles.box, nt, B->tree, l, f, cnt, off, out->parts, out->slot0,
-                                            out->item, out->slot);
+                                            order, out->item, out->slot, out->red);
     RPY_HIP(hipGetLastError());
-    int last[4];
+    int last[6];
     RPY_HIP(hipMemcpyAsync(&last[0], off + nt - 1, sizeof(int), hipMemcpyDeviceToHost, s));
     RPY_HIP(hipMemcpyAsync(&last[1], out->parts + nt - 1, sizeof(int), hipMemcpyDeviceToHost, s));
     RPY_HIP(hipMemcpyAsync(&last[2], out->slot0 + nt - 1, sizeof(int), hipMemcpyDeviceToHost, s));
     RPY_HIP(hipMemcpyAsync(&last[3], held + nt - 1, sizeof(int), hipMemcpyDeviceToHost, s));
+    RPY_HIP(hipMemcpyAsync(&last[4], order + nt - 1, sizeof(int), hipMemcpyDeviceToHost, s));
+    RPY_HIP(hipMemcpyAsync(&last[5], flag + nt - 1, sizeof(int), hipMemcpyDeviceToHost, s));
     RPY_HIP(hipStreamSynchronize(s));
     out->n = last[0] + last[1];
     out->nslot = last[2] + last[3];
+    out->nred = last[4] + last[5];
   }
   (void)hipFree(stat);
   return 0;
@@ -939,11 +947,7 @@ static hipError_t near_reduce(const Launch& l, const Tiles& tiles, const NearWor
                               const double* part, double* u, int add) {
   hipError_t he = hipGetLastError();
   if (he != hipSuccess || !g.item) return he;
-  // rows side by side only while there are few tiles (each block of a tile
-  // that is not split ends at once, but still has to be started: 1 ms for 20k
-  // tiles and 48 rows)
-  const int gy = std::max(1, std::min(nq, 4096 / tiles.n));
-  k_near_reduce<<<dim3(tiles.n, gy), P2P_T, 0, l.s>>>(tiles.t, w.parts, w.slot0, part, nq, l.B->n, add, u);
+  k_near_reduce<<<dim3(w.nred, nq), P2P_T, 0, l.s>>>(tiles.t, w.red, w.parts, w.slot0, part, nq, l.B->n, add, u);
   return hipGetLastError();
 }
 

@@ -101,18 +101,21 @@ __global__ void __launch_bounds__(P2E_THREADS) k_p2e(int p, const int* ids, cons
   constexpr int G = S / 64, NB = P2E_WAVES / G, BPW = P2E_CHUNK / NB;
   static_assert(!VEC || NB * ND * S <= P2E_CHUNK * LD, "partial sums fit in the harmonics' LDS");
   const int T = ncoef(p);
-  // S->M: one leaf per block.  S->L: one work item per block, a run of the
-  // box's X entries and a range of 64-bead chunks of each; a box whose X
-  // work was split over several items writes each item's share to its own
-  // slot of `part`, and k_p2l_reduce adds the slots in a fixed order
+  // S->M: one leaf, or a work item's range of 64-bead chunks of it, per block.
+  // S->L: one work item per block, a run of the box's X entries and a range of
+  // chunks of each.  A box whose work was split over several items writes each
+  // item's share to its own slot of `part`, and k_p2e_reduce adds the slots in
+  // a fixed order
   int b, e0 = 0, e1 = 1, clo = 0, chi = 0x7fffffff;
   int pslot = -1;
-  if (LOCAL) {
+  if (LOCAL || xwork) {
     const int4 wk = xwork[blockIdx.x];
     const int2 ch = xchunks[blockIdx.x];
     b = wk.x;
-    e0 = wk.y;
-    e1 = wk.z;
+    if (LOCAL) {
+      e0 = wk.y;
+      e1 = wk.z;
+    }
     pslot = wk.w - 1;
     clo = ch.x;
     chi = ch.y;
@@ -142,10 +145,8 @@ __global__ void __launch_bounds__(P2E_THREADS) k_p2e(int p, const int* ids, cons
   for (int e = e0; e < e1; ++e) {
     const int C = LOCAL ? X.ent[e] : b;
     int j0 = t.begin[C], j1 = t.end[C];
-    if (LOCAL) {
-      j1 = (int)min((int64_t)j1, (int64_t)j0 + (int64_t)chi * P2E_CHUNK);
-      j0 += clo * P2E_CHUNK;
-    }
+    j1 = (int)min((int64_t)j1, (int64_t)j0 + (int64_t)chi * P2E_CHUNK);
+    j0 += clo * P2E_CHUNK;
     // Q holds the fourth charge about the source leaf's centre; about c:
     // F.(r - c) = F.(r - c_C) + F.(c_C - c)
     double wx = 0.0, wy = 0.0, wz = 0.0;
@@ -298,7 +299,7 @@ __global__ void __launch_bounds__(P2E_THREADS) k_p2e(int p, const int* ids, cons
           v.x += w.x;
           v.y += w.y;
         }
-        if (LOCAL && pslot >= 0) {
+        if (pslot >= 0) {
           part[((int64_t)pslot * ND + d) * T + c] = v;
           continue;
         }
@@ -333,7 +334,7 @@ __global__ void __launch_bounds__(P2E_THREADS) k_p2e(int p, const int* ids, cons
         const int c = slot_coef[ps * S + sl];
         if (c < 0) continue;
         double x = acc[ps][q][v];
-        if (LOCAL && pslot >= 0) {
+        if (pslot >= 0) {
           reinterpret_cast<double*>(part + ((int64_t)pslot * ND + d) * T + c)[row & 1] = x;
           continue;
         }
@@ -345,39 +346,50 @@ __global__ void __launch_bounds__(P2E_THREADS) k_p2e(int p, const int* ids, cons
     }
 }
 
-// Adds the split S->L shares of one box (xred: box, first slot, slot count)
-// to its local expansion, slot by slot in item order.
-template <int ND>
-__global__ void __launch_bounds__(256) k_p2l_reduce(int p, const int4* __restrict__ xred, const double2* __restrict__ part,
-                                                    double2* E) {
+// Adds the split shares of one box (red: box, first slot, slot count), slot by
+// slot in item order: to its local expansion, or as its multipole, scaled back
+// from S_n^m to R_n^m.
+template <int ND, bool LOCAL>
+__global__ void __launch_bounds__(256) k_p2e_reduce(int p, const int4* __restrict__ red, const double2* __restrict__ part,
+                                                    const double* __restrict__ rscale, double2* E) {
   const int T = ncoef(p);
-  const int4 rd = xred[blockIdx.x];
-  for (int i = threadIdx.x; i < ND * T; i += blockDim.x) {
-    double2 v = E[(int64_t)rd.x * ND * T + i];
+  const int4 rd = red[blockIdx.x];
+  for (int i = threadIdx.x + 256 * blockIdx.y; i < ND * T; i += 256 * gridDim.y) {
+    double2 v = LOCAL ? E[(int64_t)rd.x * ND * T + i] : make_double2(0.0, 0.0);
+#pragma unroll 8
     for (int k = 0; k < rd.z; ++k) {
       const double2 w = part[(int64_t)(rd.y + k) * ND * T + i];
       v.x += w.x;
       v.y += w.y;
     }
+    if (!LOCAL) {
+      const double f = rscale[i % T];
+      v.x *= f;
+      v.y *= f;
+    }
     E[(int64_t)rd.x * ND * T + i] = v;
   }
 }
 
+// w: work items (S->M: null or n = 0 for one block per leaf)
 template <int ND, bool LOCAL, int K, int P>
-hipError_t launch_p2e(const Launch& l, const P2ESched& sc, int grid, const int* ids, const double* Q, double2* E,
+hipError_t launch_p2e(const Launch& l, const P2ESched& sc, const P2EWork* w, const double* Q, double2* E,
                       double2* part) {
   const Built* B = l.B;
+  const bool items = w && w->n > 0;
+  const int grid = items ? w->n : (LOCAL ? 0 : B->nleaf);
   if (grid == 0) return hipSuccess;
   const size_t shm = sizeof(double2) * P2E_CHUNK * (P2E_WAVES * K + 1);
   auto kern = k_p2e<ND, LOCAL, K, P>;
   hipError_t he = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
   if (he != hipSuccess) return he;
-  kern<<<grid, P2E_THREADS, shm, l.s>>>(l.p, ids, B->xwork, B->xchunks, B->tree, B->lists[LX], B->sx, B->sy, B->sz, Q,
-                                        sc.desc, sc.slot, sc.scale, l.tb->p2e_dk, E, part);
+  kern<<<grid, P2E_THREADS, shm, l.s>>>(l.p, B->leaf_ids, items ? w->work : nullptr, items ? w->chunks : nullptr,
+                                        B->tree, B->lists[LX], B->sx, B->sy, B->sz, Q, sc.desc, sc.slot, sc.scale,
+                                        l.tb->p2e_dk, E, part);
   he = hipGetLastError();
-  if (he != hipSuccess || !LOCAL || B->nxred == 0) return he;
-  k_p2l_reduce<ND><<<B->nxred, 256, 0, l.s>>>(l.p, B->xred, part, E);
+  if (he != hipSuccess || !items || w->nred == 0) return he;
+  k_p2e_reduce<ND, LOCAL><<<dim3(w->nred, ND / 4), 256, 0, l.s>>>(l.p, w->red, part, l.tb->rscale, E);
   return hipGetLastError();
 }
 
@@ -386,36 +398,35 @@ hipError_t launch_p2e(const Launch& l, const P2ESched& sc, int grid, const int* 
 // side, the orders above 21); else 16 steps (132 KB, one block per CU).  The
 // matrix-core accumulators take 8 registers per pass and row tile.
 template <int ND, bool LOCAL>
-hipError_t launch_p2e_kp(const Launch& l, int grid, const int* ids, const double* Q, double2* E, double2* part) {
+hipError_t launch_p2e_kp(const Launch& l, const P2EWork* w, const double* Q, double2* E, double2* part) {
   const P2ESched& s8 = l.tb->p2e[0];
   const P2ESched& s16 = l.tb->p2e[1];
   switch (s8.P) {
-    case 1: return launch_p2e<ND, LOCAL, 8, 1>(l, s8, grid, ids, Q, E, part);
-    case 2: return launch_p2e<ND, LOCAL, 8, 2>(l, s8, grid, ids, Q, E, part);
-    case 3: return launch_p2e<ND, LOCAL, 8, 3>(l, s8, grid, ids, Q, E, part);
-    case 4: return launch_p2e<ND, LOCAL, 8, 4>(l, s8, grid, ids, Q, E, part);
+    case 1: return launch_p2e<ND, LOCAL, 8, 1>(l, s8, w, Q, E, part);
+    case 2: return launch_p2e<ND, LOCAL, 8, 2>(l, s8, w, Q, E, part);
+    case 3: return launch_p2e<ND, LOCAL, 8, 3>(l, s8, w, Q, E, part);
+    case 4: return launch_p2e<ND, LOCAL, 8, 4>(l, s8, w, Q, E, part);
     default: break;
   }
   if constexpr (ND == 4) {
     switch (s8.P) {
-      case 5: return launch_p2e<ND, LOCAL, 8, 5>(l, s8, grid, ids, Q, E, part);
-      case 6: return launch_p2e<ND, LOCAL, 8, 6>(l, s8, grid, ids, Q, E, part);
-      case 7: return launch_p2e<ND, LOCAL, 8, 7>(l, s8, grid, ids, Q, E, part);
+      case 5: return launch_p2e<ND, LOCAL, 8, 5>(l, s8, w, Q, E, part);
+      case 6: return launch_p2e<ND, LOCAL, 8, 6>(l, s8, w, Q, E, part);
+      case 7: return launch_p2e<ND, LOCAL, 8, 7>(l, s8, w, Q, E, part);
       default: break;
     }
   }
-  if (s16.P == 1) return launch_p2e<ND, LOCAL, 16, 1>(l, s16, grid, ids, Q, E, part);
-  if (s16.P == 2) return launch_p2e<ND, LOCAL, 16, 2>(l, s16, grid, ids, Q, E, part);
+  if (s16.P == 1) return launch_p2e<ND, LOCAL, 16, 1>(l, s16, w, Q, E, part);
+  if (s16.P == 2) return launch_p2e<ND, LOCAL, 16, 2>(l, s16, w, Q, E, part);
   return hipErrorInvalidValue;
 }
 
 template <bool LOCAL>
-hipError_t launch_p2e_nd(const Launch& l, int nrc, int grid, const int* ids, const double* Q, double2* E,
-                         double2* part) {
+hipError_t launch_p2e_nd(const Launch& l, int nrc, const P2EWork* w, const double* Q, double2* E, double2* part) {
   switch (nrc) {
-    case 1: return launch_p2e_kp<4, LOCAL>(l, grid, ids, Q, E, part);
-    case 2: return launch_p2e_kp<8, LOCAL>(l, grid, ids, Q, E, part);
-    case 4: return launch_p2e_kp<16, LOCAL>(l, grid, ids, Q, E, part);
+    case 1: return launch_p2e_kp<4, LOCAL>(l, w, Q, E, part);
+    case 2: return launch_p2e_kp<8, LOCAL>(l, w, Q, E, part);
+    case 4: return launch_p2e_kp<16, LOCAL>(l, w, Q, E, part);
     default: return hipErrorInvalidValue;
   }
 }
@@ -487,74 +498,107 @@ static int build_sched(int p, int K, int maxp, P2ESched* out, Error* err, int64_
   return 1;
 }
 
-// S->L work items.  A box's X entries are cut into runs of at most `cap`
-// 64-bead chunks, and an entry longer than that into chunk ranges, so that
-// no block carries much more than its share: on 64 systems at leaf 1640 one
-// box held 344 chunks against 17 per CU on average, and its block set the
-// kernel's length.  cap = max(16, total / 2048).
-int make_p2l_work(Built* B, hipStream_t s, Error* err) {
-  if (B->xwork) (void)hipFree(B->xwork);
-  if (B->xchunks) (void)hipFree(B->xchunks);
-  if (B->xred) (void)hipFree(B->xred);
-  B->xwork = nullptr;
-  B->xchunks = nullptr;
-  B->xred = nullptr;
-  B->nxwork = B->nxshared = B->nxred = 0;
-  const List& X = B->lists[LX];
-  const int nbox = B->tree.nbox;
-  if (X.len == 0 || nbox == 0) return 0;
-  std::vector<int> off(nbox + 1), ent(X.len), beg(nbox), end(nbox);
-  RPY_HIP(hipMemcpyAsync(off.data(), X.off, sizeof(int) * (nbox + 1), hipMemcpyDeviceToHost, s));
-  RPY_HIP(hipMemcpyAsync(ent.data(), X.ent, sizeof(int) * X.len, hipMemcpyDeviceToHost, s));
-  RPY_HIP(hipMemcpyAsync(beg.data(), B->tree.begin, sizeof(int) * nbox, hipMemcpyDeviceToHost, s));
-  RPY_HIP(hipMemcpyAsync(end.data(), B->tree.end, sizeof(int) * nbox, hipMemcpyDeviceToHost, s));
-  RPY_HIP(hipStreamSynchronize(s));
+// Work items of boxes whose sources are the beads of entries ent[off[b]] ..
+// (S->L: the X list; S->M: the leaf itself): a box's entries are cut into runs
+// of at most `cap` 64-bead chunks, and an entry longer than that into chunk
+// ranges, so that no block carries much more than its share.
+static int make_items(const std::vector<int>& boxes, const std::vector<int>& off, const std::vector<int>& ent,
+                      const std::vector<int>& beg, const std::vector<int>& end, int cap, P2EWork* w, int64_t* bytes,
+                      Error* err) {
   auto chunks = [&](int e) { return (end[ent[e]] - beg[ent[e]] + P2E_CHUNK - 1) / P2E_CHUNK; };
-  int64_t total = 0;
-  for (int64_t e = 0; e < X.len; ++e) total += chunks((int)e);
-  const int cap = (int)std::max<int64_t>(16, total / 2048);
   std::vector<int4> work, red;
   std::vector<int2> rng;
   int nslot = 0;
-  for (int b = 0; b < nbox; ++b) {
+  for (size_t q = 0; q < boxes.size(); ++q) {
     const size_t first = work.size();
-    int e = off[b];
-    while (e < off[b + 1]) {
+    int e = off[q];
+    while (e < off[q + 1]) {
       const int c = chunks(e);
       if (c > cap) {  // one long entry: chunk ranges of it
         for (int lo = 0; lo < c; lo += cap) {
-          work.push_back(make_int4(b, e, e + 1, 0));
+          work.push_back(make_int4(boxes[q], e, e + 1, 0));
           rng.push_back(make_int2(lo, std::min(c, lo + cap)));
         }
         ++e;
         continue;
       }
       int e1 = e, sum = 0;
-      while (e1 < off[b + 1] && chunks(e1) <= cap && sum + chunks(e1) <= cap) sum += chunks(e1++);
-      work.push_back(make_int4(b, e, e1, 0));
+      while (e1 < off[q + 1] && chunks(e1) <= cap && sum + chunks(e1) <= cap) sum += chunks(e1++);
+      work.push_back(make_int4(boxes[q], e, e1, 0));
       rng.push_back(make_int2(0, 0x7fffffff));
       e = e1;
     }
     if (work.size() - first > 1) {
       // shares of one box: slots nslot.. in item order, reduced afterwards
-      red.push_back(make_int4(b, nslot, (int)(work.size() - first), 0));
+      red.push_back(make_int4(boxes[q], nslot, (int)(work.size() - first), 0));
       for (size_t i = first; i < work.size(); ++i) work[i].w = 1 + nslot++;
     }
   }
-  B->nxwork = (int)work.size();
-  B->nxshared = nslot;
-  B->nxred = (int)red.size();
-  RPY_HIP(hipMalloc(&B->xwork, sizeof(int4) * work.size()));
-  RPY_HIP(hipMalloc(&B->xchunks, sizeof(int2) * rng.size()));
-  RPY_HIP(hipMemcpy(B->xwork, work.data(), sizeof(int4) * work.size(), hipMemcpyHostToDevice));
-  RPY_HIP(hipMemcpy(B->xchunks, rng.data(), sizeof(int2) * rng.size(), hipMemcpyHostToDevice));
-  B->bytes += (int64_t)(sizeof(int4) + sizeof(int2)) * work.size();
-  if (!red.empty()) {
-    RPY_HIP(hipMalloc(&B->xred, sizeof(int4) * red.size()));
-    RPY_HIP(hipMemcpy(B->xred, red.data(), sizeof(int4) * red.size(), hipMemcpyHostToDevice));
-    B->bytes += (int64_t)sizeof(int4) * red.size();
+  w->n = (int)work.size();
+  w->nslot = nslot;
+  w->nred = (int)red.size();
+  if (w->n == 0) return 0;
+  const size_t nw = sizeof(int4) * work.size(), nr = sizeof(int4) * red.size(), nc = sizeof(int2) * rng.size();
+  RPY_HIP(hipMalloc(&w->work, nw + nr + nc));
+  w->red = w->work + work.size();
+  w->chunks = reinterpret_cast<int2*>(w->red + red.size());
+  RPY_HIP(hipMemcpy(w->work, work.data(), nw, hipMemcpyHostToDevice));
+  if (nr) RPY_HIP(hipMemcpy(w->red, red.data(), nr, hipMemcpyHostToDevice));
+  RPY_HIP(hipMemcpy(w->chunks, rng.data(), nc, hipMemcpyHostToDevice));
+  *bytes += (int64_t)(nw + nr + nc);
+  return 0;
+}
+
+// S->L: with cap = max(16, total / 2048) no block sets the kernel's length (on
+// 64 systems at leaf 1640 one box held 344 chunks against 17 per CU on
+// average).  Plans with little of such work are bound by the length of one
+// item instead (about 15 us per chunk at p = 21: S->M of 20k clustered beads
+// took 0.59 ms in its 39-chunk leaf and 0.05 ms in items of two chunks), so
+// they get items of total / 1024 chunks, at least two; S->M is split only
+// there.
+int make_p2e_work(Built* B, hipStream_t s, Error* err) {
+  const List& X = B->lists[LX];
+  const int nbox = B->tree.nbox;
+  constexpr int FEW = 256;  // leaves below which S->M may be split (512 leaves of 6 chunks: 70 us whole, 87 split)
+  if (nbox == 0 || B->nleaf == 0 || (X.len == 0 && B->nleaf >= FEW)) return 0;
+  std::vector<int> beg(nbox), end(nbox);
+  RPY_HIP(hipMemcpyAsync(beg.data(), B->tree.begin, sizeof(int) * nbox, hipMemcpyDeviceToHost, s));
+  RPY_HIP(hipMemcpyAsync(end.data(), B->tree.end, sizeof(int) * nbox, hipMemcpyDeviceToHost, s));
+  std::vector<int> leaf(B->nleaf), off(nbox + 1), ent(X.len), all(nbox), self(B->nleaf + 1);
+  RPY_HIP(hipMemcpyAsync(leaf.data(), B->leaf_ids, sizeof(int) * B->nleaf, hipMemcpyDeviceToHost, s));
+  if (X.len > 0) {
+    RPY_HIP(hipMemcpyAsync(off.data(), X.off, sizeof(int) * (nbox + 1), hipMemcpyDeviceToHost, s));
+    RPY_HIP(hipMemcpyAsync(ent.data(), X.ent, sizeof(int) * X.len, hipMemcpyDeviceToHost, s));
+  }
+  RPY_HIP(hipStreamSynchronize(s));
+  auto cnt = [&](int b) { return (end[b] - beg[b] + P2E_CHUNK - 1) / P2E_CHUNK; };
+  if (X.len > 0) {
+    for (int b = 0; b < nbox; ++b) all[b] = b;
+    int64_t total = 0;
+    for (int e : ent) total += cnt(e);
+    const int coarse = (int)std::max<int64_t>(16, total / 2048);
+    const int fine = (int)std::min<int64_t>(coarse, std::max<int64_t>(2, total / 1024));
+    if (int rc = make_items(all, off, ent, beg, end, coarse, &B->xw[0], &B->bytes, err)) return rc;
+    B->xfine = fine < coarse;
+    if (!B->xfine) B->xw[1] = B->xw[0];
+    else if (int rc = make_items(all, off, ent, beg, end, fine, &B->xw[1], &B->bytes, err)) return rc;
+  }
+  int64_t total = 0;
+  int most = 0;
+  for (int b : leaf) {
+    total += cnt(b);
+    most = std::max(most, cnt(b));
+  }
+  const int cap = (int)std::max<int64_t>(2, total / 1024);
+  if (B->nleaf < FEW && most > cap) {
+    for (int i = 0; i <= B->nleaf; ++i) self[i] = i;
+    return make_items(leaf, self, leaf, beg, end, cap, &B->mw, &B->bytes, err);
   }
   return 0;
+}
+
+int p2e_slots(const Built* B, bool fine) {
+  return fine ? std::max(B->xw[1].nslot, B->mw.nslot) : B->xw[0].nslot;
 }
 
 int make_p2e_tables(int p, Tables* tb, Error* err) {
@@ -592,16 +636,16 @@ hipError_t run_p2m(const Launch& l, int nrc, const double* sF, Exp e) {
   }
   hipError_t he = hipGetLastError();
   if (he != hipSuccess) return he;
-  return launch_p2e_nd<false>(l, nrc, B->nleaf, B->leaf_ids, e.Q, e.M, nullptr);
+  return launch_p2e_nd<false>(l, nrc, e.fine ? &B->mw : nullptr, e.Q, e.M, e.XP);
 }
 
 hipError_t run_p2l(const Launch& l, int nrc, const double* sF, Exp e) {
   (void)sF;  // the charges come from the per-bead array written by run_p2m
   const Built* B = l.B;
   if (B->lists[LX].len == 0) return hipSuccess;
-  if (!B->xwork && B->nxwork > 0) return hipErrorInvalidValue;
-  if (B->nxred > 0 && !e.XP) return hipErrorInvalidValue;
-  return launch_p2e_nd<true>(l, nrc, B->nxwork, nullptr, e.Q, e.L, e.XP);
+  const P2EWork& w = B->xw[e.fine ? 1 : 0];
+  if (w.n == 0 || (w.nred > 0 && !e.XP)) return hipErrorInvalidValue;
+  return launch_p2e_nd<true>(l, nrc, &w, e.Q, e.L, e.XP);
 }
 
 }  // namespace rpy

@@ -73,6 +73,8 @@ def test_empty_far_field(orc):
             P.matvec(to_dev(w.forces))
     finally:
         P.free()
+
+
 # Interaction lists built by a wave per box, bit-exact against the oracle's:
 # leaves of one bead, O lists longer than the sort's LDS buffer (dense beads in
 # tiny leaves), a depth cap, and the deepest tree (beads in pairs 2^-19 apart).
@@ -134,3 +136,21 @@ def test_matrix_core_staging(orc, n, nrhs):
     assert orc.rel_l2(u, orc.rpy_direct(w.pos, w.forces, w.a, w.eta)) <= 1e-12
     um, _ = gpu_matvec(w.pos, w.forces, w.a, w.eta, 1e-6, leaf_size=10_000, precision="mixed")
     assert orc.rel_l2(um, u) <= 5e-7
+
+
+# Small far fields: S->M, S->L, M->M, L->L and the evaluation cut into finer work
+# items, with one, two and five right-hand sides (groups of 4 + 1), in both
+# evaluation forms and at orders whose polynomials have no room for the M->M
+# shares; an adaptive tree with leaves of many chunks, and a full one of 64 leaves.
+_SMALL = [(1, 1), (3, 2), (4, 5), (5, 1), (16, 2)]
+
+
+@pytest.mark.parametrize("p,nrhs,mode", [(p, q, m) for m in ("sets", "poly") for p, q in _SMALL] +
+                         [(22, 1, "sets"), (23, 5, "sets")])  # polynomials end at order 21
+def test_small_far_field(orc, p, nrhs, mode):
+    for w, leaf in ((W.clustered(4000, 5, 12.0, 0.5, 0.02, nrhs, seed=350 + p), 700),
+                    (W.uniform_cube(5000, 1.0, 0.01, nrhs=nrhs, seed=351 + p), 150)):
+        log(f"small far field p={p} nrhs={nrhs} {mode} leaf={leaf}")
+        u, st = gpu_matvec(w.pos, w.forces, w.a, w.eta, 1e-6, order=p, leaf_size=leaf, eval_mode=mode)
+        ref = orc.fmm(w.pos, w.forces, w.a, w.eta, p, leaf, st["w_direct"])
+        assert orc.rel_l2(u, ref) <= 1e-12
