@@ -1105,8 +1105,8 @@ rpy_status rpy_sqrt_matvec(rpy_plan_t* P, int32_t nrhs, const double* z, double*
   const int kcap = max_iter + 1;
   const int64_t set = (int64_t)nrhs * L;
   const int64_t npart = rpy::krylov_part_doubles(L, kcap, nrhs);
-  // basis [kcap][nrhs][L], w [nrhs][L], partial sums, 3 coefficient blocks [nrhs][kcap], scales [nrhs]
-  const int64_t need = kcap * set + set + npart + 3 * (int64_t)nrhs * kcap + nrhs;
+  // basis [kcap][nrhs][L], w [nrhs][L], partial sums, 3 coefficient blocks [nrhs][kcap]
+  const int64_t need = kcap * set + set + npart + 3 * (int64_t)nrhs * kcap;
   hipStream_t st = P->stream;
   if (P->kbuf_doubles < need) {
     if (P->kbuf) {
@@ -1128,7 +1128,6 @@ rpy_status rpy_sqrt_matvec(rpy_plan_t* P, int32_t nrhs, const double* z, double*
   double* cA = part + npart;
   double* cB = cA + (int64_t)nrhs * kcap;
   double* cF = cB + (int64_t)nrhs * kcap;
-  double* sc = cF + (int64_t)nrhs * kcap;
   auto dev = [&](hipError_t he) {
     if (he != hipSuccess) {
       (void)hipGetLastError();
@@ -1137,7 +1136,9 @@ rpy_status rpy_sqrt_matvec(rpy_plan_t* P, int32_t nrhs, const double* z, double*
     }
     return RPY_OK;
   };
-  std::vector<double> hA((size_t)nrhs * kcap), hB((size_t)nrhs * kcap), hs(nrhs);
+  const size_t cb = (size_t)nrhs * kcap;
+  std::vector<double> hA(cb), hAll(3 * cb);  // hAll: cA, cB and cF, one after the other
+  const double *hB = hAll.data() + cb, *hn = hB + cb;
   auto fetch = [&](const double* d, std::vector<double>& h) {
     hipError_t he = hipMemcpyAsync(h.data(), d, sizeof(double) * h.size(), hipMemcpyDeviceToHost, st);
     if (he == hipSuccess) he = hipStreamSynchronize(st);
@@ -1145,16 +1146,11 @@ rpy_status rpy_sqrt_matvec(rpy_plan_t* P, int32_t nrhs, const double* z, double*
   };
   // beta_0 = |z|, v_0 = z / beta_0
   rpy_status rs = dev(rpy::krylov_mdot(z, 0, 1, z, L, nrhs, kcap, part, cA, st));
+  if (rs == RPY_OK) rs = dev(rpy::krylov_comb(nullptr, 0, 0, kcap, cA, 1.0, z, 1.0, cA, L, nrhs, V, st));
   if (rs == RPY_OK) rs = dev(fetch(cA, hA));
   if (rs != RPY_OK) return rs;
   std::vector<double> beta0(nrhs);
-  for (int r = 0; r < nrhs; ++r) {
-    beta0[r] = std::sqrt(std::max(hA[(size_t)r * kcap], 0.0));
-    hs[r] = beta0[r] > 0.0 ? 1.0 / beta0[r] : 0.0;
-  }
-  rs = dev(hipMemcpyAsync(sc, hs.data(), sizeof(double) * nrhs, hipMemcpyHostToDevice, st));
-  if (rs == RPY_OK) rs = dev(rpy::krylov_comb(nullptr, 0, 0, kcap, cA, 1.0, z, 1.0, sc, L, nrhs, V, st));
-  if (rs != RPY_OK) return rs;
+  for (int r = 0; r < nrhs; ++r) beta0[r] = std::sqrt(std::max(hA[(size_t)r * kcap], 0.0));
 
   // per right-hand side: tridiagonal entries, coefficients of y in the basis
   std::vector<std::vector<double>> alpha(nrhs), beta(nrhs), f(nrhs);
@@ -1176,16 +1172,15 @@ rpy_status rpy_sqrt_matvec(rpy_plan_t* P, int32_t nrhs, const double* z, double*
     if (rs == RPY_OK) rs = dev(rpy::krylov_comb(V, set, k + 1, kcap, cA, -1.0, W, 1.0, nullptr, L, nrhs, W, st));
     if (rs == RPY_OK) rs = dev(rpy::krylov_mdot(V, set, k + 1, W, L, nrhs, kcap, part, cB, st));
     if (rs == RPY_OK) rs = dev(rpy::krylov_comb(V, set, k + 1, kcap, cB, -1.0, W, 1.0, nullptr, L, nrhs, W, st));
-    if (rs == RPY_OK) rs = dev(fetch(cA, hA));
-    if (rs == RPY_OK) rs = dev(fetch(cB, hB));
     // |w|^2 into cF's first column
     if (rs == RPY_OK) rs = dev(rpy::krylov_mdot(W, 0, 1, W, L, nrhs, kcap, part, cF, st));
-    std::vector<double> hn((size_t)nrhs * kcap);
-    if (rs == RPY_OK) rs = dev(fetch(cF, hn));
+    // v_{k+1} = w / beta_{k+1}, also on the last step (slot k + 1 <= max_iter exists)
+    if (rs == RPY_OK) rs = dev(rpy::krylov_comb(nullptr, 0, 0, kcap, cA, 1.0, W, 1.0, cF, L, nrhs, V + (k + 1) * set, st));
+    if (rs == RPY_OK) rs = dev(fetch(cA, hAll));
     if (rs != RPY_OK) return rs;
     for (int r = 0; r < nrhs; ++r) {
       if (done[r]) continue;
-      const double a = hA[(size_t)r * kcap + k] + hB[(size_t)r * kcap + k];
+      const double a = hAll[(size_t)r * kcap + k] + hB[(size_t)r * kcap + k];
       const double b = std::sqrt(std::max(hn[(size_t)r * kcap], 0.0));
       alpha[r].push_back(a);
       beta[r].push_back(b);
@@ -1219,15 +1214,6 @@ rpy_status rpy_sqrt_matvec(rpy_plan_t* P, int32_t nrhs, const double* z, double*
     bool fin = true;
     for (int r = 0; r < nrhs; ++r) fin = fin && done[r];
     if (fin || k + 1 == max_iter) break;
-    // v_{k+1} = w / beta_{k+1} (zero for the right-hand sides that are done)
-    for (int r = 0; r < nrhs; ++r) {
-      const double b = beta[r].empty() ? 0.0 : beta[r].back();
-      hs[r] = (!done[r] && b > 0.0) ? 1.0 / b : 0.0;
-    }
-    rs = dev(hipMemcpyAsync(sc, hs.data(), sizeof(double) * nrhs, hipMemcpyHostToDevice, st));
-    if (rs == RPY_OK) rs = dev(rpy::krylov_comb(nullptr, 0, 0, kcap, cA, 1.0, W, 1.0, sc, L, nrhs, V + (k + 1) * set, st));
-    if (rs == RPY_OK) rs = dev(hipStreamSynchronize(st));  // hs is reused next step
-    if (rs != RPY_OK) return rs;
   }
   // y = sum_j f_j v_j
   std::vector<double> hf((size_t)nrhs * kcap, 0.0);

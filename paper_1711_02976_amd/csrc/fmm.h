@@ -209,13 +209,14 @@ hipError_t run_eval(const Launch& l, const EvalPlan& ep, int nrc, Exp e, double*
 // of a family of sets starts at V + j * vstride.  krylov_mdot writes
 // out[r * kcap + j] = V_j[r] . w[r] for j < k (deterministic order; part
 // holds krylov_part_doubles(L, kcap, nrhs) doubles).  krylov_comb writes
-// out[r] = s[r] * (a w[r] + sgn sum_{j<k} coef[r * kcap + j] V_j[r]) (s may
-// be null = 1, w may be null, out may alias w).
+// out[r] = s_r (a w[r] + sgn sum_{j<k} coef[r * kcap + j] V_j[r]) with
+// s_r = 1 / sqrt(nrm2[r * kcap]), 0 for a zero norm (nrm2 may be null: s_r = 1;
+// w may be null; out may alias w).
 int64_t krylov_part_doubles(int64_t L, int kcap, int nrhs);
 hipError_t krylov_mdot(const double* V, int64_t vstride, int k, const double* w, int64_t L, int nrhs, int kcap,
                        double* part, double* out, hipStream_t st);
 hipError_t krylov_comb(const double* V, int64_t vstride, int k, int kcap, const double* coef, double sgn,
-                       const double* w, double a, const double* s, int64_t L, int nrhs, double* out, hipStream_t st);
+                       const double* w, double a, const double* nrm2, int64_t L, int nrhs, double* out, hipStream_t st);
 // Eigen-decomposition of a symmetric tridiagonal matrix (host, implicit QL):
 // diagonal d[0..m), off-diagonal e[0..m-1); Q column q = eigenvector q.
 void tridiag_eig(int m, const std::vector<double>& d, const std::vector<double>& e, std::vector<double>& lam,

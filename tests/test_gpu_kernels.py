@@ -154,3 +154,49 @@ def test_small_far_field(orc, p, nrhs, mode):
         u, st = gpu_matvec(w.pos, w.forces, w.a, w.eta, 1e-6, order=p, leaf_size=leaf, eval_mode=mode)
         ref = orc.fmm(w.pos, w.forces, w.a, w.eta, p, leaf, st["w_direct"])
         assert orc.rel_l2(u, ref) <= 1e-12
+
+
+# Lanczos vectors scaled on the device: right-hand sides that end at different
+# steps (a general one, zero, an eigenvector of D, whose next vector is rounding
+# noise) in one call, one bead, and a vector of just over two chunks of the dot
+# products.
+@pytest.mark.parametrize("n", [1, 60, 683])
+def test_lanczos_mixed_ends(orc, n):
+    import paper_1711_02976_amd as R
+    from gpu_common import to_dev
+    g = np.random.default_rng(360 + n)
+    pos = g.uniform(0.0, 20.0, size=(n, 3))
+    z = g.standard_normal((3, n, 3))
+    z[1] = 0.0
+    if n == 60:
+        D = orc.rpy_direct(pos, np.eye(3 * n).reshape(3 * n, n, 3), 0.4, 1.0).reshape(3 * n, 3 * n)
+        z[2] = np.linalg.eigh(0.5 * (D + D.T))[1][:, 7].reshape(n, 3)
+    log(f"lanczos mixed ends n={n}")
+    P = R.Plan(to_dev(pos), 0.4, 1.0, 1e-6, leaf_size=1000)
+    try:
+        y, info = P.sqrt_matvec(to_dev(z), tol=1e-11, max_iter=100)
+        y = y.cpu().numpy()
+    finally:
+        P.free()
+    ref = orc.rpy_sqrt(pos, z, 0.4, 1.0)
+    assert info["converged"] and np.all(y[1] == 0.0)
+    for r in (0, 2):
+        assert orc.rel_l2(y[r], ref[r]) <= 1e-9
+
+
+# Dot products over more chunks than a wave has lanes: D^{1/2} twice is D, to
+# the plan's accuracy (its matvec is symmetric to 1e-6).
+def test_lanczos_many_chunks(orc):
+    import paper_1711_02976_amd as R
+    from gpu_common import to_dev
+    w = W.uniform_cube(45000, 1.0, 0.0005, nrhs=1, seed=370)  # 45 steps; of radius .004, over 100
+    log("lanczos many chunks n=45000")
+    P = R.Plan(to_dev(w.pos), w.a, w.eta, 1e-6)
+    try:
+        y, _ = P.sqrt_matvec(to_dev(w.forces), tol=1e-9, max_iter=100)
+        y, info = P.sqrt_matvec(y, tol=1e-9, max_iter=100)
+        u = P.matvec(to_dev(w.forces))
+        assert info["converged"]
+        assert orc.rel_l2(y.cpu().numpy(), u.cpu().numpy()) <= 1e-5
+    finally:
+        P.free()
