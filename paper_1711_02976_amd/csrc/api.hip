@@ -111,46 +111,15 @@ struct TreeCost {
 };
 
 static int model_tree(const rpy::Built& B, int order, double eps, bool mixed, int max_depth, int nrhs, int wd_opt,
-                      TreeCost* out) {
-  const rpy::Tree& t = B.tree;
-  const int nbox = t.nbox;
-  std::vector<int> beg(nbox), end(nbox), child(nbox), lev(nbox);
-  auto get = [&](std::vector<int>& h, const int* d, size_t n) {
-    return n == 0 || hipMemcpy(h.data(), d, sizeof(int) * n, hipMemcpyDeviceToHost) == hipSuccess;
-  };
-  if (!get(beg, t.begin, nbox) || !get(end, t.end, nbox) || !get(child, t.child, nbox) || !get(lev, t.level, nbox))
-    return -4;
-  const rpy::List& U = B.lists[rpy::LU];
-  const rpy::List& W = B.lists[rpy::LW];
-  const rpy::List& X = B.lists[rpy::LX];
-  std::vector<int> uo(nbox + 1), ue(U.len), wo(nbox + 1), we(W.len), xo(nbox + 1), xe(X.len);
-  if (!get(uo, U.off, nbox + 1) || !get(ue, U.ent, U.len) || !get(wo, W.off, nbox + 1) || !get(we, W.ent, W.len) ||
-      !get(xo, X.off, nbox + 1) || !get(xe, X.ent, X.len))
-    return -4;
-  const bool adaptive = W.len > 0 || X.len > 0;
+                      TreeCost* out, hipStream_t s, rpy::Error* err) {
+  const int nbox = B.tree.nbox;
+  const bool adaptive = B.lists[rpy::LW].len > 0 || B.lists[rpy::LX].len > 0;
   const int p = order ? order : order_for_eps(eps, adaptive);
   const int wmax = wd_opt == 0 ? rpy::wdirect_default(p) : wd_opt;
-  double pairs = 0, weval = 0, xpairs = 0, nleaf = 0;
-  int lo = 0, hi = 0x7fffffff;
-  for (int b = 0; b < nbox; ++b) {
-    const int nb = end[b] - beg[b];
-    if (child[b] < 0) {
-      if (lev[b] < max_depth) lo = std::max(lo, nb);
-      nleaf += 1;
-      const double padded = 64.0 * ((nb + 63) / 64);
-      double src = 0;
-      for (int k = uo[b]; k < uo[b + 1]; ++k) src += end[ue[k]] - beg[ue[k]];
-      for (int k = wo[b]; k < wo[b + 1]; ++k) {
-        const int nc = end[we[k]] - beg[we[k]];
-        if (wmax < 0 || nc > wmax) weval += nb;
-        else src += nc;
-      }
-      pairs += padded * src;
-    } else {
-      hi = std::min(hi, nb);
-    }
-    for (int k = xo[b]; k < xo[b + 1]; ++k) xpairs += end[xe[k]] - beg[xe[k]];
-  }
+  rpy::TreeSums sums;
+  if (const int rc = rpy::tree_sums(B, max_depth, wmax, &sums, s, err)) return rc;
+  const double pairs = (double)sums.pairs, weval = (double)sums.weval, xpairs = (double)sums.xpairs;
+  const double nleaf = B.nleaf;
   const double S = (p + 1.0) * (p + 2.0) * (2.0 * p + 3.0) / 6.0, T = (p + 1.0) * (p + 2.0) / 2.0;
   const double S16 = 1785.0, S21 = 3795.0, T21 = 253.0;
   // ns per unit (one density unless stated)
@@ -181,8 +150,8 @@ static int model_tree(const rpy::Built& B, int order, double eps, bool mixed, in
   }
   out->near_ns = pairs * c_pair * near_passes;
   out->ns = out->near_ns + 4.0 * r * far;
-  out->same_lo = lo;
-  out->same_hi = hi;
+  out->same_lo = sums.lo;
+  out->same_hi = sums.hi;
   out->adaptive = adaptive;
   return 0;
 }
@@ -327,11 +296,11 @@ static void fold_events(rpy_plan_t* P) {
   P->ev_pending.clear();
 }
 
+// The device must have finished with the arrays.
 static void free_ws(rpy_plan_t* P) {
   Work& w = P->ws;
   void* ps[] = {w.M, w.L, w.sF, w.u, w.uf, w.Q, w.DL, w.DW, w.XP, w.PV, w.M32, w.NP, w.EP};
-  for (void* p : ps)
-    if (p) (void)hipFree(p);
+  for (void* p : ps) rpy::dev_free(p);
   w = Work{};
   P->ws_nrc = 0;
   P->ws_nrn = 0;
@@ -342,7 +311,10 @@ static int alloc_ws(rpy_plan_t* P, int nrc, int nrn) {
   if (P->ws_nrc >= nrc && P->ws_nrn >= nrn) return 0;
   nrc = std::max(nrc, P->ws_nrc);
   nrn = std::max(nrn, P->ws_nrn);
-  free_ws(P);
+  {
+    const rpy::NoKeep nokeep(P->ws_bytes > 0 && !rpy::device_wait());
+    free_ws(P);
+  }
   size_t sz[WS_N];
   ws_sizes(P, nrc, nrn, true, sz);
   Work& w = P->ws;
@@ -356,7 +328,7 @@ static int alloc_ws(rpy_plan_t* P, int nrc, int nrn) {
   if (fail_at < WS_N) P->inject = -1;
   for (int k = 0; k < WS_N; ++k) {
     if (sz[k] == 0) continue;
-    if (k == fail_at || hipMalloc(dst[k], sz[k]) != hipSuccess) {
+    if (k == fail_at || rpy::dev_alloc_bytes(dst[k], sz[k]) != hipSuccess) {
       (void)hipGetLastError();
       *dst[k] = nullptr;
       free_ws(P);
@@ -364,8 +336,10 @@ static int alloc_ws(rpy_plan_t* P, int nrc, int nrn) {
     }
     tot += sz[k];
   }
-  // zeroed once so that every row of Q, including the padding, is finite
-  if (hipMemset(w.Q, 0, sz[5]) != hipSuccess) {
+  // zeroed once so that every row of Q, including the padding, is finite; the
+  // plan's stream need not wait for the null stream by itself
+  if (hipMemset(w.Q, 0, sz[5]) != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess) {
+    (void)hipGetLastError();
     free_ws(P);
     return -1;
   }
@@ -848,6 +822,7 @@ rpy_status rpy_plan_batched(rpy_plan_t** out, int32_t nsys, const int64_t* count
   for (int s = 0; s < nsys; ++s) sb[s + 1] = sb[s] + counts[s];
   rpy::Error err{0, ""};
   int rc = 0;
+  rpy::BuildScope scope(P->stream);
   if (o.leaf_size > 0) {
     rpy::BuildArgs ba{n, nsys, sb.data(), positions, P->leaf_size, P->max_depth, a, P->stream};
     rc = rpy::build_tree(ba, &P->B, &err);
@@ -887,7 +862,8 @@ rpy_status rpy_plan_batched(rpy_plan_t** out, int32_t nsys, const int64_t* count
       }
       TreeCost tc;
       if (rc == 0)
-        rc = model_tree(Bc, o.order, eps, o.precision == RPY_PREC_MIXED, P->max_depth, o.nrhs, o.w_direct, &tc);
+        rc = model_tree(Bc, o.order, eps, o.precision == RPY_PREC_MIXED, P->max_depth, o.nrhs, o.w_direct, &tc,
+                        P->stream, &err);
       if (rc != 0) {
         rpy::free_built(&Bc);
         break;
@@ -932,14 +908,22 @@ rpy_status rpy_plan_batched(rpy_plan_t** out, int32_t nsys, const int64_t* count
   // library choice: the component polynomials at low orders (fewer
   // operations per target), the derivative sets above
   if (P->eval_mode == 0) P->eval_mode = P->p <= EVAL_POLY_AUTO_MAX ? rpy::EVAL_POLY : rpy::EVAL_SETS;
-  if (rc == 0) rc = rpy::make_tables(P->p, P->precision == RPY_PREC_MIXED, &P->tb, P->stream, &err);
+  if (rc == 0) rc = rpy::make_tables(P->p, P->precision == RPY_PREC_MIXED, P->m2l_mode == 1, &P->tb, P->stream, &err);
   if (rc == 0) rc = rpy::make_tiles(&P->B, 128, &P->tiles, P->stream, &err);
   if (rc == 0) rc = rpy::make_near_plan(&P->B, P->tiles, P->a, P->wd, &P->np, P->stream, &err);
   if (rc == 0) rc = rpy::make_eval_plan(&P->B, P->p, P->wd, P->eval_mode, &P->ep, P->stream, &err);
   P->no_far = P->B.lists[rpy::LV].len == 0 && P->B.lists[rpy::LX].len == 0 && P->ep.nwbig == 0;
   if (rc == 0) rc = rpy::make_m2l_map(&P->B, P->stream, &err);
   if (rc == 0) rc = rpy::make_p2e_work(&P->B, P->stream, &err);
-  if (rc == 0) {
+  rpy::Lane lane;
+  if (rc == 0 && rpy::take_lane(P->device, &lane)) {
+    P->near = lane.near;
+    P->far2 = lane.far2;
+    P->ev_fork = lane.fork;
+    P->ev_join = lane.join;
+    P->ev_p2m = lane.p2m;
+    P->ev_m2l0 = lane.m2l0;
+  } else if (rc == 0) {
     // default priority (no priority argument); without it the near field
     // runs on the plan's stream
     if (hipStreamCreateWithFlags(&P->near, hipStreamNonBlocking) != hipSuccess ||
@@ -1111,11 +1095,12 @@ rpy_status rpy_sqrt_matvec(rpy_plan_t* P, int32_t nrhs, const double* z, double*
   if (P->kbuf_doubles < need) {
     if (P->kbuf) {
       (void)hipStreamSynchronize(st);
-      (void)hipFree(P->kbuf);
+      const rpy::NoKeep nokeep(!rpy::device_wait());
+      rpy::dev_free(P->kbuf);
     }
     P->kbuf = nullptr;
     P->kbuf_doubles = 0;
-    if (hipMalloc(&P->kbuf, sizeof(double) * need) != hipSuccess) {
+    if (rpy::dev_alloc(&P->kbuf, sizeof(double) * need) != hipSuccess) {
       (void)hipGetLastError();
       P->kbuf = nullptr;
       return fail(RPY_ENOMEM, "cannot allocate the Krylov workspace");
@@ -1339,26 +1324,38 @@ rpy_status rpy_plan_timings(rpy_plan_t* P, rpy_timings_t* out) {
 
 void rpy_plan_free(rpy_plan_t* P) {
   if (!P) return;
+  int dev = P->device;
+  (void)hipGetDevice(&dev);
+  if (dev != P->device) (void)hipSetDevice(P->device);
   if (P->stream) (void)hipStreamSynchronize(P->stream);
   else (void)hipDeviceSynchronize();
   if (P->near) (void)hipStreamSynchronize(P->near);
   if (P->far2) (void)hipStreamSynchronize(P->far2);
+  // the plan's work may have been replayed on other streams too; where the wait
+  // is refused (a capture), nothing is kept
+  const bool idle = rpy::device_wait();
+  const rpy::NoKeep nokeep(!idle);
   fold_events(P);
-  if (P->far2) (void)hipStreamDestroy(P->far2);
-  if (P->ev_p2m) (void)hipEventDestroy(P->ev_p2m);
-  if (P->ev_m2l0) (void)hipEventDestroy(P->ev_m2l0);
-  if (P->ev_fork) (void)hipEventDestroy(P->ev_fork);
-  if (P->ev_join) (void)hipEventDestroy(P->ev_join);
-  if (P->near) (void)hipStreamDestroy(P->near);
+  const rpy::Lane lane{P->near, P->far2, P->ev_fork, P->ev_join, P->ev_p2m, P->ev_m2l0};
+  if (!(idle && P->near && P->far2 && rpy::keep_lane(P->device, lane))) {
+    if (P->far2) (void)hipStreamDestroy(P->far2);
+    if (P->ev_p2m) (void)hipEventDestroy(P->ev_p2m);
+    if (P->ev_m2l0) (void)hipEventDestroy(P->ev_m2l0);
+    if (P->ev_fork) (void)hipEventDestroy(P->ev_fork);
+    if (P->ev_join) (void)hipEventDestroy(P->ev_join);
+    if (P->near) (void)hipStreamDestroy(P->near);
+  }
   for (hipEvent_t e : P->ev_pool) (void)hipEventDestroy(e);
   free_ws(P);
-  if (P->kbuf) (void)hipFree(P->kbuf);
+  rpy::dev_free(P->kbuf);
   rpy::free_tables(&P->tb);
-  if (P->tiles.t) (void)hipFree(P->tiles.t);
-  if (P->tiles.box) (void)hipFree(P->tiles.box);
+  rpy::dev_free(P->tiles.t);
+  rpy::dev_free(P->tiles.box);
   rpy::free_near_plan(&P->np);
   rpy::free_eval_plan(&P->ep);
   rpy::free_built(&P->B);
+  rpy::plan_freed(P->device);
+  if (dev != P->device) (void)hipSetDevice(dev);
   delete P;
 }
 

@@ -6,6 +6,8 @@
 #include <string>
 #include <vector>
 
+#include "pool.h"
+
 namespace rpy {
 
 constexpr int KBITS = 21;            // quantisation bits per axis (63-bit Morton key)
@@ -68,9 +70,25 @@ struct Error {
 
 // ---- scan (exclusive prefix sum of int32) -------------------------------
 // Scans n ints from `in` to `out` (may alias) on stream; returns 0 or a HIP
-// error code.  Uses `tmp` scratch of scan_tmp_ints(n) ints.
+// error code.  Uses `tmp` scratch of scan_tmp_ints(n) ints.  The sum of all n
+// goes to *total and *total2, where given (device or host-page memory).
 size_t scan_tmp_ints(int64_t n);
-hipError_t scan_exclusive(const int* in, int* out, int64_t n, int* tmp, hipStream_t s);
+hipError_t scan_exclusive(const int* in, int* out, int64_t n, int* tmp, hipStream_t s, int* total = nullptr,
+                          int* total2 = nullptr);
+
+// Host memory that kernels can write for a plan's build (BUILD_PAGE bytes), and
+// a host-to-device copy that has ended when it returns.
+#define RPY_PAGE(type, var)                                                        \
+  type* var = static_cast<type*>(BuildScope::current() ? BuildScope::current()->page() : nullptr); \
+  if (!var) {                                                                      \
+    err->code = -3;                                                                \
+    err->msg = "no host page for a plan's counts";                                 \
+    return -3;                                                                     \
+  }
+inline hipError_t copy_in(void* dst, const void* src, size_t bytes, hipStream_t s) {
+  const hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
+  return e == hipSuccess ? hipStreamSynchronize(s) : e;
+}
 
 // Stable LSD radix sort of (key, value) pairs by 8-bit digits: key_passes
 // digits of the key (least significant first), then sys_passes digits of
@@ -159,6 +177,15 @@ struct Built {
 };
 
 int build_tree(const BuildArgs& a, Built* out, Error* err);
+// Sums over a tree's boxes and lists, for the cost model of the leaf size:
+// direct bead pairs (targets padded to whole waves of 64), bead and box pairs of
+// evaluated W entries, and of X entries; the largest leaf above max_depth and
+// the smallest split box.
+struct TreeSums {
+  unsigned long long pairs, weval, xpairs;
+  int lo, hi;
+};
+int tree_sums(const Built& B, int max_depth, int wmax, TreeSums* out, hipStream_t s, Error* err);
 void free_built(Built* b);
 // Moves b's bead arrays into an empty spare (else leaves them in b); then
 // frees what is left of b.

@@ -724,27 +724,25 @@ int make_eval_plan(const Built* B, int p, int wd, int mode, EvalPlan* out, hipSt
   out->mode = mode;
   if (mode == EVAL_POLY) {
     const std::vector<double> k = poly_table(p);
-    RPY_HIP(hipMalloc(&out->kct, sizeof(double) * k.size()));
-    RPY_HIP(hipMemcpy(out->kct, k.data(), sizeof(double) * k.size(), hipMemcpyHostToDevice));
+    RPY_HIP(dev_alloc(&out->kct, sizeof(double) * k.size()));
+    RPY_HIP(copy_in(out->kct, k.data(), sizeof(double) * k.size(), s));
   }
   if (make_tiles(B, 64, &out->tiles, s, err) != 0) return -1;
   const int nbox = std::max(B->tree.nbox, 1);
   int *flag = nullptr, *off = nullptr, *tmp = nullptr;
-  RPY_HIP(hipMalloc(&out->widx, sizeof(int) * nbox));
-  RPY_HIP(hipMalloc(&flag, sizeof(int) * nbox));
-  RPY_HIP(hipMalloc(&off, sizeof(int) * nbox));
-  RPY_HIP(hipMalloc(&tmp, sizeof(int) * scan_tmp_ints(nbox)));
+  RPY_HIP(dev_alloc(&out->widx, sizeof(int) * nbox));
+  RPY_HIP(dev_alloc(&flag, sizeof(int) * nbox));
+  RPY_HIP(dev_alloc(&off, sizeof(int) * nbox));
+  RPY_HIP(dev_alloc(&tmp, sizeof(int) * scan_tmp_ints(nbox)));
   RPY_HIP(hipMemsetAsync(flag, 0, sizeof(int) * nbox, s));
   const List& W = B->lists[LW];
   if (W.len > 0) k_wbig_flag<<<(unsigned)((W.len + 255) / 256), 256, 0, s>>>(W, B->tree, wd, flag);
   RPY_HIP(hipGetLastError());
-  RPY_HIP(scan_exclusive(flag, off, nbox, tmp, s));
-  int last[2] = {0, 0};
-  RPY_HIP(hipMemcpyAsync(&last[0], off + nbox - 1, sizeof(int), hipMemcpyDeviceToHost, s));
-  RPY_HIP(hipMemcpyAsync(&last[1], flag + nbox - 1, sizeof(int), hipMemcpyDeviceToHost, s));
+  RPY_PAGE(int, page);
+  RPY_HIP(scan_exclusive(flag, off, nbox, tmp, s, page));
   RPY_HIP(hipStreamSynchronize(s));
-  out->nwbig = last[0] + last[1];
-  RPY_HIP(hipMalloc(&out->wbig, sizeof(int) * std::max(out->nwbig, 1)));
+  out->nwbig = page[0];
+  RPY_HIP(dev_alloc(&out->wbig, sizeof(int) * std::max(out->nwbig, 1)));
   k_wbig_index<<<(nbox + 255) / 256, 256, 0, s>>>(flag, off, nbox, out->widx, out->wbig);
   RPY_HIP(hipGetLastError());
   // one part per expansion while all of them are few enough to run at once
@@ -752,38 +750,35 @@ int make_eval_plan(const Built* B, int p, int wd, int mode, EvalPlan* out, hipSt
   const int nt = out->tiles.n;
   if (mode == EVAL_SETS && out->nwbig > 0 && nt <= EV_FEW) {
     int *cnt = nullptr, *po = nullptr, *pt = nullptr;
-    RPY_HIP(hipMalloc(&out->parts, sizeof(int) * (2 * (size_t)nt + scan_tmp_ints(nt))));
+    RPY_HIP(dev_alloc(&out->parts, sizeof(int) * (2 * (size_t)nt + scan_tmp_ints(nt))));
     cnt = out->parts;
     po = out->slot0 = cnt + nt;
     pt = po + nt;
     k_eval_count<<<(nt + 255) / 256, 256, 0, s>>>(out->tiles.t, nt, W, out->widx, cnt);
-    RPY_HIP(scan_exclusive(cnt, po, nt, pt, s));
-    RPY_HIP(hipMemcpyAsync(&last[0], po + nt - 1, sizeof(int), hipMemcpyDeviceToHost, s));
-    RPY_HIP(hipMemcpyAsync(&last[1], cnt + nt - 1, sizeof(int), hipMemcpyDeviceToHost, s));
+    RPY_HIP(scan_exclusive(cnt, po, nt, pt, s, page));
     RPY_HIP(hipStreamSynchronize(s));
-    const int total = last[0] + last[1];
+    const int total = page[0];
     if (total <= EV_FEW) {
-      RPY_HIP(hipMalloc(&out->item, sizeof(int4) * total));
+      RPY_HIP(dev_alloc(&out->item, sizeof(int4) * total));
       k_eval_fill<<<(nt + 255) / 256, 256, 0, s>>>(out->tiles.t, nt, W, out->widx, cnt, po, out->item);
       RPY_HIP(hipGetLastError());
       out->nitem = total;
     }
   }
-  RPY_HIP(hipStreamSynchronize(s));
-  (void)hipFree(flag);
-  (void)hipFree(off);
-  (void)hipFree(tmp);
+  dev_free(flag);
+  dev_free(off);
+  dev_free(tmp);
   return 0;
 }
 
 void free_eval_plan(EvalPlan* ep) {
-  if (ep->tiles.t) (void)hipFree(ep->tiles.t);
-  if (ep->tiles.box) (void)hipFree(ep->tiles.box);
-  if (ep->widx) (void)hipFree(ep->widx);
-  if (ep->wbig) (void)hipFree(ep->wbig);
-  if (ep->kct) (void)hipFree(ep->kct);
-  if (ep->item) (void)hipFree(ep->item);
-  if (ep->parts) (void)hipFree(ep->parts);
+  if (ep->tiles.t) dev_free(ep->tiles.t);
+  if (ep->tiles.box) dev_free(ep->tiles.box);
+  if (ep->widx) dev_free(ep->widx);
+  if (ep->wbig) dev_free(ep->wbig);
+  if (ep->kct) dev_free(ep->kct);
+  if (ep->item) dev_free(ep->item);
+  if (ep->parts) dev_free(ep->parts);
   ep->item = nullptr;
   ep->parts = ep->slot0 = nullptr;
   ep->nitem = 0;

@@ -1,5 +1,7 @@
 // Declarations of the matvec kernels' launchers (fmm.hip, nearfield.hip).
 #pragma once
+#include <cstring>
+#include <utility>
 #include "common.h"
 
 namespace rpy {
@@ -47,8 +49,9 @@ struct P2ESched {
 
 struct Tables {
   int p;
+  char* base;      // the block that holds all of them
   double2* oct;    // [8][(p+1)^2] R_j^mu(d/h_parent), d = child - parent centre
-  double2* itab;   // [343][(2p+1)^2] I_j^mu(t), t integer offset in box units
+  double2* itab;   // [343][(2p+1)^2] I_j^mu(t), t integer offset in box units (dense M->L only)
   // Rotation-based M->L, FP64 and FP32 copies.  rot: per degree n, the
   // +90 degree rotation about y as (n+1) rows of n+1 slots holding the
   // nonzero real-split entries (A+ on real parts, then A- on imaginary
@@ -77,10 +80,26 @@ struct Tables {
   int64_t bytes;
 };
 
-int make_tables(int p, int fp32, Tables* tb, hipStream_t s, Error* err);
-int make_m2l_tables(const std::vector<double>& rot, const std::vector<double>& zt, int fp32, Tables* tb, hipStream_t s,
-                    Error* err);  // m2l_rot.hip; called by make_tables
-int make_p2e_tables(int p, Tables* tb, Error* err);  // p2e.hip; called by make_tables
+// The host image of a plan's tables, gathered piece by piece, and copied to one
+// block of device memory at once (a copy costs about 20 us whatever its size).
+struct TableImage {
+  std::vector<char> bytes;
+  std::vector<std::pair<void**, size_t>> at;
+  // *dst = the device address of a copy of src (null: left uninitialised)
+  template <class T>
+  void add(T** dst, const void* src, size_t n) {
+    const size_t o = bytes.size();
+    bytes.resize(o + (n + 255) / 256 * 256);
+    if (src) std::memcpy(bytes.data() + o, src, n);
+    at.emplace_back(reinterpret_cast<void**>(dst), o);
+  }
+};
+// dense: with the table of the dense M->L
+int make_tables(int p, int fp32, bool dense, Tables* tb, hipStream_t s, Error* err);
+int make_m2l_tables(const std::vector<double>& rot, const std::vector<double>& zt, int fp32, Tables* tb,
+                    TableImage* im);  // m2l_rot.hip; called by make_tables
+int make_m2l_phases(Tables* tb, int fp32, hipStream_t s, Error* err);
+int make_p2e_tables(int p, Tables* tb, TableImage* im, Error* err);  // p2e.hip; called by make_tables
 
 // Host helpers (fmm.hip): paper-normalised Y_n^m for 0 <= m <= n <= p at
 // (cos theta, phi); the rotation by +90 degrees about y on degree-n sets,

@@ -328,9 +328,9 @@ int compute_tables(int p, HostTables* h, Error* err) {
 }
 }  // namespace
 
-int make_tables(int p, int fp32, Tables* tb, hipStream_t s, Error* err) {
+int make_tables(int p, int fp32, bool dense, Tables* tb, hipStream_t s, Error* err) {
+  *tb = Tables{};
   tb->p = p;
-  tb->bytes = 0;
   if (p < 0 || p > MAX_ORDER) {
     err->code = -1;
     err->msg = "expansion order out of range";
@@ -359,47 +359,28 @@ int make_tables(int p, int fp32, Tables* tb, hipStream_t s, Error* err) {
   const auto &rot32 = H.rot32, &zt32 = H.zt32;
   tb->rot_len = H.rlen;
   tb->zt_len = H.zlen;
-  RPY_HIP(hipMalloc(&tb->oct, sizeof(double2) * oct.size()));
-  RPY_HIP(hipMalloc(&tb->itab, sizeof(double2) * itab.size()));
-  RPY_HIP(hipMalloc(&tb->rot64, sizeof(double) * rot.size()));
-  RPY_HIP(hipMalloc(&tb->rot32, sizeof(float) * rot32.size()));
-  RPY_HIP(hipMalloc(&tb->zt64, sizeof(double) * zt.size()));
-  RPY_HIP(hipMalloc(&tb->zt32, sizeof(float) * zt32.size()));
-  RPY_HIP(hipMalloc(&tb->geo, sizeof(double) * geo.size()));
-  RPY_HIP(hipMalloc(&tb->sfac, sizeof(double) * sf.size()));
-  RPY_HIP(hipMalloc(&tb->rscale, sizeof(double) * rsc.size()));
-  RPY_HIP(hipMemcpy(tb->rscale, rsc.data(), sizeof(double) * rsc.size(), hipMemcpyHostToDevice));
-  tb->bytes = sizeof(double2) * (oct.size() + itab.size()) + (sizeof(double) + sizeof(float)) * (rot.size() + zt.size()) +
-              sizeof(double) * (geo.size() + sf.size() + rsc.size());
-  RPY_HIP(hipMemcpy(tb->oct, oct.data(), sizeof(double2) * oct.size(), hipMemcpyHostToDevice));
-  RPY_HIP(hipMemcpy(tb->itab, itab.data(), sizeof(double2) * itab.size(), hipMemcpyHostToDevice));
-  RPY_HIP(hipMemcpy(tb->rot64, rot.data(), sizeof(double) * rot.size(), hipMemcpyHostToDevice));
-  RPY_HIP(hipMemcpy(tb->rot32, rot32.data(), sizeof(float) * rot32.size(), hipMemcpyHostToDevice));
-  RPY_HIP(hipMemcpy(tb->zt64, zt.data(), sizeof(double) * zt.size(), hipMemcpyHostToDevice));
-  RPY_HIP(hipMemcpy(tb->zt32, zt32.data(), sizeof(float) * zt32.size(), hipMemcpyHostToDevice));
-  RPY_HIP(hipMemcpy(tb->geo, geo.data(), sizeof(double) * geo.size(), hipMemcpyHostToDevice));
-  RPY_HIP(hipMemcpy(tb->sfac, sf.data(), sizeof(double) * sf.size(), hipMemcpyHostToDevice));
-  if (const int rc = make_m2l_tables(rot, zt, fp32, tb, s, err)) return rc;
-  return make_p2e_tables(p, tb, err);
+  TableImage im;
+  im.add(&tb->rscale, rsc.data(), sizeof(double) * rsc.size());
+  im.add(&tb->oct, oct.data(), sizeof(double2) * oct.size());
+  if (dense) im.add(&tb->itab, itab.data(), sizeof(double2) * itab.size());
+  im.add(&tb->rot64, rot.data(), sizeof(double) * rot.size());
+  im.add(&tb->rot32, rot32.data(), sizeof(float) * rot32.size());
+  im.add(&tb->zt64, zt.data(), sizeof(double) * zt.size());
+  im.add(&tb->zt32, zt32.data(), sizeof(float) * zt32.size());
+  im.add(&tb->geo, geo.data(), sizeof(double) * geo.size());
+  im.add(&tb->sfac, sf.data(), sizeof(double) * sf.size());
+  if (const int rc = make_m2l_tables(rot, zt, fp32, tb, &im)) return rc;
+  if (const int rc = make_p2e_tables(p, tb, &im, err)) return rc;
+  RPY_HIP(dev_alloc(&tb->base, im.bytes.size()));
+  for (const auto& [dst, at] : im.at) *dst = tb->base + at;
+  tb->bytes = (int64_t)im.bytes.size();
+  RPY_HIP(copy_in(tb->base, im.bytes.data(), im.bytes.size(), s));
+  return make_m2l_phases(tb, fp32, s, err);
 }
 
 void free_tables(Tables* tb) {
-  void* ps[] = {tb->oct, tb->itab, tb->rot64, tb->rot32, tb->zt64, tb->zt32, tb->geo, tb->rows_rot, tb->rows_zt, tb->rows_ph, tb->sfac, tb->rscale,
-                tb->p2e[0].desc, tb->p2e[0].slot, tb->p2e[0].scale, tb->p2e[1].desc, tb->p2e[1].slot,
-                tb->p2e[1].scale, tb->p2e_dk};
-  for (void* q : ps)
-    if (q) (void)hipFree(q);
-  tb->oct = tb->itab = nullptr;
-  tb->rot64 = tb->zt64 = tb->geo = tb->sfac = tb->rscale = nullptr;
-  tb->rot32 = tb->zt32 = nullptr;
-  tb->rows_rot = tb->rows_zt = tb->rows_ph = nullptr;
-  for (P2ESched& s : tb->p2e) {
-    s.desc = nullptr;
-    s.slot = nullptr;
-    s.scale = nullptr;
-    s.P = 0;
-  }
-  tb->p2e_dk = nullptr;
+  dev_free(tb->base);
+  *tb = Tables{};
 }
 
 // ------------------------------------------------------------- permutes ----

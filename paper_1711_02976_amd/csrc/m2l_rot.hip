@@ -1136,7 +1136,7 @@ static void append_map(const std::vector<int>& off, int r0, int r1, std::vector<
 int make_m2l_map(Built* B, hipStream_t s, Error* err) {
   const int nbox = B->tree.nbox;
   if (B->m2l_map) {
-    (void)hipFree(B->m2l_map);
+    dev_free(B->m2l_map);
     B->m2l_map = nullptr;
   }
   B->m2l_part[0] = B->m2l_part[1] = B->m2l_part[2] = 0;
@@ -1152,16 +1152,16 @@ int make_m2l_map(Built* B, hipStream_t s, Error* err) {
   append_map(off, 0, deep, map);
   B->m2l_part[2] = (int)map.size();
   if (map.empty()) return 0;
-  RPY_HIP(hipMalloc(&B->m2l_map, sizeof(int) * map.size()));
-  RPY_HIP(hipMemcpy(B->m2l_map, map.data(), sizeof(int) * map.size(), hipMemcpyHostToDevice));
+  RPY_HIP(dev_alloc(&B->m2l_map, sizeof(int) * map.size()));
+  RPY_HIP(copy_in(B->m2l_map, map.data(), sizeof(int) * map.size(), s));
   B->bytes += (int64_t)sizeof(int) * map.size();
   return 0;
 }
 
 // The tables of k_m2l_rows for the plan's order and precision, from the host
 // images of the rotation and z-translation matrices.
-int make_m2l_tables(const std::vector<double>& rot, const std::vector<double>& zt, int fp32, Tables* tb, hipStream_t s,
-                    Error* err) {
+int make_m2l_tables(const std::vector<double>& rot, const std::vector<double>& zt, int fp32, Tables* tb,
+                    TableImage* im) {
   const int p = tb->p, nc = rows_cols(p, fp32 ? 4 : 8);
   tb->rows_nc = nc;
   if (nc == 0) return 0;
@@ -1169,21 +1169,18 @@ int make_m2l_tables(const std::vector<double>& rot, const std::vector<double>& z
   if (nc == 32) rows_tables<32>(p, rot, zt, tr, tz);
   else rows_tables<16>(p, rot, zt, tr, tz);
   const size_t real = fp32 ? 4 : 8, np = (size_t)2 * 343 * (p + 1);
-  RPY_HIP(hipMalloc(&tb->rows_rot, real * tr.size()));
-  RPY_HIP(hipMalloc(&tb->rows_zt, real * tz.size()));
-  RPY_HIP(hipMalloc(&tb->rows_ph, 2 * real * np));
-  if (fp32) {
-    const std::vector<float> fr(tr.begin(), tr.end()), fz(tz.begin(), tz.end());
-    RPY_HIP(hipMemcpy(tb->rows_rot, fr.data(), real * fr.size(), hipMemcpyHostToDevice));
-    RPY_HIP(hipMemcpy(tb->rows_zt, fz.data(), real * fz.size(), hipMemcpyHostToDevice));
-    k_m2l_phases<float><<<dim3(6, 2), 64, 0, s>>>(p, tb->geo, static_cast<float2*>(tb->rows_ph));
-  } else {
-    RPY_HIP(hipMemcpy(tb->rows_rot, tr.data(), real * tr.size(), hipMemcpyHostToDevice));
-    RPY_HIP(hipMemcpy(tb->rows_zt, tz.data(), real * tz.size(), hipMemcpyHostToDevice));
-    k_m2l_phases<double><<<dim3(6, 2), 64, 0, s>>>(p, tb->geo, static_cast<double2*>(tb->rows_ph));
-  }
+  const std::vector<float> fr(fp32 ? tr.begin() : tr.end(), tr.end()), fz(fp32 ? tz.begin() : tz.end(), tz.end());
+  im->add(&tb->rows_rot, fp32 ? (const void*)fr.data() : tr.data(), real * tr.size());
+  im->add(&tb->rows_zt, fp32 ? (const void*)fz.data() : tz.data(), real * tz.size());
+  im->add(&tb->rows_ph, nullptr, 2 * real * np);
+  return 0;
+}
+
+int make_m2l_phases(Tables* tb, int fp32, hipStream_t s, Error* err) {
+  if (!tb->rows_ph) return 0;
+  if (fp32) k_m2l_phases<float><<<dim3(6, 2), 64, 0, s>>>(tb->p, tb->geo, static_cast<float2*>(tb->rows_ph));
+  else k_m2l_phases<double><<<dim3(6, 2), 64, 0, s>>>(tb->p, tb->geo, static_cast<double2*>(tb->rows_ph));
   RPY_HIP(hipGetLastError());
-  tb->bytes += real * (tr.size() + tz.size() + 2 * np);
   return 0;
 }
 

@@ -76,24 +76,21 @@ int make_tiles(const Built* B, int tile, Tiles* out, hipStream_t s, Error* err) 
   out->box = nullptr;
   if (B->nleaf == 0) return 0;
   int *cnt = nullptr, *off = nullptr, *tmp = nullptr;
-  RPY_HIP(hipMalloc(&cnt, sizeof(int) * B->nleaf));
-  RPY_HIP(hipMalloc(&off, sizeof(int) * B->nleaf));
-  RPY_HIP(hipMalloc(&tmp, sizeof(int) * scan_tmp_ints(B->nleaf)));
+  RPY_HIP(dev_alloc(&cnt, sizeof(int) * B->nleaf));
+  RPY_HIP(dev_alloc(&off, sizeof(int) * B->nleaf));
+  RPY_HIP(dev_alloc(&tmp, sizeof(int) * scan_tmp_ints(B->nleaf)));
   k_tile_count<<<nblk(B->nleaf, 256), 256, 0, s>>>(B->leaf_ids, B->nleaf, B->tree, tile, cnt);
-  RPY_HIP(scan_exclusive(cnt, off, B->nleaf, tmp, s));
-  int last[2];
-  RPY_HIP(hipMemcpyAsync(&last[0], off + B->nleaf - 1, sizeof(int), hipMemcpyDeviceToHost, s));
-  RPY_HIP(hipMemcpyAsync(&last[1], cnt + B->nleaf - 1, sizeof(int), hipMemcpyDeviceToHost, s));
+  RPY_PAGE(int, page);
+  RPY_HIP(scan_exclusive(cnt, off, B->nleaf, tmp, s, page));
   RPY_HIP(hipStreamSynchronize(s));
-  out->n = last[0] + last[1];
-  RPY_HIP(hipMalloc(&out->t, sizeof(int4) * out->n));
+  out->n = page[0];
+  RPY_HIP(dev_alloc(&out->t, sizeof(int4) * out->n));
   k_tile_fill<<<nblk(B->nleaf, 256), 256, 0, s>>>(B->leaf_ids, B->nleaf, B->tree, tile, off, out->t);
   RPY_HIP(hipGetLastError());
-  RPY_HIP(hipMalloc(&out->box, sizeof(double) * 6 * std::max(out->n, 1)));
+  RPY_HIP(dev_alloc(&out->box, sizeof(double) * 6 * std::max(out->n, 1)));
   if (out->n > 0) k_tile_box<<<out->n, 64, 0, s>>>(out->t, B->sx, B->sy, B->sz, out->box);
   RPY_HIP(hipGetLastError());
-  RPY_HIP(hipStreamSynchronize(s));
-  (void)hipFree(cnt); (void)hipFree(off); (void)hipFree(tmp);
+  dev_free(cnt); dev_free(off); dev_free(tmp);
   return 0;
 }
 
@@ -229,7 +226,7 @@ static int make_near_work(const Built* B, const Tiles& tiles, const ChunkFilter&
   // scratch: the counts, two statistics, and the tables' scans
   const size_t ntmp = scan_tmp_ints(nt);
   unsigned long long* stat = nullptr;
-  RPY_HIP(hipMalloc(&stat, 2 * sizeof(unsigned long long) + sizeof(int) * (5 * (size_t)nt + ntmp)));
+  RPY_HIP(dev_alloc(&stat, 2 * sizeof(unsigned long long) + sizeof(int) * (5 * (size_t)nt + ntmp)));
   int* cnt = reinterpret_cast<int*>(stat + 2);
   int *held = cnt + nt, *off = held + nt, *flag = off + nt, *order = flag + nt, *tmp = order + nt;
   RPY_HIP(hipMemsetAsync(stat, 0, 2 * sizeof(unsigned long long), s));
@@ -243,32 +240,26 @@ static int make_near_work(const Built* B, const Tiles& tiles, const ChunkFilter&
   if (hs[1] > cap) {
     // at most total / cap + 1 per tile parts
     const size_t most = (size_t)NEAR_ITEMS + nt;
-    RPY_HIP(hipMalloc(&out->item, sizeof(int4) * most + sizeof(int) * (most + 3 * (size_t)nt)));
+    RPY_HIP(dev_alloc(&out->item, sizeof(int4) * most + sizeof(int) * (most + 3 * (size_t)nt)));
     out->slot = reinterpret_cast<int*>(out->item + most);
     out->parts = out->slot + most;
     out->slot0 = out->parts + nt;
     out->red = out->slot0 + nt;
     k_near_parts<<<nblk(nt, 256), 256, 0, s>>>(cnt, nt, (int)std::min<unsigned long long>(cap, 0x7fffffff),
                                                out->parts, held, flag);
-    RPY_HIP(scan_exclusive(out->parts, off, nt, tmp, s));
-    RPY_HIP(scan_exclusive(held, out->slot0, nt, tmp, s));
-    RPY_HIP(scan_exclusive(flag, order, nt, tmp, s));
+    RPY_PAGE(int, page);
+    RPY_HIP(scan_exclusive(out->parts, off, nt, tmp, s, page));
+    RPY_HIP(scan_exclusive(held, out->slot0, nt, tmp, s, page + 1));
+    RPY_HIP(scan_exclusive(flag, order, nt, tmp, s, page + 2));
     k_near_fill<<<nblk(nt, 64), 64, 0, s>>>(tiles.t, tiles.box, nt, B->tree, l, f, cnt, off, out->parts, out->slot0,
                                             order, out->item, out->slot, out->red);
     RPY_HIP(hipGetLastError());
-    int last[6];
-    RPY_HIP(hipMemcpyAsync(&last[0], off + nt - 1, sizeof(int), hipMemcpyDeviceToHost, s));
-    RPY_HIP(hipMemcpyAsync(&last[1], out->parts + nt - 1, sizeof(int), hipMemcpyDeviceToHost, s));
-    RPY_HIP(hipMemcpyAsync(&last[2], out->slot0 + nt - 1, sizeof(int), hipMemcpyDeviceToHost, s));
-    RPY_HIP(hipMemcpyAsync(&last[3], held + nt - 1, sizeof(int), hipMemcpyDeviceToHost, s));
-    RPY_HIP(hipMemcpyAsync(&last[4], order + nt - 1, sizeof(int), hipMemcpyDeviceToHost, s));
-    RPY_HIP(hipMemcpyAsync(&last[5], flag + nt - 1, sizeof(int), hipMemcpyDeviceToHost, s));
     RPY_HIP(hipStreamSynchronize(s));
-    out->n = last[0] + last[1];
-    out->nslot = last[2] + last[3];
-    out->nred = last[4] + last[5];
+    out->n = page[0];
+    out->nslot = page[1];
+    out->nred = page[2];
   }
-  (void)hipFree(stat);
+  dev_free(stat);
   return 0;
 }
 
@@ -281,7 +272,7 @@ int make_near_plan(const Built* B, const Tiles& tiles, double a, int wd, NearPla
 
 void free_near_plan(NearPlan* p) {
   for (NearWork* w : {&p->u, &p->w, &p->o}) {
-    if (w->item) (void)hipFree(w->item);  // the other tables follow it
+    if (w->item) dev_free(w->item);  // the other tables follow it
     *w = NearWork{};
   }
 }

@@ -451,7 +451,7 @@ bool pack_columns(int p, int cap, std::vector<std::vector<int>>& bins) {
 
 // Builds the schedule with K steps per wave and pass and the fewest passes
 // (at most maxp) whose column packing fits; false if none does.
-static int build_sched(int p, int K, int maxp, P2ESched* out, Error* err, int64_t* bytes) {
+static int build_sched(int p, int K, int maxp, P2ESched* out, TableImage* im, Error* err) {
   out->K = K;
   out->P = 0;
   std::vector<std::vector<int>> bins;
@@ -487,13 +487,9 @@ static int build_sched(int p, int K, int maxp, P2ESched* out, Error* err, int64_
         scale[(size_t)ps * S + w * K + kk] = 1.0 / (fac[n - m] * fac[n + m]);
       }
   }
-  RPY_HIP(hipMalloc(&out->desc, sizeof(P2EPass) * desc.size()));
-  RPY_HIP(hipMalloc(&out->slot, sizeof(int) * slot.size()));
-  RPY_HIP(hipMalloc(&out->scale, sizeof(double) * scale.size()));
-  RPY_HIP(hipMemcpy(out->desc, desc.data(), sizeof(P2EPass) * desc.size(), hipMemcpyHostToDevice));
-  RPY_HIP(hipMemcpy(out->slot, slot.data(), sizeof(int) * slot.size(), hipMemcpyHostToDevice));
-  RPY_HIP(hipMemcpy(out->scale, scale.data(), sizeof(double) * scale.size(), hipMemcpyHostToDevice));
-  *bytes += sizeof(P2EPass) * desc.size() + (sizeof(int) + sizeof(double)) * slot.size();
+  im->add(&out->desc, desc.data(), sizeof(P2EPass) * desc.size());
+  im->add(&out->slot, slot.data(), sizeof(int) * slot.size());
+  im->add(&out->scale, scale.data(), sizeof(double) * scale.size());
   out->P = P;
   return 1;
 }
@@ -504,7 +500,7 @@ static int build_sched(int p, int K, int maxp, P2ESched* out, Error* err, int64_
 // ranges, so that no block carries much more than its share.
 static int make_items(const std::vector<int>& boxes, const std::vector<int>& off, const std::vector<int>& ent,
                       const std::vector<int>& beg, const std::vector<int>& end, int cap, P2EWork* w, int64_t* bytes,
-                      Error* err) {
+                      hipStream_t s, Error* err) {
   auto chunks = [&](int e) { return (end[ent[e]] - beg[ent[e]] + P2E_CHUNK - 1) / P2E_CHUNK; };
   std::vector<int4> work, red;
   std::vector<int2> rng;
@@ -539,12 +535,12 @@ static int make_items(const std::vector<int>& boxes, const std::vector<int>& off
   w->nred = (int)red.size();
   if (w->n == 0) return 0;
   const size_t nw = sizeof(int4) * work.size(), nr = sizeof(int4) * red.size(), nc = sizeof(int2) * rng.size();
-  RPY_HIP(hipMalloc(&w->work, nw + nr + nc));
+  RPY_HIP(dev_alloc(&w->work, nw + nr + nc));
   w->red = w->work + work.size();
   w->chunks = reinterpret_cast<int2*>(w->red + red.size());
-  RPY_HIP(hipMemcpy(w->work, work.data(), nw, hipMemcpyHostToDevice));
-  if (nr) RPY_HIP(hipMemcpy(w->red, red.data(), nr, hipMemcpyHostToDevice));
-  RPY_HIP(hipMemcpy(w->chunks, rng.data(), nc, hipMemcpyHostToDevice));
+  work.insert(work.end(), red.begin(), red.end());
+  RPY_HIP(copy_in(w->work, work.data(), nw + nr, s));
+  RPY_HIP(copy_in(w->chunks, rng.data(), nc, s));
   *bytes += (int64_t)(nw + nr + nc);
   return 0;
 }
@@ -578,10 +574,10 @@ int make_p2e_work(Built* B, hipStream_t s, Error* err) {
     for (int e : ent) total += cnt(e);
     const int coarse = (int)std::max<int64_t>(16, total / 2048);
     const int fine = (int)std::min<int64_t>(coarse, std::max<int64_t>(2, total / 1024));
-    if (int rc = make_items(all, off, ent, beg, end, coarse, &B->xw[0], &B->bytes, err)) return rc;
+    if (int rc = make_items(all, off, ent, beg, end, coarse, &B->xw[0], &B->bytes, s, err)) return rc;
     B->xfine = fine < coarse;
     if (!B->xfine) B->xw[1] = B->xw[0];
-    else if (int rc = make_items(all, off, ent, beg, end, fine, &B->xw[1], &B->bytes, err)) return rc;
+    else if (int rc = make_items(all, off, ent, beg, end, fine, &B->xw[1], &B->bytes, s, err)) return rc;
   }
   int64_t total = 0;
   int most = 0;
@@ -592,7 +588,7 @@ int make_p2e_work(Built* B, hipStream_t s, Error* err) {
   const int cap = (int)std::max<int64_t>(2, total / 1024);
   if (B->nleaf < FEW && most > cap) {
     for (int i = 0; i <= B->nleaf; ++i) self[i] = i;
-    return make_items(leaf, self, leaf, beg, end, cap, &B->mw, &B->bytes, err);
+    return make_items(leaf, self, leaf, beg, end, cap, &B->mw, &B->bytes, s, err);
   }
   return 0;
 }
@@ -601,11 +597,10 @@ int p2e_slots(const Built* B, bool fine) {
   return fine ? std::max(B->xw[1].nslot, B->mw.nslot) : B->xw[0].nslot;
 }
 
-int make_p2e_tables(int p, Tables* tb, Error* err) {
-  int64_t bytes = 0;
-  const int r8 = build_sched(p, 8, 7, &tb->p2e[0], err, &bytes);
+int make_p2e_tables(int p, Tables* tb, TableImage* im, Error* err) {
+  const int r8 = build_sched(p, 8, 7, &tb->p2e[0], im, err);
   if (r8 < 0) return -1;
-  const int r16 = build_sched(p, 16, 2, &tb->p2e[1], err, &bytes);
+  const int r16 = build_sched(p, 16, 2, &tb->p2e[1], im, err);
   if (r16 < 0) return -1;
   if (r8 == 0 && r16 == 0) {
     err->code = -1;  // invalid argument
@@ -619,9 +614,7 @@ int make_p2e_tables(int p, Tables* tb, Error* err) {
     if (m > 0) dd *= -(2.0 * m - 1.0);
     dk[m] = dd;
   }
-  RPY_HIP(hipMalloc(&tb->p2e_dk, sizeof(double) * dk.size()));
-  RPY_HIP(hipMemcpy(tb->p2e_dk, dk.data(), sizeof(double) * dk.size(), hipMemcpyHostToDevice));
-  tb->bytes += bytes + sizeof(double) * dk.size();
+  im->add(&tb->p2e_dk, dk.data(), sizeof(double) * dk.size());
   return 0;
 }
 

@@ -14,6 +14,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 
 #include "common.h"
 
@@ -24,7 +25,8 @@ constexpr int SCAN_T = 256;
 constexpr int SCAN_ITEMS = 8;
 constexpr int SCAN_TILE = SCAN_T * SCAN_ITEMS;
 
-__global__ void __launch_bounds__(SCAN_T) k_scan_tile(const int* in, int* out, int64_t n, int* sums) {
+__global__ void __launch_bounds__(SCAN_T) k_scan_tile(const int* in, int* out, int64_t n, int* sums, int* total,
+                                                       int* total2) {
   __shared__ int warp_tot[SCAN_T / 64];
   int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_ITEMS;
   int v[SCAN_ITEMS];
@@ -52,7 +54,11 @@ __global__ void __launch_bounds__(SCAN_T) k_scan_tile(const int* in, int* out, i
 #pragma unroll
   for (int i = 0; i < SCAN_ITEMS; ++i)
     if (base + i < n) out[base + i] = v[i] + excl;
-  if (threadIdx.x == SCAN_T - 1 && sums) sums[blockIdx.x] = woff + x;
+  if (threadIdx.x == SCAN_T - 1) {
+    if (sums) sums[blockIdx.x] = woff + x;
+    if (total) *total = woff + x;
+    if (total2) *total2 = woff + x;
+  }
 }
 
 __global__ void k_scan_add(int* out, int64_t n, const int* sums) {
@@ -71,16 +77,16 @@ size_t scan_tmp_ints(int64_t n) {
   return t + 1;
 }
 
-hipError_t scan_exclusive(const int* in, int* out, int64_t n, int* tmp, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  int64_t nb = (n + SCAN_TILE - 1) / SCAN_TILE;
+hipError_t scan_exclusive(const int* in, int* out, int64_t n, int* tmp, hipStream_t s, int* total, int* total2) {
+  if (n <= 0 && !total && !total2) return hipSuccess;
+  const int64_t nb = std::max<int64_t>(1, (n + SCAN_TILE - 1) / SCAN_TILE);
   if (nb == 1) {
-    k_scan_tile<<<1, SCAN_T, 0, s>>>(in, out, n, nullptr);
+    k_scan_tile<<<1, SCAN_T, 0, s>>>(in, out, n, nullptr, total, total2);
     return hipGetLastError();
   }
   int* sums = tmp;
-  k_scan_tile<<<(unsigned)nb, SCAN_T, 0, s>>>(in, out, n, sums);
-  hipError_t e = scan_exclusive(sums, sums, nb, tmp + nb + 1, s);
+  k_scan_tile<<<(unsigned)nb, SCAN_T, 0, s>>>(in, out, n, sums, nullptr, nullptr);
+  hipError_t e = scan_exclusive(sums, sums, nb, tmp + nb + 1, s, total, total2);
   if (e != hipSuccess) return e;
   k_scan_add<<<(unsigned)nb, SCAN_T, 0, s>>>(out, n, sums);
   return hipGetLastError();
@@ -547,14 +553,50 @@ __global__ void k_leaf_compact(Tree t, const int* off, int* ids) {
   if (b < t.nbox && t.nchild[b] == 0) ids[off[b]] = b;
 }
 
+// A wave per box, lanes across its list entries; every sum is of whole numbers.
+__global__ void __launch_bounds__(256) k_tree_sums(Tree t, List U, List W, List X, int max_depth, int wmax,
+                                                   TreeSums* out) {
+  const int b = blockIdx.x * 4 + threadIdx.x / 64, lane = threadIdx.x & 63;
+  if (b >= t.nbox) return;
+  auto beads = [&](int c) { return t.end[c] - t.begin[c]; };
+  const int nb = beads(b);
+  unsigned long long src = 0, we = 0, xp = 0;
+  for (int k = X.off[b] + lane; k < X.off[b + 1]; k += 64) xp += beads(X.ent[k]);
+  if (t.child[b] < 0) {
+    for (int k = U.off[b] + lane; k < U.off[b + 1]; k += 64) src += beads(U.ent[k]);
+    for (int k = W.off[b] + lane; k < W.off[b + 1]; k += 64) {
+      const int nc = beads(W.ent[k]);
+      if (wmax < 0 || nc > wmax) we += nb;
+      else src += nc;
+    }
+  }
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) {
+    src += __shfl_xor(src, d);
+    we += __shfl_xor(we, d);
+    xp += __shfl_xor(xp, d);
+  }
+  if (lane != 0) return;
+  if (xp) atomicAdd(&out->xpairs, xp);
+  if (t.child[b] >= 0) {
+    atomicMin(&out->hi, nb);
+    return;
+  }
+  if (we) atomicAdd(&out->weval, we);
+  if (src) atomicAdd(&out->pairs, src * (64ull * ((nb + 63) / 64)));
+  if (t.level[b] < max_depth) atomicMax(&out->lo, nb);
+}
+
+__global__ void k_tree_sums_zero(TreeSums* out) { *out = TreeSums{0, 0, 0, 0, 0x7fffffff}; }
+
 hipError_t radix_sort(uint64_t** keys, int** vals, uint64_t* kalt, int* valt, int64_t n, int key_passes,
                       int sys_passes, const int* sys_begin, int nsys, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   int64_t rblk = (n + RS_TILE - 1) / RS_TILE;
   int64_t hn = 256 * rblk;
   int *hist = nullptr, *stmp = nullptr;
-  hipError_t e = hipMalloc(&hist, sizeof(int) * hn);
-  if (e == hipSuccess) e = hipMalloc(&stmp, sizeof(int) * scan_tmp_ints(hn));
+  hipError_t e = dev_alloc(&hist, sizeof(int) * hn);
+  if (e == hipSuccess) e = dev_alloc(&stmp, sizeof(int) * scan_tmp_ints(hn));
   uint64_t *k0 = *keys, *k1 = kalt;
   int *v0 = *vals, *v1 = valt;
   for (int pass = 0; e == hipSuccess && pass < key_passes + sys_passes; ++pass) {
@@ -571,15 +613,13 @@ hipError_t radix_sort(uint64_t** keys, int** vals, uint64_t* kalt, int* valt, in
     std::swap(k0, k1);
     std::swap(v0, v1);
   }
-  if (hipStreamSynchronize(s) != hipSuccess && e == hipSuccess) e = hipErrorUnknown;
-  if (hist) (void)hipFree(hist);
-  if (stmp) (void)hipFree(stmp);
+  dev_free(hist);
+  dev_free(stmp);
   // result in k0/v0; hand the other buffers back through kalt/valt's owners
   if (k0 != *keys) {
     // the sorted data lives in the alternate buffers: copy back
     if (e == hipSuccess) e = hipMemcpyAsync(*keys, k0, sizeof(uint64_t) * n, hipMemcpyDeviceToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(*vals, v0, sizeof(int) * n, hipMemcpyDeviceToDevice, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
   }
   return e;
 }
@@ -590,10 +630,10 @@ namespace {
 template <class T>
 int dalloc(T** p, int64_t count, Built* out, Error* err) {
   if (count <= 0) count = 1;
-  hipError_t e = hipMalloc((void**)p, sizeof(T) * count);
+  hipError_t e = dev_alloc(p, sizeof(T) * count);
   if (e != hipSuccess) {
     err->code = -3;
-    err->msg = "hipMalloc failed (" + std::to_string(sizeof(T) * count) + " bytes)";
+    err->msg = "device allocation failed (" + std::to_string(sizeof(T) * count) + " bytes)";
     *p = nullptr;
     return -3;
   }
@@ -614,10 +654,9 @@ int grow_tree(Built* B, int need, hipStream_t s, Error* err) {
     if (fields_old[f])
       RPY_HIP(hipMemcpyAsync(fields_new[f], fields_old[f], sizeof(int) * B->cap, hipMemcpyDeviceToDevice, s));
   }
-  RPY_HIP(hipStreamSynchronize(s));
   for (int f = 0; f < 10; ++f) {
     if (fields_old[f]) {
-      RPY_HIP(hipFree(fields_old[f]));
+      dev_free(fields_old[f]);
       B->bytes -= sizeof(int) * B->cap;
     }
   }
@@ -650,7 +689,7 @@ void free_spare(Spare* spare) {
   if (!spare) return;
   void* ps[] = {spare->keys, spare->perm, spare->sx, spare->sy, spare->sz};
   for (void* p : ps)
-    if (p) (void)hipFree(p);
+    if (p) dev_free(p);
   *spare = Spare{};
 }
 
@@ -662,10 +701,10 @@ void free_built(Built* b) {
                 b->tree.cz, b->tree.h, b->colleague, b->leaf_ids, b->m2l_map, b->mw.work, b->xw[0].work,
                 b->xfine ? b->xw[1].work : nullptr};
   for (void* p : ps)
-    if (p) (void)hipFree(p);
+    if (p) dev_free(p);
   for (auto& L : b->lists) {
-    if (L.off) (void)hipFree(L.off);
-    if (L.ent) (void)hipFree(L.ent);
+    if (L.off) dev_free(L.off);
+    if (L.ent) dev_free(L.ent);
   }
   *b = Built{};
 }
@@ -679,7 +718,8 @@ int build_tree(const BuildArgs& A, Built* B, Error* err) {
   std::vector<int> sb(nsys + 1);
   for (int i = 0; i <= nsys; ++i) sb[i] = (int)A.sys_begin_h[i];
   if (dalloc(&B->d_sys_begin, nsys + 1, B, err)) return -3;
-  RPY_HIP(hipMemcpy(B->d_sys_begin, sb.data(), sizeof(int) * (nsys + 1), hipMemcpyHostToDevice));
+  RPY_HIP(copy_in(B->d_sys_begin, sb.data(), sizeof(int) * (nsys + 1), s));
+  RPY_PAGE(int, page);
 
   if (A.presorted) {
     // Same beads and systems as an earlier tree: its cubes, keys and sorted
@@ -717,13 +757,12 @@ int build_tree(const BuildArgs& A, Built* B, Error* err) {
     }
   } else {
     // Bounding cubes and the non-finite check.
-    int nblk = 64;
+    const int nblk = 64;
     double* part = nullptr;
     double* bb = nullptr;
-    int* bad = nullptr;
     if (dalloc(&part, (int64_t)nsys * nblk * 6, B, err)) return -3;
-    if (dalloc(&bb, nsys * 6, B, err)) return -3;
-    if (dalloc(&bad, 1, B, err)) return -3;
+    if (dalloc(&bb, nsys * 6 + 1, B, err)) return -3;
+    int* bad = reinterpret_cast<int*>(bb + 6 * (int64_t)nsys);
     RPY_HIP(hipMemsetAsync(bad, 0, sizeof(int), s));
     // the bead passes (bounding cubes, keys, sort, gather) are timed with
     // events for the plan statistics
@@ -743,13 +782,13 @@ int build_tree(const BuildArgs& A, Built* B, Error* err) {
     k_check_finite<<<1024, 256, 0, s>>>(A.pos, 3 * n, bad);
     rec(1);
     RPY_HIP(hipGetLastError());
-    std::vector<double> hbb(nsys * 6);
-    int hbad = 0;
-    RPY_HIP(hipMemcpyAsync(hbb.data(), bb, sizeof(double) * nsys * 6, hipMemcpyDeviceToHost, s));
-    RPY_HIP(hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, s));
+    std::vector<double> hbb(nsys * 6 + 1);
+    RPY_HIP(hipMemcpyAsync(hbb.data(), bb, sizeof(double) * (nsys * 6 + 1), hipMemcpyDeviceToHost, s));
     RPY_HIP(hipStreamSynchronize(s));
-    (void)hipFree(part); (void)hipFree(bb); (void)hipFree(bad);
-    B->bytes -= sizeof(double) * ((int64_t)nsys * nblk * 6 + nsys * 6) + sizeof(int);
+    int hbad = 0;
+    std::memcpy(&hbad, &hbb[6 * (size_t)nsys], sizeof(int));
+    dev_free(part); dev_free(bb);
+    B->bytes -= sizeof(double) * ((int64_t)nsys * nblk * 6 + nsys * 6 + 1);
     if (hbad) {
       drop();
       err->code = -2;
@@ -784,7 +823,7 @@ int build_tree(const BuildArgs& A, Built* B, Error* err) {
     int npass_sys = nsys > 1 ? (nsys > 256 ? 2 : 1) : 0;
     B->sort_passes = 8 + npass_sys;
     RPY_HIP(radix_sort(&k0, &v0, k1, v1, n, 8, npass_sys, B->d_sys_begin, nsys, s));
-    (void)hipFree(k1); (void)hipFree(v1);
+    dev_free(k1); dev_free(v1);
     B->bytes -= (sizeof(uint64_t) + sizeof(int)) * std::max<int64_t>(n, 1);
     B->keys = k0;
     B->perm = v0;
@@ -821,7 +860,7 @@ int build_tree(const BuildArgs& A, Built* B, Error* err) {
     int ls = B->level_start[lev], le = B->level_start[lev + 1];
     int nb = le - ls;
     if (nb > ccap) {
-      if (cnt) { (void)hipFree(cut); (void)hipFree(cnt); (void)hipFree(off); (void)hipFree(tmp); }
+      if (cnt) { dev_free(cut); dev_free(cnt); dev_free(off); dev_free(tmp); }
       ccap = std::max<int64_t>(nb, 2 * ccap);
       if (dalloc(&cut, 8 * ccap, B, err) || dalloc(&cnt, ccap, B, err) || dalloc(&off, ccap, B, err) ||
           dalloc(&tmp, (int64_t)scan_tmp_ints(ccap), B, err))
@@ -830,12 +869,9 @@ int build_tree(const BuildArgs& A, Built* B, Error* err) {
     k_tree_count<<<nblocks(8 * (int64_t)nb, 256), 256, 0, s>>>(t, B->keys, ls, le, lev, A.leaf_size, A.max_depth, cut,
                                                              cnt);
     RPY_HIP(hipGetLastError());
-    RPY_HIP(scan_exclusive(cnt, off, nb, tmp, s));
-    int last[2] = {0, 0};
-    RPY_HIP(hipMemcpyAsync(&last[0], off + nb - 1, sizeof(int), hipMemcpyDeviceToHost, s));
-    RPY_HIP(hipMemcpyAsync(&last[1], cnt + nb - 1, sizeof(int), hipMemcpyDeviceToHost, s));
+    RPY_HIP(scan_exclusive(cnt, off, nb, tmp, s, page));
     RPY_HIP(hipStreamSynchronize(s));
-    int nnext = last[0] + last[1];
+    const int nnext = page[0];
     if (grow_tree(B, le + nnext, s, err)) return err->code;
     k_tree_write<<<nblocks(8 * (int64_t)nb, 256), 256, 0, s>>>(t, ls, le, lev, cut, cnt, off);
     RPY_HIP(hipGetLastError());
@@ -843,7 +879,7 @@ int build_tree(const BuildArgs& A, Built* B, Error* err) {
     B->level_start.push_back(le + nnext);
     ++lev;
   }
-  (void)hipFree(cut); (void)hipFree(cnt); (void)hipFree(off); (void)hipFree(tmp);
+  dev_free(cut); dev_free(cnt); dev_free(off); dev_free(tmp);
   B->bytes -= sizeof(int) * (10 * ccap + scan_tmp_ints(ccap));
   B->depth = (int)B->level_start.size() - 2;
   t.nbox = B->level_start.back();
@@ -870,16 +906,12 @@ int build_tree(const BuildArgs& A, Built* B, Error* err) {
       dalloc(&ltmp, (int64_t)scan_tmp_ints(nbox), B, err))
     return -3;
   k_leaf_flags<<<nblocks(nbox, 256), 256, 0, s>>>(t, flag);
-  RPY_HIP(scan_exclusive(flag, loff, nbox, ltmp, s));
-  int lastf[2];
-  RPY_HIP(hipMemcpyAsync(&lastf[0], loff + nbox - 1, sizeof(int), hipMemcpyDeviceToHost, s));
-  RPY_HIP(hipMemcpyAsync(&lastf[1], flag + nbox - 1, sizeof(int), hipMemcpyDeviceToHost, s));
-  RPY_HIP(hipStreamSynchronize(s));
-  B->nleaf = lastf[0] + lastf[1];
-  if (dalloc(&B->leaf_ids, B->nleaf, B, err)) return -3;
+  // their number is read with the lists' below; there are at most nbox
+  RPY_HIP(scan_exclusive(flag, loff, nbox, ltmp, s, page + 5));
+  if (dalloc(&B->leaf_ids, nbox, B, err)) return -3;
   k_leaf_compact<<<nblocks(nbox, 256), 256, 0, s>>>(t, loff, B->leaf_ids);
   RPY_HIP(hipGetLastError());
-  (void)hipFree(flag); (void)hipFree(loff); (void)hipFree(ltmp);
+  dev_free(flag); dev_free(loff); dev_free(ltmp);
   B->bytes -= sizeof(int) * (2 * (int64_t)nbox + scan_tmp_ints(nbox));
 
   // Interaction lists: count, scan, fill (sorted by box id).  The O list is
@@ -894,41 +926,35 @@ int build_tree(const BuildArgs& A, Built* B, Error* err) {
   k_lists<<<nbox, 64, 0, s>>>(t, B->colleague, nbox, 0, lcnt, none[0], none[1], none[2], none[3],
                                            none[4], want_o, B->d_side, A.a);
   RPY_HIP(hipGetLastError());
-  // The five scans, then one read-back of their last offsets and counts.
-  // Copies to or from the host arrays below are drained before any return.
-  int lastc[5][2];
-  int tot32[5];
-  hipError_t le = hipSuccess;
-  int lrc = 0;
-  for (int L = 0; L < 5 && le == hipSuccess; ++L) {
-    if ((lrc = dalloc(&B->lists[L].off, nbox + 1, B, err)) != 0) break;
-    le = scan_exclusive(lcnt + (int64_t)L * nbox, B->lists[L].off, nbox, lt, s);
-    if (le == hipSuccess)
-      le = hipMemcpyAsync(&lastc[L][0], B->lists[L].off + nbox - 1, sizeof(int), hipMemcpyDeviceToHost, s);
-    if (le == hipSuccess)
-      le = hipMemcpyAsync(&lastc[L][1], lcnt + (int64_t)L * nbox + nbox - 1, sizeof(int), hipMemcpyDeviceToHost, s);
-  }
-  hipError_t se = hipStreamSynchronize(s);
-  if (lrc) return lrc;
-  RPY_HIP(le);
-  RPY_HIP(se);
+  // The five scans, which leave the lists' lengths at their ends, then one wait.
   for (int L = 0; L < 5; ++L) {
-    const int64_t total = (int64_t)lastc[L][0] + lastc[L][1];
-    B->lists[L].len = total;
-    tot32[L] = (int)total;
-    if (dalloc(&B->lists[L].ent, total, B, err)) return -3;
+    if (dalloc(&B->lists[L].off, nbox + 1, B, err)) return -3;
+    RPY_HIP(scan_exclusive(lcnt + (int64_t)L * nbox, B->lists[L].off, nbox, lt, s, page + L, B->lists[L].off + nbox));
   }
-  for (int L = 0; L < 5 && le == hipSuccess; ++L)
-    le = hipMemcpyAsync(B->lists[L].off + nbox, &tot32[L], sizeof(int), hipMemcpyHostToDevice, s);
-  se = hipStreamSynchronize(s);
-  RPY_HIP(le);
-  RPY_HIP(se);
+  RPY_HIP(hipStreamSynchronize(s));
+  B->nleaf = page[5];
+  for (int L = 0; L < 5; ++L) {
+    B->lists[L].len = page[L];
+    if (dalloc(&B->lists[L].ent, B->lists[L].len, B, err)) return -3;
+  }
   k_lists<<<nbox, 64, 0, s>>>(t, B->colleague, nbox, 1, lcnt, B->lists[0], B->lists[1], B->lists[2],
                                            B->lists[3], B->lists[4], want_o, B->d_side, A.a);
   RPY_HIP(hipGetLastError());
-  RPY_HIP(hipStreamSynchronize(s));
-  (void)hipFree(lcnt); (void)hipFree(lt);
+  dev_free(lcnt); dev_free(lt);
   B->bytes -= sizeof(int) * (5 * (int64_t)nbox + scan_tmp_ints(nbox + 1));
+  return 0;
+}
+
+int tree_sums(const Built& B, int max_depth, int wmax, TreeSums* out, hipStream_t s, Error* err) {
+  TreeSums* d = nullptr;
+  RPY_HIP(dev_alloc(&d, sizeof(TreeSums)));
+  k_tree_sums_zero<<<1, 1, 0, s>>>(d);
+  k_tree_sums<<<nblocks(B.tree.nbox, 4), 256, 0, s>>>(B.tree, B.lists[LU], B.lists[LW], B.lists[LX], max_depth, wmax,
+                                                      d);
+  RPY_HIP(hipGetLastError());
+  RPY_HIP(hipMemcpyAsync(out, d, sizeof(TreeSums), hipMemcpyDeviceToHost, s));
+  RPY_HIP(hipStreamSynchronize(s));
+  dev_free(d);
   return 0;
 }
 

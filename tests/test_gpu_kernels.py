@@ -200,3 +200,49 @@ def test_lanczos_many_chunks(orc):
         assert orc.rel_l2(y.cpu().numpy(), u.cpu().numpy()) <= 1e-5
     finally:
         P.free()
+
+
+# Memory, streams and host pages kept between plans: plans of several sizes made,
+# used and freed by two threads on streams of their own, blocks of one reused by
+# the other, give what a plan on its own gives, bit for bit.
+def test_plans_share_kept_memory():
+    import threading
+
+    import paper_1711_02976_amd as R
+    import torch
+    from gpu_common import to_dev
+    log("kept memory: two threads, two streams")
+    work = []
+    for i, (n, nrhs, leaf) in enumerate([(300, 1, 40), (5000, 3, 60), (20000, 1, 0), (900, 2, 25)]):
+        w = W.clustered(n, 4, 12.0, 0.7, 0.05, nrhs, seed=380 + i)
+        work.append((to_dev(w.pos), to_dev(w.forces), w.a, w.eta, leaf))
+
+    def one(c, stream):
+        pos, F, a, eta, leaf = c
+        P = R.Plan(pos, a, eta, 1e-6, leaf_size=leaf, stream=stream.cuda_stream)
+        try:
+            return P.matvec(F).clone()
+        finally:
+            P.free()
+
+    torch.cuda.synchronize()
+    ref = [one(c, torch.cuda.current_stream()) for c in work]
+    torch.cuda.synchronize()
+    bad = []
+
+    def run(k):
+        st = torch.cuda.Stream()
+        with torch.cuda.stream(st):
+            for it in range(6):
+                i = (it * (k + 1) + k) % len(work)
+                got = one(work[i], st)
+                st.synchronize()
+                if not torch.equal(got, ref[i]):
+                    bad.append((k, it, i))
+
+    ts = [threading.Thread(target=run, args=(k,)) for k in range(2)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert not bad
