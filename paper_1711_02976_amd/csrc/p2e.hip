@@ -175,6 +175,17 @@ __global__ void __launch_bounds__(P2E_THREADS) k_p2e(int p, const int* ids, cons
         sc = 1.0;
       }
       if (lane >= nb) sc = 0.0;  // every harmonic of an idle lane is zero
+      // S->M: the chunk's charges as matrix-core operands, for all passes: loaded
+      // here, they arrive while the harmonics are generated
+      double bq[VEC || LOCAL ? 1 : P2E_CHUNK / 4];
+      if constexpr (!VEC && !LOCAL)
+#pragma unroll
+        for (int q = 0; q < P2E_CHUNK / 4; ++q) bq[q] = li < ND ? Q[(int64_t)(jc + 4 * q + lk) * ND + li] : 0.0;
+      double ql[LOCAL && !VEC ? 4 : 1];  // S->L: one bead's and right-hand side's charges, on their way to Qs
+      if constexpr (LOCAL && !VEC)
+        if ((int)threadIdx.x < P2E_CHUNK * NRC)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) ql[q] = Q[(int64_t)jc * ND + 4 * (int)threadIdx.x + q];
       double2 h0 = make_double2(0.0, 0.0), h1 = h0;
       double ca = 0.0, cb = 0.0;  // 2n - 1 and (n-1)^2 - m^2 for the next degree n
 #pragma unroll
@@ -183,7 +194,7 @@ __global__ void __launch_bounds__(P2E_THREADS) k_p2e(int p, const int* ids, cons
         uint64_t ml = ((uint64_t)d.mhi << 32) | d.mlo;
         double2* hw = Hs + lane * LD + wv * K;  // this lane's row, this wave's slots
         __syncthreads();                        // the previous accumulation is done with Hs
-        if (LOCAL && ps == 0 && (int)threadIdx.x < P2E_CHUNK * NRC) {
+        if (LOCAL && VEC && ps == 0 && (int)threadIdx.x < P2E_CHUNK * NRC) {
           const int bb = threadIdx.x % P2E_CHUNK, r = threadIdx.x / P2E_CHUNK;
           const double* q = Q + (int64_t)(jc + bb) * ND + 4 * r;
           const double q0 = q[0], q1 = q[1], q2 = q[2];
@@ -241,6 +252,14 @@ __global__ void __launch_bounds__(P2E_THREADS) k_p2e(int p, const int* ids, cons
           }
         }
         for (; k < K; ++k) hw[k] = make_double2(0.0, 0.0);
+        if constexpr (LOCAL && !VEC)
+          if (ps == 0 && (int)threadIdx.x < P2E_CHUNK * NRC) {
+            double* o = Qs + 4 * (int)threadIdx.x;  // bead threadIdx.x / NRC, right-hand side threadIdx.x % NRC
+            o[0] = ql[0];
+            o[1] = ql[1];
+            o[2] = ql[2];
+            o[3] = fma(ql[0], wx, fma(ql[1], wy, fma(ql[2], wz, ql[3])));
+          }
         __syncthreads();
         // D += H^T Q over the chunk's beads, 4 per instruction: A[row][k] in
         // lane row + 16 k (row = real or imaginary part of a slot), B[k][d]
@@ -264,15 +283,21 @@ __global__ void __launch_bounds__(P2E_THREADS) k_p2e(int p, const int* ids, cons
           }
         } else {
           const double* hd = reinterpret_cast<const double*>(Hs);
-          for (int kk = 0; kk < nb; kk += 4) {
-            const int bb = kk + lk;
-            double bq = 0.0;
-            if (li < ND) bq = LOCAL ? Qs[bb * ND + li] : Q[(int64_t)(jc + bb) * ND + li];
+          const auto steps = [&](int kk, double c) {
 #pragma unroll
             for (int q = 0; q < TPW; ++q) {
               const int row = (wv + 8 * q) * 16 + li;
-              const double a = hd[2 * (bb * LD + (row >> 1)) + (row & 1)];
-              acc[ps][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, bq, acc[ps][q], 0, 0, 0);
+              const double a = hd[2 * ((kk + lk) * LD + (row >> 1)) + (row & 1)];
+              acc[ps][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, c, acc[ps][q], 0, 0, 0);
+            }
+          };
+          if constexpr (LOCAL) {
+            for (int kk = 0; kk < nb; kk += 4) steps(kk, li < ND ? Qs[(kk + lk) * ND + li] : 0.0);
+          } else {
+#pragma unroll
+            for (int kk = 0; kk < P2E_CHUNK; kk += 4) {
+              if (kk >= nb) break;
+              steps(kk, bq[kk / 4]);
             }
           }
         }
