@@ -376,15 +376,20 @@ static hipError_t matvec_group(rpy_plan_t* P, const rpy::Launch& l, const Work& 
     if (untimed) return f();
     return timed(P, phase, launches, st, f, mc);
   };
-  hipError_t he = step(RPY_PH_PERMUTE, 1, s0, [&] { return rpy::permute_forces(l, forces, nrhs, r0, cn, w.sF); });
+  const bool direct = rpy::direct_fits(P->np, cn, w.NP);
+  hipError_t he = step(RPY_PH_PERMUTE, direct ? 0 : 1, s0, [&] {
+    return direct ? hipSuccess : rpy::permute_forces(l, forces, nrhs, r0, cn, w.sF);
+  });
   // near field on s1, after the permute
   if (he == hipSuccess && fork) {
     he = hipEventRecord(P->ev_fork, s0);
     if (he == hipSuccess) he = hipStreamWaitEvent(s1, P->ev_fork, 0);
   }
   if (he == hipSuccess)
-    he = step(RPY_PH_P2P, 1, s1, [&] { return rpy::run_p2p(ln, P->tiles, P->np, cn, w.sF, w.u, w.NP, mixed); },
-              cn >= rpy::NEAR_MC_RHS ? cn : 0);
+    he = step(RPY_PH_P2P, 1, s1, [&] {
+      return direct ? rpy::run_direct(ln, P->tiles, P->np, cn, forces + r0 * n3, w.NP, mixed)
+                    : rpy::run_p2p(ln, P->tiles, P->np, cn, w.sF, w.u, w.NP, mixed);
+    }, cn >= rpy::NEAR_MC_RHS ? cn : 0);
   if (he == hipSuccess && haveO)
     he = step(RPY_PH_OVERLAP, 1, s1, [&] { return rpy::run_overlap(ln, P->tiles, P->np, cn, w.sF, w.u, w.NP, mixed); });
   if (he == hipSuccess && haveW)
@@ -394,8 +399,10 @@ static hipError_t matvec_group(rpy_plan_t* P, const rpy::Launch& l, const Work& 
     for (int ph : {RPY_PH_P2M, RPY_PH_M2M, RPY_PH_M2L, RPY_PH_P2L, RPY_PH_L2L, RPY_PH_EVAL})
       if (he == hipSuccess && (ph != RPY_PH_P2L || haveX)) he = step(ph, 0, s0, [] { return hipSuccess; });
     if (he == hipSuccess)
-      he = step(RPY_PH_UNPERMUTE, 1, s0,
-                [&] { return rpy::unpermute_velocities(l, w.u, nullptr, r0, cn, velocities); });
+      he = step(RPY_PH_UNPERMUTE, 1, s0, [&] {
+        return direct ? rpy::direct_out(l, P->tiles, P->np, cn, w.NP, velocities + r0 * n3)
+                      : rpy::unpermute_velocities(l, w.u, nullptr, r0, cn, velocities);
+      });
     if (P->timing && !untimed) P->acc.passes += 1;
     return he;
   }
@@ -913,6 +920,8 @@ rpy_status rpy_plan_batched(rpy_plan_t** out, int32_t nsys, const int64_t* count
   if (rc == 0) rc = rpy::make_near_plan(&P->B, P->tiles, P->a, P->wd, &P->np, P->stream, &err);
   if (rc == 0) rc = rpy::make_eval_plan(&P->B, P->p, P->wd, P->eval_mode, &P->ep, P->stream, &err);
   P->no_far = P->B.lists[rpy::LV].len == 0 && P->B.lists[rpy::LX].len == 0 && P->ep.nwbig == 0;
+  rpy::plan_direct(P->tiles, P->no_far && P->B.lists[rpy::LW].len == 0 && P->B.lists[rpy::LO].len == 0,
+                   P->precision == RPY_PREC_MIXED, &P->np);
   if (rc == 0) rc = rpy::make_m2l_map(&P->B, P->stream, &err);
   if (rc == 0) rc = rpy::make_p2e_work(&P->B, P->stream, &err);
   rpy::Lane lane;

@@ -162,12 +162,24 @@ struct NearWork {
   int* parts = nullptr;   // per tile: parts
   int* slot0 = nullptr;   // per tile: first slot
   int* red = nullptr;     // the tiles with several parts
+  int* off = nullptr;     // per tile: first part
   int nslot = 0, nred = 0;
   bool nothing = false;   // the kernel would sum no bead pair
 };
 struct NearPlan {
   NearWork u, w, o;
+  int sub = 0;     // direct launches (run_direct): blocks per part, 0: not taken
+  int direct = 0;  // and blocks
 };
+// Decides on direct launches: the P2P is all that a matvec runs (alone), and
+// takes few blocks.
+void plan_direct(const Tiles& tiles, bool alone, bool mixed, NearPlan* np);
+bool direct_fits(const NearPlan& np, int nrc, const double* part);
+// The P2P from the caller's forces (right-hand side 0 of the group) to slots, and
+// from the slots to the caller's velocities.
+hipError_t run_direct(const Launch& l, const Tiles& tiles, const NearPlan& np, int nrc, const double* F, double* part,
+                      int mixed);
+hipError_t direct_out(const Launch& l, const Tiles& tiles, const NearPlan& np, int nrc, const double* part, double* out);
 int make_near_plan(const Built* B, const Tiles& tiles, double a, int wd, NearPlan* out, hipStream_t s, Error* err);
 void free_near_plan(NearPlan* p);
 int64_t near_part_bytes(const NearPlan& np, int nrn);

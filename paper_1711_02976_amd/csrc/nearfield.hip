@@ -226,9 +226,9 @@ static int make_near_work(const Built* B, const Tiles& tiles, const ChunkFilter&
   // scratch: the counts, two statistics, and the tables' scans
   const size_t ntmp = scan_tmp_ints(nt);
   unsigned long long* stat = nullptr;
-  RPY_HIP(dev_alloc(&stat, 2 * sizeof(unsigned long long) + sizeof(int) * (5 * (size_t)nt + ntmp)));
+  RPY_HIP(dev_alloc(&stat, 2 * sizeof(unsigned long long) + sizeof(int) * (4 * (size_t)nt + ntmp)));
   int* cnt = reinterpret_cast<int*>(stat + 2);
-  int *held = cnt + nt, *off = held + nt, *flag = off + nt, *order = flag + nt, *tmp = order + nt;
+  int *held = cnt + nt, *flag = held + nt, *order = flag + nt, *tmp = order + nt;
   RPY_HIP(hipMemsetAsync(stat, 0, 2 * sizeof(unsigned long long), s));
   k_near_count<<<nblk(nt, 256), 256, 0, s>>>(tiles.t, tiles.box, nt, B->tree, l, f, cnt, stat);
   RPY_HIP(hipGetLastError());
@@ -240,19 +240,20 @@ static int make_near_work(const Built* B, const Tiles& tiles, const ChunkFilter&
   if (hs[1] > cap) {
     // at most total / cap + 1 per tile parts
     const size_t most = (size_t)NEAR_ITEMS + nt;
-    RPY_HIP(dev_alloc(&out->item, sizeof(int4) * most + sizeof(int) * (most + 3 * (size_t)nt)));
+    RPY_HIP(dev_alloc(&out->item, sizeof(int4) * most + sizeof(int) * (most + 4 * (size_t)nt)));
     out->slot = reinterpret_cast<int*>(out->item + most);
     out->parts = out->slot + most;
     out->slot0 = out->parts + nt;
     out->red = out->slot0 + nt;
+    out->off = out->red + nt;
     k_near_parts<<<nblk(nt, 256), 256, 0, s>>>(cnt, nt, (int)std::min<unsigned long long>(cap, 0x7fffffff),
                                                out->parts, held, flag);
     RPY_PAGE(int, page);
-    RPY_HIP(scan_exclusive(out->parts, off, nt, tmp, s, page));
+    RPY_HIP(scan_exclusive(out->parts, out->off, nt, tmp, s, page));
     RPY_HIP(scan_exclusive(held, out->slot0, nt, tmp, s, page + 1));
     RPY_HIP(scan_exclusive(flag, order, nt, tmp, s, page + 2));
-    k_near_fill<<<nblk(nt, 64), 64, 0, s>>>(tiles.t, tiles.box, nt, B->tree, l, f, cnt, off, out->parts, out->slot0,
-                                            order, out->item, out->slot, out->red);
+    k_near_fill<<<nblk(nt, 64), 64, 0, s>>>(tiles.t, tiles.box, nt, B->tree, l, f, cnt, out->off, out->parts,
+                                            out->slot0, order, out->item, out->slot, out->red);
     RPY_HIP(hipGetLastError());
     RPY_HIP(hipStreamSynchronize(s));
     out->n = page[0];
@@ -272,9 +273,10 @@ int make_near_plan(const Built* B, const Tiles& tiles, double a, int wd, NearPla
 
 void free_near_plan(NearPlan* p) {
   for (NearWork* w : {&p->u, &p->w, &p->o}) {
-    if (w->item) dev_free(w->item);  // the other tables follow it
+    dev_free(w->item);  // the other tables follow it
     *w = NearWork{};
   }
+  p->sub = p->direct = 0;
 }
 
 // The part of a tile's source chunks that a block sums: from NearWork's
@@ -371,19 +373,30 @@ __device__ inline double rinv_of(double r2) {
 // The FP32 launch of 4 right-hand sides (the rest of 20 after the
 // matrix-core group) is held to 96 registers, five waves per SIMD instead of
 // four (two registers spill; 192 instead of 196 ms on cube-15M).
-template <int NRC, bool MIXED>
+// DIRECT: plans without a far field whose near field is this kernel alone and
+// takes few blocks (2,000 beads in one leaf), where launches and a block's own
+// length are what counts.  Forces come straight from the caller's array sF
+// ([n][3] per right-hand side) through perm, every block writes its sums to the
+// slot of its own number, and k_direct_out adds them into the caller's array:
+// two launches instead of four.  A part is split further over `sub` blocks, each
+// taking P2P_T / sub sources of every chunk (FP64 form only: the mixed form's
+// FP32 sums stay sums over whole chunks).  2,000 beads, FP64, one right-hand
+// side: 22.7 us whole, 12.1 so.
+template <int NRC, bool MIXED, bool DIRECT = false>
 __global__ void __launch_bounds__(P2P_T, (NRC == 4 && MIXED) ? 5 : 1) k_p2p(const int4* tiles, const int4* item, const int* slots,
                                                Tree t, List U, const double* sx,
                                                const double* sy, const double* sz, const double* sF, int64_t n,
                                                PairK<typename std::conditional<MIXED, float, double>::type> k,
-                                               double S, double c1, double* u, double* part) {
+                                               double S, double c1, double* u, double* part,
+                                               const int* perm = nullptr, int sub = 1) {
   using R = typename std::conditional<MIXED, float, double>::type;
   using V4 = typename std::conditional<MIXED, float4, double4>::type;
   __shared__ alignas(32) R xs[P2P_T];
   __shared__ alignas(32) R ys[P2P_T];
   __shared__ alignas(32) R zs[P2P_T];
   __shared__ alignas(32) R fs[NRC * 3][P2P_T];
-  Part w(item, slots, xcd_run(blockIdx.x, gridDim.x), tiles, U);
+  Part w(item, slots, DIRECT ? blockIdx.x / sub : xcd_run(blockIdx.x, gridDim.x), tiles, U);
+  const int take = DIRECT ? P2P_T / sub : P2P_T, skip = DIRECT ? blockIdx.x % sub * take : 0;
   const int4 tl = tiles[w.tile];
   const int b = tl.x;
   const bool valid = (int)threadIdx.x < tl.z;
@@ -398,16 +411,19 @@ __global__ void __launch_bounds__(P2P_T, (NRC == 4 && MIXED) ? 5 : 1) k_p2p(cons
     const int C = __builtin_amdgcn_readfirstlane(U.ent[w.e]);
     const int j1 = __builtin_amdgcn_readfirstlane(t.end[C]);
     for (int jc = __builtin_amdgcn_readfirstlane(t.begin[C]) + w.c * P2P_T; jc < j1 && w.left > 0; jc += P2P_T, --w.left) {
-      const int ns = min(P2P_T, j1 - jc);
+      const int ns = min(take, j1 - jc - skip);
+      if (DIRECT && ns <= 0) continue;
       // the tile is padded to a multiple of 4 sources with inert ones: zero
       // force at 1e30, where 1/r, A' and B' all evaluate to exactly zero
       const int ns4 = (ns + 3) & ~3;
       __syncthreads();
       if ((int)threadIdx.x < ns) {
-        int j = jc + threadIdx.x;
+        const int j = jc + skip + threadIdx.x;
         xs[threadIdx.x] = (R)((sx[j] - ox) * S); ys[threadIdx.x] = (R)((sy[j] - oy) * S);
         zs[threadIdx.x] = (R)((sz[j] - oz) * S);
-        for (int q = 0; q < NRC * 3; ++q) fs[q][threadIdx.x] = (R)sF[(int64_t)q * n + j];
+        const int64_t pj = DIRECT ? perm[j] : 0;
+        for (int q = 0; q < NRC * 3; ++q)
+          fs[q][threadIdx.x] = (R)(DIRECT ? sF[((q / 3) * n + pj) * 3 + q % 3] : sF[(int64_t)q * n + j]);
       } else if ((int)threadIdx.x < ns4) {
         xs[threadIdx.x] = (R)1e30; ys[threadIdx.x] = (R)1e30; zs[threadIdx.x] = (R)1e30;
         for (int q = 0; q < NRC * 3; ++q) fs[q][threadIdx.x] = (R)0;
@@ -475,10 +491,33 @@ __global__ void __launch_bounds__(P2P_T, (NRC == 4 && MIXED) ? 5 : 1) k_p2p(cons
         for (int c = 0; c < 3; ++c) acc[r][c] += (double)ar[r][c];
     }
   }
+  if (DIRECT) w.slot = blockIdx.x;
   const Sums o(w, tl, 3 * NRC, n, u, part);
   if (valid)
     for (int r = 0; r < NRC; ++r)
       for (int c = 0; c < 3; ++c) *o.at(3 * r + c, threadIdx.x) = c1 * acc[r][c];
+}
+
+// The direct sums into the caller's array: the slots of tile i's parts (cnt[i]
+// from off[i] on; without tables, part i), sub of each, in order.  One block per
+// tile and component row: DO_G waves' worth of slots side by side, then their sum.
+constexpr int DO_G = 4;
+__global__ void __launch_bounds__(P2P_T * DO_G) k_direct_out(const int4* tiles, const int* off, const int* cnt, int sub,
+                                                             const double* __restrict__ part, int nq, int64_t n,
+                                                             const int* perm, double* out) {
+  const int i = blockIdx.x, q = blockIdx.y, x = threadIdx.x % P2P_T, g = threadIdx.x / P2P_T;
+  const int4 tl = tiles[i];
+  const int s0 = (off ? off[i] : i) * sub, k = (off ? cnt[i] : 1) * sub;
+  const double* p = part + ((int64_t)s0 * nq + q) * P2P_T + x;
+  __shared__ double sum[DO_G][P2P_T];
+  double s = 0.0;
+  if (x < tl.z)
+#pragma unroll 8
+    for (int j = g; j < k; j += DO_G) s += p[(int64_t)j * nq * P2P_T];
+  sum[g][x] = s;
+  __syncthreads();
+  if (g == 0 && x < tl.z)
+    out[((q / 3) * n + perm[tl.y + x]) * 3 + q % 3] = (sum[0][x] + sum[1][x]) + (sum[2][x] + sum[3][x]);
 }
 
 // ------------------------------------------- P2P on the matrix cores ----
@@ -988,6 +1027,50 @@ hipError_t run_p2p(const Launch& l, const Tiles& tiles, const NearPlan& np, int 
   return near_reduce(l, tiles, np.u, g, 3 * nrc, part, u, 0);
 }
 
+// Blocks of a direct launch: a chip's worth, 16 waves per CU, at most.
+constexpr int DIRECT_BLOCKS = 2048;
+void plan_direct(const Tiles& tiles, bool alone, bool mixed, NearPlan* np) {
+  const int items = np->u.item ? np->u.n : tiles.n;
+  np->sub = 0;
+  if (!alone || items == 0 || items > DIRECT_BLOCKS) return;
+  for (np->sub = mixed ? 1 : 4; np->sub * items > DIRECT_BLOCKS;) np->sub /= 2;
+  np->direct = np->sub * items;
+}
+
+bool direct_fits(const NearPlan& np, int nrc, const double* part) { return np.sub > 0 && part && nrc <= NEAR_VEC_RHS; }
+
+hipError_t run_direct(const Launch& l, const Tiles& tiles, const NearPlan& np, int nrc, const double* F, double* part,
+                      int mixed) {
+  const Built* B = l.B;
+  const PairLaunch q = pair_launch(l.a, l.eta);
+#define DIRECT_CASE(NR)                                                                                              \
+  case NR:                                                                                                           \
+    if (mixed)                                                                                                       \
+      k_p2p<NR, true, true><<<np.direct, P2P_T, 0, l.s>>>(tiles.t, np.u.item, np.u.slot, B->tree, B->lists[LU], B->sx,   \
+                                                          B->sy, B->sz, F, B->n, q.kf, q.S, q.c1S, nullptr, part,      \
+                                                          B->perm, np.sub);                                            \
+    else                                                                                                             \
+      k_p2p<NR, false, true><<<np.direct, P2P_T, 0, l.s>>>(tiles.t, np.u.item, np.u.slot, B->tree, B->lists[LU], B->sx,  \
+                                                           B->sy, B->sz, F, B->n, q.kd, q.S, q.c1S, nullptr, part,     \
+                                                           B->perm, np.sub);                                           \
+    break;
+  switch (nrc) {
+    DIRECT_CASE(1)
+    DIRECT_CASE(2)
+    DIRECT_CASE(4)
+    DIRECT_CASE(8)
+    default: return hipErrorInvalidValue;
+  }
+#undef DIRECT_CASE
+  return hipGetLastError();
+}
+
+hipError_t direct_out(const Launch& l, const Tiles& tiles, const NearPlan& np, int nrc, const double* part, double* out) {
+  k_direct_out<<<dim3(tiles.n, 3 * nrc), P2P_T * DO_G, 0, l.s>>>(tiles.t, np.u.off, np.u.parts, np.sub, part, 3 * nrc,
+                                                                 l.B->n, l.B->perm, out);
+  return hipGetLastError();
+}
+
 // The overlap correction: FP32 pair arithmetic (the factored differences)
 // with FP64 sums per staged chunk in the mixed form, FP64 otherwise.
 hipError_t run_overlap(const Launch& l, const Tiles& tiles, const NearPlan& np, int nrc, const double* sF, double* u,
@@ -1057,10 +1140,11 @@ hipError_t run_wdirect(const Launch& l, const Tiles& tiles, const NearPlan& np, 
 }
 
 // Bytes of the partial-sum slots for near-field groups of nrn right-hand
-// sides (0: no tile is split).
+// sides (0: no tile is split and no direct launch taken).
 int64_t near_part_bytes(const NearPlan& np, int nrn) {
   const int64_t vec = std::max(np.w.nslot, np.o.nslot);  // launches of at most NEAR_VEC_RHS
-  const int64_t rows = std::max((int64_t)np.u.nslot * nrn, vec * std::min(nrn, NEAR_VEC_RHS));
+  const int64_t rows = std::max((int64_t)np.u.nslot * nrn,
+                                std::max(vec, (int64_t)np.direct) * std::min(nrn, NEAR_VEC_RHS));
   return rows * 3 * P2P_T * (int64_t)sizeof(double);
 }
 

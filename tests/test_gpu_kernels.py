@@ -246,3 +246,33 @@ def test_plans_share_kept_memory():
     for t in ts:
         t.join()
     assert not bad
+
+
+# Plans without a far field in two launches, forces read and velocities written
+# in the caller's order: systems of 0 to 1,300 beads side by side, every group of
+# right-hand sides, the velocities written over the forces, and many small
+# systems (one part per block, then more blocks than are taken at all).
+@pytest.mark.parametrize("counts,nrhs", [([5, 0, 130, 1300], 1), ([64, 700], 7), ([1, 129, 33], 11),
+                                         ([7] * 1500, 2), ([3] * 2500, 1)])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_direct_plans(orc, counts, nrhs, precision):
+    import paper_1711_02976_amd as R
+    from gpu_common import to_dev
+    n = sum(counts)
+    w = W.uniform_cube(n, 1.0, 0.02, nrhs=nrhs, seed=390 + n)
+    log(f"direct plans {len(counts)} systems n={n} nrhs={nrhs} {precision}")
+    P = R.Plan(to_dev(w.pos), w.a, w.eta, 1e-6, leaf_size=10_000, counts=counts, precision=precision)
+    try:
+        F = to_dev(w.forces)
+        u = P.matvec(F).cpu().numpy()
+        R.rpy_matvec(P.handle, nrhs, F.data_ptr(), F.data_ptr())
+        over = F.cpu().numpy()
+    finally:
+        P.free()
+    assert np.array_equal(over, u)
+    ref, at = np.empty_like(u), 0
+    for c in counts:
+        if c:
+            ref[:, at:at + c] = orc.rpy_direct(w.pos[at:at + c], w.forces[:, at:at + c], w.a, w.eta)
+        at += c
+    assert orc.rel_l2(u, ref) <= (1e-12 if precision == "fp64" else 5e-7)
