@@ -80,8 +80,17 @@ __global__ void __launch_bounds__(256) k_leaf_q(const int* leaves, Tree t, const
 //
 // K generation steps per wave and pass, P passes: S = 8 K slots per pass,
 // G = S / 64 slot groups, NB = 8 / G bead subsets (partial sums per slot).
+//
+// The charges of S->M are loaded once per chunk, before the harmonics are
+// generated, and serve all passes: as matrix-core operands in registers, or
+// with one right-hand side in scalar registers.  Loaded step by step, each
+// waited for memory (15M beads, 20 right-hand sides, p = 16: 57.5 ms, 39.3 now,
+// of 12 for the matrix-core products and 9 for the harmonics; 8M beads on a
+// sphere, one right-hand side, p = 21: 3.05 and 2.6).  Two blocks share a CU
+// (LDS), so the registers are held to 128 (p = 27 S->M: 168 and 157 us, spills
+// included), but for S->L above p = 21.
 template <int ND, bool LOCAL, int K, int P>
-__global__ void __launch_bounds__(P2E_THREADS) k_p2e(int p, const int* ids, const int4* __restrict__ xwork,
+__global__ void __launch_bounds__(P2E_THREADS, LOCAL && P > 4 ? 1 : 4) k_p2e(int p, const int* ids, const int4* __restrict__ xwork,
                                                      const int2* __restrict__ xchunks, Tree t, List X, const double* sx,
                                                      const double* sy, const double* sz, const double* __restrict__ Q,
                                                      const P2EPass* __restrict__ desc,
@@ -181,8 +190,15 @@ __global__ void __launch_bounds__(P2E_THREADS) k_p2e(int p, const int* ids, cons
       if constexpr (!VEC && !LOCAL)
 #pragma unroll
         for (int q = 0; q < P2E_CHUNK / 4; ++q) bq[q] = li < ND ? Q[(int64_t)(jc + 4 * q + lk) * ND + li] : 0.0;
-      double ql[LOCAL && !VEC ? 4 : 1];  // S->L: one bead's and right-hand side's charges, on their way to Qs
-      if constexpr (LOCAL && !VEC)
+      // S->M with one right-hand side: the wave's beads' charges, in scalar registers
+      double qs[VEC && !LOCAL ? BPW : 1][ND];
+      if constexpr (VEC && !LOCAL)
+#pragma unroll
+        for (int i = 0; i < BPW; ++i)
+#pragma unroll
+          for (int dd = 0; dd < ND; ++dd) qs[i][dd] = Q[(int64_t)(jc + sub * BPW + i) * ND + dd];
+      double ql[LOCAL ? 4 : 1];  // S->L: one bead's and right-hand side's charges, on their way to Qs
+      if constexpr (LOCAL)
         if ((int)threadIdx.x < P2E_CHUNK * NRC)
 #pragma unroll
           for (int q = 0; q < 4; ++q) ql[q] = Q[(int64_t)jc * ND + 4 * (int)threadIdx.x + q];
@@ -194,16 +210,6 @@ __global__ void __launch_bounds__(P2E_THREADS) k_p2e(int p, const int* ids, cons
         uint64_t ml = ((uint64_t)d.mhi << 32) | d.mlo;
         double2* hw = Hs + lane * LD + wv * K;  // this lane's row, this wave's slots
         __syncthreads();                        // the previous accumulation is done with Hs
-        if (LOCAL && VEC && ps == 0 && (int)threadIdx.x < P2E_CHUNK * NRC) {
-          const int bb = threadIdx.x % P2E_CHUNK, r = threadIdx.x / P2E_CHUNK;
-          const double* q = Q + (int64_t)(jc + bb) * ND + 4 * r;
-          const double q0 = q[0], q1 = q[1], q2 = q[2];
-          double* o = Qs + bb * ND + 4 * r;
-          o[0] = q0;
-          o[1] = q1;
-          o[2] = q2;
-          o[3] = fma(q0, wx, fma(q1, wy, fma(q2, wz, q[3])));
-        }
         // conj(h) obeys the same recurrence (real coefficients): generate it directly
         int k = 0;
         while (k < d.nvalid) {
@@ -252,7 +258,7 @@ __global__ void __launch_bounds__(P2E_THREADS) k_p2e(int p, const int* ids, cons
           }
         }
         for (; k < K; ++k) hw[k] = make_double2(0.0, 0.0);
-        if constexpr (LOCAL && !VEC)
+        if constexpr (LOCAL)
           if (ps == 0 && (int)threadIdx.x < P2E_CHUNK * NRC) {
             double* o = Qs + 4 * (int)threadIdx.x;  // bead threadIdx.x / NRC, right-hand side threadIdx.x % NRC
             o[0] = ql[0];
@@ -271,11 +277,12 @@ __global__ void __launch_bounds__(P2E_THREADS) k_p2e(int p, const int* ids, cons
 #pragma unroll
             for (int i = 0; i < BPW; ++i) {
               const int bb = sub * BPW + i;
-              const double* q = LOCAL ? Qs + bb * ND : Q + (int64_t)(jc + bb) * ND;
               const double2 h = Hs[bb * LD + slot];
 #pragma unroll
               for (int dd = 0; dd < ND; ++dd) {
-                const double qd = q[dd];
+                double qd;
+                if constexpr (LOCAL) qd = Qs[bb * ND + dd];
+                else qd = qs[i][dd];
                 vacc[ps][dd].x = fma(qd, h.x, vacc[ps][dd].x);
                 vacc[ps][dd].y = fma(qd, h.y, vacc[ps][dd].y);
               }
