@@ -340,28 +340,41 @@ struct PairK {
 // Power of two S with 2aS in [1, 2).
 static double pair_scale(double a) { return std::ldexp(1.0, -std::ilogb(2.0 * a)); }
 
+// The FP64 kernels' positions are scaled by 2S instead: with r' = 2r the
+// reciprocal square root's Newton step gives 1/r = 2/r' one operation sooner
+// (rinv_of).  1/r and A' stay as they are; B', which multiplies d' d'^T = 4 d d^T,
+// is a quarter.  All of it is exact scaling by powers of two.  With the wave's
+// test for overlaps on FP32 roundings, the FP64 P2P of one right-hand side takes
+// 28 FP64 operations and roots per pair (30 before; 1M beads in leaves of 244:
+// 7.18 ms and 6.96 now, at its issue rate).
+template <class R>
+constexpr double PAIR_ZOOM = std::is_same<R, double>::value ? 2.0 : 1.0;
+template <class R>
+constexpr R B_ONE = (R)(1.0 / (PAIR_ZOOM<R> * PAIR_ZOOM<R>));
+
 // Constants for the scaled radius as = a S.
 template <class R>
 static PairK<R> pair_const(double as) {
-  const double oc = 4.0 / (3.0 * as);
-  return PairK<R>{(R)(2.0 * as * as / 3.0), (R)(2.0 * as * as), (R)(4.0 * as * as), (R)oc,
-                  (R)(oc * 9.0 / (32.0 * as)), (R)(oc * 3.0 / (32.0 * as)), (R)1e-30, (R)(0.5 / as)};
+  const double oc = 4.0 / (3.0 * as), z2 = PAIR_ZOOM<R> * PAIR_ZOOM<R>;
+  return PairK<R>{(R)(2.0 * as * as / 3.0), (R)(2.0 * as * as / z2), (R)(4.0 * as * as * z2), (R)oc,
+                  (R)(oc * 9.0 / (32.0 * as) / z2), (R)(oc * 3.0 / (32.0 * as) / z2), (R)(1e-30 * z2), (R)(0.5 / as)};
 }
 
+// 1/r from (PAIR_ZOOM r)^2.
 __device__ inline float rinv_of(float r2) { return __builtin_amdgcn_rsqf(r2); }
-// single-precision estimate refined by one Newton step (relative error
-// below 2^-44); r2 >= 1e-30 here (a normal FP32 number), so the estimate is
-// finite
+// single-precision estimate w of 1/r' refined by one Newton step (relative error
+// below 2^-44), 2/r' = w (3 - r'^2 w^2); r2 >= 4e-30 here (a normal FP32 number),
+// so the estimate is finite
 __device__ inline double rinv_of(double r2) {
-  double y = (double)__builtin_amdgcn_rsqf((float)r2);
-  return y * fma(-0.5 * r2, y * y, 1.5);
+  const double w = (double)__builtin_amdgcn_rsqf((float)r2);
+  return w * fma(-r2, w * w, 3.0);
 }
 
 // --------------------------------------------------------------- P2P -----
 // The overlap formula is evaluated only when some lane of the wave has a
 // source closer than 2a (a wave-uniform branch), since such pairs are rare
 // apart from each target's own bead.  For r = 0 (the bead itself, or a
-// coincident bead) r^2 carries a floor of 1e-30 in the scaled units (added
+// coincident bead) r^2 carries a floor of 1e-30 in the scaled units (r2min) (added
 // in the first FMA) before the reciprocal square root: the far values are
 // then finite and discarded, and the overlap values give the r -> 0 limit
 // A' = c0/c1, B' d = 0.  Since 2a >= 1 in these units, the floor changes
@@ -449,10 +462,12 @@ __global__ void __launch_bounds__(P2P_T, (NRC == 4 && MIXED) ? 5 : 1) k_p2p(cons
           rinv[q] = rinv_of(r2[q]);
           const R ri2 = rinv[q] * rinv[q], ri3 = ri2 * rinv[q];
           A[q] = fma(k.a3, ri3, rinv[q]);
-          B[q] = ri3 * fma(-k.a2, ri2, (R)1);
+          B[q] = ri3 * fma(-k.a2, ri2, B_ONE<R>);
         }
-        const R r2lo = min(min(r2[0], r2[1]), min(r2[2], r2[3]));
-        if (__builtin_expect(__any(r2lo < k.four_a2), 0)) {
+        // in FP32 also in the FP64 form: r2 < (2a)^2 implies the same, or
+        // equality, of their roundings, and the exact test follows
+        const float r2lo = fminf(fminf((float)r2[0], (float)r2[1]), fminf((float)r2[2], (float)r2[3]));
+        if (__builtin_expect(__any(MIXED ? r2lo < (float)k.four_a2 : r2lo <= (float)k.four_a2), 0)) {
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             const bool ov = r2[q] < k.four_a2;
@@ -649,7 +664,7 @@ __global__ void __launch_bounds__(64 * MF_W) k_p2p_mfma(const int4* tiles, const
             const R rinv = rinv_of(r2);
             const R ri2 = rinv * rinv, ri3 = ri2 * rinv;
             R A = fma(k.a3, ri3, rinv);
-            R B = ri3 * fma(-k.a2, ri2, (R)1);
+            R B = ri3 * fma(-k.a2, ri2, B_ONE<R>);
             if (__builtin_expect(__any(r2 < k.four_a2), 0)) {
               const bool ov = r2 < k.four_a2;
               const R Ao = fma(-k.ock9, (r2 - k.r2min) * rinv, k.oc), Bo = k.ob * rinv;
@@ -784,7 +799,7 @@ __global__ void __launch_bounds__(P2P_T) k_wdirect(const int4* tiles, const int4
         const R r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, k.r2min)));
         const R rinv = rinv_of(r2);
         const R ri2 = rinv * rinv, ri3 = ri2 * rinv;
-        const R A = fma(k.a3, ri3, rinv), B = ri3 * fma(-k.a2, ri2, (R)1);
+        const R A = fma(k.a3, ri3, rinv), B = ri3 * fma(-k.a2, ri2, B_ONE<R>);
 #pragma unroll
         for (int r = 0; r < NRC; ++r) {
           const R fx = fs[3 * r][s], fy = fs[3 * r + 1][s], fz = fs[3 * r + 2][s];
@@ -917,7 +932,7 @@ __global__ void __launch_bounds__(P2P_T) k_overlap(const int4* tiles, const doub
             A = ov ? -k.a3 * wt * fma(fma((R)9, rho, (R)2), rho, (R)1) : (R)0;
             B = ov ? k.a2 * wt * (op * op) * ri2 : (R)0;
           } else {  // the two branches and their difference (fewer operations)
-            const R Af = fma(k.a3, ri3, rinv), Bf = ri3 * fma(-k.a2, ri2, (R)1);
+            const R Af = fma(k.a3, ri3, rinv), Bf = ri3 * fma(-k.a2, ri2, B_ONE<R>);
             const R Ao = fma(-k.ock9, (r2 - k.r2min) * rinv, k.oc), Bo = k.ob * rinv;
             A = ov ? Ao - Af : (R)0;
             B = ov ? Bo - Bf : (R)0;
@@ -945,11 +960,12 @@ __global__ void __launch_bounds__(P2P_T) k_overlap(const int4* tiles, const doub
       }
 }
 
-// Launch arguments shared by the pair kernels: the scale S (2aS in [1, 2)),
+// Launch arguments shared by the pair kernels: the scale S (2aS in [1, 2)) and the
+// FP64 kernels' 2S,
 // the constants of the scaled radius in both precisions and the prefactor
 // c1 S = S / (8 pi eta) that undoes the scaling of the sums.
 struct PairLaunch {
-  double S, c1S;
+  double S, Sd, c1S;
   PairK<float> kf;
   PairK<double> kd;
 };
@@ -957,6 +973,7 @@ struct PairLaunch {
 static PairLaunch pair_launch(double a, double eta) {
   PairLaunch q;
   q.S = pair_scale(a);
+  q.Sd = PAIR_ZOOM<double> * q.S;
   q.c1S = q.S / (8.0 * PI * eta);
   q.kf = pair_const<float>(a * q.S);
   q.kd = pair_const<double>(a * q.S);
@@ -994,7 +1011,7 @@ hipError_t run_p2p(const Launch& l, const Tiles& tiles, const NearPlan& np, int 
                                                    B->sz, sF, B->n, q.kf, q.S, q.c1S, u, part);                    \
     else                                                                                                           \
       k_p2p<NR, false><<<g.blocks, P2P_T, 0, l.s>>>(tiles.t, g.item, g.slots, B->tree, B->lists[LU], B->sx, B->sy,   \
-                                                    B->sz, sF, B->n, q.kd, q.S, q.c1S, u, part);                   \
+                                                    B->sz, sF, B->n, q.kd, q.Sd, q.c1S, u, part);                   \
     break;
   switch (nrc) {
     P2P_CASE(1)
@@ -1007,14 +1024,14 @@ hipError_t run_p2p(const Launch& l, const Tiles& tiles, const NearPlan& np, int 
                                                              B->sy, B->sz, sF, B->n, q.kf, q.S, q.c1S, u, part);
       else
         k_p2p_mfma<false, 0><<<g.blocks, 64 * MF_W, 0, l.s>>>(tiles.t, g.item, g.slots, B->tree, B->lists[LU], B->sx,
-                                                              B->sy, B->sz, sF, B->n, q.kd, q.S, q.c1S, u, part);
+                                                              B->sy, B->sz, sF, B->n, q.kd, q.Sd, q.c1S, u, part);
       break;
     // 16 + XR: the FP64 form only
 #define MF_CASE(XR)                                                                                                \
   case MF_R + XR:                                                                                                  \
     if (mixed) return hipErrorInvalidValue;                                                                        \
     k_p2p_mfma<false, XR><<<g.blocks, 64 * MF_W, 0, l.s>>>(tiles.t, g.item, g.slots, B->tree, B->lists[LU], B->sx,   \
-                                                           B->sy, B->sz, sF, B->n, q.kd, q.S, q.c1S, u, part);     \
+                                                           B->sy, B->sz, sF, B->n, q.kd, q.Sd, q.c1S, u, part);     \
     break;
     MF_CASE(1)
     MF_CASE(2)
@@ -1051,7 +1068,7 @@ hipError_t run_direct(const Launch& l, const Tiles& tiles, const NearPlan& np, i
                                                           B->perm, np.sub);                                            \
     else                                                                                                             \
       k_p2p<NR, false, true><<<np.direct, P2P_T, 0, l.s>>>(tiles.t, np.u.item, np.u.slot, B->tree, B->lists[LU], B->sx,  \
-                                                           B->sy, B->sz, F, B->n, q.kd, q.S, q.c1S, nullptr, part,     \
+                                                           B->sy, B->sz, F, B->n, q.kd, q.Sd, q.c1S, nullptr, part,     \
                                                            B->perm, np.sub);                                           \
     break;
   switch (nrc) {
@@ -1092,7 +1109,7 @@ hipError_t run_overlap(const Launch& l, const Tiles& tiles, const NearPlan& np, 
                                                        f, B->sx, B->sy, B->sz, sF, B->n, q.kf, q.S, q.c1S, u, part); \
     else                                                                                                            \
       k_overlap<NR, false><<<g.blocks, P2P_T, 0, l.s>>>(tiles.t, tiles.box, g.item, g.slots, B->tree, B->lists[LO], \
-                                                        f, B->sx, B->sy, B->sz, sF, B->n, q.kd, q.S, q.c1S, u, part); \
+                                                        f, B->sx, B->sy, B->sz, sF, B->n, q.kd, q.Sd, q.c1S, u, part); \
     break;
   switch (nrc) {
     OV_CASE(1)
@@ -1126,7 +1143,7 @@ hipError_t run_wdirect(const Launch& l, const Tiles& tiles, const NearPlan& np, 
                                                        B->sy, B->sz, sF, B->n, q.kf, q.S, q.c1S, u, part);          \
     else                                                                                                            \
       k_wdirect<NR, false><<<g.blocks, P2P_T, 0, l.s>>>(tiles.t, g.item, g.slots, B->tree, B->lists[LW], f, B->sx,  \
-                                                        B->sy, B->sz, sF, B->n, q.kd, q.S, q.c1S, u, part);         \
+                                                        B->sy, B->sz, sF, B->n, q.kd, q.Sd, q.c1S, u, part);         \
     break;
   switch (nrc) {
     WD_CASE(1)
