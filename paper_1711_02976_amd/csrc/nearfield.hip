@@ -839,7 +839,10 @@ __global__ void __launch_bounds__(P2P_T) k_wdirect(const int4* tiles, const int4
 // branches (fewer operations; the cancellation costs digits FP64 can spare).
 // Most pairs of two such leaves are farther apart than 2a, so the staged
 // sources are cut into groups of OV_G with bounding boxes, and a wave skips a
-// group whose box is 2a or more from every one of the wave's targets.
+// group whose box is 2a or more from every one of the wave's targets.  The lanes
+// first test all of a chunk's groups at once against the box of the wave's
+// targets (4M clustered beads, 4 right-hand sides, of all groups two in five are
+// out of reach: 84.7 ms and 79.8, at the issue rate of the pairs in reach).
 constexpr int OV_G = 4;
 
 template <int NRC, bool MIXED>
@@ -870,6 +873,18 @@ __global__ void __launch_bounds__(P2P_T) k_overlap(const int4* tiles, const doub
   const R skip2 = k.four_a2 * (R)(1.0 + 1e-4);
   double acc[NRC][3];
   for (int r = 0; r < NRC; ++r) acc[r][0] = acc[r][1] = acc[r][2] = 0.0;
+  R wb[6];  // the wave's targets' bounding box (idle lanes repeat a target)
+  {
+    const R p[3] = {xi, yi, zi};
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      wb[q] = wb[3 + q] = p[q];
+      for (int d = 1; d < 64; d <<= 1) {
+        wb[q] = min(wb[q], __shfl_xor(wb[q], d));
+        wb[3 + q] = max(wb[3 + q], __shfl_xor(wb[3 + q], d));
+      }
+    }
+  }
   double tb[6];  // the tile's bounding box
   for (int q = 0; q < 6; ++q) tb[q] = tbox[6 * (int64_t)w.tile + q];
   for (; w.e < e1 && w.left > 0; ++w.e, w.c = 0) {
@@ -908,7 +923,18 @@ __global__ void __launch_bounds__(P2P_T) k_overlap(const int4* tiles, const doub
       __syncthreads();
       R ar[NRC][3];
       for (int r = 0; r < NRC; ++r) ar[r][0] = ar[r][1] = ar[r][2] = (R)0;
-      for (int g = 0; g < (wlive ? ng : 0); ++g) {
+      // the groups whose boxes come within 2a of the wave's targets' box, one per
+      // lane (at most 32 of them)
+      unsigned long long near = 0;
+      {
+        const int g = (threadIdx.x & 63) < (unsigned)ng ? threadIdx.x & 63 : 0;
+        const R gx = max((R)0, max(gbox[g][0] - wb[3], wb[0] - gbox[g][3]));
+        const R gy = max((R)0, max(gbox[g][1] - wb[4], wb[1] - gbox[g][4]));
+        const R gz = max((R)0, max(gbox[g][2] - wb[5], wb[2] - gbox[g][5]));
+        near = __ballot((int)(threadIdx.x & 63) < (wlive ? ng : 0) && fma(gx, gx, fma(gy, gy, gz * gz)) < skip2);
+      }
+      for (; near; near &= near - 1) {
+        const int g = __builtin_ctzll(near);
         // distance from this lane's target to the group's box; the wave
         // skips the group when no lane comes within 2a of it
         const R gx = max((R)0, max(gbox[g][0] - xi, xi - gbox[g][3]));
