@@ -115,6 +115,20 @@ __device__ inline void put_row(typename Cx<R>::T* col, int mp, int ld, R yr, R y
   col[mp * ld] = o;
 }
 
+// A row of K table entries by scalar loads, issued before the previous row's
+// multiply-adds: in the FP64 form, whose tables (28 KB at p = 16) outgrow the
+// scalar cache, one load wait per two rows is covered that way (p = 16,
+// 778k beads, 20 right-hand sides: 59.9 ms with a row pair loaded and then used,
+// 57.9 now; 100k beads: 389 and 373 us).  A wait before each issue, which leaves
+// none open, costs more in scalar instructions than it gains.
+template <int K, class R>
+__device__ inline void load_row(const R* __restrict__ a, R* r) {
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int j = 0; j < K; ++j) r[j] = a[j];
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 // col[mp] = e^{mp} (SR Re(R x)_mp + i SI Im(R x)_mp) for mp = 0..N, with
 // e = (bx, by) when PH (else 1); SR = SI = 1 gives R, SR = (-1)^N and
 // SI = -(-1)^N give the inverse rotation S R S on the same table.
@@ -123,6 +137,24 @@ __device__ inline void rot_apply(const R* __restrict__ A, const R* xr, const R* 
                                  typename Cx<R>::T* col, int ld) {
   constexpr int K = N + 1;
   R fr = 1, fi = 0;
+  if constexpr (sizeof(R) == 8) {
+    R ra[K], rb[K], yr, yi;
+    load_row<K, R>(A, ra);
+#pragma unroll 1
+    for (int mp = 0; mp < K - 1; mp += 2) {
+      load_row<K, R>(A + (mp + 1) * K, rb);
+      rot_row<N, (N & 1), R>(ra, xr, xi, yr, yi);
+      put_row<PH, SR, SI, R>(col, mp, ld, yr, yi, fr, fi, bx, by);
+      load_row<K, R>(A + min(mp + 2, K - 1) * K, ra);
+      rot_row<N, ((N + 1) & 1), R>(rb, xr, xi, yr, yi);
+      put_row<PH, SR, SI, R>(col, mp + 1, ld, yr, yi, fr, fi, bx, by);
+    }
+    if (K & 1) {
+      rot_row<N, (N & 1), R>(ra, xr, xi, yr, yi);
+      put_row<PH, SR, SI, R>(col, N, ld, yr, yi, fr, fi, bx, by);
+    }
+    return;
+  }
 #pragma unroll 1
   for (int mp = 0; mp < K - 1; mp += 2) {
     R yr, yi;
@@ -194,9 +226,7 @@ __device__ void ztrans(int l, int c, int ld, const ColData<R>& cd, const R* __re
   }
   R so = 1;
   for (int j = 0; j <= l; ++j) so *= ri;
-#pragma unroll 2
-  for (int kk = 0; kk < KK; ++kk) {
-    const R* h = H + kk * KK;
+  const auto row = [&](int kk, const R* h) {
     R ar = 0, ai = 0;
 #pragma unroll
     for (int j = 0; j < KK; ++j) {
@@ -209,7 +239,22 @@ __device__ void ztrans(int l, int c, int ld, const ColData<R>& cd, const R* __re
     o.y = ai * so;
     X[(k * (k + 1) / 2 + l) * ld + c] = o;
     so *= ri;
+  };
+  if constexpr (sizeof(R) == 8) {
+    R ha[KK], hb[KK];
+    load_row<KK, R>(H, ha);
+#pragma unroll 1
+    for (int kk = 0; kk < KK - 1; kk += 2) {
+      load_row<KK, R>(H + (kk + 1) * KK, hb);
+      row(kk, ha);
+      load_row<KK, R>(H + min(kk + 2, KK - 1) * KK, ha);
+      row(kk + 1, hb);
+    }
+    if (KK & 1) row(KK - 1, ha);
+    return;
   }
+#pragma unroll 2
+  for (int kk = 0; kk < KK; ++kk) row(kk, H + kk * KK);
 }
 
 // Phase 3 for degree N of column c: R, Phi(theta), S R S, Phi(phi - pi/2).
