@@ -401,8 +401,8 @@ def run(args):
 PMC_KERNELS = {  # rocprofv3 kernel-name pattern -> (phase, precision form, source file)
     r"rpy::k_p2p_mfma<true": ("p2p_mc", "mixed", "nearfield.hip"),
     r"rpy::k_p2p_mfma<false": ("p2p_mc", "fp64", "nearfield.hip"),
-    r"rpy::k_p2p<\d+, true>": ("p2p", "mixed", "nearfield.hip"),
-    r"rpy::k_p2p<\d+, false>": ("p2p", "fp64", "nearfield.hip"),
+    r"rpy::k_p2p<\d+, true, false>": ("p2p", "mixed", "nearfield.hip"),
+    r"rpy::k_p2p<\d+, false, false>": ("p2p", "fp64", "nearfield.hip"),
     r"rpy::k_m2l_rot<\d+, float": ("m2l", "mixed", "m2l_rot.hip"),
     r"rpy::k_m2l_rot<\d+, double": ("m2l", "fp64", "m2l_rot.hip"),
 }

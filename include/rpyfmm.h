@@ -305,7 +305,9 @@ rpy_status rpy_plan_inject_error(rpy_plan_t* plan, int32_t phase);
 
 /* Release a plan and its device memory; NULL is a no-op.  Waits for the
  * plan's streams first.  The host images of the translation tables stay
- * cached per expansion order for the life of the process. */
+ * cached per expansion order for the life of the process; device blocks of up
+ * to 64 MB, at most 256 MB per device, are kept for later plans and given back
+ * when an allocation fails or 16 plans did not use them. */
 void rpy_plan_free(rpy_plan_t* plan);
 
 const char* rpy_status_string(rpy_status s);

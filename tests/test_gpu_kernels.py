@@ -276,3 +276,34 @@ def test_direct_plans(orc, counts, nrhs, precision):
             ref[:, at:at + c] = orc.rpy_direct(w.pos[at:at + c], w.forces[:, at:at + c], w.a, w.eta)
         at += c
     assert orc.rel_l2(u, ref) <= (1e-12 if precision == "fp64" else 5e-7)
+
+
+# A captured matvec replayed with eager work in between equals the eager result
+# each time: direct launches, and split phases of a small adaptive tree.
+@pytest.mark.parametrize("n,leaf,nrhs", [(700, 1000, 2), (4000, 300, 3)])
+def test_captured_matvec(n, leaf, nrhs):
+    import paper_1711_02976_amd as R
+    import torch
+    from gpu_common import to_dev
+    w = W.clustered(n, 4, 12.0, 0.6, 0.05, nrhs, seed=395)
+    log(f"captured matvec n={n} leaf={leaf} nrhs={nrhs}")
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        P = R.Plan(to_dev(w.pos), w.a, w.eta, 1e-6, leaf_size=leaf, stream=st.cuda_stream)
+        F = to_dev(w.forces)
+        ref = P.matvec(F).clone()
+    torch.cuda.synchronize()
+    try:
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=st):
+            out = P.matvec(F)
+        for it in range(4):
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, ref)
+            out.zero_()
+            with torch.cuda.stream(st):
+                assert torch.equal(P.matvec(F), ref)
+            torch.cuda.synchronize()
+    finally:
+        P.free()
