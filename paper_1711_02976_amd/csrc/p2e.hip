@@ -421,7 +421,7 @@ hipError_t launch_p2e(const Launch& l, const P2ESched& sc, const P2EWork* w, con
                                         l.tb->p2e_dk, E, part);
   he = hipGetLastError();
   if (he != hipSuccess || !items || w->nred == 0) return he;
-  k_p2e_reduce<ND, LOCAL><<<dim3(w->nred, ND / 4), 256, 0, l.s>>>(l.p, w->red, part, l.tb->rscale, E);
+  k_p2e_reduce<ND, LOCAL><<<dim3(w->nred, (ND * ncoef(l.p) + 255) / 256), 256, 0, l.s>>>(l.p, w->red, part, l.tb->rscale, E);
   return hipGetLastError();
 }
 
