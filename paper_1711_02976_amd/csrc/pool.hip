@@ -150,7 +150,8 @@ void dev_free(void* p) {
       P.live.erase(it);
     }
   }
-  if (b.first == 0 || b.first > POOL_BLOCK || t_nokeep) {
+  // (a block of another device than the current one, which the caller waited for)
+  if (b.first == 0 || b.first > POOL_BLOCK || t_nokeep || b.second != current_device()) {
     (void)hipFree(p);
     return;
   }
