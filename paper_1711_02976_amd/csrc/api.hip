@@ -228,8 +228,7 @@ struct rpy_plan_s {
 // Bytes of each Work array for nrc right-hand sides per far-field pass and
 // nrn per near-field group (sF and u hold a group); split: with the
 // partial-sum slots that finer work items need.  Q carries 64 rows past
-// the last bead that the S->M/S->L kernels may read (with zero weight); they
-// must hold finite values (zeros).
+// the last bead that the S->M/S->L kernels may read and do not use.
 static void ws_sizes(const rpy_plan_t* P, int nrc, int nrn, bool split, size_t sz[WS_N]) {
   const int64_t T = rpy::ncoef(P->p);
   const int64_t nbox = std::max(P->B.tree.nbox, 1);
@@ -336,8 +335,9 @@ static int alloc_ws(rpy_plan_t* P, int nrc, int nrn) {
     }
     tot += sz[k];
   }
-  // zeroed once so that every row of Q, including the padding, is finite; the
-  // plan's stream need not wait for the null stream by itself
+  // cleared once, on the null stream, which the plan's stream need not wait for by
+  // itself; a first matvec under capture, whose memory would be the graph's, is
+  // refused here also where all of it came from kept blocks
   if (hipMemset(w.Q, 0, sz[5]) != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess) {
     (void)hipGetLastError();
     free_ws(P);
@@ -472,11 +472,6 @@ hipError_t scratch_address(int dev, void** out) {
   }
   *out = g_scratch_ptr[dev];
   return hipSuccess;
-}
-
-__global__ void k_zero(double* p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0.0;
 }
 
 inline size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
@@ -1060,12 +1055,6 @@ rpy_status rpy_matvec_noalloc(rpy_plan_t* P, int32_t nrhs, const double* forces,
       q += align256(sz[k]);
     }
   }
-  // the 64 charge rows past the last bead are read with zero weight and must
-  // be finite: cleared by a kernel on every call (earlier calls leave other
-  // contents in the scratch)
-  const int64_t pad = (int64_t)64 * 4 * nrc;
-  k_zero<<<(unsigned)((pad + 255) / 256), 256, 0, P->stream>>>(w.Q + P->B.n * 4 * nrc, pad);
-  he = hipGetLastError();
   rpy::Launch l{&P->B, &P->tb, P->p, P->a, P->eta, P->stream, P->wd};
   const int mixed = P->precision == RPY_PREC_MIXED;
   for (int r0 = 0; he == hipSuccess && r0 < nrhs;) {

@@ -185,23 +185,40 @@ __global__ void __launch_bounds__(P2E_THREADS, LOCAL && P > 4 ? 1 : 4) k_p2e(int
       }
       if (lane >= nb) sc = 0.0;  // every harmonic of an idle lane is zero
       // S->M: the chunk's charges as matrix-core operands, for all passes: loaded
-      // here, they arrive while the harmonics are generated
-      double bq[VEC || LOCAL ? 1 : P2E_CHUNK / 4];
-      if constexpr (!VEC && !LOCAL)
+      // here, they arrive while the harmonics are generated.  Beads past nb must
+      // not take part, not even with a zero harmonic: the rows read for them (the
+      // next leaf's, another system's, or past the last bead) may hold anything,
+      // and zero times NaN or infinity would reach this box.  So a last group of
+      // fewer than four beads has its own operand, zero past nb
+      double bq[VEC || LOCAL ? 1 : P2E_CHUNK / 4], bt = 0.0;
+      if constexpr (!VEC && !LOCAL) {
 #pragma unroll
         for (int q = 0; q < P2E_CHUNK / 4; ++q) bq[q] = li < ND ? Q[(int64_t)(jc + 4 * q + lk) * ND + li] : 0.0;
-      // S->M with one right-hand side: the wave's beads' charges, in scalar registers
+        if ((nb & 3) > lk && li < ND) bt = Q[(int64_t)(jc + (nb & ~3) + lk) * ND + li];
+      }
+      // S->M with one right-hand side: the wave's beads' charges, in scalar
+      // registers, zero past nb (in a branch of its own: selected in every chunk
+      // they cost 4 % of S->M)
       double qs[VEC && !LOCAL ? BPW : 1][ND];
-      if constexpr (VEC && !LOCAL)
+      if constexpr (VEC && !LOCAL) {
 #pragma unroll
         for (int i = 0; i < BPW; ++i)
 #pragma unroll
           for (int dd = 0; dd < ND; ++dd) qs[i][dd] = Q[(int64_t)(jc + sub * BPW + i) * ND + dd];
+        if (sub * BPW + BPW > nb)
+#pragma unroll
+          for (int i = 0; i < BPW; ++i)
+#pragma unroll
+            for (int dd = 0; dd < ND; ++dd) qs[i][dd] = sub * BPW + i < nb ? qs[i][dd] : 0.0;
+      }
       double ql[LOCAL ? 4 : 1];  // S->L: one bead's and right-hand side's charges, on their way to Qs
       if constexpr (LOCAL)
         if ((int)threadIdx.x < P2E_CHUNK * NRC)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) ql[q] = Q[(int64_t)jc * ND + 4 * (int)threadIdx.x + q];
+          for (int q = 0; q < 4; ++q) {
+            const double v = Q[(int64_t)jc * ND + 4 * (int)threadIdx.x + q];
+            ql[q] = (int)threadIdx.x / NRC < nb ? v : 0.0;
+          }
       double2 h0 = make_double2(0.0, 0.0), h1 = h0;
       double ca = 0.0, cb = 0.0;  // 2n - 1 and (n-1)^2 - m^2 for the next degree n
 #pragma unroll
@@ -269,10 +286,9 @@ __global__ void __launch_bounds__(P2E_THREADS, LOCAL && P > 4 ? 1 : 4) k_p2e(int
         __syncthreads();
         // D += H^T Q over the chunk's beads, 4 per instruction: A[row][k] in
         // lane row + 16 k (row = real or imaginary part of a slot), B[k][d]
-        // in lane d + 16 k, D[row][d] in lane d + 16 (row % 4), item row / 4;
-        // beads past nb have zero harmonics and finite (padded) charges
+        // in lane d + 16 k, D[row][d] in lane d + 16 (row % 4), item row / 4
         if constexpr (VEC) {
-          // beads past nb have zero harmonics; Q is padded past the last bead
+          // beads past nb have zero harmonics and zero charges
           if (sub * BPW < nb) {
 #pragma unroll
             for (int i = 0; i < BPW; ++i) {
@@ -303,9 +319,10 @@ __global__ void __launch_bounds__(P2E_THREADS, LOCAL && P > 4 ? 1 : 4) k_p2e(int
           } else {
 #pragma unroll
             for (int kk = 0; kk < P2E_CHUNK; kk += 4) {
-              if (kk >= nb) break;
+              if (kk + 4 > nb) break;
               steps(kk, bq[kk / 4]);
             }
+            if (nb & 3) steps(nb & ~3, bt);
           }
         }
       }

@@ -307,3 +307,70 @@ def test_captured_matvec(n, leaf, nrhs):
             torch.cuda.synchronize()
     finally:
         P.free()
+
+
+# Non-finite forces stay where they belong: a call with NaN and infinite forces
+# leaves nothing behind for the plan's next calls (wider passes first, whose
+# charges lie where narrower ones have their rows past the last bead), reaches no
+# other right-hand side of its call and no other system of its plan.  Leaves of
+# odd sizes on adaptive trees: S->M and S->L on the vector units and the matrix
+# cores, the allocating and the allocation-free call.
+def _poison(F):
+    F = F.copy()
+    F[..., 0] = np.nan
+    F[..., 1] = np.inf
+    return F
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_nonfinite_forces_leave_nothing_behind(noalloc):
+    import paper_1711_02976_amd as R
+    import torch
+    from gpu_common import to_dev
+    w = W.clustered(3001, 5, 12.0, 0.6, 0.05, 4, seed=400)
+    log(f"non-finite forces, later calls, noalloc={noalloc}")
+    kw = dict(leaf_size=37, order=8, w_direct=20, eval_mode="sets")
+
+    def call(P, F):
+        U = torch.full_like(F, float("nan"))
+        (R.rpy_matvec_noalloc if noalloc else R.rpy_matvec)(P.handle, F.shape[0], F.data_ptr(), U.data_ptr())
+        return U.cpu().numpy()
+
+    F, bad = to_dev(w.forces), to_dev(_poison(w.forces))
+    P, Q = (R.Plan(to_dev(w.pos), w.a, w.eta, 1e-6, **kw) for _ in range(2))
+    try:
+        assert P.stats()["list_len"]["X"] > 0
+        call(Q, F)  # the workspace of four right-hand sides, as P's
+        ref = {k: call(Q, F[:k].contiguous()) for k in (1, 2, 3, 4)}
+        assert all(np.isfinite(r).all() for r in ref.values())
+        for k in (1, 2, 3, 4):
+            call(P, bad)
+            assert np.array_equal(call(P, F[:k].contiguous()), ref[k]), k
+        mix = F[:3].clone()
+        mix[:2] = bad[:2]  # a pass of two, then the third right-hand side alone
+        assert np.array_equal(call(P, mix)[2], ref[3][2])
+    finally:
+        P.free()
+        Q.free()
+
+
+@pytest.mark.parametrize("nrhs", [1, 2, 4])
+def test_nonfinite_forces_stay_in_their_system(nrhs):
+    import paper_1711_02976_amd as R
+    from gpu_common import to_dev
+    counts = [1501, 1499]
+    w = W.clustered(sum(counts), 5, 12.0, 0.6, 0.05, nrhs, seed=401)
+    log(f"non-finite forces, other systems, nrhs={nrhs}")
+    P = R.Plan(to_dev(w.pos), w.a, w.eta, 1e-6, leaf_size=37, order=8, counts=counts, eval_mode="sets")
+    try:
+        ref = P.matvec(to_dev(w.forces)).cpu().numpy()
+        F = w.forces.copy()
+        F[:, counts[0]:] = _poison(F[:, counts[0]:])
+        u = P.matvec(to_dev(F)).cpu().numpy()
+        assert np.isfinite(ref).all() and np.array_equal(u[:, :counts[0]], ref[:, :counts[0]])
+        F = w.forces.copy()
+        F[:, :counts[0]] = _poison(F[:, :counts[0]])
+        u = P.matvec(to_dev(F)).cpu().numpy()
+        assert np.array_equal(u[:, counts[0]:], ref[:, counts[0]:])
+    finally:
+        P.free()
