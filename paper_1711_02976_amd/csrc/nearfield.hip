@@ -340,13 +340,15 @@ struct PairK {
 // Power of two S with 2aS in [1, 2).
 static double pair_scale(double a) { return std::ldexp(1.0, -std::ilogb(2.0 * a)); }
 
-// The FP64 kernels' positions are scaled by 2S instead: with r' = 2r the
-// reciprocal square root's Newton step gives 1/r = 2/r' one operation sooner
-// (rinv_of).  1/r and A' stay as they are; B', which multiplies d' d'^T = 4 d d^T,
-// is a quarter.  All of it is exact scaling by powers of two.  With the wave's
-// test for overlaps on FP32 roundings, the FP64 P2P of one right-hand side takes
-// 28 FP64 operations and roots per pair (30 before; 1M beads in leaves of 244:
-// 7.18 ms and 6.96 now, at its issue rate).
+// The FP64 kernels take the scaled positions as twice the distances in units twice
+// as long, in which 2a lies in [1/2, 1): with r' = 2r the reciprocal square root's
+// Newton step gives 1/r = 2/r' one operation sooner (rinv_of), and r'^2, which
+// passes through an FP32 estimate, has the range that r^2 would have.  1/r and A'
+// stay as they are; B', which multiplies d' d'^T = 4 d d^T, is a quarter.  All of
+// it is exact scaling by powers of two.  With the wave's test for overlaps on FP32
+// roundings, the FP64 P2P of one right-hand side takes 28 FP64 operations and roots
+// per pair (30 before; 1M beads in leaves of 244: 7.18 ms and 6.96 now, at its
+// issue rate).
 template <class R>
 constexpr double PAIR_ZOOM = std::is_same<R, double>::value ? 2.0 : 1.0;
 template <class R>
@@ -377,8 +379,8 @@ __device__ inline double rinv_of(double r2) {
 // coincident bead) r^2 carries a floor of 1e-30 in the scaled units (r2min) (added
 // in the first FMA) before the reciprocal square root: the far values are
 // then finite and discarded, and the overlap values give the r -> 0 limit
-// A' = c0/c1, B' d = 0.  Since 2a >= 1 in these units, the floor changes
-// r^2 by a relative amount below 1e-30 at every r >= 2a, where the far
+// A' = c0/c1, B' d = 0.  Since 2a >= 1/2 in these units, the floor changes
+// r^2 by a relative amount below 1e-29 at every r >= 2a, where the far
 // formula applies.
 // Positions enter the pair arithmetic relative to the target leaf's centre
 // (differences taken in FP64, scaled by S and rounded once); in the mixed
@@ -986,12 +988,11 @@ __global__ void __launch_bounds__(P2P_T) k_overlap(const int4* tiles, const doub
       }
 }
 
-// Launch arguments shared by the pair kernels: the scale S (2aS in [1, 2)) and the
-// FP64 kernels' 2S,
-// the constants of the scaled radius in both precisions and the prefactor
-// c1 S = S / (8 pi eta) that undoes the scaling of the sums.
+// Launch arguments shared by the pair kernels: the scale S of the positions (2aS in
+// [1, 2)), the constants of the scaled radius in both precisions and the
+// prefactors c1 S = S / (8 pi eta) that undo the scaling of the sums (FP64: of S / 2).
 struct PairLaunch {
-  double S, Sd, c1S;
+  double S, c1S, c1Sd;
   PairK<float> kf;
   PairK<double> kd;
 };
@@ -999,10 +1000,10 @@ struct PairLaunch {
 static PairLaunch pair_launch(double a, double eta) {
   PairLaunch q;
   q.S = pair_scale(a);
-  q.Sd = PAIR_ZOOM<double> * q.S;
   q.c1S = q.S / (8.0 * PI * eta);
+  q.c1Sd = q.c1S / PAIR_ZOOM<double>;
   q.kf = pair_const<float>(a * q.S);
-  q.kd = pair_const<double>(a * q.S);
+  q.kd = pair_const<double>(a * q.S / PAIR_ZOOM<double>);
   return q;
 }
 
@@ -1037,7 +1038,7 @@ hipError_t run_p2p(const Launch& l, const Tiles& tiles, const NearPlan& np, int 
                                                    B->sz, sF, B->n, q.kf, q.S, q.c1S, u, part);                    \
     else                                                                                                           \
       k_p2p<NR, false><<<g.blocks, P2P_T, 0, l.s>>>(tiles.t, g.item, g.slots, B->tree, B->lists[LU], B->sx, B->sy,   \
-                                                    B->sz, sF, B->n, q.kd, q.Sd, q.c1S, u, part);                   \
+                                                    B->sz, sF, B->n, q.kd, q.S, q.c1Sd, u, part);                   \
     break;
   switch (nrc) {
     P2P_CASE(1)
@@ -1050,14 +1051,14 @@ hipError_t run_p2p(const Launch& l, const Tiles& tiles, const NearPlan& np, int 
                                                              B->sy, B->sz, sF, B->n, q.kf, q.S, q.c1S, u, part);
       else
         k_p2p_mfma<false, 0><<<g.blocks, 64 * MF_W, 0, l.s>>>(tiles.t, g.item, g.slots, B->tree, B->lists[LU], B->sx,
-                                                              B->sy, B->sz, sF, B->n, q.kd, q.Sd, q.c1S, u, part);
+                                                              B->sy, B->sz, sF, B->n, q.kd, q.S, q.c1Sd, u, part);
       break;
     // 16 + XR: the FP64 form only
 #define MF_CASE(XR)                                                                                                \
   case MF_R + XR:                                                                                                  \
     if (mixed) return hipErrorInvalidValue;                                                                        \
     k_p2p_mfma<false, XR><<<g.blocks, 64 * MF_W, 0, l.s>>>(tiles.t, g.item, g.slots, B->tree, B->lists[LU], B->sx,   \
-                                                           B->sy, B->sz, sF, B->n, q.kd, q.Sd, q.c1S, u, part);     \
+                                                           B->sy, B->sz, sF, B->n, q.kd, q.S, q.c1Sd, u, part);     \
     break;
     MF_CASE(1)
     MF_CASE(2)
@@ -1094,7 +1095,7 @@ hipError_t run_direct(const Launch& l, const Tiles& tiles, const NearPlan& np, i
                                                           B->perm, np.sub);                                            \
     else                                                                                                             \
       k_p2p<NR, false, true><<<np.direct, P2P_T, 0, l.s>>>(tiles.t, np.u.item, np.u.slot, B->tree, B->lists[LU], B->sx,  \
-                                                           B->sy, B->sz, F, B->n, q.kd, q.Sd, q.c1S, nullptr, part,     \
+                                                           B->sy, B->sz, F, B->n, q.kd, q.S, q.c1Sd, nullptr, part,     \
                                                            B->perm, np.sub);                                           \
     break;
   switch (nrc) {
@@ -1135,7 +1136,7 @@ hipError_t run_overlap(const Launch& l, const Tiles& tiles, const NearPlan& np, 
                                                        f, B->sx, B->sy, B->sz, sF, B->n, q.kf, q.S, q.c1S, u, part); \
     else                                                                                                            \
       k_overlap<NR, false><<<g.blocks, P2P_T, 0, l.s>>>(tiles.t, tiles.box, g.item, g.slots, B->tree, B->lists[LO], \
-                                                        f, B->sx, B->sy, B->sz, sF, B->n, q.kd, q.Sd, q.c1S, u, part); \
+                                                        f, B->sx, B->sy, B->sz, sF, B->n, q.kd, q.S, q.c1Sd, u, part); \
     break;
   switch (nrc) {
     OV_CASE(1)
@@ -1169,7 +1170,7 @@ hipError_t run_wdirect(const Launch& l, const Tiles& tiles, const NearPlan& np, 
                                                        B->sy, B->sz, sF, B->n, q.kf, q.S, q.c1S, u, part);          \
     else                                                                                                            \
       k_wdirect<NR, false><<<g.blocks, P2P_T, 0, l.s>>>(tiles.t, g.item, g.slots, B->tree, B->lists[LW], f, B->sx,  \
-                                                        B->sy, B->sz, sF, B->n, q.kd, q.Sd, q.c1S, u, part);         \
+                                                        B->sy, B->sz, sF, B->n, q.kd, q.S, q.c1Sd, u, part);         \
     break;
   switch (nrc) {
     WD_CASE(1)

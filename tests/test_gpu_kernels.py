@@ -374,3 +374,23 @@ def test_nonfinite_forces_stay_in_their_system(nrhs):
         assert np.array_equal(u[:, counts[0]:], ref[:, counts[0]:])
     finally:
         P.free()
+
+
+# Pairs of the FP64 form as far apart as the FP32 range of their squared distances
+# allows in the units of the pair kernels (r of 1.3e19 to 1.8e19 times a power of
+# two near the diameter): the far terms are there in full.  The forces are on one
+# bead, so that its own term does not hide them.
+@pytest.mark.parametrize("nrhs", [1, 4, 16])
+def test_most_distant_pairs(orc, nrhs):
+    g = np.random.default_rng(410)
+    a, m = 2.0**-64, 2.0**63  # 2 a m = 1
+    v = g.standard_normal((40, 3))
+    pos = np.concatenate([np.zeros((1, 3)), v / np.linalg.norm(v, axis=1, keepdims=True) * g.uniform(1.45, 1.95, (40, 1))])
+    assert 1.3e19 < 1.45 * m and 1.95 * m < np.sqrt(np.finfo(np.float32).max)
+    F = np.zeros((nrhs, 41, 3))
+    F[:, 0] = g.standard_normal((nrhs, 3))
+    log(f"most distant pairs nrhs={nrhs}")
+    u, st = gpu_matvec(pos, F, a, leaf_size=1000)
+    ref = orc.rpy_direct(pos, F, a, 1.0)
+    assert st["nleaf"] == 1
+    assert orc.rel_l2(u[:, 1:], ref[:, 1:]) <= 1e-12
