@@ -297,10 +297,14 @@ rpy_status rpy_plan_timings(rpy_plan_t* plan, rpy_timings_t* out);
  * allocation fail part-way, as a failed hipMalloc would: rpy_matvec frees
  * what it had allocated and returns RPY_ENOMEM before issuing any work, the
  * velocities are not written, and the plan stays usable (the next call
- * allocates again).  A call that needs no new workspace leaves the injection
- * pending.  phase = -1 clears a pending injection.  Returns RPY_EINVAL for
- * other values.  No kernel is made to fail on the device. */
+ * allocates again).  phase = RPY_INJECT_SLOTS makes the next workspace with
+ * partial-sum slots not fit, as too little free memory would: rpy_matvec runs
+ * without them (results equal to rounding).  A call that needs no new workspace
+ * leaves either injection pending.  phase = -1 clears a pending injection.
+ * Returns RPY_EINVAL for other values.  No kernel is made to fail on the
+ * device. */
 #define RPY_INJECT_ALLOC 100
+#define RPY_INJECT_SLOTS 101
 rpy_status rpy_plan_inject_error(rpy_plan_t* plan, int32_t phase);
 
 /* Release a plan and its device memory; NULL is a no-op.  Waits for the

@@ -28,6 +28,7 @@ LIB_PATH = os.path.join(_HERE, "librpyfmm.so")
 
 RPY_OK, RPY_EINVAL, RPY_ENONFINITE, RPY_ENOMEM, RPY_EDEVICE, RPY_EUNSUPPORTED = 0, -1, -2, -3, -4, -5
 RPY_INJECT_ALLOC = 100  # rpy_plan_inject_error: fail the next matvec-workspace allocation
+RPY_INJECT_SLOTS = 101  # rpy_plan_inject_error: no room for the next workspace's partial-sum slots
 PREC_FP64, PREC_MIXED = 0, 1
 LIST_NAMES = ("U", "V", "W", "X", "O")
 
@@ -317,13 +318,15 @@ class Plan:
     def inject_error(self, phase):
         """Failure-path testing: the next matvec pass reports a HIP error at
         `phase` (a name from PHASES or its index; -1 clears), or with
-        phase "alloc" the next matvec-workspace allocation fails."""
-        if phase == "alloc":
-            phase = RPY_INJECT_ALLOC
+        phase "alloc" the next matvec-workspace allocation fails, with "slots"
+        only the room for its partial-sum slots is missing."""
+        special = {"alloc": RPY_INJECT_ALLOC, "slots": RPY_INJECT_SLOTS}
+        if phase in special:
+            phase = special[phase]
         elif isinstance(phase, str):
             phase = PHASES.index(phase)
-        if not (-1 <= int(phase) < len(PHASES) or phase == RPY_INJECT_ALLOC):
-            raise ValueError(f"phase must be -1, 'alloc' or one of {PHASES}")
+        if not (-1 <= int(phase) < len(PHASES) or phase in special.values()):
+            raise ValueError(f"phase must be -1, 'alloc', 'slots' or one of {PHASES}")
         rpy_plan_inject_error(self.handle, phase)
 
     def free(self):

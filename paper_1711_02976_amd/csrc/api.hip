@@ -306,25 +306,16 @@ static void free_ws(rpy_plan_t* P) {
   P->ws_bytes = 0;
 }
 
-static int alloc_ws(rpy_plan_t* P, int nrc, int nrn) {
-  if (P->ws_nrc >= nrc && P->ws_nrn >= nrn) return 0;
-  nrc = std::max(nrc, P->ws_nrc);
-  nrn = std::max(nrn, P->ws_nrn);
-  {
-    const rpy::NoKeep nokeep(P->ws_bytes > 0 && !rpy::device_wait());
-    free_ws(P);
-  }
-  size_t sz[WS_N];
-  ws_sizes(P, nrc, nrn, true, sz);
+// The arrays of Work for nrc and nrn right-hand sides, with or without the
+// partial-sum slots; on failure frees what it had allocated.
+static int alloc_ws_arrays(rpy_plan_t* P, const size_t sz[WS_N]) {
   Work& w = P->ws;
   void** dst[WS_N] = {(void**)&w.M, (void**)&w.L, (void**)&w.sF, (void**)&w.u, (void**)&w.uf,
                       (void**)&w.Q, (void**)&w.DL, (void**)&w.DW, (void**)&w.XP, (void**)&w.PV,
                       (void**)&w.M32, (void**)&w.NP, (void**)&w.EP};
-  int64_t tot = 0;
   // an injected allocation failure (rpy_plan_inject_error) hits half-way,
   // after some arrays are allocated, like a device that runs out of memory
   const int fail_at = P->inject == RPY_INJECT_ALLOC ? WS_N / 2 : WS_N;
-  if (fail_at < WS_N) P->inject = -1;
   for (int k = 0; k < WS_N; ++k) {
     if (sz[k] == 0) continue;
     if (k == fail_at || rpy::dev_alloc_bytes(dst[k], sz[k]) != hipSuccess) {
@@ -333,7 +324,6 @@ static int alloc_ws(rpy_plan_t* P, int nrc, int nrn) {
       free_ws(P);
       return -1;
     }
-    tot += sz[k];
   }
   // cleared once, on the null stream, which the plan's stream need not wait for by
   // itself; a first matvec under capture, whose memory would be the graph's, is
@@ -343,10 +333,36 @@ static int alloc_ws(rpy_plan_t* P, int nrc, int nrn) {
     free_ws(P);
     return -1;
   }
-  P->ws_nrc = nrc;
-  P->ws_nrn = nrn;
-  P->ws_bytes = tot;
   return 0;
+}
+
+static int alloc_ws(rpy_plan_t* P, int nrc, int nrn) {
+  if (P->ws_nrc >= nrc && P->ws_nrn >= nrn) return 0;
+  nrc = std::max(nrc, P->ws_nrc);
+  nrn = std::max(nrn, P->ws_nrn);
+  {
+    const rpy::NoKeep nokeep(P->ws_bytes > 0 && !rpy::device_wait());
+    free_ws(P);
+  }
+  // where the partial-sum slots (up to 1.2 GB at 24 right-hand sides) do not fit,
+  // whole tiles and coarse items, which need none
+  for (const bool split : {true, false}) {
+    size_t sz[WS_N];
+    ws_sizes(P, nrc, nrn, split, sz);
+    const bool no_slots = split && P->inject == RPY_INJECT_SLOTS;
+    const bool injected = no_slots || P->inject == RPY_INJECT_ALLOC;
+    const int rc = no_slots ? -1 : alloc_ws_arrays(P, sz);
+    if (injected) P->inject = -1;
+    if (rc == 0) {
+      P->ws.fine = split;
+      P->ws_nrc = nrc;
+      P->ws_nrn = nrn;
+      for (size_t b : sz) P->ws_bytes += (int64_t)b;
+      return 0;
+    }
+    if (injected && !no_slots) break;
+  }
+  return -1;
 }
 
 // One matvec group over right-hand sides r0 .. r0 + cn - 1: the near field
@@ -1253,8 +1269,8 @@ rpy_status rpy_plan_stats(const rpy_plan_t* P, rpy_plan_stats_t* out) {
 
 rpy_status rpy_plan_inject_error(rpy_plan_t* P, int32_t phase) {
   if (!P) return fail(RPY_EINVAL, "plan is NULL");
-  if ((phase < -1 || phase >= RPY_NPHASE) && phase != RPY_INJECT_ALLOC)
-    return fail(RPY_EINVAL, "phase must be -1, a rpy_phase or RPY_INJECT_ALLOC");
+  if ((phase < -1 || phase >= RPY_NPHASE) && phase != RPY_INJECT_ALLOC && phase != RPY_INJECT_SLOTS)
+    return fail(RPY_EINVAL, "phase must be -1, a rpy_phase, RPY_INJECT_ALLOC or RPY_INJECT_SLOTS");
   P->inject = phase;
   return RPY_OK;
 }

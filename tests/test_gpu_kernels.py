@@ -394,3 +394,48 @@ def test_most_distant_pairs(orc, nrhs):
     ref = orc.rpy_direct(pos, F, a, 1.0)
     assert st["nleaf"] == 1
     assert orc.rel_l2(u[:, 1:], ref[:, 1:]) <= 1e-12
+
+
+# A workspace whose partial-sum slots do not fit: the matvec runs in whole tiles
+# and coarse items instead, as before there were slots.  Adaptive trees with
+# split U, W and O lists, S->M, S->L and evaluation items (FP64 and mixed, on the
+# vector units and the matrix cores), and a plan of direct launches.
+@pytest.mark.parametrize("n,leaf,nrhs", [(9000, 300, 3), (9000, 300, 18), (4000, 700, 1), (700, 1000, 2)])
+def test_workspace_without_slots(orc, n, leaf, nrhs):
+    import paper_1711_02976_amd as R
+    import torch
+    from gpu_common import to_dev
+    w = W.clustered(n, 4, 12.0, 0.6, 0.3, nrhs, seed=420)
+    log(f"workspace without slots n={n} leaf={leaf} nrhs={nrhs}")
+    F = to_dev(w.forces)
+    ref = None
+    for precision in ("fp64", "mixed"):
+        P, Q = (R.Plan(to_dev(w.pos), w.a, w.eta, 1e-6, leaf_size=leaf, order=12, w_direct=60, precision=precision)
+                for _ in range(2))
+        try:
+            P.inject_error("slots")
+            u = P.matvec(F)
+            v = Q.matvec(F)
+            st, sq = P.stats(), Q.stats()
+            assert st["device_bytes"] < sq["device_bytes"]
+            if n > leaf:
+                assert st["list_len"]["X"] > 0
+            if n == 9000:
+                assert st["list_len"]["O"] > 0
+            if ref is None:
+                ref = orc.fmm(w.pos, w.forces, w.a, w.eta, 12, leaf, 60)
+            u, v = u.cpu().numpy(), v.cpu().numpy()
+            if precision == "fp64":
+                assert orc.rel_l2(u, ref) <= 1e-12
+            else:
+                assert orc.rel_l2(u, ref) <= 5e-7
+            assert orc.rel_l2(u, v) <= 1e-13
+            # the next call needs no new workspace; a larger one has its slots again
+            assert torch.equal(P.matvec(F), to_dev(u))
+            if nrhs < 16:
+                F24 = to_dev(np.resize(w.forces, (24, n, 3)))
+                assert torch.equal(P.matvec(F24), Q.matvec(F24))
+                assert P.stats()["device_bytes"] == Q.stats()["device_bytes"]
+        finally:
+            P.free()
+            Q.free()
