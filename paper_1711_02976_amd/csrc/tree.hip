@@ -732,7 +732,12 @@ int build_tree(const BuildArgs& A, Built* B, Error* err) {
   std::vector<int> sb(nsys + 1);
   for (int i = 0; i <= nsys; ++i) sb[i] = (int)A.sys_begin_h[i];
   if (dalloc(&B->d_sys_begin, nsys + 1, B, err)) return -3;
-  RPY_HIP(copy_in(B->d_sys_begin, sb.data(), sizeof(int) * (nsys + 1), s));
+  // A plan's first copy is on the null stream and waits for it: positions that
+  // the default stream still writes are there when s reads them, also where s does
+  // not wait for the null stream by itself.  (Nothing on s uses the block yet; a
+  // later trial tree's may be one that s has not finished with.)
+  if (A.presorted) RPY_HIP(copy_in(B->d_sys_begin, sb.data(), sizeof(int) * (nsys + 1), s));
+  else RPY_HIP(hipMemcpy(B->d_sys_begin, sb.data(), sizeof(int) * (nsys + 1), hipMemcpyHostToDevice));
   RPY_PAGE(int, page);
 
   if (A.presorted) {

@@ -439,3 +439,32 @@ def test_workspace_without_slots(orc, n, leaf, nrhs):
         finally:
             P.free()
             Q.free()
+
+
+# Positions produced by the default stream for a plan on a stream of its own that
+# does not wait for it (the plan's: no wait on the caller's side either): the plan
+# is of the new positions.  The old ones are as good, so that a plan of them would
+# be whole, and wrong.
+def test_positions_of_the_default_stream():
+    import paper_1711_02976_amd as R
+    import torch
+    from gpu_common import to_dev
+    w, old = (W.uniform_cube(3000, 1.0, 0.01, nrhs=1, seed=s) for s in (430, 431))
+    log("positions of the default stream")
+    side = torch.cuda.Stream()
+    new, pos = to_dev(w.pos), to_dev(old.pos)
+    R.Plan(pos, w.a, w.eta, 1e-6, leaf_size=40, stream=side.cuda_stream).free()  # the kernels are loaded
+    torch.cuda.synchronize()
+    torch.cuda._sleep(100_000_000)  # 40 ms at the least
+    pos.copy_(new)
+    P = R.Plan(pos, w.a, w.eta, 1e-6, leaf_size=40, stream=side.cuda_stream)
+    try:
+        torch.cuda.synchronize()
+        keys = P.export()["keys"]
+    finally:
+        P.free()
+    Q = R.Plan(new, w.a, w.eta, 1e-6, leaf_size=40)
+    try:
+        assert np.array_equal(keys, Q.export()["keys"])
+    finally:
+        Q.free()
