@@ -664,6 +664,12 @@ __device__ inline void rows_class(const LaneCol<R>& lc, bool ph, R cj, R fac, co
   }
 }
 
+// Orders a wave's own LDS accesses: its lane groups read rows that others of them
+// wrote, and write rows that others have read.  The LDS takes a wave's accesses in
+// the order of its instructions, so no wait is needed, but the compiler must keep
+// that order, which a lane's own accesses alone would not require of it.
+__device__ inline void wave_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local"); }
+
 // The tables' base as an opaque offset: otherwise the addresses of all
 // degrees are kept in registers through the loop over batches.
 __device__ inline int opaque_zero() {
@@ -690,7 +696,9 @@ __device__ inline void rows_degree(const LaneCol<R>& lc, R cj, bool scale, const
 #pragma unroll 1
   for (int k = 0; k < 2; ++k) {
     R xr[N + 1], xi[N + 1];
+    wave_order();  // the first pass's rows are written
     load_col<N, R>(col, ld, xr, xi);
+    wave_order();  // all rows are read before any is written
     rows_class<N, 0, NC, R>(lc, k == 0, cj, fac, tab, lo, g, ld, xr, xi, col + 2 * g * ld, dump);
     rows_class<N, 1, NC, R>(lc, k == 0, cj, fac, tab, lo, g, ld, xr, xi, col + 2 * g * ld, dump);
   }
@@ -715,6 +723,7 @@ __device__ inline void rows_ztrans(int l, const LaneCol<R>& lc, const R* __restr
     vr[j] = v.x;
     vi[j] = v.y;
   }
+  wave_order();  // all degrees are read before any is written
   const R* row = tab + RT::z_off(KK);
   R so = 1, st = 1;
   if constexpr (sizeof(R) == 8) {
