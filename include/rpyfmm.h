@@ -121,7 +121,8 @@ typedef struct {
   double plan_ms;        /* wall time of rpy_plan / rpy_plan_batched */
   int32_t w_direct;      /* W boxes of at most this many beads are summed
                             directly (-1: none) */
-  int32_t p2l_items;     /* S->L work items (a box's X list may be split) */
+  int32_t p2l_items;     /* S->L work items of rpy_matvec (a box's X list may be
+                            split); fewer where its workspace has no slots */
   int32_t p2l_split_boxes; /* boxes whose S->L work is split over several
                             items (their shares are added in a fixed order) */
   int32_t sort_passes;   /* radix-sort passes of the bead sort */
@@ -267,8 +268,10 @@ typedef enum {
 
 typedef struct {
   double ms[RPY_NPHASE];         /* accumulated GPU time per phase (HIP events) */
-  int64_t launches[RPY_NPHASE];  /* kernel launches per phase */
-  int64_t passes;                /* matvec passes (right-hand-side chunks) timed */
+  int64_t launches[RPY_NPHASE];  /* launches per phase of the kernels that do its work; kernels that
+                                    only prepare their input or add their partial sums not counted */
+  int64_t passes;                /* far-field passes (right-hand-side chunks) timed, also of plans
+                                    without a far field */
   double p2p_mc_ms;              /* part of ms[RPY_PH_P2P] spent in P2P launches on the matrix
                                     cores (near-field groups of 16 right-hand sides there; in
                                     the FP64 form plus up to 8 on the vector units of the same

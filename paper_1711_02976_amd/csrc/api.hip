@@ -365,6 +365,9 @@ static int alloc_ws(rpy_plan_t* P, int nrc, int nrn) {
   return -1;
 }
 
+// Right-hand sides of the next far-field pass with `left` still to do, at most nrc.
+static int far_pass(int left, int nrc) { return left >= nrc ? nrc : (left >= 2 && nrc >= 2 ? 2 : 1); }
+
 // One matvec group over right-hand sides r0 .. r0 + cn - 1: the near field
 // (P2P, overlap correction, direct W sums) for the whole group on the second
 // stream, the far field in passes of at most nrc right-hand sides on the
@@ -419,13 +422,14 @@ static hipError_t matvec_group(rpy_plan_t* P, const rpy::Launch& l, const Work& 
         return direct ? rpy::direct_out(l, P->tiles, P->np, cn, w.NP, velocities + r0 * n3)
                       : rpy::unpermute_velocities(l, w.u, nullptr, r0, cn, velocities);
       });
-    if (P->timing && !untimed) P->acc.passes += 1;
+    if (P->timing && !untimed)
+      for (int q0 = 0; q0 < cn; q0 += far_pass(cn - q0, nrc)) P->acc.passes += 1;
     return he;
   }
   // far field on s0, pass by pass over slices of the group's forces
   bool joined = !fork;
   for (int q0 = 0; he == hipSuccess && q0 < cn;) {
-    const int c = cn - q0 >= nrc ? nrc : (cn - q0 >= 2 && nrc >= 2 ? 2 : 1);
+    const int c = far_pass(cn - q0, nrc);
     const double* sFq = w.sF + q0 * n3;
     const rpy::Exp e{w.M, w.L, w.Q, w.DL, w.DW, w.XP, w.EP, w.fine, w.PV, w.M32};
     he = step(RPY_PH_P2M, 1, s0, [&] { return rpy::run_p2m(l, c, sFq, e); });
@@ -1260,8 +1264,9 @@ rpy_status rpy_plan_stats(const rpy_plan_t* P, rpy_plan_stats_t* out) {
   out->eval_mode = P->eval_mode;
   out->tuned = P->tuned ? (P->tune_hit ? 2 : 1) : 0;
   out->tune_err = P->tune_err;
-  out->p2l_items = P->B.xw[1].n;
-  out->p2l_split_boxes = P->B.xw[1].nred;
+  const rpy::P2EWork& xw = P->B.xw[P->ws.fine ? 1 : 0];
+  out->p2l_items = xw.n;
+  out->p2l_split_boxes = xw.nred;
   out->bead_pass_ms = P->bead_pass_ms;
   out->sort_passes = P->sort_passes;
   return RPY_OK;

@@ -468,3 +468,41 @@ def test_positions_of_the_default_stream():
         assert np.array_equal(keys, Q.export()["keys"])
     finally:
         Q.free()
+
+
+# What the statistics count: a pass per far-field chunk of right-hand sides, with
+# and without a far field, and the S->L items of the workspace in use.
+@pytest.mark.parametrize("n,leaf", [(300, 1000), (3000, 40)])
+def test_timed_passes(n, leaf):
+    import paper_1711_02976_amd as R
+    from gpu_common import to_dev
+    log(f"timed passes n={n}")
+    w = W.uniform_cube(n, 1.0, 0.01, nrhs=20, seed=440)
+    P = R.Plan(to_dev(w.pos), w.a, w.eta, 1e-3, leaf_size=leaf)
+    try:
+        P.set_timing(1)
+        done = 0
+        for nrhs, passes in ((1, 1), (3, 2), (8, 2), (11, 4), (20, 5)):  # 2 + 1; 4 + 4; 4 + 4, 2, 1; five of 4
+            P.matvec(to_dev(w.forces[:nrhs]))
+            done += passes
+            assert P.timings()["passes"] == done, nrhs
+    finally:
+        P.free()
+
+
+def test_counted_s2l_items():
+    import paper_1711_02976_amd as R
+    from gpu_common import to_dev
+    w = W.clustered(9000, 4, 12.0, 0.6, 0.05, 1, seed=441)
+    log("counted S->L items")
+    F = to_dev(w.forces)
+    P, Q = (R.Plan(to_dev(w.pos), w.a, w.eta, 1e-6, leaf_size=700, order=8) for _ in range(2))
+    try:
+        Q.inject_error("slots")
+        P.matvec(F)
+        Q.matvec(F)
+        assert 0 < Q.stats()["p2l_items"] < P.stats()["p2l_items"]
+        assert Q.stats()["p2l_split_boxes"] <= P.stats()["p2l_split_boxes"]
+    finally:
+        P.free()
+        Q.free()
