@@ -15,10 +15,12 @@
 //   * Idle blocks of a device are bounded by POOL_IDLE bytes (the longest idle are
 //     given back first), those that POOL_AGE plans came and went without are given
 //     back, and all of them are when an allocation fails, before it is tried again.
-// Larger blocks go straight to hipMalloc and hipFree.
+// Larger blocks go straight to hipMalloc and hipFree.  Nothing here throws: where
+// the host has no memory for a record, a block is not kept, or not handed out.
 #include <algorithm>
 #include <map>
 #include <mutex>
+#include <new>
 #include <unordered_map>
 
 #include "pool.h"
@@ -47,9 +49,11 @@ struct Pool {
   std::unordered_map<void*, std::pair<size_t, int>> live;  // block -> size, device
   std::map<int, DevPool> dev;
 };
-// never destroyed: the runtime may be gone by then, and takes the memory with it
+// never destroyed: the runtime may be gone by then, and takes the memory with it;
+// in storage of its own, so that it is always there
 Pool& pool() {
-  static Pool* p = new Pool;
+  alignas(Pool) static char at[sizeof(Pool)];
+  static Pool* p = new (at) Pool;
   return *p;
 }
 thread_local BuildScope* t_scope = nullptr;
@@ -107,37 +111,43 @@ hipError_t dev_alloc_bytes(void** out, size_t n) {
   const int dev = current_device();
   size_t size = block_size(n);
   void* p = nullptr;
-  Pool& P = pool();
-  if (size <= POOL_BLOCK) {
-    if (t_scope && t_scope->device() == dev)
-      p = take_fit(t_scope->freed, size, &size, [](const IdleBlock& b) -> const IdleBlock& { return b; });
-    if (!p) {
-      std::lock_guard<std::mutex> lk(P.mu);
-      DevPool& d = P.dev[dev];
-      p = take_fit(d.idle, size, &size, [](const Idle& i) -> const IdleBlock& { return i.b; });
-      if (p) d.bytes -= size;
-    }
-  }
-  if (!p) {
-    hipError_t he = hipMalloc(&p, size);
-    if (he == hipErrorOutOfMemory) {
-      // give everything idle back, and try once more
-      (void)hipGetLastError();
-      if (t_scope) t_scope->flush();
-      {
+  try {
+    Pool& P = pool();
+    if (size <= POOL_BLOCK) {
+      if (t_scope && t_scope->device() == dev)
+        p = take_fit(t_scope->freed, size, &size, [](const IdleBlock& b) -> const IdleBlock& { return b; });
+      if (!p) {
         std::lock_guard<std::mutex> lk(P.mu);
-        give_back(P.dev[dev], 0, ~(uint64_t)0);
+        DevPool& d = P.dev[dev];
+        p = take_fit(d.idle, size, &size, [](const Idle& i) -> const IdleBlock& { return i.b; });
+        if (p) d.bytes -= size;
       }
-      he = hipMalloc(&p, size);
     }
-    if (he != hipSuccess) return he;
+    if (!p) {
+      hipError_t he = hipMalloc(&p, size);
+      if (he == hipErrorOutOfMemory) {
+        // give everything idle back, and try once more
+        (void)hipGetLastError();
+        if (t_scope) t_scope->flush();
+        {
+          std::lock_guard<std::mutex> lk(P.mu);
+          give_back(P.dev[dev], 0, ~(uint64_t)0);
+        }
+        he = hipMalloc(&p, size);
+      }
+      if (he != hipSuccess) return he;
+    }
+    std::lock_guard<std::mutex> lk(P.mu);
+    P.live[p] = {size, dev};
+  } catch (const std::bad_alloc&) {  // no host memory for the record of the block
+    if (p) (void)hipFree(p);
+    return hipErrorOutOfMemory;
   }
-  std::lock_guard<std::mutex> lk(P.mu);
-  P.live[p] = {size, dev};
   *out = p;
   return hipSuccess;
 }
 
+// A list that cannot grow does not keep the block.
 void dev_free(void* p) {
   if (!p) return;
   Pool& P = pool();
@@ -151,27 +161,31 @@ void dev_free(void* p) {
     }
   }
   // (a block of another device than the current one, which the caller waited for)
-  if (b.first == 0 || b.first > POOL_BLOCK || t_nokeep || b.second != current_device()) {
-    (void)hipFree(p);
-    return;
-  }
-  if (t_scope && t_scope->device() == b.second) {
-    t_scope->freed.push_back(IdleBlock{p, b.first});
-    return;
-  }
-  std::lock_guard<std::mutex> lk(P.mu);
-  make_idle(P, b.second, IdleBlock{p, b.first});
+  if (b.first > 0 && b.first <= POOL_BLOCK && !t_nokeep && b.second == current_device()) try {
+      if (t_scope && t_scope->device() == b.second) {
+        t_scope->freed.push_back(IdleBlock{p, b.first});
+        return;
+      }
+      std::lock_guard<std::mutex> lk(P.mu);
+      make_idle(P, b.second, IdleBlock{p, b.first});
+      return;
+    } catch (const std::bad_alloc&) {
+    }
+  (void)hipFree(p);
 }
 
 BuildScope::BuildScope(hipStream_t s) : s_(s), dev_(current_device()), outer_(t_scope) {
-  t_scope = this;
-  Pool& P = pool();
-  std::lock_guard<std::mutex> lk(P.mu);
-  DevPool& d = P.dev[dev_];
-  if (!d.pages.empty()) {
-    page_ = d.pages.back();
-    d.pages.pop_back();
+  try {
+    Pool& P = pool();
+    std::lock_guard<std::mutex> lk(P.mu);
+    DevPool& d = P.dev[dev_];
+    if (!d.pages.empty()) {
+      page_ = d.pages.back();
+      d.pages.pop_back();
+    }
+  } catch (const std::bad_alloc&) {
   }
+  t_scope = this;
 }
 
 BuildScope::~BuildScope() {
@@ -180,14 +194,22 @@ BuildScope::~BuildScope() {
   if (!done) (void)hipGetLastError();
   Pool& P = pool();
   std::lock_guard<std::mutex> lk(P.mu);
-  for (const IdleBlock& b : freed) {
-    if (done) make_idle(P, dev_, b);
-    else (void)hipFree(b.p);
-  }
+  for (const IdleBlock& b : freed) try {
+      if (done) make_idle(P, dev_, b);
+      else (void)hipFree(b.p);
+    } catch (const std::bad_alloc&) {
+      (void)hipFree(b.p);
+    }
   if (!page_) return;
-  DevPool& d = P.dev[dev_];
-  if (done && d.pages.size() < POOL_LANES) d.pages.push_back(page_);
-  else (void)hipHostFree(page_);
+  try {
+    DevPool& d = P.dev[dev_];
+    if (done && d.pages.size() < POOL_LANES) {
+      d.pages.push_back(page_);
+      return;
+    }
+  } catch (const std::bad_alloc&) {
+  }
+  (void)hipHostFree(page_);
 }
 
 void BuildScope::flush() {
@@ -218,10 +240,10 @@ NoKeep::~NoKeep() { t_nokeep = before_; }
 bool take_lane(int dev, Lane* out) {
   Pool& P = pool();
   std::lock_guard<std::mutex> lk(P.mu);
-  DevPool& d = P.dev[dev];
-  if (d.lanes.empty()) return false;
-  *out = d.lanes.back();
-  d.lanes.pop_back();
+  const auto it = P.dev.find(dev);
+  if (it == P.dev.end() || it->second.lanes.empty()) return false;
+  *out = it->second.lanes.back();
+  it->second.lanes.pop_back();
   return true;
 }
 
@@ -236,16 +258,22 @@ bool keep_lane(int dev, const Lane& l) {
   }
   Pool& P = pool();
   std::lock_guard<std::mutex> lk(P.mu);
-  DevPool& d = P.dev[dev];
-  if (d.lanes.size() >= POOL_LANES) return false;
-  d.lanes.push_back(l);
+  try {
+    DevPool& d = P.dev[dev];
+    if (d.lanes.size() >= POOL_LANES) return false;
+    d.lanes.push_back(l);
+  } catch (const std::bad_alloc&) {
+    return false;
+  }
   return true;
 }
 
 void plan_freed(int dev) {
   Pool& P = pool();
   std::lock_guard<std::mutex> lk(P.mu);
-  DevPool& d = P.dev[dev];
+  const auto it = P.dev.find(dev);
+  if (it == P.dev.end()) return;  // nothing was kept or asked for
+  DevPool& d = it->second;
   ++d.plans;
   if (d.plans > POOL_AGE) give_back(d, POOL_IDLE, d.plans - POOL_AGE);
 }
