@@ -506,3 +506,45 @@ def test_counted_s2l_items():
     finally:
         P.free()
         Q.free()
+
+
+# The allocation-free matvec of plans whose workspace fits its 128 MiB only without
+# partial-sum slots: whole tiles and coarse items.  A uniform plan of 20 right-hand
+# sides, and an adaptive one with W, X and O lists, evaluated W multipoles and
+# S->L items that would be finer; FP64 against the oracle FMM, the mixed form
+# against it to half its accuracy setting.
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("kind", ["uniform", "adaptive"])
+def test_noalloc_without_slots(orc, kind, precision):
+    import paper_1711_02976_amd as R
+    import torch
+    from gpu_common import to_dev
+    if kind == "uniform":
+        w, leaf, p, wd = W.uniform_cube(12000, 1.0, 0.005, nrhs=20, seed=450), 250, 12, 0
+    else:
+        w, leaf, p, wd = W.clustered(9000, 4, 12.0, 0.6, 0.3, 18, seed=451), 300, 12, 60
+    log(f"noalloc without slots {kind} {precision}")
+    P, Q = (R.Plan(to_dev(w.pos), w.a, w.eta, 1e-6, leaf_size=leaf, order=p, w_direct=wd, precision=precision)
+            for _ in range(2))
+    try:
+        F = to_dev(w.forces)
+        st = P.stats()
+        if kind == "adaptive":
+            assert st["list_len"]["W"] > 0 and st["list_len"]["X"] > 0 and st["list_len"]["O"] > 0
+        U = torch.full_like(F, float("nan"))
+        R.rpy_matvec_noalloc(P.handle, w.nrhs, F.data_ptr(), U.data_ptr())
+        u = U.cpu().numpy()
+        assert P.stats()["device_bytes"] == st["device_bytes"]  # nothing allocated
+        Q.inject_error("slots")
+        v = Q.matvec(F).cpu().numpy()
+        without = Q.stats()["device_bytes"] - st["device_bytes"]
+        x = P.matvec(F).cpu().numpy()
+        full = P.stats()["device_bytes"] - st["device_bytes"]
+        log(f"  workspace {full >> 20} MiB with slots, {without >> 20} without, items {P.stats()['p2l_items']} {Q.stats()['p2l_items']}")
+        assert without < 127 << 20 and full > 128 << 20
+    finally:
+        P.free()
+        Q.free()
+    ref = orc.fmm(w.pos, w.forces, w.a, w.eta, p, leaf, st["w_direct"])
+    assert orc.rel_l2(u, ref) <= (1e-12 if precision == "fp64" else 5e-7)
+    assert np.array_equal(u, v) and orc.rel_l2(u, x) <= 1e-13
