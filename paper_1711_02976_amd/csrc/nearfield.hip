@@ -102,9 +102,17 @@ int make_tiles(const Built* B, int tile, Tiles* out, hipStream_t s, Error* err) 
 // (P2P_T beads of one list entry each) are split over several blocks when it
 // has more than cap = max(1, total / NEAR_ITEMS) of them: the parts' FP64
 // sums go to slots of P2P_T targets each and are added in part order
-// (k_near_reduce), so results do not depend on timing.  With many even tiles
-// nothing is split and no table is kept.  NEAR_ITEMS blocks fill the chip
-// twice over in the lightest kernel (16 blocks of two waves per CU).
+// (k_near_reduce), so results do not depend on timing.  With many more than
+// NEAR_ITEMS even tiles nothing is split and no table is kept.  Around that
+// number the tiles just above the mean are cut in two: of a uniform cube's 8,192
+// all interior ones, whose 54 chunks are 1.14 times the mean.  That pays too, since
+// the shorter blocks end more evenly and share the chip better with the far field
+// (whole tiles up to twice the mean and split ones: 778k beads, 20 right-hand
+// sides, P2P 31.0 and 28.4 ms, matvec 100.4 and 98.5; 1M beads, one, matvec
+// FP64 at 3 digits 7.60 and 7.33, mixed at 6 digits 6.25 and 6.12), at the price of
+// the slots' memory (3 kB per slot and right-hand side, 0.67 GB for the 778k
+// beads; without room for it the matvec runs whole tiles).  NEAR_ITEMS blocks fill
+// the chip twice over in the lightest kernel (16 blocks of two waves per CU).
 constexpr int NEAR_ITEMS = 8192;
 
 // A W-list box of more than wmax beads is evaluated through its multipole.
