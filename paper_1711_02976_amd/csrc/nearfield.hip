@@ -124,8 +124,11 @@ struct ChunkFilter {
 
 // Whether the near field sums list entry C for a tile with bounding box tb
 // (lo xyz, hi xyz): W boxes of few beads only; O leaves whose cube comes
-// closer than 2a to the tile's beads.
+// closer than 2a to the tile's beads.  The counting and filling of the parts and
+// the kernels that walk them must agree on it to the last bit, so nothing of it is
+// left to the compiler's choice of contractions.
 __device__ inline bool near_takes(const ChunkFilter& f, const Tree& t, int C, const double* tb) {
+#pragma clang fp contract(off)
   if (f.kind == LW) return t.end[C] - t.begin[C] <= f.wmax;
   if (f.kind == LO) {
     const double hc = 0.5 * t.h[C], cc[3] = {t.cx[C], t.cy[C], t.cz[C]};
