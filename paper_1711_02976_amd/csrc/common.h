@@ -34,6 +34,10 @@ __device__ inline int xcd_run(int i, int G) {
   return (8 * (k / XCD_CHUNK) + x) * XCD_CHUNK + k % XCD_CHUNK;
 }
 
+// Most blocks of `threads` per launch: HIP takes fewer than 2^32 threads along x
+// (whole rounds over the 8 XCDs).
+constexpr int64_t launch_blocks(int threads) { return (int64_t(1) << 32) / threads / 8 * 8 - 8; }
+
 // Device view of the octree.  Boxes are numbered by (level, system, Morton
 // key); begin/end index the sorted bead order.
 struct Tree {

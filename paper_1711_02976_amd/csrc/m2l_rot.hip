@@ -1058,13 +1058,15 @@ static hipError_t launch_nd(const Launch& l, Exp e, const R* rot, const R* zt, i
   if (he != hipSuccess) return he;
   if (!B->m2l_map || B->m2l_part[2] < B->tree.nbox) return hipErrorInvalidValue;
   const int b0 = part == 1 ? B->m2l_part[1] : 0, b1 = part == 0 ? B->m2l_part[1] : B->m2l_part[2];
-  if (b1 <= b0) return hipSuccess;
   // the map runs are whole multiples of 8 blocks, so every density group of
   // a box lands on the same XCD
-  kern<<<dim3(b1 - b0, nsplit), 64 * RW, shm, l.s>>>(l.p, ND * nsplit, B->tree, B->lists[LV], sc, rot, zt,
-                                                 l.tb->rot_len, l.tb->geo, l.tb->sfac, e.M, e.M32, e.L,
-                                                 B->m2l_map + b0);
-  return hipGetLastError();
+  for (int64_t b = b0; he == hipSuccess && b < b1; b += launch_blocks(64 * RW)) {
+    const unsigned nb = (unsigned)std::min<int64_t>(b1 - b, launch_blocks(64 * RW));
+    kern<<<dim3(nb, nsplit), 64 * RW, shm, l.s>>>(l.p, ND * nsplit, B->tree, B->lists[LV], sc, rot, zt, l.tb->rot_len,
+                                                  l.tb->geo, l.tb->sfac, e.M, e.M32, e.L, B->m2l_map + b);
+    he = hipGetLastError();
+  }
+  return he;
 }
 
 // The FP32 M->L reads the multipoles of its source boxes in the paper's
@@ -1093,11 +1095,15 @@ static hipError_t launch_rows(const Launch& l, int nrc, Exp e, int part) {
   if (he != hipSuccess) return he;
   if (!B->m2l_map || B->m2l_part[2] < B->tree.nbox || !l.tb->rows_rot || l.tb->rows_nc != NC) return hipErrorInvalidValue;
   const int b0 = part == 1 ? B->m2l_part[1] : 0, b1 = part == 0 ? B->m2l_part[1] : B->m2l_part[2];
-  if (b1 <= b0) return hipSuccess;
-  kern<<<dim3(b1 - b0, nrc), 64 * RW, shm, l.s>>>(
-      p, 4 * nrc, B->tree, B->lists[LV], sc, static_cast<const R*>(l.tb->rows_rot), static_cast<const R*>(l.tb->rows_zt),
-      l.tb->geo, static_cast<const typename Cx<R>::T*>(l.tb->rows_ph), l.tb->sfac, e.M, e.M32, e.L, B->m2l_map + b0);
-  return hipGetLastError();
+  for (int64_t b = b0; he == hipSuccess && b < b1; b += launch_blocks(64 * RW)) {
+    const unsigned nb = (unsigned)std::min<int64_t>(b1 - b, launch_blocks(64 * RW));
+    kern<<<dim3(nb, nrc), 64 * RW, shm, l.s>>>(
+        p, 4 * nrc, B->tree, B->lists[LV], sc, static_cast<const R*>(l.tb->rows_rot),
+        static_cast<const R*>(l.tb->rows_zt), l.tb->geo, static_cast<const typename Cx<R>::T*>(l.tb->rows_ph),
+        l.tb->sfac, e.M, e.M32, e.L, B->m2l_map + b);
+    he = hipGetLastError();
+  }
+  return he;
 }
 
 template <class R>

@@ -88,8 +88,11 @@ int make_tiles(const Built* B, int tile, Tiles* out, hipStream_t s, Error* err) 
   k_tile_fill<<<nblk(B->nleaf, 256), 256, 0, s>>>(B->leaf_ids, B->nleaf, B->tree, tile, off, out->t);
   RPY_HIP(hipGetLastError());
   RPY_HIP(dev_alloc(&out->box, sizeof(double) * 6 * std::max(out->n, 1)));
-  if (out->n > 0) k_tile_box<<<out->n, 64, 0, s>>>(out->t, B->sx, B->sy, B->sz, out->box);
-  RPY_HIP(hipGetLastError());
+  for (int64_t q = 0; q < out->n; q += launch_blocks(64)) {
+    k_tile_box<<<(unsigned)std::min<int64_t>(out->n - q, launch_blocks(64)), 64, 0, s>>>(out->t + q, B->sx, B->sy, B->sz,
+                                                                                      out->box + 6 * q);
+    RPY_HIP(hipGetLastError());
+  }
   dev_free(cnt); dev_free(off); dev_free(tmp);
   return 0;
 }

@@ -295,10 +295,13 @@ __global__ void k_tree_roots(Tree t, const int* sys_begin, int nsys) {
 // one before, run side by side and once (20 + 16 us per level of 200k beads
 // with a thread per box searching one octant after another, for the count and
 // again for the children; 6 + 3 us now).
-__global__ void __launch_bounds__(256) k_tree_count(Tree t, const uint64_t* keys, int ls, int le, int lev,
+// The nb boxes from ls on: a level, or LEVEL_PIECE boxes of it (a launch has fewer
+// than 2^32 threads, and g must fit).
+constexpr int LEVEL_PIECE = 1 << 22;
+__global__ void __launch_bounds__(256) k_tree_count(Tree t, const uint64_t* keys, int ls, int nb, int lev,
                                                     int leaf_size, int max_depth, int* cut, int* cnt) {
   const int g = blockIdx.x * 256 + threadIdx.x, b = ls + (g >> 3), o = g & 7;
-  const bool live = b < le;
+  const bool live = (g >> 3) < nb;
   const int b0 = live ? t.begin[b] : 0, b1 = live ? t.end[b] : 0;
   const bool split = live && b1 - b0 > leaf_size && lev < max_depth;
   const int lo = split ? (o ? lower_digit(keys, b0, b1, lev + 1, o) : b0) : 0;
@@ -309,11 +312,12 @@ __global__ void __launch_bounds__(256) k_tree_count(Tree t, const uint64_t* keys
   if (o == 0) cnt[b - ls] = __popcll((full >> (threadIdx.x & 56)) & 0xffull);
 }
 
-// The children of the level's boxes, one lane per octant.
-__global__ void __launch_bounds__(256) k_tree_write(Tree t, int ls, int le, int lev, const int* cut, const int* cnt,
-                                                    const int* off) {
+// The children of the level's boxes (the next level starts at le), one lane per
+// octant.
+__global__ void __launch_bounds__(256) k_tree_write(Tree t, int ls, int nb, int le, int lev, const int* cut,
+                                                    const int* cnt, const int* off) {
   const int g = blockIdx.x * 256 + threadIdx.x, b = ls + (g >> 3), o = g & 7;
-  const bool live = b < le;
+  const bool live = (g >> 3) < nb;
   const int nc = live ? cnt[b - ls] : 0;
   const int lo = nc ? cut[g] : 0, nx = __shfl_down(lo, 1, 8), hi = nc ? (o < 7 ? nx : t.end[b]) : 0;
   const unsigned long long full = (__ballot(hi > lo) >> (threadIdx.x & 56)) & 0xffull;
@@ -445,9 +449,9 @@ __device__ inline void sort_list(int* v, int n, int* buf, int lane) {
 // per box takes 0.02 and 1.1 ms.
 // A descent's stack grows by at most 56 boxes per level.
 constexpr int LIST_STACK = NSLOT + 64 * (KBITS + 1);
-__global__ void __launch_bounds__(64) k_lists(Tree t, const int* col, int nbox, int mode, int* cnt, List l0, List l1,
+__global__ void __launch_bounds__(64) k_lists(Tree t, const int* col, int b0, int nbox, int mode, int* cnt, List l0, List l1,
                                               List l2, List l3, List l4, int want_o, const double* side, double a) {
-  const int b = blockIdx.x, lane = threadIdx.x;
+  const int b = b0 + blockIdx.x, lane = threadIdx.x;
   __shared__ int num[5], sp, stack[LIST_STACK], buf[SORT_LDS];
   int* dst[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
   if (mode) {
@@ -885,15 +889,21 @@ int build_tree(const BuildArgs& A, Built* B, Error* err) {
           dalloc(&tmp, (int64_t)scan_tmp_ints(ccap), B, err))
         return -3;
     }
-    k_tree_count<<<nblocks(8 * (int64_t)nb, 256), 256, 0, s>>>(t, B->keys, ls, le, lev, A.leaf_size, A.max_depth, cut,
-                                                             cnt);
-    RPY_HIP(hipGetLastError());
+    for (int64_t q = 0; q < nb; q += LEVEL_PIECE) {
+      const int m = (int)std::min<int64_t>(LEVEL_PIECE, nb - q);
+      k_tree_count<<<nblocks(8 * (int64_t)m, 256), 256, 0, s>>>(t, B->keys, ls + (int)q, m, lev, A.leaf_size, A.max_depth,
+                                                              cut + 8 * q, cnt + q);
+      RPY_HIP(hipGetLastError());
+    }
     RPY_HIP(scan_exclusive(cnt, off, nb, tmp, s, page));
     RPY_HIP(hipStreamSynchronize(s));
     const int nnext = page[0];
     if (grow_tree(B, le + nnext, s, err)) return err->code;
-    k_tree_write<<<nblocks(8 * (int64_t)nb, 256), 256, 0, s>>>(t, ls, le, lev, cut, cnt, off);
-    RPY_HIP(hipGetLastError());
+    for (int64_t q = 0; q < nb; q += LEVEL_PIECE) {
+      const int m = (int)std::min<int64_t>(LEVEL_PIECE, nb - q);
+      k_tree_write<<<nblocks(8 * (int64_t)m, 256), 256, 0, s>>>(t, ls + (int)q, m, le, lev, cut + 8 * q, cnt + q, off + q);
+      RPY_HIP(hipGetLastError());
+    }
     if (nnext == 0) break;
     B->level_start.push_back(le + nnext);
     ++lev;
@@ -913,8 +923,10 @@ int build_tree(const BuildArgs& A, Built* B, Error* err) {
   if (dalloc(&B->colleague, (int64_t)nbox * NSLOT, B, err)) return -3;
   for (int l = 0; l <= B->depth; ++l) {
     int ls = B->level_start[l], le = B->level_start[l + 1];
-    k_colleagues<<<le - ls, 64, 0, s>>>(t, ls, B->colleague);
-    RPY_HIP(hipGetLastError());
+    for (int64_t q = ls; q < le; q += launch_blocks(64)) {
+      k_colleagues<<<(unsigned)std::min<int64_t>(le - q, launch_blocks(64)), 64, 0, s>>>(t, (int)q, B->colleague);
+      RPY_HIP(hipGetLastError());
+    }
   }
 
   // Leaves.
@@ -942,9 +954,15 @@ int build_tree(const BuildArgs& A, Built* B, Error* err) {
   int* lt = nullptr;
   if (dalloc(&lcnt, 5 * (int64_t)nbox, B, err) || dalloc(&lt, (int64_t)scan_tmp_ints(nbox + 1), B, err)) return -3;
   List none[5] = {};
-  k_lists<<<nbox, 64, 0, s>>>(t, B->colleague, nbox, 0, lcnt, none[0], none[1], none[2], none[3],
-                                           none[4], want_o, B->d_side, A.a);
-  RPY_HIP(hipGetLastError());
+  const auto lists = [&](int mode, const List* l) -> hipError_t {
+    for (int64_t q = 0; q < nbox; q += launch_blocks(64)) {
+      k_lists<<<(unsigned)std::min<int64_t>(nbox - q, launch_blocks(64)), 64, 0, s>>>(
+          t, B->colleague, (int)q, nbox, mode, lcnt, l[0], l[1], l[2], l[3], l[4], want_o, B->d_side, A.a);
+      if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  };
+  RPY_HIP(lists(0, none));
   // The five scans, which leave the lists' lengths at their ends, then one wait.
   for (int L = 0; L < 5; ++L) {
     if (dalloc(&B->lists[L].off, nbox + 1, B, err)) return -3;
@@ -956,9 +974,7 @@ int build_tree(const BuildArgs& A, Built* B, Error* err) {
     B->lists[L].len = page[L];
     if (dalloc(&B->lists[L].ent, B->lists[L].len, B, err)) return -3;
   }
-  k_lists<<<nbox, 64, 0, s>>>(t, B->colleague, nbox, 1, lcnt, B->lists[0], B->lists[1], B->lists[2],
-                                           B->lists[3], B->lists[4], want_o, B->d_side, A.a);
-  RPY_HIP(hipGetLastError());
+  RPY_HIP(lists(1, B->lists));
   dev_free(lcnt); dev_free(lt);
   B->bytes -= sizeof(int) * (5 * (int64_t)nbox + scan_tmp_ints(nbox + 1));
   return 0;

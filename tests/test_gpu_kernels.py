@@ -548,3 +548,56 @@ def test_noalloc_without_slots(orc, kind, precision):
     ref = orc.fmm(w.pos, w.forces, w.a, w.eta, p, leaf, st["w_direct"])
     assert orc.rel_l2(u, ref) <= (1e-12 if precision == "fp64" else 5e-7)
     assert np.array_equal(u, v) and orc.rel_l2(u, x) <= 1e-13
+
+
+# More boxes than one launch of a block per box takes (fewer than 2^32 threads
+# along x).  Coincident pairs in leaves of one bead: a chain of boxes per pair down
+# to the deepest level.
+def _pairs(m, seed):
+    import torch
+    from gpu_common import torch_cuda
+    torch_cuda()
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    return torch.rand((m, 3), generator=g, device="cuda", dtype=torch.float64).repeat(2, 1)
+
+
+# M->L of 12 waves (FP64, order 11) over more than 2^32 / 768 boxes, against the
+# dense operator on the same tree, whose blocks of 256 threads fit one launch.
+def test_more_boxes_than_a_launch_m2l():
+    import paper_1711_02976_amd as R
+    import torch
+    log("M->L over more boxes than a launch takes")
+    pos = _pairs(430_000, 460)
+    F = torch.randn((1, pos.shape[0], 3), generator=torch.Generator(device="cuda").manual_seed(461), device="cuda",
+                    dtype=torch.float64)
+    u = []
+    for mode in ("dense", "rotation"):
+        P = R.Plan(pos, 2e-3, 1.0, 3e-5, leaf_size=1, order=11, max_depth=21, m2l=mode)
+        try:
+            st = P.stats()
+            u.append(P.matvec(F))
+            torch.cuda.synchronize()
+        finally:
+            P.free()
+    assert st["nbox"] - st["nleaf"] > 2**32 // 768 and st["list_len"]["V"] > 0
+    assert float((u[1] - u[0]).norm() / u[0].norm()) <= 1e-12
+
+
+# The tree and its lists over more than 2^32 / 64 boxes: the two levels more add a
+# box each per pair and no list entries (the pairs are far apart there).
+def test_more_boxes_than_a_launch_tree():
+    import paper_1711_02976_amd as R
+    log("tree over more boxes than a launch takes")
+    pos = _pairs(5_300_000, 462)
+    st = []
+    for depth in (19, 21):
+        P = R.Plan(pos, 1e-12, 1.0, 1e-3, leaf_size=1, order=1, max_depth=depth)
+        try:
+            st.append(P.stats())
+        finally:
+            P.free()
+    a, b = st
+    log(f"  boxes {a['nbox']} {b['nbox']}, plans {a['plan_ms']:.0f} {b['plan_ms']:.0f} ms")
+    assert a["nbox"] <= 2**32 // 64 - 8 < b["nbox"]
+    assert a["nleaf"] == b["nleaf"] == 5_300_000 and b["nbox"] == a["nbox"] + 2 * a["nleaf"]
+    assert a["list_len"] == b["list_len"] and a["list_len"]["U"] == a["nleaf"]
