@@ -314,8 +314,15 @@ rpy_status rpy_plan_inject_error(rpy_plan_t* plan, int32_t phase);
  * plan's streams first.  The host images of the translation tables stay
  * cached per expansion order for the life of the process; device blocks of up
  * to 64 MB, at most 256 MB per device, are kept for later plans and given back
- * when an allocation fails or 16 plans did not use them. */
+ * when an allocation of the library fails, 16 plans did not use them, or by
+ * rpy_release_memory. */
 void rpy_plan_free(rpy_plan_t* plan);
+
+/* Gives back what freed plans left with the library on the current device (device
+ * blocks, two streams and a host page each), for a program that wants the memory
+ * itself.  Plans in use are not touched, and later ones allocate anew.  Any
+ * thread; waits for the device.  RPY_EDEVICE if there is no device. */
+rpy_status rpy_release_memory(void);
 
 const char* rpy_status_string(rpy_status s);
 const char* rpy_last_error(void);

@@ -7,7 +7,7 @@ paper_1711_02976_amd.build``) -- there is no CPU fallback.
 
 Functions mirror the C entry points (``rpy_plan``, ``rpy_plan_batched``,
 ``rpy_matvec``, ``rpy_sqrt_matvec``, ``rpy_plan_stats``, ``rpy_plan_export``,
-``rpy_plan_free``); ``Plan`` wraps them for torch tensors::
+``rpy_plan_free``, ``rpy_release_memory``); ``Plan`` wraps them for torch tensors::
 
     import torch, paper_1711_02976_amd as R
     pos = torch.rand(100_000, 3, dtype=torch.float64, device="cuda") * 50
@@ -74,7 +74,7 @@ _lib = None
 EXPORTED = ("rpy_default_options", "rpy_plan", "rpy_plan_batched", "rpy_matvec", "rpy_matvec_noalloc",
             "rpy_sqrt_matvec", "rpy_plan_stats",
             "rpy_plan_export", "rpy_plan_set_timing", "rpy_plan_timings", "rpy_plan_inject_error", "rpy_plan_free",
-            "rpy_status_string", "rpy_last_error")
+            "rpy_release_memory", "rpy_status_string", "rpy_last_error")
 
 
 def lib():
@@ -109,6 +109,8 @@ def lib():
         L.rpy_plan_inject_error.argtypes = [C.c_void_p, C.c_int32]
         L.rpy_plan_inject_error.restype = C.c_int
         L.rpy_plan_free.argtypes = [C.c_void_p]
+        L.rpy_release_memory.argtypes = []
+        L.rpy_release_memory.restype = C.c_int
         L.rpy_status_string.argtypes = [C.c_int]
         L.rpy_status_string.restype = C.c_char_p
         L.rpy_last_error.restype = C.c_char_p
@@ -229,6 +231,11 @@ def rpy_plan_inject_error(plan, phase):
 def rpy_plan_free(plan):
     if plan:
         lib().rpy_plan_free(plan)
+
+
+def rpy_release_memory():
+    """Give back the device memory that freed plans left with the library."""
+    _check(lib().rpy_release_memory())
 
 
 # ---- torch convenience ----------------------------------------------------

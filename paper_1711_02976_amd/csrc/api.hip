@@ -295,6 +295,13 @@ static void fold_events(rpy_plan_t* P) {
   P->ev_pending.clear();
 }
 
+static void destroy_lane(const rpy::Lane& l) {
+  if (l.far2) (void)hipStreamDestroy(l.far2);
+  for (hipEvent_t e : {l.p2m, l.m2l0, l.fork, l.join})
+    if (e) (void)hipEventDestroy(e);
+  if (l.near) (void)hipStreamDestroy(l.near);
+}
+
 // The device must have finished with the arrays.
 static void free_ws(rpy_plan_t* P) {
   Work& w = P->ws;
@@ -1356,14 +1363,7 @@ void rpy_plan_free(rpy_plan_t* P) {
   const rpy::NoKeep nokeep(!idle);
   fold_events(P);
   const rpy::Lane lane{P->near, P->far2, P->ev_fork, P->ev_join, P->ev_p2m, P->ev_m2l0};
-  if (!(idle && P->near && P->far2 && rpy::keep_lane(P->device, lane))) {
-    if (P->far2) (void)hipStreamDestroy(P->far2);
-    if (P->ev_p2m) (void)hipEventDestroy(P->ev_p2m);
-    if (P->ev_m2l0) (void)hipEventDestroy(P->ev_m2l0);
-    if (P->ev_fork) (void)hipEventDestroy(P->ev_fork);
-    if (P->ev_join) (void)hipEventDestroy(P->ev_join);
-    if (P->near) (void)hipStreamDestroy(P->near);
-  }
+  if (!(idle && P->near && P->far2 && rpy::keep_lane(P->device, lane))) destroy_lane(lane);
   for (hipEvent_t e : P->ev_pool) (void)hipEventDestroy(e);
   free_ws(P);
   rpy::dev_free(P->kbuf);
@@ -1376,6 +1376,18 @@ void rpy_plan_free(rpy_plan_t* P) {
   rpy::plan_freed(P->device);
   if (dev != P->device) (void)hipSetDevice(dev);
   delete P;
+}
+
+rpy_status rpy_release_memory(void) {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(RPY_EDEVICE, "hipGetDevice failed");
+  }
+  rpy::give_idle_back(dev);
+  rpy::Lane lane;
+  while (rpy::take_lane(dev, &lane)) destroy_lane(lane);
+  return RPY_OK;
 }
 
 }  // extern "C"

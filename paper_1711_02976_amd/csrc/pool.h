@@ -75,5 +75,6 @@ struct Lane {
 bool take_lane(int dev, Lane* out);         // false: none idle
 bool keep_lane(int dev, const Lane& lane);  // idle streams and events; false: not kept
 void plan_freed(int dev);                   // a plan's memory has been freed
+void give_idle_back(int dev);               // the device's idle blocks and host pages
 
 }  // namespace rpy

@@ -14,7 +14,8 @@
 //     goes to its device's idle list, for any thread and stream.
 //   * Idle blocks of a device are bounded by POOL_IDLE bytes (the longest idle are
 //     given back first), those that POOL_AGE plans came and went without are given
-//     back, and all of them are when an allocation fails, before it is tried again.
+//     back, and all of them are when an allocation fails, before it is tried again,
+//     or when the program asks for it (rpy_release_memory).
 // Larger blocks go straight to hipMalloc and hipFree.  Nothing here throws: where
 // the host has no memory for a record, a block is not kept, or not handed out.
 #include <algorithm>
@@ -276,6 +277,16 @@ void plan_freed(int dev) {
   DevPool& d = it->second;
   ++d.plans;
   if (d.plans > POOL_AGE) give_back(d, POOL_IDLE, d.plans - POOL_AGE);
+}
+
+void give_idle_back(int dev) {
+  Pool& P = pool();
+  std::lock_guard<std::mutex> lk(P.mu);
+  const auto it = P.dev.find(dev);
+  if (it == P.dev.end()) return;
+  give_back(it->second, 0, ~(uint64_t)0);
+  for (void* q : it->second.pages) (void)hipHostFree(q);
+  it->second.pages.clear();
 }
 
 }  // namespace rpy

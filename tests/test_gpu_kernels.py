@@ -601,3 +601,40 @@ def test_more_boxes_than_a_launch_tree():
     assert a["nbox"] <= 2**32 // 64 - 8 < b["nbox"]
     assert a["nleaf"] == b["nleaf"] == 5_300_000 and b["nbox"] == a["nbox"] + 2 * a["nleaf"]
     assert a["list_len"] == b["list_len"] and a["list_len"]["U"] == a["nleaf"]
+
+
+# What freed plans left with the library goes back to the device when the program
+# asks for it, and a plan in use and the next one are none the worse.
+def test_release_memory(orc):
+    import paper_1711_02976_amd as R
+    import torch
+    from gpu_common import to_dev
+    w = W.uniform_cube(20000, 1.0, 0.005, nrhs=2, seed=470)
+    log("released memory")
+    pos, F = to_dev(w.pos), to_dev(w.forces)
+
+    def free_bytes():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    P = R.Plan(pos, w.a, w.eta, 1e-6, leaf_size=100, order=8)
+    try:
+        u = P.matvec(F)
+        u2 = torch.empty_like(u)
+        for _ in range(2):  # the first time, the runtime makes its hardware queues
+            R.rpy_release_memory()
+            before = free_bytes()
+            Q = R.Plan(pos, w.a, w.eta, 1e-6, leaf_size=100, order=8)
+            R.rpy_matvec(Q.handle, 2, F.data_ptr(), u2.data_ptr())
+            Q.free()
+            kept = before - free_bytes()
+            R.rpy_release_memory()
+        log(f"  kept {kept >> 10} KiB, after the release {(before - free_bytes()) >> 10}")
+        assert kept >= 8 << 20 and before - free_bytes() <= 2 << 20
+        R.rpy_matvec(P.handle, 2, F.data_ptr(), u2.data_ptr())
+        assert torch.equal(u2, u)
+        Q = R.Plan(pos, w.a, w.eta, 1e-6, leaf_size=100, order=8)
+        assert torch.equal(Q.matvec(F), u)
+        Q.free()
+    finally:
+        P.free()

@@ -248,6 +248,32 @@ void threads() {
   CHECK(D.used <= 256 * MB && D.pages <= 4);
 }
 
+// What the program asks back: idle blocks and pages of one device, nothing in use.
+void release() {
+  give_idle_back(0);  // a device that the pool has no record of
+  char *a = get(3 * MB), *b = get(5 * MB), *c = nullptr;
+  {
+    BuildScope s(nullptr);
+    CHECK(s.page());
+    dev_free(a);
+    give_idle_back(0);  // a scope's blocks are in use
+    CHECK(s.freed.size() == 1 && D.blocks.count(a) && D.pages == 1);
+  }
+  cur = 1;
+  c = get(2 * MB);
+  dev_free(c);
+  cur = 0;
+  CHECK(D.used == 10 * MB);
+  give_idle_back(0);
+  CHECK(D.used == 7 * MB && D.blocks.count(b) && D.blocks.count(c) && D.pages == 0);
+  dev_free(b);
+  CHECK(get(5 * MB) == b);  // kept again
+  dev_free(b);
+  give_idle_back(1);
+  give_idle_back(0);
+  CHECK(D.used == 0 && D.blocks.empty());
+}
+
 // Every host allocation of a plan's course fails in turn.
 void no_host_memory() {
   for (ll k = 0; k < 60; ++k) {
@@ -289,7 +315,7 @@ void no_host_memory() {
 
 int main(int, char** argv) {
   const std::string t = argv[1];
-  t == "bounds" ? bounds() : t == "failure" ? failure() : t == "scopes" ? scopes() : t == "threads" ? threads() : no_host_memory();
+  t == "bounds" ? bounds() : t == "release" ? release() : t == "failure" ? failure() : t == "scopes" ? scopes() : t == "threads" ? threads() : no_host_memory();
   std::printf("ok\n");
 }
 """
@@ -311,7 +337,7 @@ def exe(tmp_path_factory):
     return _build(tmp_path_factory.mktemp("pool"), None)
 
 
-@pytest.mark.parametrize("what", ["bounds", "failure", "scopes", "threads", "no_host_memory"])
+@pytest.mark.parametrize("what", ["bounds", "release", "failure", "scopes", "threads", "no_host_memory"])
 def test_kept_memory(exe, what):
     r = subprocess.run([str(exe), what], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout + r.stderr
