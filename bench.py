@@ -351,7 +351,7 @@ def run(args):
                 "avg_launch_ms": d["avg_launch_ms"], "algorithmic_flops_per_launch": d["flops_per_matvec"] / launches,
                 "count": count, "kernel_count_achieved": d["kernel_count_tflops"]}
     else:
-        roof = {"bound": "alu", "kernel": "k_m2l_rot", "achieved": d["achieved_tflops"], "peak": d["peak_tflops"],
+        roof = {"bound": "alu", "kernel": m2l_kernel(r["stats"]["order"], mixed), "achieved": d["achieved_tflops"], "peak": d["peak_tflops"],
                 "unit": "TFLOP/s", "frac": d["frac"],
                 "traffic": traffic_for("m2l_rot.hip", f"m2l:{args.workload}:{best}"),
                 "algorithmic_flops_per_matvec": d["flops_per_matvec"],
@@ -405,7 +405,15 @@ PMC_KERNELS = {  # rocprofv3 kernel-name pattern -> (phase, precision form, sour
     r"rpy::k_p2p<\d+, false, false>": ("p2p", "fp64", "nearfield.hip"),
     r"rpy::k_m2l_rot<\d+, float": ("m2l", "mixed", "m2l_rot.hip"),
     r"rpy::k_m2l_rot<\d+, double": ("m2l", "fp64", "m2l_rot.hip"),
+    # above order 21 (FP64: 16) instead of k_m2l_rot
+    r"rpy::k_m2l_rows<float": ("m2l", "mixed", "m2l_rot.hip"),
+    r"rpy::k_m2l_rows<double": ("m2l", "fp64", "m2l_rot.hip"),
 }
+
+
+def m2l_kernel(order, mixed):
+    """The rotation M->L kernel of a plan."""
+    return "k_m2l_rows" if order > (21 if mixed else 16) else "k_m2l_rot"
 
 
 def pmc_summary(args):

@@ -57,3 +57,29 @@ def test_counters_scaled_by_the_copy_and_withheld_when_stale(tmp_path, monkeypat
     with open(os.path.join(csrc, "fmm.h"), "a") as fh:
         fh.write("\n")
     assert bench.traffic_for("nearfield.hip", key) is None
+
+
+def test_every_kernel_of_a_phase_has_a_traffic_figure(tmp_path, monkeypatch):
+    """The matrix-core and vector P2P and both rotation M->L kernels, in both
+    precision forms, as the counter files name them."""
+    tmp = str(tmp_path)
+    _tree(tmp)
+    monkeypatch.setattr(bench, "ROOT", tmp)
+    names = {"p2p_mc:w:mixed": "rpy::k_p2p_mfma<true, 0>", "p2p_mc:w:fp64": "rpy::k_p2p_mfma<false, 4>",
+             "p2p:w:mixed": "rpy::k_p2p<4, true, false>", "p2p:w:fp64": "rpy::k_p2p<1, false, false>"}
+    m2l = [("m2l:w:mixed", "rpy::k_m2l_rot<4, float, 16, 8, 4>"), ("m2l:w:fp64", "rpy::k_m2l_rot<4, double, 16, 12, 3>"),
+           ("m2l:w:mixed", "rpy::k_m2l_rows<float, 27, 32, 16, 4>"),
+           ("m2l:w:fp64", "rpy::k_m2l_rows<double, 21, 32, 12, 3>"),
+           ("m2l:w:fp64", "rpy::k_m2l_rows<double, 27, 16, 12, 3>")]
+    for i, (key, name) in enumerate(list(names.items()) + m2l):
+        rows = lambda c, v: [(f"void {name}(int, rpy::Tree)", c, v)]
+        d = [_run_dir(os.path.join(tmp, f"{x}{i}"), r) for x, r in
+             (("f", rows("FETCH_SIZE", 8.0 + i)), ("w", rows("WRITE_SIZE", 4.0)),
+              ("cf", [("__amd_rocclr_copyBuffer", "FETCH_SIZE", 1024.0)]),
+              ("cw", [("__amd_rocclr_copyBuffer", "WRITE_SIZE", 1024.0)]))]
+        args = argparse.Namespace(pmc_summary=d, copy_probe=1, workload="w")
+        assert bench.pmc_summary(args) == 0
+        src = "m2l_rot.hip" if "m2l" in key else "nearfield.hip"
+        assert bench.traffic_for(src, key) == round((12.0 + i) * 1024), name
+    assert [bench.m2l_kernel(*a) for a in ((16, False), (17, False), (21, True), (22, True))] == \
+        ["k_m2l_rot", "k_m2l_rows"] * 2
