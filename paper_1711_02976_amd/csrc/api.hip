@@ -75,6 +75,11 @@ int order_for_eps(double eps, bool adaptive) {
 //     (target bead, W box) (O(p^2)).
 // The overlap correction is not modelled: trial trees have no O list.  Also
 // returns the range of refinement limits that produce this same tree.
+// The M->L constants are those of earlier kernels.  M->L has become cheaper since
+// (FP64 order 16: 78 -> 58 ms on 778k beads, order 21: 83 -> 53 ms; order 27: 6.0 ->
+// 2.5; FP32 17..21: 36 -> 29), so on surfaces, clusters and batches the FP64 form
+// gets larger leaves than the present times call for.  They are kept because the
+// tree, and with it the order and the results of a plan, would change with them.
 // Right-hand sides of the near-field group with `left` still to do and
 // groups of at most nrn: 16 on the matrix cores, else 8, 4, 2 or 1 on the
 // vector units.  In the FP64 form the group of 16 also takes x = 1, 2, 4 or
@@ -124,8 +129,6 @@ static int model_tree(const rpy::Built& B, int order, double eps, bool mixed, in
   const double S16 = 1785.0, S21 = 3795.0, T21 = 253.0;
   // ns per unit (one density unless stated)
   const double c_pair = mixed ? 0.53e-3 : 0.98e-3;  // per padded pair, one right-hand side
-  // the FP32 rotation M2L up to p = 16 fits two blocks per CU; the FP64 one
-  // above p = 16 takes 32 columns per batch
   // up to p = 16 the M->L per (V pair, density) is affine in S: a part
   // that does not shrink with the order (gathers, phases, column sums,
   // barriers) equal to 655 units of S (cube-15M, FP32: 0.70 ns at p = 16,

@@ -314,7 +314,7 @@ __global__ void __launch_bounds__(64 * EV_WAVES, 4) k_eval_apply(int p, const in
                                                    const double* __restrict__ DL, const double* __restrict__ DW,
                                                    double C1, double* __restrict__ u) {
   // consecutive tiles (mostly of one leaf) share a block, hence a CU and its
-  // scalar cache, and walk the same set coefficients at about the same time
+  // vector cache, and walk the same set coefficients at about the same time
   const int ti = blockIdx.x * EV_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (ti >= (item ? nitem : ntiles)) return;
   const int4 it = item ? item[ti] : make_int4(ti, -1, -1, 0);

@@ -1134,8 +1134,13 @@ static hipError_t launch_rot(const Launch& l, int nrc, Exp e, const R* rot, cons
   //   FP32 17..21, 131 KB: one block of 16 waves (8 before: 64 systems of 16
   //     right-hand sides 35.6 -> 28.8 ms), all densities in one block where
   //     the V lists are too short to fill the batches of one right-hand side
-  //     (below 54 entries per box; dense clusters, 43: 27 against 31 ms, the
-  //     64 systems, 64: 32 against 29);
+  //     (16 entries).  The line, 54 entries per box, lies between dense clusters
+  //     (43: 27 against 31 ms) and the 64 systems (64: 32 against 29).  It is a
+  //     rough one: over fourteen more trees of four right-hand sides one block
+  //     for all took 0.79 to 0.90 of the time at 27 to 43 entries, 0.87 at 53, 0.93
+  //     and 0.86 at 74 and 77, 0.96 at 115 to 123 and 1.02 at 137, and on trees of
+  //     fewer boxes than would fill the chip up to 3.0 (73 boxes, 42 entries: 0.34
+  //     against 0.11 ms) and 1.2 (585 boxes, 97);
   //   FP64 up to 10: two blocks of 8 waves (order 7: 1.27 -> 0.74 ms);
   //   FP64 11..16, 160 KB: 12 waves (8 waves with all densities 78 ms, 12 with
   //     one right-hand side's 61, 16 spill and take 69).

@@ -361,8 +361,8 @@ static double pair_scale(double a) { return std::ldexp(1.0, -std::ilogb(2.0 * a)
 // stay as they are; B', which multiplies d' d'^T = 4 d d^T, is a quarter.  All of
 // it is exact scaling by powers of two.  With the wave's test for overlaps on FP32
 // roundings, the FP64 P2P of one right-hand side takes 28 FP64 operations and roots
-// per pair (30 before; 1M beads in leaves of 244: 7.18 ms and 6.96 now, at its
-// issue rate).
+// per pair (30 before; 1M beads in leaves of 244: 7.18 ms and 6.96 now, 0.17 vector
+// instructions per SIMD cycle of 2.4 GHz; FP64 alone reaches 0.21 to 0.24, roots 0.12).
 template <class R>
 constexpr double PAIR_ZOOM = std::is_same<R, double>::value ? 2.0 : 1.0;
 template <class R>
@@ -570,12 +570,14 @@ __global__ void __launch_bounds__(P2P_T * DO_G) k_direct_out(const int4* tiles, 
 // once for 16 + XR right-hand sides.  FP32 and FP64 products and vector
 // instructions do not overlap on this chip (measured: their times add at one
 // to eight waves per SIMD), so the bound is their sum: per step nine products
-// of 32 (FP32) or 64 (FP64) cycles and about 27 (FP64 16 + 4: 80) vector
-// instructions.  The forces are staged row by row as they lie in memory, in
-// rows whose padding keeps both the stores and the reads free of bank
-// conflicts; that took the FP32 launch on 15M beads from 506 to 480 ms, 93 %
-// of that bound (index arithmetic per staged force and 16 lanes per bank
-// before).  Their per-lane partial sums are added
+// (290 cycles of 2.4 GHz in FP32, 687 in FP64, whose load lowers the clock) and
+// about 27 (FP64 16 + 4: 80) vector instructions of 2.4 (FP64: 4.2).  Products and
+// plain multiply-adds in these numbers alone take 374 (1,020) cycles per step, 423
+// ms (1,157) on 15M beads; the launches take 480 (1,202), 88 % (96 %) of it.  The
+// forces are staged row by row as they lie in memory, in rows whose padding keeps
+// both the stores and the reads free of bank conflicts (with index arithmetic per
+// staged force and 16 lanes per bank the FP32 launch took 506).  Their per-lane
+// partial sums are added
 // over the four source lanes of a target after each staged chunk, and lane
 // (t, k) keeps the FP64 sums of the right-hand sides k, k + 4.  (The mixed
 // form runs its extra right-hand sides in the vector kernel: there the
@@ -858,7 +860,8 @@ __global__ void __launch_bounds__(P2P_T) k_wdirect(const int4* tiles, const int4
 // group whose box is 2a or more from every one of the wave's targets.  The lanes
 // first test all of a chunk's groups at once against the box of the wave's
 // targets (4M clustered beads, 4 right-hand sides, of all groups two in five are
-// out of reach: 84.7 ms and 79.8, at the issue rate of the pairs in reach).
+// out of reach: 84.7 ms and 79.8; the pairs in reach issue 0.27 vector
+// instructions per SIMD cycle of the 0.41 that plain FP32 reaches).
 constexpr int OV_G = 4;
 
 template <int NRC, bool MIXED>
