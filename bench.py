@@ -108,10 +108,10 @@ def source_sha(kernel_file):
     return h.hexdigest()[:16]
 
 
-def traffic_for(kernel_file, launches_key):
+def traffic_for(kernel_file, launches_key, kernel=None):
     """HBM bytes per launch from committed rocprofv3 counter runs, if they were
-    taken on the current source of the kernel (and the shared headers); else
-    None."""
+    taken on the current source of the kernel (and the shared headers), and of
+    the kernel named, where one is; else None."""
     path = os.path.join(ROOT, "profiles", "pmc_traffic.json")
     if not os.path.exists(path):
         return None
@@ -119,6 +119,8 @@ def traffic_for(kernel_file, launches_key):
     if not rec:
         return None
     if rec.get("source_sha") != source_sha(kernel_file):
+        return None
+    if kernel and f"::{kernel}<" not in rec.get("kernel", ""):
         return None
     return rec.get("bytes_per_launch")
 
@@ -351,9 +353,10 @@ def run(args):
                 "avg_launch_ms": d["avg_launch_ms"], "algorithmic_flops_per_launch": d["flops_per_matvec"] / launches,
                 "count": count, "kernel_count_achieved": d["kernel_count_tflops"]}
     else:
-        roof = {"bound": "alu", "kernel": m2l_kernel(r["stats"]["order"], mixed), "achieved": d["achieved_tflops"], "peak": d["peak_tflops"],
+        kernel = m2l_kernel(r["stats"]["order"], mixed)
+        roof = {"bound": "alu", "kernel": kernel, "achieved": d["achieved_tflops"], "peak": d["peak_tflops"],
                 "unit": "TFLOP/s", "frac": d["frac"],
-                "traffic": traffic_for("m2l_rot.hip", f"m2l:{args.workload}:{best}"),
+                "traffic": traffic_for("m2l_rot.hip", f"m2l:{args.workload}:{best}", kernel),
                 "algorithmic_flops_per_matvec": d["flops_per_matvec"],
                 "count": "per V pair and density: 20 S flops, S = sum_n (n+1)^2"}
     tm = r["timings"]

@@ -81,5 +81,9 @@ def test_every_kernel_of_a_phase_has_a_traffic_figure(tmp_path, monkeypatch):
         assert bench.pmc_summary(args) == 0
         src = "m2l_rot.hip" if "m2l" in key else "nearfield.hip"
         assert bench.traffic_for(src, key) == round((12.0 + i) * 1024), name
+        kernel = name[len("rpy::"):name.index("<")]
+        assert bench.traffic_for(src, key, kernel) == round((12.0 + i) * 1024), name
+        # a run whose order takes the other M->L kernel
+        assert bench.traffic_for(src, key, "k_m2l_rows" if kernel == "k_m2l_rot" else "k_m2l_rot") is None
     assert [bench.m2l_kernel(*a) for a in ((16, False), (17, False), (21, True), (22, True))] == \
         ["k_m2l_rot", "k_m2l_rows"] * 2
