@@ -84,7 +84,7 @@ __global__ void __launch_bounds__(256) k_leaf_q(const int* leaves, Tree t, const
 // The charges of S->M are loaded once per chunk, before the harmonics are
 // generated, and serve all passes: as matrix-core operands in registers, or
 // with one right-hand side in scalar registers.  Loaded step by step, each
-// waited for memory (15M beads, 20 right-hand sides, p = 16: 57.5 ms, 39.3 now,
+// waited for memory (15M beads, 20 right-hand sides, p = 16: 57.5 ms, 37.8 now,
 // of 12 for the matrix-core products and 9 for the harmonics; 8M beads on a
 // sphere, one right-hand side, p = 21: 3.05 and 2.6).  Two blocks share a CU
 // (LDS), so the registers are held to 128 (p = 27 S->M: 168 and 157 us, spills
