@@ -739,8 +739,9 @@ int build_tree(const BuildArgs& A, Built* B, Error* err) {
   // A plan's first copy is on the null stream and waits for it: positions that
   // the default stream still writes are there when s reads them, also where s does
   // not wait for the null stream by itself.  (Nothing on s uses the block yet; a
-  // later trial tree's may be one that s has not finished with.)
-  if (A.presorted) RPY_HIP(copy_in(B->d_sys_begin, sb.data(), sizeof(int) * (nsys + 1), s));
+  // later trial tree's may be one that s has not finished with.  On the null stream
+  // itself the asynchronous copy and its wait do the same, 25 us sooner.)
+  if (A.presorted || !s) RPY_HIP(copy_in(B->d_sys_begin, sb.data(), sizeof(int) * (nsys + 1), s));
   else RPY_HIP(hipMemcpy(B->d_sys_begin, sb.data(), sizeof(int) * (nsys + 1), hipMemcpyHostToDevice));
   RPY_PAGE(int, page);
 
